@@ -774,6 +774,18 @@ struct PhaseClock {
 };
 #endif
 
+// Does any first-layer run start at an odd byte of its window (NetDiagonal's copies do)?
+template <class Net>
+constexpr bool has_odd_runs() {
+    for (int kbi = 0; kbi < Net::kb(0); ++kbi)
+        for (int g = 0; g < 4; ++g)
+            for (int half = 0; half < 2; ++half) {
+                int dr = 0, off = 0;
+                if (Net::run_desc(kbi, g, half, dr, off) && (off & 1) != 0) return true;
+            }
+    return false;
+}
+
 // decode LDS: the CDF table, two activation buffers, head outputs, mixtures, ring
 template <class Net>
 struct DecLds {
@@ -793,14 +805,17 @@ struct DecLds {
     static constexpr int kCpStride = 3 * Net::K <= 16 ? 20 : 24;       // mixture of one (pixel, channel): pi[K], mu[K], a[K]
     static constexpr int kHeadOff = kAct1Off + kActBytes;              // [16 pixels][kHeadStride] fp32, (group, register) layout
     static constexpr int kCpOff = kHeadOff + 16 * kHeadStride * 4;     // [16 pixels][3 channels][kCpStride] fp32
-    // Ring of recently decoded pixels as first-layer inputs: [18 rows][2 * kRingCols columns][3] bf16.
-    // Rows 0,1 are the two rows above the band.  Column c lives at slots c mod kRingCols and
-    // that + kRingCols, so the values of a run of neighbour columns are always contiguous.
-    // The pad keeps the 16 rows of a gather off each other's LDS banks; which pad is fastest was measured per network.
-    static constexpr int kRingRowElems = 2 * Net::kRingCols * 3 + Net::kRingPad;
+    // Ring of recently decoded pixels as first-layer inputs, bf16: [18 rows][2 copies][2 * kRingCols columns][3].
+    // Rows 0,1 are the two rows above the band.  Column c lives at slots c mod kRingCols and that + kRingCols, so the
+    // values of a run of neighbour columns are always contiguous.  The second copy is one element further on, so
+    // that a run of four values, which may start at any element, is two aligned dwords in one of the copies: LDS takes
+    // 512 cycles over two 8-byte reads of four waves that are not 8-byte aligned, and 64 over two pairs of dwords.
+    static constexpr int kRingCopyElems = 2 * Net::kRingCols * 3 + 1;  // from an element to the same one in the second copy
+    static constexpr int kRingRowElems = 2 * kRingCopyElems + Net::kRingPad;
     static constexpr int kRingOff = kCpOff + 16 * 3 * kCpStride * 4;
     static constexpr int kMiscOff = kRingOff + 18 * kRingRowElems * 2; // ticket, abort flag
-    static constexpr int kBytes = (kMiscOff + 64 + 15) / 16 * 16;
+    static constexpr int kSinkOff = kMiscOff + 16;                     // where lanes with no ring element to write write
+    static constexpr int kBytes = (kSinkOff + 64 * 4 + 8 + 15) / 16 * 16;
     // Two workgroups per CU have 256 registers per lane each, too few for the whole of a wave's weight slices: there
     // the biases, and the weights of the first layer and of the head where two workgroups' LDS then still fits a CU,
     // are kept in LDS behind the above and read when used.
@@ -847,6 +862,8 @@ struct DecLds {
     // With one idle wave it does both.
     static constexpr int kIdleWaves = kIdleSlack > 0 ? 4 * ((Net::ob(kIdleLayer) + 3) / 4) - Net::ob(kIdleLayer) : 0;
     static constexpr int kStoreWave = kLastWave;
+    // Waves from this one on have no block in those rounds (the last wave alone, which fetches and stores, if there are none).
+    static constexpr int kFirstIdleWave = kIdleWaves > 0 ? kLastWave + 1 - kIdleWaves : kLastWave + 1;
     static constexpr int kFetchWave = kIdleWaves >= 2 ? kLastWave - 1 : kLastWave;
     // Does wave w have a round without an out-block in layer l?
     static constexpr bool wave_idles(int l, int w) { return w + 4 * ((Net::ob(l) + 3) / 4 - 1) >= Net::ob(l); }
@@ -860,100 +877,39 @@ struct DecLds {
     static_assert(Net::kReach1 <= Net::kDelay - 1 && Net::kReach2 <= 2 * Net::kDelay - 1, "schedule is not causal");
 };
 
-// All-reduce over the 16 lanes of a DPP row by rotations.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_row(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-__device__ __forceinline__ uint32_t row_allmax(uint32_t v) {
-    v = max(v, dpp_row<0x121>(v)); v = max(v, dpp_row<0x122>(v));
-    v = max(v, dpp_row<0x124>(v)); v = max(v, dpp_row<0x128>(v));
-    return v;
-}
-__device__ __forceinline__ uint32_t row_allmin(uint32_t v) {
-    v = min(v, dpp_row<0x121>(v)); v = min(v, dpp_row<0x122>(v));
-    v = min(v, dpp_row<0x124>(v)); v = min(v, dpp_row<0x128>(v));
-    return v;
-}
-
-// rANS reader of one row, replicated in the 16 lanes of the pixel's group.  The
-// stream words of two consecutive blocks of 16 sit in registers, lane j holding
-// words 16 blk + j and 16 (blk + 1) + j, so a renormalisation never waits for
-// memory: a pixel consumes at most three words, and the refill issued at the end
-// of the step in which a block is used up is not needed for another 13 words.
+// rANS reader of one row, replicated in the 16 lanes of the pixel's group.  A pixel consumes at most three of the
+// row's 32-bit words; the next three, w[0..2], are requested at the end of a step's bookkeeping (settle, in
+// decode_kernel) and wanted a third of a step later, so a renormalisation never waits for memory.
 struct RowReader {
-    uint64_t x, y;            // the two coder states: x is the next symbol's, y the one after's (they swap per symbol)
-    const uint32_t* payload;  // the row's payload: the two 8-byte states, then the words
-    uint32_t last;            // index of the payload's last 32-bit word (>= 3: the states are four words)
-    uint32_t nwords, pos;     // words after the state; words consumed so far
-    uint32_t blk;             // block held in cur; pos >> 4 is blk or, within a step, blk + 1
-    uint32_t cur, nxt;
+    uint64_t x, y;            // the two coder states: x is the next symbol's, y the one after's
+    uint32_t w[3];            // words pos, pos + 1, pos + 2
+    uint32_t at;              // offset of word 0 (the one after the states) from the wave's stream window, bytes
+    uint32_t nwords, pos;     // words after the states; words consumed so far
     bool bad;
 };
 
-// Word i of the row (i counted after the state).  Indices past the end read the
-// payload's last word instead: such a value is only ever consumed by a damaged
-// stream, which the position check in reader_advance reports.  The load carries
-// no condition, so its result can stay in flight until it is needed, and it is
-// in bounds for every i as long as payload[0 .. last] is readable.
-__device__ __forceinline__ uint32_t reader_word(const RowReader& rd, uint32_t i) {
-    return rd.payload[min(i + 4u, rd.last)];
+// All ones where `c` holds.  The selects of a pop are made with masks: two or more v_cndmask in a row on one condition in
+// VCC take 16 cycles each while four waves of a compute unit do the same (one alone, or apart from each other, 4).
+__device__ __forceinline__ uint32_t mask_of(bool c) {
+    uint32_t m = c ? 0xFFFFFFFFu : 0u;
+    asm volatile("" : "+v"(m));            // (not to be turned into selects again)
+    return m;
 }
+__device__ __forceinline__ uint32_t pick(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
 
-// A reader over no words at all (rows outside the image, rows whose offsets are
-// damaged): `safe` is any readable pair of words; every renormalisation then counts as an over-read.
-__device__ __forceinline__ void reader_init_empty(RowReader& rd, const uint32_t* safe, bool bad) {
-    rd.x = kRansL; rd.y = kRansL; rd.payload = safe; rd.last = 1; rd.nwords = 0; rd.pos = 0; rd.blk = 0; rd.cur = 0; rd.nxt = 0;
-    rd.bad = bad;
-}
-
-__device__ __forceinline__ void reader_init(RowReader& rd, const uint32_t* payload, uint32_t nwords_total, int j) {
-    rd.x = (uint64_t)payload[0] | ((uint64_t)payload[1] << 32);
-    rd.y = (uint64_t)payload[2] | ((uint64_t)payload[3] << 32);
-    rd.payload = payload;
-    rd.last = nwords_total - 1;
-    rd.nwords = nwords_total - 4;
-    rd.pos = 0;
-    rd.blk = 0;
-    rd.cur = reader_word(rd, (uint32_t)j);
-    rd.nxt = reader_word(rd, (uint32_t)j + 16u);
-    rd.bad = false;
-    if (rd.x < kRansL || (rd.x >> 63)) { rd.bad = true; rd.x = kRansL; }
-    if (rd.y < kRansL || (rd.y >> 63)) { rd.bad = true; rd.y = kRansL; }
-}
-
-// D(x) for the symbol found at (start, freq), and the renormalisation read.  No branches:
-// the next channel's search only waits for the arithmetic, never for control flow.
-// `state` is the state the symbol was coded on (rd.x for a pixel's first and third symbol, rd.y for its second).
-__device__ __forceinline__ void reader_advance(RowReader& rd, uint64_t& state, uint32_t slot, uint32_t start, uint32_t freq,
-                                               int j, bool active) {
-    const uint32_t held = (rd.pos >> 4) != rd.blk ? rd.nxt : rd.cur;
-    const uint32_t w = row_allmax((uint32_t)j == (rd.pos & 15u) ? held : 0u);   // words[pos], in every lane of the group
-    const uint64_t x1 = (uint64_t)freq * (state >> 16) + slot - start;
-    const bool renorm = active && x1 < kRansL;
-    state = active ? (renorm ? ((x1 << 32) | w) : x1) : state;
-    rd.bad = rd.bad | (renorm & (rd.pos >= rd.nwords));
-    rd.pos += renorm ? 1u : 0u;
-}
-
-// After a pixel's three symbols (states x, y, x) the next symbol's state is y.
-__device__ __forceinline__ void reader_next_pixel(RowReader& rd, bool active) {
-    const uint64_t x = rd.x, y = rd.y;
-    rd.x = active ? y : x;
-    rd.y = active ? x : y;
-}
-
-// Once per step, after the pixel's three symbols: when a block has been used up, move on
-// and request the block after the next.
-__device__ __forceinline__ void reader_refill(RowReader& rd, int j) {
-    if ((rd.pos >> 4) != rd.blk) {
-        rd.blk += 1;
-        rd.cur = rd.nxt;
-        // scheduling only: the copy is made before the load is issued, so that the load can
-        // write rd.nxt in place and stay in flight
-        asm volatile("" : "+v"(rd.cur));
-        rd.nxt = reader_word(rd, 16u * (rd.blk + 1u) + (uint32_t)j);
-    }
+// D(x) for the symbol found at (start, freq) and the renormalisation read.  No branches.  An inactive pixel (active: a
+// mask) pops the whole range, which leaves the state as it is and reads nothing.  The state has at most 63 bits and freq
+// 17, so the product's upper part fits a 24-bit multiplication.  A damaged stream may run past the row's words: what it
+// reads there are words of another row or zeros, and the position check at the band's end reports it.
+__device__ __forceinline__ void reader_pop(RowReader& rd, uint64_t& state, uint32_t start, uint32_t freq, uint32_t active) {
+    const uint32_t slot = (uint32_t)state & 0xFFFFu, f = pick(active, freq, 65536u);
+    uint64_t x1 = (uint64_t)(uint32_t)(state >> 16) * f + (uint64_t)(slot - (start & active));
+    const uint32_t lo = (uint32_t)x1, hi = (uint32_t)(x1 >> 32) + __umul24(f, (uint32_t)(state >> 48));
+    const uint32_t renorm = mask_of((((uint64_t)hi << 32) | lo) < kRansL);
+    state = (uint64_t)pick(renorm, rd.w[0], lo) | ((uint64_t)pick(renorm, lo, hi) << 32);
+    rd.w[0] = pick(renorm, rd.w[1], rd.w[0]);
+    rd.w[1] = pick(renorm, rd.w[2], rd.w[1]);
+    rd.pos -= renorm;
 }
 
 // This wave's weight slices of one layer: out-blocks ob = wave + 4 s.  Where the
@@ -1004,15 +960,12 @@ struct WaveLayer {
 // as hidden_layer<> in pcc_device.h: bias, then k-blocks in order, each hi then
 // lo; activation; split into hi + lo.  The out-blocks are taken one after the
 // other (an accumulation chain of MFMAs issues back to back at full rate).
-// In a layer's last round some waves may have no block (ob >= NOB): such a wave skips the round (a branch on
-// `wave_s`, the wave's index as a scalar) and calls idle() instead, if RUN_IDLE.  Every block is finished
-// (activation, split, store) inside the branch that computed it: an MFMA result is never first read behind a
-// branch that the MFMA's own block does not contain.
-template <int NOB, int NKB, int SLOTS, bool W_LDS, bool B_LDS, bool SPLIT_IN, bool LEAKY, bool SKIP_UNOWNED, bool RUN_IDLE,
+// In a layer's last round some waves may have no block (OWNS_LAST is false): such a wave skips the round and calls
+// idle() instead, if RUN_IDLE.
+template <int NOB, int NKB, int SLOTS, bool W_LDS, bool B_LDS, bool SPLIT_IN, bool LEAKY, bool ONE_BY_ONE, bool OWNS_LAST, bool RUN_IDLE,
           class Idle>
 __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS, W_LDS, B_LDS>& wl, int lane, int wave,
-                                                 int wave_s, const u32x4_t (&in)[NKB][2], uint8_t* __restrict__ act_out,
-                                                 Idle& idle) {
+                                                 const u32x4_t (&in)[NKB][2], uint8_t* __restrict__ act_out, Idle& idle) {
     auto finish = [&](int s, const f32x4_t& acc) {
         const int ob = wave + 4 * s;
         uint32_t l0, l1;
@@ -1034,17 +987,14 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
         asm volatile("" : "+v"(acc));            // register allocation only: the result where the vector ALU reads it
     };
     constexpr bool kLastShared = 4 * (SLOTS - 1) + 3 >= NOB;      // not every wave has a block in the last round
+    constexpr int kBlocks = !kLastShared || OWNS_LAST ? SLOTS : SLOTS - 1;
     f32x4_t acc[SLOTS];
-    if constexpr (SKIP_UNOWNED) {
+    if constexpr (ONE_BY_ONE) {
         // Two workgroups per CU share the matrix cores: block after block, each finished before the next begins.
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            if (s < SLOTS - 1 || !kLastShared || wave_s + 4 * s < NOB) {
-                chain(s, acc[s]);
-                finish(s, acc[s]);
-            } else if constexpr (RUN_IDLE) {
-                idle();
-            }
+        for (int s = 0; s < kBlocks; ++s) {
+            chain(s, acc[s]);
+            finish(s, acc[s]);
             __builtin_amdgcn_sched_barrier(0);      // the next block's instructions stay behind this one's
         }
     } else {
@@ -1052,33 +1002,23 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
         // every block: per output element the order stays bias, k-blocks in order, hi then lo).  A k-block's input is
         // then wanted once per SLOTS x 2 MFMAs, which is the pace at which LDS delivers the layer's input to four
         // waves reading at once; block after block, the first block's chain waited for every one of its reads.
-        auto chains = [&](auto count) __attribute__((always_inline)) {
-            constexpr int N = decltype(count)::value;
 #pragma unroll
-            for (int s = 0; s < N; ++s) acc[s] = wl.B(s, wave);
+        for (int s = 0; s < kBlocks; ++s) acc[s] = wl.B(s, wave);
 #pragma unroll
-            for (int kb = 0; kb < NKB; ++kb) {
+        for (int kb = 0; kb < NKB; ++kb) {
 #pragma unroll
-                for (int s = 0; s < N; ++s) acc[s] = mfma16(wl.A(s, kb, wave), in[kb][0], acc[s]);
-                if (SPLIT_IN) {
+            for (int s = 0; s < kBlocks; ++s) acc[s] = mfma16(wl.A(s, kb, wave), in[kb][0], acc[s]);
+            if (SPLIT_IN) {
 #pragma unroll
-                    for (int s = 0; s < N; ++s) acc[s] = mfma16(wl.A(s, kb, wave), in[kb][1], acc[s]);
-                }
+                for (int s = 0; s < kBlocks; ++s) acc[s] = mfma16(wl.A(s, kb, wave), in[kb][1], acc[s]);
             }
-#pragma unroll
-            for (int s = 0; s < N; ++s) asm volatile("" : "+v"(acc[s]));    // register allocation only, see chain()
-#pragma unroll
-            for (int s = 0; s < N; ++s) finish(s, acc[s]);
-        };
-        if constexpr (!kLastShared) {
-            chains(std::integral_constant<int, SLOTS>());
-        } else if (wave_s + 4 * (SLOTS - 1) < NOB) {
-            chains(std::integral_constant<int, SLOTS>());
-        } else {
-            chains(std::integral_constant<int, SLOTS - 1>());
-            if constexpr (RUN_IDLE) idle();
         }
+#pragma unroll
+        for (int s = 0; s < kBlocks; ++s) asm volatile("" : "+v"(acc[s]));    // register allocation only, see chain()
+#pragma unroll
+        for (int s = 0; s < kBlocks; ++s) finish(s, acc[s]);
     }
+    if constexpr (kBlocks < SLOTS && RUN_IDLE) idle();
 }
 
 template <int NKB>
@@ -1112,12 +1052,13 @@ struct WaveNet {
         wl.load(w, reinterpret_cast<const float*>(b), lane, wave);
         rest.load(model, lds, lane, wave);
     }
-    // wave_s: the wave's index as a scalar (for branches); idle: what a wave without a block in the last round of
-    // layer DecLds::kIdleLayer does in its place (the fetch wave is the only one that has work there).
-    template <bool SKIP_UNOWNED, class Idle>
-    __device__ __forceinline__ void run(const u32x4_t (&in)[NKB][2], int lane, int wave, int wave_s,
-                                        uint8_t* __restrict__ act0, uint8_t* __restrict__ act1,
-                                        float* __restrict__ headout, Idle& idle, PhaseClock& clk) const {
+    // OWNS_LAST: has this wave a block in the last round of the layers whose block count is no multiple of four?  (The
+    // same waves have in all of them.)  idle: what a wave that has none does in its place.
+    // settle: work of every wave that nothing waits for before the searches; it goes where the matrix cores are busy and
+    // every wave computes blocks in every round: the last hidden layer.
+    template <bool OWNS_LAST, class Idle, class Settle>
+    __device__ __forceinline__ void run(const u32x4_t (&in)[NKB][2], int lane, int wave, uint8_t* __restrict__ act0, uint8_t* __restrict__ act1,
+                                        float* __restrict__ headout, Idle& idle, Settle& settle, PhaseClock& clk) const {
         // what waves without an out-block in this layer's last round do instead (decode_kernel says what)
         constexpr bool kRunIdle = DecLds<Net>::kIdleSlack > 0 &&
                                   (L == DecLds<Net>::kIdleLayer || (L == 0 && DecLds<Net>::kIdleInFirstLayer));
@@ -1125,30 +1066,37 @@ struct WaveNet {
         if constexpr (kHead) {
             // registers s = 4 ob + i of group g, kept in (group, register) order; out-blocks ob = wave + 4 slot
             constexpr int HS = Layout<Net>::kHeadSlots;
+            constexpr int kBlocks = 4 * (SLOTS - 1) + 3 < NOB || OWNS_LAST ? SLOTS : SLOTS - 1;
 #pragma unroll
-            for (int slot = 0; slot < SLOTS; ++slot) {
-                // a wave without a block in this round skips it; the store follows the MFMAs inside the branch
-                if (4 * slot + 3 < NOB || wave_s + 4 * slot < NOB) {
-                    f32x4_t acc = wl.B(slot, wave);
+            for (int slot = 0; slot < kBlocks; ++slot) {
+                f32x4_t acc = wl.B(slot, wave);
 #pragma unroll
-                    for (int kb = 0; kb < NKB; ++kb) {
-                        const u32x4_t a = wl.A(slot, kb, wave);
-                        acc = mfma16(a, in[kb][0], acc);
-                        acc = mfma16(a, in[kb][1], acc);
-                    }
-                    const int ob = wave + 4 * slot;
-                    *reinterpret_cast<f32x4_t*>(headout + (lane & 15) * DecLds<Net>::kHeadStride + (lane >> 4) * HS + 4 * ob) = acc;
-                } else if constexpr (kRunIdle) {
-                    idle_here();
+                for (int kb = 0; kb < NKB; ++kb) {
+                    const u32x4_t a = wl.A(slot, kb, wave);
+                    acc = mfma16(a, in[kb][0], acc);
+                    acc = mfma16(a, in[kb][1], acc);
                 }
-                if constexpr (SKIP_UNOWNED) __builtin_amdgcn_sched_barrier(0);
+                const int ob = wave + 4 * slot;
+                *reinterpret_cast<f32x4_t*>(headout + (lane & 15) * DecLds<Net>::kHeadStride + (lane >> 4) * HS + 4 * ob) = acc;
+                if constexpr (SHARED) __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (kBlocks < SLOTS && kRunIdle) idle_here();
             lds_barrier();
             clk.mark(kPhLayer0 + L);
         } else {
             uint8_t* out = (L & 1) ? act1 : act0;
-            dec_hidden_layer<NOB, NKB, SLOTS, kWLds, kBLds, (L > 0), Net::kLeaky, SKIP_UNOWNED, kRunIdle>(wl, lane, wave, wave_s, in,
-                                                                                                        out, idle_here);
+            static_assert(Net::kLayers >= 4, "the layer after the first is not the last hidden one");
+            if constexpr (L == 1 || L == Net::kLayers - 2) settle(std::integral_constant<bool, L == Net::kLayers - 2>());
+            dec_hidden_layer<NOB, NKB, SLOTS, kWLds, kBLds, (L > 0), Net::kLeaky, SHARED, OWNS_LAST, kRunIdle>(wl, lane, wave, in, out,
+                                                                                                               idle_here);
+            if constexpr (L == Net::kLayers - 2 && !SHARED) {
+                // scheduling only: settle's instructions go between the MFMAs, three behind each
+#pragma unroll
+                for (int i = 0; i < SLOTS * NKB * 2; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                }
+            }
             lds_barrier();
             clk.mark(kPhLayer0 + L);
             u32x4_t nxt[Net::kb(L + 1)][2];
@@ -1156,7 +1104,7 @@ struct WaveNet {
             // scheduling only: every read of the layer's input is issued before its first MFMA, so
             // the LDS latency is paid once per layer and not once per k-block
             __builtin_amdgcn_sched_barrier(0);
-            rest.template run<SKIP_UNOWNED>(nxt, lane, wave, wave_s, act0, act1, headout, idle, clk);
+            rest.template run<OWNS_LAST>(nxt, lane, wave, act0, act1, headout, idle, settle, clk);
         }
     }
 };
@@ -1165,38 +1113,65 @@ struct WaveNet<Net, SHARED, L, true> {
     __device__ __forceinline__ void load(const uint8_t* __restrict__, const uint8_t* __restrict__, int, int) {}
 };
 
-// Symbol search by the 16 lanes (j = 0..15) of one pixel: two sweeps of 16
-// evaluations.  All lanes of the group return the same x, start, freq.
-// prefetch(): called once the second sweep's table reads are issued; memory requests made there (the next channel's
-// parameters) queue behind those reads and arrive while this channel's reductions and the coder's update run.
-template <int K, class Prefetch>
-__device__ __forceinline__ int group_search(const ChanParams<K>& cp, uint32_t slot, const float2* __restrict__ lut, int lane,
-                                            uint32_t& start, uint32_t& freq, Prefetch& prefetch) {
-    const int j = lane & 15, shift = lane & 48;
-    // first sweep: Cq(16 j); lanes 0..b satisfy Cq <= slot (Cq is increasing and Cq(0) = 0).
-    // Lane 0 evaluates too and discards the value: no branch.
-    const uint32_t e1 = cq_eval<K>(cp, 16 * j, lut);
-    const uint32_t c1 = j == 0 ? 0u : e1;
-    const bool p1 = c1 <= slot;
-    const int b = __popcll((__ballot(p1) >> shift) & 0xFFFFull) - 1;
-    // Cq(16 b + 16), the bound of the symbol's interval if it is the block's last: it sits in lane b + 1 (65536 behind
-    // the group's last lane); one lane shift brings it to lane b, which offers it to the closing minimum below.
-    // (No reduction over the group is needed for it, nor for Cq(16 b): the second sweep's lane 0 evaluates that again.)
-    const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp(65536, (int)c1, 0x101 /* row_shl:1 */, 0xF, 0xF, false);
-    const uint32_t hi_b = j == b ? up : 0xFFFFFFFFu;
-    // second sweep: Cq(16 b + j)
-    CqLookup<K> look;
-    cq_lookup<K>(cp, 16 * b + j, lut, look);
+// Symbol search by the 16 lanes (j = 0..15) of one pixel: two sweeps of 16 evaluations, Cq(16 j) and, in the
+// block b found, Cq(16 b + j).  The search compares 65280 F(edge) with slot + 1 - e in floating point, both exact:
+// floor(v) + e <= slot exactly when v < slot + 1 - e.  Lane 0 always passes (Cq(0) = 0; in the second sweep Cq(16 b)
+// is known to pass): its own constants are minus infinity.  What the symbol's interval needs is left in `found`, for
+// group_interval, which is off the path from symbol to symbol.
+struct SearchLane {            // a lane's constants
+    float edge1, edge2;        // (2 (16 j) - 1) / 512 and (2 j - 1) / 512
+    float e1, e2;              // 16 j and j; minus infinity in lane 0
+    int j, shift;              // lane of the group; position of the group's 16 bits in a ballot
+    int base4;                 // 4 x first lane of the group
+};
+struct Found {
+    uint32_t next1;            // Cq(16 j + 16), 65536 in lane 15
+    uint32_t c2;               // Cq(16 b + j), but for b = j = 0
+    int b, count, x;           // block, lanes that passed in the second sweep, the symbol 16 b + count - 1
+};
+
+// during1(), during2(): called when a sweep's table reads are issued; memory requests made there queue behind them.
+template <int K, class During1, class During2>
+__device__ __forceinline__ int group_search(const ChanParams<K>& cp, float slot1, const float2* __restrict__ lut, const SearchLane& sl,
+                                            Found& found, During1&& during1, During2&& during2) {
+    CqLookup<K> q1, q2;
+    cq_lookup<K>(cp, sl.edge1, lut, q1);
     asm volatile("" ::: "memory");           // ordering of memory requests only: the table reads first
-    prefetch();
+    during1();
+    float limit1 = slot1 - sl.e1;
+    asm volatile("" : "+v"(limit1) :: "memory");      // (computed before the table reads are waited for)
+    const float v1 = cq_scaled<K>(cp, q1);
+    const int b = __popcll((__ballot(v1 < limit1) >> sl.shift) & 0xFFFFull) - 1;
+    const float bf = (float)b;
+    cq_lookup<K>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2);
     asm volatile("" ::: "memory");
-    const uint32_t e2 = cq_finish<K>(cp, 16 * b + j, look);
-    const uint32_t c2 = (b | j) == 0 ? 0u : e2;
-    const bool p2 = c2 <= slot;
-    const int cnt2 = __popcll((__ballot(p2) >> shift) & 0xFFFFull);
-    start = row_allmax(p2 ? c2 : 0u);
-    freq = row_allmin(min(p2 ? 0xFFFFFFFFu : c2, hi_b)) - start;
-    return 16 * b + cnt2 - 1;
+    during2();
+    float limit2 = __builtin_fmaf(bf, -16.0f, slot1 - sl.e2);
+    asm volatile("" : "+v"(limit2) :: "memory");
+    const float v2 = cq_scaled<K>(cp, q2);
+    found.count = __popcll((__ballot(v2 < limit2) >> sl.shift) & 0xFFFFull);
+    found.b = b;
+    found.x = 16 * b + found.count - 1;
+    found.next1 = (uint32_t)__builtin_amdgcn_update_dpp(65536, (int)((uint32_t)v1 + 16u * (uint32_t)sl.j), 0x101 /* row_shl:1 */,
+                                                        0xF, 0xF, false);
+    found.c2 = (uint32_t)v2 + (uint32_t)(16 * b + sl.j);
+    return found.x;
+}
+
+// Cq(x) and Cq(x + 1) - Cq(x), picked from the lanes that evaluated them, in three parts that can stand apart: two
+// lane picks, one that needs the first's result, and the interval.
+struct Interval { uint32_t up, lower, upper; };
+__device__ __forceinline__ void interval_pick(const Found& f, const SearchLane& sl, Interval& v) {
+    v.up = (uint32_t)__builtin_amdgcn_ds_bpermute(sl.base4 + 4 * f.b, (int)f.next1);                   // Cq(16 b + 16)
+    v.lower = (uint32_t)__builtin_amdgcn_ds_bpermute(sl.base4 + 4 * f.count - 4, (int)f.c2);
+}
+__device__ __forceinline__ void interval_pick_upper(const Found& f, const SearchLane& sl, Interval& v) {
+    // lane 0 is nobody's upper end: it stands in for the block's end
+    v.upper = (uint32_t)__builtin_amdgcn_ds_bpermute(sl.base4 + 4 * (f.count & 15), (int)(sl.j == 0 ? v.up : f.c2));
+}
+__device__ __forceinline__ void interval_of(const Found& f, const Interval& v, uint32_t& start, uint32_t& freq) {
+    start = f.x == 0 ? 0u : v.lower;
+    freq = v.upper - start;
 }
 
 // N consecutive floats (N <= 16) from a 16-byte aligned LDS address, as whole vector reads.
@@ -1212,6 +1187,13 @@ __device__ __forceinline__ void lds_read_floats(const float* __restrict__ src, f
         dst[i] = (i & 3) == 0 ? q.x : (i & 3) == 1 ? q.y : (i & 3) == 2 ? q.z : q.w;
     }
 }
+
+// What a wave of the decoder does besides its blocks: fetch the rows above the band, store decoded pixels (to the image
+// and for the band below); and whether it has a block in the last round of layers that do not fill it.
+template <bool FETCHES, bool STORES, bool OWNS_LAST>
+struct StepRole {
+    static constexpr bool kFetches = FETCHES, kStores = STORES, kOwnsLast = OWNS_LAST;
+};
 
 // MINBLOCKS = 1: all registers to one workgroup per CU (lowest latency per step).  MINBLOCKS = 2: two
 // workgroups share a CU (some spills; a step takes about twice as long, so this only pays for jobs of
@@ -1242,6 +1224,12 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     const int g = lane >> 4, nl = lane & 15;
     // search role: pixel q of the band, lane j of its group
     const int q = 4 * wave + (lane >> 4), j = lane & 15;
+    SearchLane sl;
+    sl.j = j; sl.shift = lane & 48; sl.base4 = 4 * (lane & 48);
+    sl.edge1 = (float)(32 * j - 1) * (1.0f / 512.0f);
+    sl.edge2 = (float)(2 * j - 1) * (1.0f / 512.0f);
+    sl.e1 = j == 0 ? -__builtin_inff() : (float)(16 * j);
+    sl.e2 = j == 0 ? -__builtin_inff() : (float)j;
 
     {
         const float2* src = reinterpret_cast<const float2*>(model + Lay::kLutOff);
@@ -1265,7 +1253,8 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     // network role: this lane's first-layer inputs are runs of four consecutive ring values
     // (ring row, offset within the row's window that starts at column c-2); a run the
     // network does not use reads as zero
-    const uint16_t* run_ptr[KB0][2];
+    uint32_t run_at[KB0][2];         // LDS offset of the run for a window at slot 0
+    bool run_odd[KB0][2];            // does the run start at an odd element of the window?
     bool run_used[KB0][2];
 #pragma unroll
     for (int kbi = 0; kbi < KB0; ++kbi) {
@@ -1273,7 +1262,8 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         for (int half = 0; half < 2; ++half) {
             int dr = 0, off = 0;
             run_used[kbi][half] = Net::run_desc(kbi, g, half, dr, off);
-            run_ptr[kbi][half] = ring + (nl + 2 + dr) * D::kRingRowElems + off;
+            run_at[kbi][half] = D::kRingOff + 2u * ((nl + 2 + dr) * D::kRingRowElems + off);
+            run_odd[kbi][half] = has_odd_runs<Net>() && (off & 1) != 0;
         }
     }
 
@@ -1332,17 +1322,41 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     const int qrow = r0 + q;
     const bool qrow_ok = qrow < H;
     RowReader rd;
-    reader_init_empty(rd, reinterpret_cast<const uint32_t*>(stream), false);   // the stream header is always readable
-    if (qrow_ok) {
-        const uint64_t* offs = reinterpret_cast<const uint64_t*>(stream + kStreamHeader);
-        const uint64_t rowg = (uint64_t)im * H + qrow;
-        const uint64_t a = offs[rowg], b = offs[rowg + 1];
-        if (a > b || b > payload_bytes || (b - a) < 16 || ((b - a) & 3) != 0 || (a & 3) != 0 ||
-            (b - a) > 4ull * slab_words(W))
-            rd.bad = true;
-        else
-            reader_init(rd, reinterpret_cast<const uint32_t*>(stream + table + a), (uint32_t)((b - a) / 4), j);
+    rd.x = rd.y = kRansL; rd.w[0] = rd.w[1] = rd.w[2] = 0; rd.at = 0; rd.nwords = rd.pos = 0; rd.bad = false;
+    // The wave's window of the stream starts at its first row's payload: loads address it with 32-bit offsets and read
+    // zero behind the stream's end.
+    uint64_t window = 0;
+    {
+        uint64_t a = 0, b = 0;
+        if (qrow_ok) {
+            const uint64_t* offs = reinterpret_cast<const uint64_t*>(stream + kStreamHeader);
+            const uint64_t rowg = (uint64_t)im * H + qrow;
+            a = offs[rowg]; b = offs[rowg + 1];
+            if (a > b || b > payload_bytes || (b - a) < 16 || ((b - a) & 3) != 0 || (a & 3) != 0 ||
+                (b - a) > 4ull * slab_words(W))
+                rd.bad = true;
+        }
+        const uint64_t first = rd.bad ? 0 : a;
+        window = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)first) |
+                 ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(first >> 32)) << 32);
+        // (rows follow each other in the stream, at most slab_words each: a row that is not within reach is damage)
+        if (qrow_ok && !rd.bad && (a < window || a - window > (1u << 30))) rd.bad = true;
+        if (qrow_ok && !rd.bad) {
+            const uint32_t* payload = reinterpret_cast<const uint32_t*>(stream + table + a);
+            rd.x = (uint64_t)payload[0] | ((uint64_t)payload[1] << 32);
+            rd.y = (uint64_t)payload[2] | ((uint64_t)payload[3] << 32);
+            rd.at = (uint32_t)(a - window) + 16u;
+            rd.nwords = (uint32_t)((b - a) / 4) - 4u;
+            if (rd.x < kRansL || (rd.x >> 63)) { rd.bad = true; rd.x = kRansL; }
+            if (rd.y < kRansL || (rd.y >> 63)) { rd.bad = true; rd.y = kRansL; }
+        }
+        // The states trade places at every step's bookkeeping, the row's first pixel comes kDelay q + 1 of them on.
+        if (((kDelay * q + 1) & 1) != 0) { const uint64_t x = rd.x; rd.x = rd.y; rd.y = x; }
     }
+    const uint64_t window_bytes = payload_bytes - window;
+    const auto words = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(stream + table + window), 0,
+                                                         (int)(uint32_t)(window_bytes < 0xFFFFFFFFull ? window_bytes : 0xFFFFFFFFull),
+                                                         0x00020000 /* untyped dwords */);
 
     uint8_t* out_img = img_out + (size_t)im * H * W * 3;
     const uint32_t* mail_in = mailbox + ((size_t)im * nbands + (band > 0 ? band - 1 : 0)) * 2 * (size_t)W;
@@ -1350,10 +1364,10 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
 
     const int last_row = min(r0 + kBandRows - 1, H - 1);
     const int t_begin = kDelay * r0, t_end = kDelay * last_row + W - 1;
-    // The first two lanes of the fetch wave bring in the rows above the band: lane 0 row r0-2 -> ring row 0, lane 1
-    // row r0-1 -> ring row 1.  That wave has a round without an out-block in one of the layers (DecLds::kIdleLayer)
+    // The first eight lanes of the fetch wave bring in the rows above the band: even lanes row r0-2 -> ring row 0, odd
+    // lanes row r0-1 -> ring row 1, each pair to one of a pixel's four places.  That wave has a round without an out-block in one of the layers (DecLds::kIdleLayer)
     // and does the fetch there, off the path that all four waves share.
-    const bool fetcher = band > 0 && tid >= D::kFetchWave * 64 && tid < D::kFetchWave * 64 + 2;
+    const bool fetcher = band > 0 && tid >= D::kFetchWave * 64 && tid < D::kFetchWave * 64 + 8;
     const uint32_t* mail_row = mail_in + (size_t)(tid & 1) * W;
     // Columns right of the band's first row's column that the fetched row must be known to: row r0-2 is
     // read by the band's first row only; row r0-1 by the first row and, one delay later, by the second.
@@ -1361,13 +1375,14 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
                                 : Net::kReach2;
     uint32_t pf = 0;                              // mailbox word for the next column, requested a step early
 
-    // bf16 of the three channels of pixel word px into both copies of column cc of a ring row
-    auto ring_put = [&](int rrow, int cc, uint32_t px) {
-        uint16_t* d = ring + rrow * D::kRingRowElems + (cc & (RC - 1)) * 3;
-        const uint16_t v0 = (uint16_t)byte_to_bf16(px & 0xFFu), v1 = (uint16_t)byte_to_bf16((px >> 8) & 0xFFu),
-                       v2 = (uint16_t)byte_to_bf16((px >> 16) & 0xFFu);
-        d[0] = v0; d[1] = v1; d[2] = v2;
-        d[3 * RC] = v0; d[3 * RC + 1] = v1; d[3 * RC + 2] = v2;
+    // offset, in elements, of place i (0..3) that a pixel's values are written to: two slots in each of the two copies
+    auto ring_place = [](int i) { return (i & 1) * 3 * RC + (i >> 1) * D::kRingCopyElems; };
+    // bf16 of the three channels of pixel word px into one place of column cc of a ring row
+    auto ring_put = [&](int rrow, int cc, int place, uint32_t px) {
+        uint16_t* d = ring + rrow * D::kRingRowElems + ring_place(place) + (cc & (RC - 1)) * 3;
+        d[0] = (uint16_t)byte_to_bf16(px & 0xFFu);
+        d[1] = (uint16_t)byte_to_bf16((px >> 8) & 0xFFu);
+        d[2] = (uint16_t)byte_to_bf16((px >> 16) & 0xFFu);
     };
     // Bring columns 0 .. ahead of the two rows above the band into the ring, then keep
     // one column ahead: the step at t needs column (t - t_begin) + ahead.
@@ -1397,7 +1412,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         for (int cc = 0; cc <= ahead; ++cc) {
             if (ok && cc < W) {
                 const uint32_t v = wait_word(cc, 0u, ok);
-                if (ok) ring_put(tid & 1, cc, v);
+                if (ok) ring_put(tid & 1, cc, (tid >> 1) & 3, v);
             }
         }
         // Start one column further behind the band above than the data requires: the word requested a
@@ -1434,7 +1449,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     auto fetch_put = [&](int t) __attribute__((always_inline)) {
         if (fetcher) {
             const int cc = t - t_begin + ahead + 1;
-            if (cc < W + kMaxReach) ring_put(tid & 1, cc, fetched);
+            if (cc < W + kMaxReach) ring_put(tid & 1, cc, (tid >> 1) & 3, fetched);
             if constexpr (!kLateRequest) pf = __hip_atomic_load(mail_row + min(cc + 1, W - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
@@ -1450,7 +1465,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     // step, where all four waves would wait for it.  Again in two halves: the ring read, then the stores.
     uint16_t held[3] = {0, 0, 0};
     auto store_read = [&](int t_done) __attribute__((always_inline)) {
-        if ((tid >> 6) == D::kStoreWave && lane < kBandRows) {
+        if (lane < kBandRows) {
             const int cc = t_done - kDelay * (r0 + lane);
             const uint16_t* e = ring + (lane + 2) * D::kRingRowElems + (cc & (RC - 1)) * 3;
 #pragma unroll
@@ -1458,7 +1473,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         }
     };
     auto store_write = [&](int t_done) __attribute__((always_inline)) {
-        if ((tid >> 6) == D::kStoreWave && lane < kBandRows) {
+        if (lane < kBandRows) {
             const int row = r0 + lane, cc = t_done - kDelay * row;
             if (row < H && cc >= 0 && cc < W) {
                 uint8_t* o = out_img + ((size_t)row * W + cc) * 3;
@@ -1469,41 +1484,113 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     };
     constexpr bool kStoreInIdle = D::kIdleSlack > 0;
     int t = t_begin;
-    auto idle = [&](auto layer) __attribute__((always_inline)) {
-        constexpr int L = decltype(layer)::value;
-        if constexpr (!D::kIdleInFirstLayer) {
-            fetch_check(t); fetch_put(t);
-            store_read(t - 1); store_write(t - 1);
-        } else if constexpr (L == 0) {
-            fetch_check(t);
-            store_read(t - 1);
-        } else {
-            fetch_put(t);
-            store_write(t - 1);
-        }
+    // The bookkeeping of a step's pixel that the symbols themselves do not wait for: the pops of G and B, the words the
+    // next pixel may read, and where that pixel goes in the ring.  It is done a step later, in the shadow of the matrix
+    // instructions of the last hidden layer (settle); R's pop has to be done before B's search and is done during G's.
+    // Two VALU instructions issue for free beside an MFMA of 16 cycles; done at the end of the step, as all three pops
+    // once were, this was 500 of its 7,250 cycles.
+    Found found_g = {0, 0, 0, 1, 0}, found_b = {0, 0, 0, 1, 0};
+    uint32_t active = 0, settle_active = 0;            // does this step's / the last step's pixel exist?  (masks)
+    float slot1_x = 0.0f, slot1_y = 0.0f;
+    uint16_t* ring_elem = nullptr;                     // where this lane writes the pixel: [channel]
+    uint32_t mail_px = 0;
+    const uint32_t row_end = qrow_ok ? (uint32_t)W : 0u, ring_end = qrow_ok && j < 4 ? (uint32_t)(W + kMaxReach) : 0u;
+    const uint32_t ring_at = D::kRingOff + 2u * ((q + 2) * D::kRingRowElems + ring_place(j & 3));
+    // where a step's gather reads: the window's offset for runs that start at an even element of it and at an odd one
+    uint32_t window_at[2];
+    auto gather_window = [&](int at) __attribute__((always_inline)) {
+        const uint32_t slot = (uint32_t)(at - kDelay * (r0 + nl) - 2) & (RC - 1);
+        const uint32_t second = (slot & 1u) * (2u * D::kRingCopyElems);
+        window_at[0] = 6u * slot + second;
+        window_at[1] = 6u * slot + 2u * D::kRingCopyElems - second;
+    };
+    gather_window(t);
+    // The lane picks come first, in two stages, each where the next wait for LDS is one of the network's own.
+    Interval settle_g = {0, 0, 0}, settle_b = {0, 0, 0};
+    auto settle_pick = [&]() __attribute__((always_inline)) {
+        interval_pick(found_g, sl, settle_g);
+        interval_pick(found_b, sl, settle_b);
+    };
+    auto settle_pick_upper = [&]() __attribute__((always_inline)) {
+        interval_pick_upper(found_g, sl, settle_g);
+        interval_pick_upper(found_b, sl, settle_b);
+    };
+    auto settle_pops = [&]() __attribute__((always_inline)) {
+        uint32_t start, freq;
+        interval_of(found_g, settle_g, start, freq);
+        reader_pop(rd, rd.y, start, freq, settle_active);
+        interval_of(found_b, settle_b, start, freq);
+        reader_pop(rd, rd.x, start, freq, settle_active);
+        asm volatile("" : "+v"(rd.x), "+v"(rd.y), "+v"(rd.pos));     // scheduling only: done here
+        const uint64_t x = rd.x;       // the next pixel's first symbol is on the state of this one's second
+        rd.x = rd.y;
+        rd.y = x;
+    };
+    auto settle = [&](auto last_hidden) __attribute__((always_inline)) {
+        if constexpr (!decltype(last_hidden)::value) { settle_pick_upper(); return; }
+        settle_pops();
+        typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
+        const u32x3_t next = __builtin_bit_cast(u32x3_t, __builtin_amdgcn_raw_buffer_load_b96(words, (int)(rd.at + 4u * rd.pos), 0, 0));
+        rd.w[0] = next.x; rd.w[1] = next.y; rd.w[2] = next.z;
+        slot1_x = (float)(((uint32_t)rd.x & 0xFFFFu) + 1u);
+        slot1_y = (float)(((uint32_t)rd.y & 0xFFFFu) + 1u);
+        const int c = t - kDelay * qrow;
+        active = mask_of((uint32_t)c < row_end);
+        // Lanes 0 to 3 of a pixel write its four places; the columns right of the image are written as zeros when
+        // their turn comes; all other lanes write where nobody reads.
+        const bool writes = (uint32_t)c < ring_end;
+        uint32_t elem = ring_at + 6u * (uint32_t)(c & (RC - 1));
+        asm volatile("" : "+v"(elem));         // scheduling only: no branch round its computation
+        ring_elem = reinterpret_cast<uint16_t*>(lds + (writes ? elem : (uint32_t)(D::kSinkOff + 4 * lane)));
+        gather_window(t + 1);
+    };
+    // the last step's pixel of the band's last two rows, for the band below
+    auto mail = [&](int t_done) __attribute__((always_inline)) {
+        if (j == 0 && q >= kBandRows - 2 && settle_active != 0)
+            __hip_atomic_store(mail_out + (size_t)(q - (kBandRows - 2)) * W + (t_done - kDelay * qrow), mail_px, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     };
 
     PhaseClock clk;
     clk.reset();
-    for (; t <= t_end; ++t) {
-        if ((t & 7) == 0 && misc[1] != 0) break;  // uniform: written before the last barrier; a late exit only decodes garbage
+    // The steps, for a wave of a given role.  Each role has a loop of its own: a taken branch costs up to a hundred cycles
+    // where four waves take it together (they all fetch from its target), so the loop has none but its own end.
+    auto steps = [&](auto role) __attribute__((always_inline)) {
+    using Role = decltype(role);
+    auto idle = [&](auto layer) __attribute__((always_inline)) {
+        constexpr int L = decltype(layer)::value;
+        if constexpr (D::kIdleInFirstLayer && L == 0) {
+            if constexpr (Role::kStores) store_read(t - 1);
+        } else {
+            if constexpr (Role::kFetches) { fetch_check(t); fetch_put(t); }
+            if constexpr (Role::kStores) {
+                if constexpr (!D::kIdleInFirstLayer) store_read(t - 1);
+                store_write(t - 1);
+            }
+        }
+    };
+    int stop = 0;       // has a band given up?  (set by the fetch wave before the first layer's barrier, read behind it)
+    do {
         clk.mark(kPhTop);
 
         // ---- gather C_ij from the ring (zeros stand for pixels outside the image); every wave builds the full tile
         u32x4_t in1[KB0][2];
         {
-            const int c = t - kDelay * (r0 + nl);
-            const int w0 = ((c - 2) & (RC - 1)) * 3;
-            // a run is four consecutive bf16 values of a ring row (8 bytes at a 2-byte aligned address): read as two
-            // dwords, which are the operand's registers as they stand
+            // a run is four consecutive bf16 values of a ring row: two dwords, which are the operand's registers as
+            // they stand
             uint32_t v[KB0][4];
 #pragma unroll
             for (int kbi = 0; kbi < KB0; ++kbi) {
-                uint2 lo, hi;
-                __builtin_memcpy(&lo, run_ptr[kbi][0] + w0, 8);
-                __builtin_memcpy(&hi, run_ptr[kbi][1] + w0, 8);
-                v[kbi][0] = lo.x; v[kbi][1] = lo.y; v[kbi][2] = hi.x; v[kbi][3] = hi.y;
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const uint32_t* run = reinterpret_cast<const uint32_t*>(lds + run_at[kbi][half] + window_at[run_odd[kbi][half] ? 1 : 0]);
+                    v[kbi][2 * half] = run[0];
+                    v[kbi][2 * half + 1] = run[1];
+                }
             }
+            asm volatile("" ::: "memory");
+            settle_pick();      // while the reads are under way
+            if constexpr (Role::kStores) mail(t - 1);
             // one batch of LDS reads
             static_assert(KB0 == 1 || KB0 == 2, "the scheduling barrier below lists the reads explicitly");
             if constexpr (KB0 == 1)
@@ -1524,7 +1611,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
 
         clk.mark(kPhGather);
         // ---- network, layers meeting in LDS
-        net.template run<(MINBLOCKS > 1)>(in1, lane, wave, wave_s, act0, act1, headout, idle, clk);
+        net.template run<Role::kOwnsLast>(in1, lane, wave, act0, act1, headout, idle, settle, clk);
 
         // ---- mixtures: lane j < 3K of pixel q prepares component j % K of channel j / K
         auto prepare = [&](int jj) __attribute__((always_inline)) {
@@ -1533,9 +1620,21 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
             float pk, mk, ak;
             if constexpr (K >= 5) {
                 // only this component's sigma and weight are computed (measured faster for K = 5, slower for K = 3)
+                // the channel's logits (for the softmax sum) and this component's own three values
+                constexpr int NV = (K + 3) / 4;
+                f32x4_t lv[NV];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) lv[i] = reinterpret_cast<const f32x4_t*>(hc)[i];
+                float logit_k = hc[k], mu_k = hc[K + k], ls_k = hc[2 * K + k];
+                // scheduling only: all reads are issued before the first is used (whole vectors, so that the registers of
+                // the padding are not wanted for the next read's address)
+                asm volatile("" : "+v"(lv[0]), "+v"(lv[NV - 1]), "+v"(logit_k), "+v"(mu_k), "+v"(ls_k));
                 float logits[K];
-                lds_read_floats<K>(hc, logits);                       // the channel's logits (for the softmax sum) ...
-                const float logit_k = hc[k], mu_k = hc[K + k], ls_k = hc[2 * K + k];   // ... and this component's own three values
+#pragma unroll
+                for (int i = 0; i < K; ++i) {
+                    const f32x4_t v = lv[i >> 2];
+                    logits[i] = (i & 3) == 0 ? v.x : (i & 3) == 1 ? v.y : (i & 3) == 2 ? v.z : v.w;
+                }
                 channel_setup_one<K>(logits, logit_k, mu_k, ls_k, lut_scale, pk, mk, ak);
             } else {
                 float raw[3 * K];
@@ -1594,61 +1693,68 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
             });
         };
         auto load_nothing = [&]() __attribute__((always_inline)) {};
+        auto load_stop = [&]() __attribute__((always_inline)) { stop = misc[1]; };
         load_cp(0, cpr, tail_r);
         asm volatile("" ::: "memory");
 
         clk.mark(kPhMixture);
-        const int c = t - kDelay * qrow;
-        const bool active = qrow_ok && c >= 0 && c < W;
         uint32_t start, freq;
+        Found found_r;
         // R
-        uint32_t slot = (uint32_t)rd.x & 0xFFFFu;
-        const int sr = group_search<K>(cpr, slot, lut, lane, start, freq, load_g);
-        reader_advance(rd, rd.x, slot, start, freq, j, active);
-        float rhat = (float)sr * (1.0f / 256.0f);
+        const int sr = group_search<K>(cpr, slot1_x, lut, sl, found_r, load_nothing, load_g);
+        float rhat = (float)sr;
+        ring_elem[0] = bf16_bits(rhat) & active;
+        Interval iv_r;
+        interval_pick(found_r, sl, iv_r);
+        rhat = rhat * (1.0f / 256.0f);
         clk.mark(kPhR);
-        // G given R
+        // G given R; meanwhile R's pop, whose state B is coded on
         asm volatile("" : "+v"(rhat) : "v"(tail_r), "v"(tail_g));    // (tied to a value known only now: stays here)
         couple_green<K>(cpg, alpha, rhat);
-        slot = (uint32_t)rd.y & 0xFFFFu;
-        const int sg = group_search<K>(cpg, slot, lut, lane, start, freq, load_b);
-        reader_advance(rd, rd.y, slot, start, freq, j, active);
-        float ghat = (float)sg * (1.0f / 256.0f);
+        auto pick_r_upper = [&]() __attribute__((always_inline)) { interval_pick_upper(found_r, sl, iv_r); };
+        auto pop_r = [&]() __attribute__((always_inline)) {
+            load_b();
+            interval_of(found_r, iv_r, start, freq);
+            reader_pop(rd, rd.x, start, freq, active);
+        };
+        const int sg = group_search<K>(cpg, slot1_y, lut, sl, found_g, pick_r_upper, pop_r);
+        float ghat = (float)sg;
+        ring_elem[1] = bf16_bits(ghat) & active;
+        ghat = ghat * (1.0f / 256.0f);
         clk.mark(kPhG);
         // B given R, G
         asm volatile("" : "+v"(ghat) : "v"(tail_b));
         couple_blue<K>(cpb, beta, gamma, rhat, ghat);
-        slot = (uint32_t)rd.x & 0xFFFFu;
-        const int sb = group_search<K>(cpb, slot, lut, lane, start, freq, load_nothing);
-        reader_advance(rd, rd.x, slot, start, freq, j, active);
-        reader_next_pixel(rd, active);
-        reader_refill(rd, j);
+        const int sb = group_search<K>(cpb, (float)(((uint32_t)rd.x & 0xFFFFu) + 1u), lut, sl, found_b, load_stop, load_nothing);
+        ring_elem[2] = bf16_bits((float)sb) & active;
         clk.mark(kPhB);
 
         // ---- publish
-        if (j == 0 && active) {
-            const uint32_t px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16);
-            ring_put(q + 2, c, px);
-            if (c == W - 1) {                       // the columns right of the image read as zero
-#pragma unroll
-                for (int z = 0; z < kMaxReach; ++z) ring_put(q + 2, W + z, 0u);
-            }
-            if constexpr (!kStoreInIdle) {
-                uint8_t* o = out_img + ((size_t)qrow * W + c) * 3;
+        if constexpr (!kStoreInIdle) {
+            if (j == 0 && active != 0) {
+                uint8_t* o = out_img + ((size_t)qrow * W + (t - kDelay * qrow)) * 3;
                 o[0] = (uint8_t)sr; o[1] = (uint8_t)sg; o[2] = (uint8_t)sb;
             }
-            if (q >= kBandRows - 2)
-                __hip_atomic_store(mail_out + (size_t)(q - (kBandRows - 2)) * W + c, px | kMailTag, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            if (c == W - 1 && (rd.bad || rd.x != kRansL || rd.y != kRansL || rd.pos != rd.nwords)) set_error(status, PCC_E_STREAM);
         }
-        if constexpr (kLateRequest) fetch_request(t);
+        mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
+        settle_active = active;
+        if constexpr (kLateRequest && Role::kFetches) fetch_request(t);
         clk.mark(kPhPublish);
         // ---- rows above the band, where no layer leaves the fetch wave spare time for it
-        if constexpr (D::kIdleSlack == 0) { fetch_check(t); fetch_put(t); }
+        if constexpr (D::kIdleSlack == 0 && Role::kFetches) { fetch_check(t); fetch_put(t); }
         clk.mark(kPhFetch);
         lds_barrier();
         clk.mark(kPhBarrier);
+        ++t;
+    } while (t <= t_end && __builtin_amdgcn_readfirstlane(stop) == 0);
+    };
+    if constexpr (D::kFetchWave == D::kStoreWave) {
+        if (wave_s != D::kStoreWave) steps(StepRole<false, false, true>());
+        else steps(StepRole<true, true, D::kStoreWave < D::kFirstIdleWave>());
+    } else {
+        if (wave_s < D::kFetchWave) steps(StepRole<false, false, true>());
+        else if (wave_s == D::kFetchWave) steps(StepRole<true, false, false>());
+        else steps(StepRole<false, true, false>());
     }
 #ifdef PCC_PHASE_TIMING
     if (ticket == min(kPhaseTicket, total_bands - 1) && lane == 0) {
@@ -1656,8 +1762,14 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         phase_cycles[wave][kPhCount] = (unsigned long long)(t_end - t_begin + 1);
     }
 #endif
-    if constexpr (kStoreInIdle) { store_read(t_end); store_write(t_end); }      // the last step's pixels (the loop ended behind a barrier)
+    if constexpr (kStoreInIdle) if (wave_s == D::kStoreWave) { store_read(t_end); store_write(t_end); }      // the last step's pixels (the loop ended behind a barrier)
     if (misc[1] != 0) break;    // uniform: written before the last barrier.  The call has failed; no further bands.
+    if (wave_s == D::kStoreWave) mail(t_end);
+    settle_pick();
+    settle_pick_upper();
+    settle_pops();
+    // every row's states are back where the coder started and its words are used up, neither more nor fewer
+    if (j == 0 && qrow_ok && (rd.bad || rd.x != kRansL || rd.y != kRansL || rd.pos != rd.nwords)) set_error(status, PCC_E_STREAM);
     }
 }
 

@@ -277,6 +277,9 @@ __device__ __forceinline__ uint32_t byte_to_bf16(uint32_t x) {
     return __float_as_uint((float)x) >> 16;
 }
 
+// The same of a float that holds such an integer.
+__device__ __forceinline__ uint16_t bf16_bits(float x) { return (uint16_t)(__float_as_uint(x) >> 16); }
+
 // Four bytes of a run -> four bf16 (two packed pairs): the upper halves of the fp32 conversions.
 __device__ __forceinline__ void run_to_bf16(uint32_t run, uint32_t& p01, uint32_t& p23) {
     const uint32_t sel = 0x07060302u;
@@ -491,26 +494,32 @@ __device__ __forceinline__ void couple_blue(ChanParams<K>& cp, const float (&bet
 // differences are exact, so one fma per lookup is non-decreasing in z; with
 // pi_k >= 0 every later step (fma, floor) keeps that, hence Cq is strictly
 // increasing in e and every symbol has frequency >= 1.
-// In two halves, so that a caller can put other memory requests between the table reads and their use:
-// cq_lookup computes the table coordinates and issues the reads, cq_finish interpolates, sums and rounds.
+// In two halves, so that a caller can put other work between the table reads and their use: cq_lookup computes the
+// table coordinates and issues the reads, cq_scaled interpolates, sums and scales.
 template <int K>
 struct CqLookup {
-    float t[K];
+    float frac[K];
     float2 td[K];
 };
 
+// edge: the bin edge's position (2 e - 1) / 512, exact for every e.
 template <int K>
-__device__ __forceinline__ void cq_lookup(const ChanParams<K>& cp, int e, const float2* __restrict__ lut, CqLookup<K>& q) {
-    const float edge = (float)(2 * e - 1) * (1.0f / 512.0f);
+__device__ __forceinline__ void cq_lookup(const ChanParams<K>& cp, float edge, const float2* __restrict__ lut, CqLookup<K>& q) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        q.t[k] = __builtin_amdgcn_fmed3f(__builtin_fmaf(edge - cp.mu[k], cp.a[k], kLutBias), 0.0f, kLutMax);
-        q.td[k] = lut[(int)q.t[k]];                                // t >= 0: truncation is floor
+        const float t = __builtin_amdgcn_fmed3f(__builtin_fmaf(edge - cp.mu[k], cp.a[k], kLutBias), 0.0f, kLutMax);
+        q.td[k] = lut[(int)t];                                     // t >= 0: truncation is floor
+        q.frac[k] = __builtin_amdgcn_fractf(t);
     }
+    // scheduling only: computed here, while the table reads are under way
+#pragma unroll
+    for (int k = 0; k < K; ++k) asm volatile("" : "+v"(q.frac[k]));
 }
 
+// 65280 min(sum, 1), whose floor is Cq(e) - e.  The sum is at least 0 and exceeds 1 by rounding at most; limited to
+// [0, 1] it costs nothing (the result modifier of the last fma), and 65280 times it is what min(65280 sum, 65280) is.
 template <int K>
-__device__ __forceinline__ uint32_t cq_finish(const ChanParams<K>& cp, int e, CqLookup<K>& q) {
+__device__ __forceinline__ float cq_scaled(const ChanParams<K>& cp, CqLookup<K>& q) {
     static_assert(K == 3 || K == 5 || K == 7, "the scheduling barrier below lists the table reads explicitly");
     float2 (&td)[K] = q.td;
     // Scheduling only: all table reads are in flight before the first is used
@@ -528,19 +537,17 @@ __device__ __forceinline__ uint32_t cq_finish(const ChanParams<K>& cp, int e, Cq
     float acc = 0.0f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const float phi = __builtin_fmaf(__builtin_amdgcn_fractf(q.t[k]), td[k].y, td[k].x);
+        const float phi = __builtin_fmaf(q.frac[k], td[k].y, td[k].x);
         acc = __builtin_fmaf(cp.pi[k], phi, acc);
     }
-    // acc >= 0: the conversion to an unsigned integer, which drops the fraction, is the floor
-    const float v = fminf(acc * 65280.0f, 65280.0f);
-    return (uint32_t)e + (uint32_t)v;
+    return __builtin_amdgcn_fmed3f(acc, 0.0f, 1.0f) * 65280.0f;
 }
 
 template <int K>
 __device__ __forceinline__ uint32_t cq_eval(const ChanParams<K>& cp, int e, const float2* __restrict__ lut) {
     CqLookup<K> q;
-    cq_lookup<K>(cp, e, lut, q);
-    return cq_finish<K>(cp, e, q);
+    cq_lookup<K>(cp, (float)(2 * e - 1) * (1.0f / 512.0f), lut, q);
+    return (uint32_t)e + (uint32_t)cq_scaled<K>(cp, q);       // not negative: the conversion's truncation is the floor
 }
 
 template <int K>
