@@ -815,7 +815,7 @@ struct DecLds {
     static constexpr int kRingOff = kCpOff + 16 * 3 * kCpStride * 4;
     static constexpr int kMiscOff = kRingOff + 18 * kRingRowElems * 2; // ticket, abort flag
     static constexpr int kSinkOff = kMiscOff + 16;                     // where lanes with no ring element to write write
-    static constexpr int kBytes = (kSinkOff + 64 * 4 + 8 + 15) / 16 * 16;
+    static constexpr int kBytes = (kSinkOff + 64 * 4 + 8 * Net::K + 15) / 16 * 16;
     // Two workgroups per CU have 256 registers per lane each, too few for the whole of a wave's weight slices: there
     // the biases, and the weights of the first layer and of the head where two workgroups' LDS then still fits a CU,
     // are kept in LDS behind the above and read when used.
@@ -998,25 +998,20 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
             __builtin_amdgcn_sched_barrier(0);      // the next block's instructions stay behind this one's
         }
     } else {
-        // One workgroup per CU: the wave's blocks advance together, k-block by k-block (hi of every block, then lo of
-        // every block: per output element the order stays bias, k-blocks in order, hi then lo).  A k-block's input is
-        // then wanted once per SLOTS x 2 MFMAs, which is the pace at which LDS delivers the layer's input to four
-        // waves reading at once; block after block, the first block's chain waited for every one of its reads.
+        // One workgroup per CU: block after block, too, but a block is finished (activation, split, store) among the MFMAs
+        // of the next one: two VALU instructions issue for free beside an MFMA (16 cycles; alone it would leave 8 idle).
+        // Only the last block's split is left at the end.  The first block's chain takes a k-block's input in 32 cycles,
+        // the pace at which LDS delivers it to four waves.
 #pragma unroll
-        for (int s = 0; s < kBlocks; ++s) acc[s] = wl.B(s, wave);
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-#pragma unroll
-            for (int s = 0; s < kBlocks; ++s) acc[s] = mfma16(wl.A(s, kb, wave), in[kb][0], acc[s]);
-            if (SPLIT_IN) {
-#pragma unroll
-                for (int s = 0; s < kBlocks; ++s) acc[s] = mfma16(wl.A(s, kb, wave), in[kb][1], acc[s]);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < kBlocks; ++s) asm volatile("" : "+v"(acc[s]));    // register allocation only, see chain()
+        for (int s = 0; s < kBlocks; ++s) chain(s, acc[s]);
 #pragma unroll
         for (int s = 0; s < kBlocks; ++s) finish(s, acc[s]);
+        // scheduling only
+#pragma unroll
+        for (int i = 0; i < kBlocks * NKB * (SPLIT_IN ? 2 : 1); ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+        }
     }
     if constexpr (kBlocks < SLOTS && RUN_IDLE) idle();
 }
@@ -1054,8 +1049,8 @@ struct WaveNet {
     }
     // OWNS_LAST: has this wave a block in the last round of the layers whose block count is no multiple of four?  (The
     // same waves have in all of them.)  idle: what a wave that has none does in its place.
-    // settle: work of every wave that nothing waits for before the searches; it goes where the matrix cores are busy and
-    // every wave computes blocks in every round: the last hidden layer.
+    // settle: work of every wave that nothing waits for before the searches, in parts for the layers; it goes between the
+    // MFMAs.
     template <bool OWNS_LAST, class Idle, class Settle>
     __device__ __forceinline__ void run(const u32x4_t (&in)[NKB][2], int lane, int wave, uint8_t* __restrict__ act0, uint8_t* __restrict__ act1,
                                         float* __restrict__ headout, Idle& idle, Settle& settle, PhaseClock& clk) const {
@@ -1081,29 +1076,22 @@ struct WaveNet {
                 if constexpr (SHARED) __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (kBlocks < SLOTS && kRunIdle) idle_here();
+            settle(std::integral_constant<int, L>());
             lds_barrier();
             clk.mark(kPhLayer0 + L);
         } else {
             uint8_t* out = (L & 1) ? act1 : act0;
-            static_assert(Net::kLayers >= 4, "the layer after the first is not the last hidden one");
-            if constexpr (L == 1 || L == Net::kLayers - 2) settle(std::integral_constant<bool, L == Net::kLayers - 2>());
+            settle(std::integral_constant<int, L>());
             dec_hidden_layer<NOB, NKB, SLOTS, kWLds, kBLds, (L > 0), Net::kLeaky, SHARED, OWNS_LAST, kRunIdle>(wl, lane, wave, in, out,
                                                                                                                idle_here);
-            if constexpr (L == Net::kLayers - 2 && !SHARED) {
-                // scheduling only: settle's instructions go between the MFMAs, three behind each
-#pragma unroll
-                for (int i = 0; i < SLOTS * NKB * 2; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
-                }
-            }
             lds_barrier();
             clk.mark(kPhLayer0 + L);
             u32x4_t nxt[Net::kb(L + 1)][2];
             dec_load_act<Net::kb(L + 1)>(out, lane, nxt);
             // scheduling only: every read of the layer's input is issued before its first MFMA, so
-            // the LDS latency is paid once per layer and not once per k-block
-            __builtin_amdgcn_sched_barrier(0);
+            // the LDS latency is paid once per layer and not once per k-block.  With two workgroups per CU the other one
+            // hides the latency, and the registers of 40 values are better spent otherwise (24 images 7.23 -> 7.06 ms).
+            if constexpr (!SHARED) __builtin_amdgcn_sched_barrier(0);
             rest.template run<OWNS_LAST>(nxt, lane, wave, act0, act1, headout, idle, settle, clk);
         }
     }
@@ -1147,14 +1135,15 @@ __device__ __forceinline__ int group_search(const ChanParams<K>& cp, float slot1
     asm volatile("" ::: "memory");
     during2();
     float limit2 = __builtin_fmaf(bf, -16.0f, slot1 - sl.e2);
-    asm volatile("" : "+v"(limit2) :: "memory");
+    found.next1 = (uint32_t)__builtin_amdgcn_update_dpp(65536, (int)((uint32_t)v1 + 16u * (uint32_t)sl.j), 0x101 /* row_shl:1 */,
+                                                        0xF, 0xF, false);
+    int first = 16 * b - 1;
+    asm volatile("" : "+v"(limit2), "+v"(found.next1), "+v"(first) :: "memory");
     const float v2 = cq_scaled<K>(cp, q2);
     found.count = __popcll((__ballot(v2 < limit2) >> sl.shift) & 0xFFFFull);
     found.b = b;
-    found.x = 16 * b + found.count - 1;
-    found.next1 = (uint32_t)__builtin_amdgcn_update_dpp(65536, (int)((uint32_t)v1 + 16u * (uint32_t)sl.j), 0x101 /* row_shl:1 */,
-                                                        0xF, 0xF, false);
-    found.c2 = (uint32_t)v2 + (uint32_t)(16 * b + sl.j);
+    found.x = first + found.count;
+    found.c2 = (uint32_t)v2 + (uint32_t)(first + 1 + sl.j);
     return found.x;
 }
 
@@ -1526,23 +1515,31 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         rd.x = rd.y;
         rd.y = x;
     };
-    auto settle = [&](auto last_hidden) __attribute__((always_inline)) {
-        if constexpr (!decltype(last_hidden)::value) { settle_pick_upper(); return; }
-        settle_pops();
-        typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
-        const u32x3_t next = __builtin_bit_cast(u32x3_t, __builtin_amdgcn_raw_buffer_load_b96(words, (int)(rd.at + 4u * rd.pos), 0, 0));
-        rd.w[0] = next.x; rd.w[1] = next.y; rd.w[2] = next.z;
-        slot1_x = (float)(((uint32_t)rd.x & 0xFFFFu) + 1u);
-        slot1_y = (float)(((uint32_t)rd.y & 0xFFFFu) + 1u);
-        const int c = t - kDelay * qrow;
-        active = mask_of((uint32_t)c < row_end);
-        // Lanes 0 to 3 of a pixel write its four places; the columns right of the image are written as zeros when
-        // their turn comes; all other lanes write where nobody reads.
-        const bool writes = (uint32_t)c < ring_end;
-        uint32_t elem = ring_at + 6u * (uint32_t)(c & (RC - 1));
-        asm volatile("" : "+v"(elem));         // scheduling only: no branch round its computation
-        ring_elem = reinterpret_cast<uint16_t*>(lds + (writes ? elem : (uint32_t)(D::kSinkOff + 4 * lane)));
-        gather_window(t + 1);
+    auto settle = [&](auto layer) __attribute__((always_inline)) {
+        constexpr int L = decltype(layer)::value;
+        if constexpr (L == 0) settle_pick_upper();
+        if constexpr (L == 1) {
+            settle_pops();
+            typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
+            const u32x3_t next = __builtin_bit_cast(u32x3_t, __builtin_amdgcn_raw_buffer_load_b96(words, (int)(rd.at + 4u * rd.pos), 0, 0));
+            rd.w[0] = next.x; rd.w[1] = next.y; rd.w[2] = next.z;
+        }
+        if constexpr (L == Net::kLayers - 1) {
+            slot1_x = (float)(((uint32_t)rd.x & 0xFFFFu) + 1u);
+            slot1_y = (float)(((uint32_t)rd.y & 0xFFFFu) + 1u);
+            const int c = t - kDelay * qrow;
+            active = mask_of((uint32_t)c < row_end);
+            // Lanes 0 to 3 of a pixel write its four places; the columns right of the image are written as zeros when
+            // their turn comes; all other lanes write where nobody reads.
+            const bool writes = (uint32_t)c < ring_end;
+            uint32_t elem = ring_at + 6u * (uint32_t)(c & (RC - 1));
+            asm volatile("" : "+v"(elem));         // scheduling only: no branch round its computation
+            elem = writes ? elem : (uint32_t)(D::kSinkOff + 4 * lane);
+            gather_window(t + 1);
+            // scheduling only: done here
+            asm volatile("" : "+v"(slot1_x), "+v"(slot1_y), "+v"(elem), "+v"(window_at[0]), "+v"(window_at[1]));
+            ring_elem = reinterpret_cast<uint16_t*>(lds + elem);
+        }
     };
     // the last step's pixel of the band's last two rows, for the band below
     auto mail = [&](int t_done) __attribute__((always_inline)) {
@@ -1591,6 +1588,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
             asm volatile("" ::: "memory");
             settle_pick();      // while the reads are under way
             if constexpr (Role::kStores) mail(t - 1);
+            __builtin_amdgcn_sched_barrier(0);      // scheduling only: the lane picks are asked for before the reads are waited for
             // one batch of LDS reads
             static_assert(KB0 == 1 || KB0 == 2, "the scheduling barrier below lists the reads explicitly");
             if constexpr (KB0 == 1)
@@ -1645,11 +1643,11 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
 #pragma unroll
                 for (int kk = 1; kk < K; ++kk) if (k == kk) { pk = all.pi[kk]; mk = all.mu[kk]; ak = all.a[kk]; }
             }
-            float* dst = cpbuf + (q * 3 + ch) * D::kCpStride + k;
+            float* dst = jj < 3 * K ? cpbuf + (q * 3 + ch) * D::kCpStride + k : reinterpret_cast<float*>(lds + D::kSinkOff + 4 * lane);
             dst[0] = pk; dst[K] = mk; dst[2 * K] = ak;
         };
         if constexpr (3 * K <= 16) {
-            if (j < 3 * K) prepare(j);
+            prepare(j);        // (lanes without a component prepare what nobody reads: no branch)
         } else {
             for (int jj = j; jj < 3 * K; jj += 16) prepare(jj);      // two passes for the first lanes
         }
@@ -1716,6 +1714,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
             load_b();
             interval_of(found_r, iv_r, start, freq);
             reader_pop(rd, rd.x, start, freq, active);
+            asm volatile("" : "+v"(rd.x), "+v"(rd.w[0]), "+v"(rd.w[1]), "+v"(rd.pos));     // scheduling only: done here
         };
         const int sg = group_search<K>(cpg, slot1_y, lut, sl, found_g, pick_r_upper, pop_r);
         float ghat = (float)sg;
@@ -1730,14 +1729,15 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         clk.mark(kPhB);
 
         // ---- publish
+        mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
+        settle_active = active;
+        asm volatile("" : "+v"(found_b.c2), "+v"(mail_px), "+v"(settle_active));   // scheduling only: while the ring is written
         if constexpr (!kStoreInIdle) {
             if (j == 0 && active != 0) {
                 uint8_t* o = out_img + ((size_t)qrow * W + (t - kDelay * qrow)) * 3;
                 o[0] = (uint8_t)sr; o[1] = (uint8_t)sg; o[2] = (uint8_t)sb;
             }
         }
-        mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
-        settle_active = active;
         if constexpr (kLateRequest && Role::kFetches) fetch_request(t);
         clk.mark(kPhPublish);
         // ---- rows above the band, where no layer leaves the fetch wave spare time for it

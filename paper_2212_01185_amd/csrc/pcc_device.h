@@ -53,11 +53,11 @@ struct NetWorkload {
     static constexpr bool kLeaky = false;
     // Decoder with two workgroups per CU (256 registers per lane each): what of a wave's weight slices is then read
     // from a copy in LDS instead of held in registers, chosen by measurement (batches of 24 and 48 images of 768x512;
-    // 24 images: none 7.21 ms, first layer 7.00, head 6.95, both 7.24, both and the biases 7.59): LDS copies cost
-    // time too, so a few spilled registers can be the better deal.  1: the biases, 2: the first layer's weights,
-    // 4: the head's.
+    // 24 images: none 8.39 ms, first layer 8.05, head 7.60, head and biases 7.49, first layer and head 7.23, all 7.51): LDS
+    // copies cost time too, so a few spilled registers can be the better deal.  1: the biases, 2: the first layer's
+    // weights, 4: the head's.
     static constexpr int kEncodeVariant = 1;      // pixel kernel: two tiles per work item, 512 threads (index into the host's table)
-    static constexpr int kSharedCuLds = 4;
+    static constexpr int kSharedCuLds = 6;
     // Time of a decode step when both workgroups of a CU are busy, in percent of a step of a workgroup that has its
     // CU alone (measured the same way; the host chooses between the two launches with it).
     static constexpr unsigned kSharedStepPercent = 150;
@@ -96,7 +96,7 @@ struct NetPaper {
     static constexpr int kRingPad = 4;
     static constexpr bool kLeaky = true;
     static constexpr int kEncodeVariant = 1;
-    static constexpr int kSharedCuLds = 4;      // 24 images of 768x512: none 8.75 ms, first layer 8.78, head 8.61, both 8.68
+    static constexpr int kSharedCuLds = 4;      // 24 images of 768x512: none 8.04 ms, first layer 7.61, head 7.34, both 7.61
     static constexpr unsigned kSharedStepPercent = 145;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
