@@ -1118,27 +1118,38 @@ struct Found {
     int b, count, x;           // block, lanes that passed in the second sweep, the symbol 16 b + count - 1
 };
 
+// Scheduling only: the fractions are computed here.
+template <int K>
+__device__ __forceinline__ void pin(CqLookup<K>& q) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) asm volatile("" : "+v"(q.t[k]));
+}
+
 // during1(), during2(): called when a sweep's table reads are issued; memory requests made there queue behind them.
 template <int K, class During1, class During2>
 __device__ __forceinline__ int group_search(const ChanParams<K>& cp, float slot1, const float2* __restrict__ lut, const SearchLane& sl,
                                             Found& found, During1&& during1, During2&& during2) {
     CqLookup<K> q1, q2;
     cq_lookup<K>(cp, sl.edge1, lut, q1);
-    asm volatile("" ::: "memory");           // ordering of memory requests only: the table reads first
+    __builtin_amdgcn_sched_barrier(0);       // scheduling only: the table reads first, then what they leave time for
     during1();
+    cq_fractions<K>(q1);
     float limit1 = slot1 - sl.e1;
-    asm volatile("" : "+v"(limit1) :: "memory");      // (computed before the table reads are waited for)
+    asm volatile("" : "+v"(limit1) :: "memory");
+    pin<K>(q1);
     const float v1 = cq_scaled<K>(cp, q1);
     const int b = __popcll((__ballot(v1 < limit1) >> sl.shift) & 0xFFFFull) - 1;
     const float bf = (float)b;
     cq_lookup<K>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2);
-    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     during2();
+    cq_fractions<K>(q2);
     float limit2 = __builtin_fmaf(bf, -16.0f, slot1 - sl.e2);
     found.next1 = (uint32_t)__builtin_amdgcn_update_dpp(65536, (int)((uint32_t)v1 + 16u * (uint32_t)sl.j), 0x101 /* row_shl:1 */,
                                                         0xF, 0xF, false);
     int first = 16 * b - 1;
     asm volatile("" : "+v"(limit2), "+v"(found.next1), "+v"(first) :: "memory");
+    pin<K>(q2);
     const float v2 = cq_scaled<K>(cp, q2);
     found.count = __popcll((__ballot(v2 < limit2) >> sl.shift) & 0xFFFFull);
     found.b = b;
@@ -1289,7 +1300,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     }
     for (int i = tid; i < 18 * D::kRingRowElems; i += kDecThreads) ring[i] = 0;
     __syncthreads();
-    const int ticket = misc[0];
+    const int ticket = __builtin_amdgcn_readfirstlane(misc[0]);
     first_band = false;
     if (ticket >= total_bands) break;
     const int band = ticket / n, im = ticket - band * n;
@@ -1451,25 +1462,27 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     // The pixels decoded in step t_done go from the ring (which holds a pixel for kRingCols steps, as three bf16 of
     // its bytes) to the image: by the 16 first lanes of the storing wave, a lane per row of the band, a step later,
     // where that wave has no out-block to compute, instead of by the lanes that decoded them at the end of their
-    // step, where all four waves would wait for it.  Again in two halves: the ring read, then the stores.
+    // step, where all four waves would wait for it.  Again in two halves: the ring read, then the stores.  The image is
+    // addressed as a buffer: lanes and columns without a pixel store beyond its end, which the hardware drops.
     uint16_t held[3] = {0, 0, 0};
+    const auto image = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, 3 * H * W, 0x00020000 /* untyped */);
+    const uint16_t* held_at = ring + ((lane & 15) + 2) * D::kRingRowElems;
+    const uint32_t store_end = lane < kBandRows && r0 + lane < H ? (uint32_t)W : 0u;
     auto store_read = [&](int t_done) __attribute__((always_inline)) {
-        if (lane < kBandRows) {
-            const int cc = t_done - kDelay * (r0 + lane);
-            const uint16_t* e = ring + (lane + 2) * D::kRingRowElems + (cc & (RC - 1)) * 3;
+        const int cc = t_done - kDelay * (r0 + lane);
+        const uint16_t* e = held_at + (cc & (RC - 1)) * 3;
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) held[ch] = e[ch];
-        }
+        for (int ch = 0; ch < 3; ++ch) held[ch] = e[ch];
     };
     auto store_write = [&](int t_done) __attribute__((always_inline)) {
-        if (lane < kBandRows) {
-            const int row = r0 + lane, cc = t_done - kDelay * row;
-            if (row < H && cc >= 0 && cc < W) {
-                uint8_t* o = out_img + ((size_t)row * W + cc) * 3;
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) o[ch] = (uint8_t)(uint32_t)__uint_as_float((uint32_t)held[ch] << 16);
-            }
-        }
+        const int cc = t_done - kDelay * (r0 + lane);
+        uint32_t at = 3u * (uint32_t)((r0 + lane) * W + cc);
+        asm volatile("" : "+v"(at));        // scheduling only: no branch round its computation
+        at = (uint32_t)cc < store_end ? at : 0xFFFFFFF0u;
+        const uint32_t x0 = (uint32_t)__uint_as_float((uint32_t)held[0] << 16), x1 = (uint32_t)__uint_as_float((uint32_t)held[1] << 16),
+                       x2 = (uint32_t)__uint_as_float((uint32_t)held[2] << 16);
+        __builtin_amdgcn_raw_buffer_store_b16((short)(x0 | (x1 << 8)), image, (int)at, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b8((char)x2, image, (int)at, 2, 0);
     };
     constexpr bool kStoreInIdle = D::kIdleSlack > 0;
     int t = t_begin;
@@ -1567,28 +1580,31 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         }
     };
     int stop = 0;       // has a band given up?  (set by the fetch wave before the first layer's barrier, read behind it)
+    // Gather C_ij from the ring (zeros stand for pixels outside the image), for the step's tile of 16 pixels; every wave
+    // builds the full tile.  A run is four consecutive bf16 values of a ring row: two dwords, which are the operand's
+    // registers as they stand.
+    uint32_t v[KB0][4];
+    auto gather = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int kbi = 0; kbi < KB0; ++kbi) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const uint32_t* run = reinterpret_cast<const uint32_t*>(lds + run_at[kbi][half] + window_at[run_odd[kbi][half] ? 1 : 0]);
+                v[kbi][2 * half] = run[0];
+                v[kbi][2 * half + 1] = run[1];
+            }
+        }
+        asm volatile("" ::: "memory");
+        settle_pick();
+        __builtin_amdgcn_sched_barrier(0);      // scheduling only: all of these are asked for before any is waited for
+    };
     do {
         clk.mark(kPhTop);
+        gather();
 
-        // ---- gather C_ij from the ring (zeros stand for pixels outside the image); every wave builds the full tile
         u32x4_t in1[KB0][2];
         {
-            // a run is four consecutive bf16 values of a ring row: two dwords, which are the operand's registers as
-            // they stand
-            uint32_t v[KB0][4];
-#pragma unroll
-            for (int kbi = 0; kbi < KB0; ++kbi) {
-#pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const uint32_t* run = reinterpret_cast<const uint32_t*>(lds + run_at[kbi][half] + window_at[run_odd[kbi][half] ? 1 : 0]);
-                    v[kbi][2 * half] = run[0];
-                    v[kbi][2 * half + 1] = run[1];
-                }
-            }
-            asm volatile("" ::: "memory");
-            settle_pick();      // while the reads are under way
             if constexpr (Role::kStores) mail(t - 1);
-            __builtin_amdgcn_sched_barrier(0);      // scheduling only: the lane picks are asked for before the reads are waited for
             // one batch of LDS reads
             static_assert(KB0 == 1 || KB0 == 2, "the scheduling barrier below lists the reads explicitly");
             if constexpr (KB0 == 1)
@@ -1649,7 +1665,8 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         if constexpr (3 * K <= 16) {
             prepare(j);        // (lanes without a component prepare what nobody reads: no branch)
         } else {
-            for (int jj = j; jj < 3 * K; jj += 16) prepare(jj);      // two passes for the first lanes
+            prepare(j);
+            prepare(j + 16);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
         __builtin_amdgcn_wave_barrier();
@@ -1746,7 +1763,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         lds_barrier();
         clk.mark(kPhBarrier);
         ++t;
-    } while (t <= t_end && __builtin_amdgcn_readfirstlane(stop) == 0);
+    } while (((int)(t <= t_end) & (int)(__builtin_amdgcn_readfirstlane(stop) == 0)) != 0);
     };
     if constexpr (D::kFetchWave == D::kStoreWave) {
         if (wave_s != D::kStoreWave) steps(StepRole<false, false, true>());

@@ -494,26 +494,30 @@ __device__ __forceinline__ void couple_blue(ChanParams<K>& cp, const float (&bet
 // differences are exact, so one fma per lookup is non-decreasing in z; with
 // pi_k >= 0 every later step (fma, floor) keeps that, hence Cq is strictly
 // increasing in e and every symbol has frequency >= 1.
-// In two halves, so that a caller can put other work between the table reads and their use: cq_lookup computes the
-// table coordinates and issues the reads, cq_scaled interpolates, sums and scales.
+// In three parts, so that a caller can put other work between the table reads and their use: cq_lookup computes the
+// table coordinates and issues the reads, cq_fractions needs the coordinates alone, cq_scaled interpolates, sums and scales.
 template <int K>
 struct CqLookup {
-    float frac[K];
+    float t[K];
     float2 td[K];
 };
 
-// edge: the bin edge's position (2 e - 1) / 512, exact for every e.
+// edge: the bin edge's position (2 e - 1) / 512, exact for every e. 
 template <int K>
 __device__ __forceinline__ void cq_lookup(const ChanParams<K>& cp, float edge, const float2* __restrict__ lut, CqLookup<K>& q) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const float t = __builtin_amdgcn_fmed3f(__builtin_fmaf(edge - cp.mu[k], cp.a[k], kLutBias), 0.0f, kLutMax);
-        q.td[k] = lut[(int)t];                                     // t >= 0: truncation is floor
-        q.frac[k] = __builtin_amdgcn_fractf(t);
+        q.t[k] = __builtin_amdgcn_fmed3f(__builtin_fmaf(edge - cp.mu[k], cp.a[k], kLutBias), 0.0f, kLutMax);
+        const uint32_t i = (uint32_t)(int)q.t[k];                  // t >= 0: truncation is floor
+        q.td[k] = lut[i];
     }
-    // scheduling only: computed here, while the table reads are under way
+}
+
+// What can be done while the reads are under way: t becomes its fraction.
+template <int K>
+__device__ __forceinline__ void cq_fractions(CqLookup<K>& q) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) asm volatile("" : "+v"(q.frac[k]));
+    for (int k = 0; k < K; ++k) q.t[k] = __builtin_amdgcn_fractf(q.t[k]);
 }
 
 // 65280 min(sum, 1), whose floor is Cq(e) - e.  The sum is at least 0 and exceeds 1 by rounding at most; limited to
@@ -537,7 +541,7 @@ __device__ __forceinline__ float cq_scaled(const ChanParams<K>& cp, CqLookup<K>&
     float acc = 0.0f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const float phi = __builtin_fmaf(q.frac[k], td[k].y, td[k].x);
+        const float phi = __builtin_fmaf(q.t[k], td[k].y, td[k].x);
         acc = __builtin_fmaf(cp.pi[k], phi, acc);
     }
     return __builtin_amdgcn_fmed3f(acc, 0.0f, 1.0f) * 65280.0f;
@@ -547,6 +551,7 @@ template <int K>
 __device__ __forceinline__ uint32_t cq_eval(const ChanParams<K>& cp, int e, const float2* __restrict__ lut) {
     CqLookup<K> q;
     cq_lookup<K>(cp, (float)(2 * e - 1) * (1.0f / 512.0f), lut, q);
+    cq_fractions<K>(q);
     return (uint32_t)e + (uint32_t)cq_scaled<K>(cp, q);       // not negative: the conversion's truncation is the floor
 }
 
