@@ -797,7 +797,7 @@ struct DecLds {
     static constexpr int kHS = Layout<Net>::kHeadSlots;
     static constexpr int kActBytes = max_kb() * 2 * 64 * 16;           // one layer's activations: [k-block][hi,lo][lane][16 B]
     static constexpr int kLutOff = 0;
-    static constexpr int kAct0Off = (kLutEntries + 1) * 8;
+    static constexpr int kAct0Off = (kSpreadLutBytes + 15) / 16 * 16;
     static constexpr int kAct1Off = kAct0Off + kActBytes;
     // Strides in floats, padded by one 16-byte vector: consecutive pixels (and channels) then start
     // four LDS banks apart instead of on the same bank.
@@ -1130,7 +1130,7 @@ template <int K, class During1, class During2>
 __device__ __forceinline__ int group_search(const ChanParams<K>& cp, float slot1, const float2* __restrict__ lut, const SearchLane& sl,
                                             Found& found, During1&& during1, During2&& during2) {
     CqLookup<K> q1, q2;
-    cq_lookup<K>(cp, sl.edge1, lut, q1);
+    cq_lookup<K, true>(cp, sl.edge1, lut, q1);
     __builtin_amdgcn_sched_barrier(0);       // scheduling only: the table reads first, then what they leave time for
     during1();
     cq_fractions<K>(q1);
@@ -1140,7 +1140,7 @@ __device__ __forceinline__ int group_search(const ChanParams<K>& cp, float slot1
     const float v1 = cq_scaled<K>(cp, q1);
     const int b = __popcll((__ballot(v1 < limit1) >> sl.shift) & 0xFFFFull) - 1;
     const float bf = (float)b;
-    cq_lookup<K>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2);
+    cq_lookup<K, true>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2);
     __builtin_amdgcn_sched_barrier(0);
     during2();
     cq_fractions<K>(q2);
@@ -1233,7 +1233,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
 
     {
         const float2* src = reinterpret_cast<const float2*>(model + Lay::kLutOff);
-        for (int i = tid; i < kLutEntries + 1; i += kDecThreads) lut[i] = src[i];
+        for (int i = tid; i < kLutEntries + 1; i += kDecThreads) *reinterpret_cast<float2*>(lds + D::kLutOff + spread_at((uint32_t)i)) = src[i];
     }
     if constexpr (MINBLOCKS > 1) {
         auto stage = [&](int dst_off, int src_off, int bytes) {

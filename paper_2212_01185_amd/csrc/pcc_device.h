@@ -502,14 +502,26 @@ struct CqLookup {
     float2 td[K];
 };
 
-// edge: the bin edge's position (2 e - 1) / 512, exact for every e. 
-template <int K>
+// Where entry i of the table lies in a copy of kSpreadLutBytes with 16 free bytes behind every 16 entries.  The decoder's
+// 16 lanes of a pixel look up entries that lie equally far apart, and where that is a multiple of eight entries (eight for
+// sigma = 1, the first sweep), four LDS banks would serve all of them.
+__host__ __device__ constexpr uint32_t spread_at(uint32_t i) { return 8u * i + (i & ~15u); }
+constexpr int kSpreadLutBytes = (int)spread_at(kLutEntries) + 8;
+
+// edge: the bin edge's position (2 e - 1) / 512, exact for every e.  SPREAD: the table is such a copy, at LDS address 0
+// (an address the compiler knows: two instructions a look-up, a base it does not know would make it three).
+template <int K, bool SPREAD = false>
 __device__ __forceinline__ void cq_lookup(const ChanParams<K>& cp, float edge, const float2* __restrict__ lut, CqLookup<K>& q) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         q.t[k] = __builtin_amdgcn_fmed3f(__builtin_fmaf(edge - cp.mu[k], cp.a[k], kLutBias), 0.0f, kLutMax);
         const uint32_t i = (uint32_t)(int)q.t[k];                  // t >= 0: truncation is floor
-        q.td[k] = lut[i];
+        if constexpr (SPREAD) {
+            const f32x2_t v = *(const __attribute__((address_space(3))) f32x2_t*)(spread_at(i));
+            q.td[k].x = v.x; q.td[k].y = v.y;
+        } else {
+            q.td[k] = lut[i];
+        }
     }
 }
 
