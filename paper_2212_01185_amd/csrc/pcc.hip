@@ -206,6 +206,7 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
     const int lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar: the item's row and strip are scalars too
     const int g = lane >> 4, nl = lane & 15;
+    const bf16x4_bits_t minus_one = minus_identity(lane);
     const uint32_t rows = (uint32_t)n * (uint32_t)H;
     const uint32_t P = rows * (uint32_t)W;
     const uint32_t items = strip_count * rows;              // this launch's strips: strip_begin .. strip_begin + strip_count - 1
@@ -269,7 +270,7 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
             }
         }
         f32x4_t out[T][Lay::kHeadOB];
-        mlp_from<Net, T, (T == 1 && THREADS <= 512), 0, RESIDENT>(lds + opaque_zero(), model, lane, in, out);
+        mlp_from<Net, T, (T == 1 && THREADS <= 512), 0, RESIDENT>(lds + opaque_zero(), model, lane, minus_one, in, out);
         // The head's results are first read behind branches (which outputs are wanted, border tiles).  The wait
         // states an MFMA's result needs are counted along the instruction stream as laid out, not along a taken
         // branch, so the accumulators are made to settle here, in straight-line code.
@@ -965,16 +966,25 @@ struct WaveLayer {
 template <int NOB, int NKB, int SLOTS, bool W_LDS, bool B_LDS, bool SPLIT_IN, bool LEAKY, bool ONE_BY_ONE, bool OWNS_LAST, bool RUN_IDLE,
           class Idle>
 __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS, W_LDS, B_LDS>& wl, int lane, int wave,
-                                                 const u32x4_t (&in)[NKB][2], uint8_t* __restrict__ act_out, Idle& idle) {
+                                                 bf16x4_bits_t minus_one, const u32x4_t (&in)[NKB][2], uint8_t* __restrict__ act_out, Idle& idle) {
     auto finish = [&](int s, const f32x4_t& acc) {
         const int ob = wave + 4 * s;
-        uint32_t l0, l1;
-        const uint32_t h0 = act_split_bf16<LEAKY>(acc.x, acc.y, l0);
-        const uint32_t h1 = act_split_bf16<LEAKY>(acc.z, acc.w, l1);
+        u32x2_t hi, lo;
+        // The matrix core's subtraction saves issue slots and adds its latency to the step.  It is the faster one where two
+        // workgroups share the slots (24 images of 768x512 6.30 -> 6.23 ms) and with LeakyReLU (512x512 of the paper's shape
+        // 5.39 -> 5.31), the slower one for a workgroup alone with ReLU (768x512 4.69 -> 4.75).
+        if constexpr (ONE_BY_ONE || LEAKY) {
+            act_split4_bf16<LEAKY>(acc, minus_one, hi, lo);
+        } else {
+            uint32_t l0, l1;
+            hi.x = act_split_bf16<LEAKY>(acc.x, acc.y, l0);
+            hi.y = act_split_bf16<LEAKY>(acc.z, acc.w, l1);
+            lo.x = l0; lo.y = l1;
+        }
         // out-block ob is half (ob & 1) of k-block ob/2 of the next layer's operand
         uint8_t* dst = act_out + (((ob >> 1) * 2) * 64 + lane) * 16 + 8 * (ob & 1);
-        *reinterpret_cast<uint2*>(dst) = make_uint2(h0, h1);
-        *reinterpret_cast<uint2*>(dst + 64 * 16) = make_uint2(l0, l1);
+        *reinterpret_cast<u32x2_t*>(dst) = hi;
+        *reinterpret_cast<u32x2_t*>(dst + 64 * 16) = lo;
     };
     auto chain = [&](int s, f32x4_t& acc) {
         acc = wl.B(s, wave);
@@ -1008,7 +1018,7 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
         for (int s = 0; s < kBlocks; ++s) finish(s, acc[s]);
         // scheduling only
 #pragma unroll
-        for (int i = 0; i < kBlocks * NKB * (SPLIT_IN ? 2 : 1); ++i) {
+        for (int i = 0; i < kBlocks * (NKB * (SPLIT_IN ? 2 : 1) + (LEAKY ? 1 : 0)); ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
         }
@@ -1052,7 +1062,7 @@ struct WaveNet {
     // settle: work of every wave that nothing waits for before the searches, in parts for the layers; it goes between the
     // MFMAs.
     template <bool OWNS_LAST, class Idle, class Settle>
-    __device__ __forceinline__ void run(const u32x4_t (&in)[NKB][2], int lane, int wave, uint8_t* __restrict__ act0, uint8_t* __restrict__ act1,
+    __device__ __forceinline__ void run(const u32x4_t (&in)[NKB][2], int lane, int wave, bf16x4_bits_t minus_one, uint8_t* __restrict__ act0, uint8_t* __restrict__ act1,
                                         float* __restrict__ headout, Idle& idle, Settle& settle, PhaseClock& clk) const {
         // what waves without an out-block in this layer's last round do instead (decode_kernel says what)
         constexpr bool kRunIdle = DecLds<Net>::kIdleSlack > 0 &&
@@ -1082,7 +1092,7 @@ struct WaveNet {
         } else {
             uint8_t* out = (L & 1) ? act1 : act0;
             settle(std::integral_constant<int, L>());
-            dec_hidden_layer<NOB, NKB, SLOTS, kWLds, kBLds, (L > 0), Net::kLeaky, SHARED, OWNS_LAST, kRunIdle>(wl, lane, wave, in, out,
+            dec_hidden_layer<NOB, NKB, SLOTS, kWLds, kBLds, (L > 0), Net::kLeaky, SHARED, OWNS_LAST, kRunIdle>(wl, lane, wave, minus_one, in, out,
                                                                                                                idle_here);
             lds_barrier();
             clk.mark(kPhLayer0 + L);
@@ -1092,7 +1102,7 @@ struct WaveNet {
             // the LDS latency is paid once per layer and not once per k-block.  With two workgroups per CU the other one
             // hides the latency, and the registers of 40 values are better spent otherwise (24 images 7.23 -> 7.06 ms).
             if constexpr (!SHARED) __builtin_amdgcn_sched_barrier(0);
-            rest.template run<OWNS_LAST>(nxt, lane, wave, act0, act1, headout, idle, settle, clk);
+            rest.template run<OWNS_LAST>(nxt, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
         }
     }
 };
@@ -1222,6 +1232,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     const int wave_s = __builtin_amdgcn_readfirstlane(tid >> 6);     // for branches that whole waves take
     // network role: pixel nl of the tile, k-slot group g
     const int g = lane >> 4, nl = lane & 15;
+    const bf16x4_bits_t minus_one = minus_identity(lane);
     // search role: pixel q of the band, lane j of its group
     const int q = 4 * wave + (lane >> 4), j = lane & 15;
     SearchLane sl;
@@ -1625,7 +1636,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
 
         clk.mark(kPhGather);
         // ---- network, layers meeting in LDS
-        net.template run<Role::kOwnsLast>(in1, lane, wave, act0, act1, headout, idle, settle, clk);
+        net.template run<Role::kOwnsLast>(in1, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
 
         // ---- mixtures: lane j < 3K of pixel q prepares component j % K of channel j / K
         auto prepare = [&](int jj) __attribute__((always_inline)) {

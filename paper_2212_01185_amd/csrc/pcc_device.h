@@ -19,6 +19,7 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------
 // Network descriptions.  Tiles are v_mfma_f32_16x16x32_bf16: out-blocks of 16
@@ -249,8 +250,6 @@ __host__ __device__ constexpr int kslot_feature(int g, int i) { return 16 * (i >
 // hi = bf16(a), lo = bf16(a - hi) (both round to nearest even): 16 significant
 // bits, so that the bf16 matrix cores reproduce the fp32 network to ~1e-5
 // instead of ~1e-2.  Each weight tile is multiplied with hi and then with lo.
-// Applies the activation (ReLU, or LeakyReLU with slope 0.01) to two values and
-// packs them: returns the hi pair, writes the lo pair.
 // ReLU as a signed integer maximum of the bit pattern (negative floats are negative
 // integers), LeakyReLU as the median of {a, 0.01 a, +inf}: one instruction each, where
 // fmaxf() would first re-canonicalise its operand.  Inputs are finite.
@@ -260,6 +259,18 @@ __device__ __forceinline__ float activation(float a) {
     else return __int_as_float(max(__float_as_int(a), 0));
 }
 
+typedef short bf16x4_bits_t __attribute__((ext_vector_type(4)));
+
+// This lane's row of minus the 4x4 identity (rows repeat every four lanes), as bf16: the A operand of act_split4_bf16.
+__device__ __forceinline__ bf16x4_bits_t minus_identity(int lane) {
+    const uint32_t one = 0xBF80u;                                    // -1
+    u32x2_t v = {(lane & 2) ? 0u : ((lane & 1) ? one << 16 : one), (lane & 2) ? ((lane & 1) ? one << 16 : one) : 0u};
+    asm volatile("" : "+v"(v));                                      // held in two registers, not made again where it is used
+    return __builtin_bit_cast(bf16x4_bits_t, v);
+}
+
+// Applies the activation (ReLU, or LeakyReLU with slope 0.01) to two values and
+// packs them: returns the hi pair, writes the lo pair.
 template <bool LEAKY>
 __device__ __forceinline__ uint32_t act_split_bf16(float a0, float a1, uint32_t& lo_pair) {
     a0 = activation<LEAKY>(a0);
@@ -269,6 +280,24 @@ __device__ __forceinline__ uint32_t act_split_bf16(float a0, float a1, uint32_t&
     const f32x2_t r = {a0 - __uint_as_float(hi << 16), a1 - __uint_as_float(hi & 0xFFFF0000u)};
     lo_pair = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
     return hi;
+}
+
+// The same for four values, with the subtractions on the matrix core: hi pairs and lo pairs.
+// a - hi is one v_mfma_f32_4x4x4_16b_bf16, whose 16 blocks multiply, lane by lane, the lane's own four bf16 values with a
+// 4x4 matrix: C - I hi, exact as the subtraction is (one product is not zero, and the difference has no more bits than a).
+// Expanding hi and subtracting took eight vector instructions, a shift among them at half rate: 28 cycles for two waves
+// of a SIMD against 8.3, and some 8 more where the matrix core changes between the two shapes.
+template <bool LEAKY>
+__device__ __forceinline__ void act_split4_bf16(const f32x4_t& acc, bf16x4_bits_t minus_one, u32x2_t& hi, u32x2_t& lo) {
+    const f32x4_t a = {activation<LEAKY>(acc.x), activation<LEAKY>(acc.y), activation<LEAKY>(acc.z), activation<LEAKY>(acc.w)};
+    const f32x2_t a01 = {a.x, a.y}, a23 = {a.z, a.w};
+    hi.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(a01, bf16x2_t));
+    hi.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(a23, bf16x2_t));
+    f32x4_t r = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(minus_one, __builtin_bit_cast(bf16x4_bits_t, hi), a, 0, 0, 0);
+    asm("" : "+v"(r));                                               // register allocation only: where the vector ALU reads it
+    const f32x2_t r01 = {r.x, r.y}, r23 = {r.z, r.w};
+    lo.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(r01, bf16x2_t));
+    lo.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(r23, bf16x2_t));
 }
 
 // bf16 bit pattern of an integer 0..255 (exact).  The 1/256 input scaling is
@@ -303,7 +332,7 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
 // k-block before the previous one (left to itself the compiler issues a whole layer's reads at once and spills).
 template <int T, int NOB, int NKB, int OBG, bool SPLIT_IN, bool LEAKY, bool FAR = false>
 __device__ __forceinline__ void hidden_layer(const uint8_t* __restrict__ w, const float* __restrict__ bias,
-                                             int lane, const u32x4_t (&in)[T][NKB][2],
+                                             int lane, bf16x4_bits_t minus_one, const u32x4_t (&in)[T][NKB][2],
                                              u32x4_t (&out)[T][NOB / 2][2]) {
     static_assert(NOB % OBG == 0 && OBG % 2 == 0, "out-block group must be even and divide the layer");
     const int g = lane >> 4;
@@ -347,13 +376,10 @@ __device__ __forceinline__ void hidden_layer(const uint8_t* __restrict__ w, cons
         for (int j = 0; j < OBG; j += 2) {
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                uint32_t l0, l1, l2, l3;
-                u32x4_t hi, lo;
-                hi.x = act_split_bf16<LEAKY>(acc[j][t].x, acc[j][t].y, l0);
-                hi.y = act_split_bf16<LEAKY>(acc[j][t].z, acc[j][t].w, l1);
-                hi.z = act_split_bf16<LEAKY>(acc[j + 1][t].x, acc[j + 1][t].y, l2);
-                hi.w = act_split_bf16<LEAKY>(acc[j + 1][t].z, acc[j + 1][t].w, l3);
-                lo.x = l0; lo.y = l1; lo.z = l2; lo.w = l3;
+                u32x2_t h0, h1, l0, l1;
+                act_split4_bf16<LEAKY>(acc[j][t], minus_one, h0, l0);
+                act_split4_bf16<LEAKY>(acc[j + 1][t], minus_one, h1, l1);
+                const u32x4_t hi = {h0.x, h0.y, h1.x, h1.y}, lo = {l0.x, l0.y, l1.x, l1.y};
                 out[t][(ob0 + j) / 2][0] = hi;
                 out[t][(ob0 + j) / 2][1] = lo;
             }
@@ -403,7 +429,7 @@ __device__ __forceinline__ void head_layer(const uint8_t* __restrict__ w, const 
 // image itself when RESIDENT is the number of layers); the other layers' tiles are read from the image at `rest`.
 template <class Net, int T, bool WIDE, int L, int RESIDENT = Net::kLayers>
 __device__ __forceinline__ void mlp_from(const uint8_t* __restrict__ model, const uint8_t* __restrict__ rest, int lane,
-                                         const u32x4_t (&in)[T][Net::kb(L)][2],
+                                         bf16x4_bits_t minus_one, const u32x4_t (&in)[T][Net::kb(L)][2],
                                          f32x4_t (&out)[T][Layout<Net>::kHeadOB]) {
     using Lay = Layout<Net>;
     const uint8_t* w = (L < RESIDENT ? model : rest) + Lay::w_off(L);
@@ -413,8 +439,8 @@ __device__ __forceinline__ void mlp_from(const uint8_t* __restrict__ model, cons
     } else {
         static_assert(Net::ob(L) == 2 * Net::kb(L + 1), "two out-blocks form one k-block of the next layer");
         u32x4_t h[T][Net::kb(L + 1)][2];
-        hidden_layer<T, Net::ob(L), Net::kb(L), (WIDE ? Net::ob(L) : 2), (L > 0), Net::kLeaky, (L >= RESIDENT)>(w, b, lane, in, h);
-        mlp_from<Net, T, WIDE, L + 1, RESIDENT>(model, rest, lane, h, out);
+        hidden_layer<T, Net::ob(L), Net::kb(L), (WIDE ? Net::ob(L) : 2), (L > 0), Net::kLeaky, (L >= RESIDENT)>(w, b, lane, minus_one, in, h);
+        mlp_from<Net, T, WIDE, L + 1, RESIDENT>(model, rest, lane, minus_one, h, out);
     }
 }
 
