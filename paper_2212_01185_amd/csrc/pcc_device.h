@@ -330,7 +330,8 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
 // ---------------------------------------------------------------------------
 // FAR: the weight tiles come from global memory; the reads of a k-block's tiles then stay behind the MFMAs of the
 // k-block before the previous one (left to itself the compiler issues a whole layer's reads at once and spills).
-template <int T, int NOB, int NKB, int OBG, bool SPLIT_IN, bool LEAKY, bool FAR = false>
+// MFMA_SPLIT: activations are split by act_split4_bf16, else by act_split_bf16 (the same numbers).
+template <int T, int NOB, int NKB, int OBG, bool SPLIT_IN, bool LEAKY, bool FAR, bool MFMA_SPLIT>
 __device__ __forceinline__ void hidden_layer(const uint8_t* __restrict__ w, const float* __restrict__ bias,
                                              int lane, bf16x4_bits_t minus_one, const u32x4_t (&in)[T][NKB][2],
                                              u32x4_t (&out)[T][NOB / 2][2]) {
@@ -376,10 +377,23 @@ __device__ __forceinline__ void hidden_layer(const uint8_t* __restrict__ w, cons
         for (int j = 0; j < OBG; j += 2) {
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                u32x2_t h0, h1, l0, l1;
-                act_split4_bf16<LEAKY>(acc[j][t], minus_one, h0, l0);
-                act_split4_bf16<LEAKY>(acc[j + 1][t], minus_one, h1, l1);
-                const u32x4_t hi = {h0.x, h0.y, h1.x, h1.y}, lo = {l0.x, l0.y, l1.x, l1.y};
+                u32x4_t hi, lo;
+                if constexpr (MFMA_SPLIT) {
+                    u32x2_t h0, h1, l0, l1;
+                    act_split4_bf16<LEAKY>(acc[j][t], minus_one, h0, l0);
+                    act_split4_bf16<LEAKY>(acc[j + 1][t], minus_one, h1, l1);
+                    hi.x = h0.x; hi.y = h0.y; hi.z = h1.x; hi.w = h1.y;
+                    lo.x = l0.x; lo.y = l0.y; lo.z = l1.x; lo.w = l1.y;
+                } else {
+                    // Where layers' weights come from global memory the matrix core is seldom busy and the subtraction's
+                    // latency counts instead (192 filters, 4 images of 640x480: 1,403 us this way, 1,440 the other).
+                    uint32_t l0, l1, l2, l3;
+                    hi.x = act_split_bf16<LEAKY>(acc[j][t].x, acc[j][t].y, l0);
+                    hi.y = act_split_bf16<LEAKY>(acc[j][t].z, acc[j][t].w, l1);
+                    hi.z = act_split_bf16<LEAKY>(acc[j + 1][t].x, acc[j + 1][t].y, l2);
+                    hi.w = act_split_bf16<LEAKY>(acc[j + 1][t].z, acc[j + 1][t].w, l3);
+                    lo.x = l0; lo.y = l1; lo.z = l2; lo.w = l3;
+                }
                 out[t][(ob0 + j) / 2][0] = hi;
                 out[t][(ob0 + j) / 2][1] = lo;
             }
@@ -439,7 +453,7 @@ __device__ __forceinline__ void mlp_from(const uint8_t* __restrict__ model, cons
     } else {
         static_assert(Net::ob(L) == 2 * Net::kb(L + 1), "two out-blocks form one k-block of the next layer");
         u32x4_t h[T][Net::kb(L + 1)][2];
-        hidden_layer<T, Net::ob(L), Net::kb(L), (WIDE ? Net::ob(L) : 2), (L > 0), Net::kLeaky, (L >= RESIDENT)>(w, b, lane, minus_one, in, h);
+        hidden_layer<T, Net::ob(L), Net::kb(L), (WIDE ? Net::ob(L) : 2), (L > 0), Net::kLeaky, (L >= RESIDENT), (RESIDENT == Net::kLayers)>(w, b, lane, minus_one, in, h);
         mlp_from<Net, T, WIDE, L + 1, RESIDENT>(model, rest, lane, minus_one, h, out);
     }
 }
