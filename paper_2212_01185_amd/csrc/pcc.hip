@@ -1539,6 +1539,12 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
         rd.x = rd.y;
         rd.y = x;
     };
+    // Has this band given up?  The fetch wave says so where it checks the row above: in layer kIdleLayer, and then all waves
+    // read the flag during B's search, behind that layer's barrier; or, where no layer leaves it time, at the step's end,
+    // and then they read it in the next step's head, in front of that layer's barrier (in the gather it cost 1 % of the
+    // step).  A barrier lies between write and read either way, so that all waves leave after the same step.
+    constexpr bool kStopInSearch = D::kIdleSlack > 0;
+    int stop = 0;
     auto settle = [&](auto layer) __attribute__((always_inline)) {
         constexpr int L = decltype(layer)::value;
         if constexpr (L == 0) settle_pick_upper();
@@ -1549,6 +1555,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
             rd.w[0] = next.x; rd.w[1] = next.y; rd.w[2] = next.z;
         }
         if constexpr (L == Net::kLayers - 1) {
+            if constexpr (!kStopInSearch) stop = misc[1];
             slot1_x = (float)(((uint32_t)rd.x & 0xFFFFu) + 1u);
             slot1_y = (float)(((uint32_t)rd.y & 0xFFFFu) + 1u);
             const int c = t - kDelay * qrow;
@@ -1590,7 +1597,6 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
             }
         }
     };
-    int stop = 0;       // has a band given up?  (set by the fetch wave before the first layer's barrier, read behind it)
     // Gather C_ij from the ring (zeros stand for pixels outside the image), for the step's tile of 16 pixels; every wave
     // builds the full tile.  A run is four consecutive bf16 values of a ring row: two dwords, which are the operand's
     // registers as they stand.
@@ -1719,7 +1725,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
             });
         };
         auto load_nothing = [&]() __attribute__((always_inline)) {};
-        auto load_stop = [&]() __attribute__((always_inline)) { stop = misc[1]; };
+        auto load_stop = [&]() __attribute__((always_inline)) { if constexpr (kStopInSearch) stop = misc[1]; };
         load_cp(0, cpr, tail_r);
         asm volatile("" ::: "memory");
 
@@ -1791,7 +1797,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     }
 #endif
     if constexpr (kStoreInIdle) if (wave_s == D::kStoreWave) { store_read(t_end); store_write(t_end); }      // the last step's pixels (the loop ended behind a barrier)
-    if (misc[1] != 0) break;    // uniform: written before the last barrier.  The call has failed; no further bands.
+    if (misc[1] != 0) break;    // uniform: the last step's barriers lie behind any write.  The call has failed; no further bands.
     if (wave_s == D::kStoreWave) mail(t_end);
     settle_pick();
     settle_pick_upper();

@@ -148,3 +148,28 @@ def test_roundtrip(variant):
             torch.cuda.synchronize()
             np.testing.assert_array_equal(out.cpu().numpy(), imgs, err_msg="%s %s %s" % (name, what, which))
 
+
+
+@pytest.mark.parametrize("launch", ["1", "2"])
+def test_a_band_that_gives_up_ends_the_call_where_no_layer_has_an_idle_round(launch, monkeypatch):
+    """Five mixtures: every layer's blocks fill its rounds, so the rows above a band are checked at a step's end and the
+    flag that a band has given up is read in the next step's head layer.  With the limit of a band's polls set to zero from
+    the host the call returns an error, and the next one works."""
+    from paper_2212_01185_amd import binding
+    blob = synth.make_ablation_blob(*synth.ABLATION_SHAPES["more_mixtures"])
+    monkeypatch.setenv("PCC_DECODE_VARIANT", launch)
+    good = binding.Codec(blob, 0)
+    monkeypatch.setenv("PCC_DECODE_SPIN_LIMIT", "0")
+    hasty = binding.Codec(blob, 0)
+    try:
+        imgs = _dev(np.random.default_rng(79).integers(0, 256, (120, 40, 24, 3), dtype=np.uint8))       # 360 bands
+        for n in (120, 1):
+            stream = good.pcc_encode(imgs[:n])
+            _log("decode without patience, launch %s: %d images" % (launch, n))
+            with pytest.raises(binding.PccError) as e:
+                hasty.pcc_decode(stream, n, 40, 24)
+            assert e.value.code == binding.PCC_E_INTERNAL
+            assert torch.equal(good.pcc_decode(stream, n, 40, 24), imgs[:n])
+    finally:
+        good.close()
+        hasty.close()

@@ -16,7 +16,12 @@ with the 16x16x32 bf16 shape it is eight, for vector-ALU and LDS consumers alike
 History: the decoder with two workgroups per compute unit once decoded wrongly now and then (different from run to
 run) when a scalar branch sat between a block's last MFMA and the first read of its accumulators; the kernels now
 finish every block (activation, split, store) inside the branch region that computed it, which this walk confirms
-for whatever the compiler lays out."""
+for whatever the compiler lays out.
+
+A second check on the same assembly, for the decoder's flag that a band has given up: a wave sets it and every wave reads
+it in each step, and the waves leave their loops together only if a workgroup barrier lies between any write and any
+read."""
+import functools
 import os
 import re
 import shutil
@@ -175,17 +180,119 @@ def test_scanner_finds_planted_cases():
     assert calibrate(list(_functions(asm.replace("\ts_cbranch_vccnz .LBB0_2\n", "").split("\n"))))["v_mfma_f32_16x16x32_bf16"] == 8
 
 
-@pytest.mark.skipif(shutil.which(pcc_build.HIPCC) is None and not os.path.exists(pcc_build.HIPCC), reason="no hipcc")
-def test_no_mfma_result_is_touched_early_on_any_path():
+@functools.lru_cache(maxsize=None)
+def _assembly():
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "pcc.s")
         flags = [f for f in pcc_build.FLAGS if f not in ("-shared", "-fPIC")]
         cmd = [pcc_build.HIPCC] + flags + ["--cuda-device-only", "-S", "-o", out, pcc_build.SRC]
         res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert res.returncode == 0, res.stdout[-2000:]
-        asm = open(out).read()
+        return open(out).read()
+
+
+needs_hipcc = pytest.mark.skipif(shutil.which(pcc_build.HIPCC) is None and not os.path.exists(pcc_build.HIPCC), reason="no hipcc")
+
+
+@needs_hipcc
+def test_no_mfma_result_is_touched_early_on_any_path():
+    asm = _assembly()
     assert asm.count("v_mfma_f32_16x16x32_bf16") > 1000          # the kernels are in there
     found, need = early_reads(asm)
     print("wait states the compiler leaves in straight-line code:", need)
     assert need.get("v_mfma_f32_16x16x32_bf16", 0) >= 4, need     # calibration cases exist for the shape the kernels use
     assert not found, "MFMA results touched too soon:\n" + "\n".join("%d of %d wait states: %s" % f for f in sorted(found)[:10])
+
+
+def _successors(body, labels):
+    out = []
+    for i, ins in enumerate(body):
+        op = ins.split()[0]
+        nxt = [] if op in ("s_branch", "s_endpgm") else [i + 1]
+        if op.startswith(("s_branch", "s_cbranch")):
+            nxt.append(labels[ins.split()[-1]])
+        out.append([n for n in nxt if n < len(body)])
+    return out
+
+
+def _barrier_loops(body, labels):
+    """[(number of barriers of one pass, {instruction: barriers passed since the loop's head})] for the innermost loops
+    that hold barriers: the decoder's steps, one loop per role of a wave."""
+    succ = _successors(body, labels)
+    pred = [[] for _ in body]
+    for i, ns in enumerate(succ):
+        for n in ns:
+            pred[n].append(i)
+    loops = []
+    for u, ns in enumerate(succ):
+        for head in ns:
+            if head > u:
+                continue
+            inside, stack = {head, u}, [u]
+            while stack:
+                i = stack.pop()
+                if i == head:
+                    continue
+                for p in pred[i]:
+                    if p not in inside:
+                        inside.add(p)
+                        stack.append(p)
+            if any(body[i].startswith("s_barrier") for i in inside):
+                loops.append((head, inside))
+    innermost = [(h, s) for h, s in loops if not any(other < s for _, other in loops)]
+    found = []
+    for head, inside in innermost:
+        passed, stack, total = {head: 0}, [head], None
+        while stack:
+            i = stack.pop()
+            after = passed[i] + (1 if body[i].startswith("s_barrier") else 0)
+            for n in succ[i]:
+                if n == head:
+                    assert total in (None, after), "paths with different numbers of barriers"
+                    total = after
+                elif n in inside:
+                    assert passed.get(n, after) == after, "paths with different numbers of barriers"
+                    if n not in passed:
+                        passed[n] = after
+                        stack.append(n)
+        found.append((total, passed))
+    return found
+
+
+def flag_races(body, labels):
+    """(intervals between barriers of a step in which the flag is written, ... read).  The flag is the one LDS word that is
+    both read and written by its constant address."""
+    at = {"read": {}, "write": {}}
+    for i, ins in enumerate(body):
+        m = re.match(r"ds_(read|write)_b32 .*offset:(\d+)$", ins)
+        if m:
+            at[m.group(1)].setdefault(int(m.group(2)), []).append(i)
+    flag = set(at["read"]) & set(at["write"])
+    assert len(flag) == 1, flag
+    where = flag.pop()
+    loops = _barrier_loops(body, labels)
+    steps = [(n, passed) for n, passed in loops if any(i in passed for i in at["read"][where])]
+    assert steps and len({n for n, _ in steps}) == 1, "the roles' steps differ in their barriers"
+    # what follows a pass's last barrier lies in the interval that the next pass begins with
+    return tuple({passed[i] % n for n, passed in steps for i in at[what][where] if i in passed} for what in ("write", "read"))
+
+
+def test_flag_race_is_found_where_planted():
+    # two roles: one reads the flag behind the second barrier, one writes it there (a race) or behind the first (none)
+    asm = ["_Z6kernelv: ; @_Z6kernelv", ".LBB0_1:", "\ts_barrier", "\tds_write_b32 v0, v1 offset:64", "\ts_barrier",
+           "\tds_read_b32 v2, v0 offset:64", "\ts_cbranch_scc1 .LBB0_1", ".LBB0_2:", "\ts_barrier", "\ts_barrier",
+           "\tds_read_b32 v2, v0 offset:64", "\ts_cbranch_scc1 .LBB0_2", "\ts_endpgm", ".Lfunc_end0:"]
+    (_, body, labels), = _functions(asm)
+    assert flag_races(body, labels) == ({1}, {0})
+    asm[3], asm[4] = asm[4], asm[3]
+    (_, body, labels), = _functions(asm)
+    assert flag_races(body, labels) == ({0}, {0})
+
+
+@needs_hipcc
+def test_a_barrier_lies_between_writes_and_reads_of_the_decoders_flag():
+    kernels = [(name, body, labels) for name, body, labels in _functions(_assembly().split("\n")) if "decode_kernel" in name]
+    assert len(kernels) == 18                                       # nine networks, one and two workgroups per unit
+    for name, body, labels in kernels:
+        written, read = flag_races(body, labels)
+        assert written and read and not written & read, "%s: written in %s, read in %s" % (name, written, read)
