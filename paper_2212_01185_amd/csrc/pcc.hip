@@ -2104,6 +2104,13 @@ bool set_kernel_attributes() {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, dec) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<Net, 2>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net>::kBytesShared) == hipSuccess;
+    // The decoders read the CDF table at LDS address 0 (cq_lookup<K, true>): their dynamic array must begin there, that is,
+    // they must have no static one in front of it.
+    static_assert(DecLds<Net>::kLutOff == 0, "the table's LDS address is a literal in cq_lookup");
+    for (const void* decoder : {reinterpret_cast<const void*>(&decode_kernel<Net, 1>), reinterpret_cast<const void*>(&decode_kernel<Net, 2>)}) {
+        hipFuncAttributes attr;
+        ok = ok && hipFuncGetAttributes(&attr, decoder) == hipSuccess && attr.sharedSizeBytes == 0;
+    }
     return ok;
 }
 

@@ -549,7 +549,8 @@ __host__ __device__ constexpr uint32_t spread_at(uint32_t i) { return 8u * i + (
 constexpr int kSpreadLutBytes = (int)spread_at(kLutEntries) + 8;
 
 // edge: the bin edge's position (2 e - 1) / 512, exact for every e.  SPREAD: the table is such a copy, at LDS address 0
-// (an address the compiler knows: two instructions a look-up, a base it does not know would make it three).
+// (an address the compiler knows: two instructions a look-up, a base it does not know would make it three).  The kernel
+// that uses it has no static LDS, which would move its dynamic array: pcc_create refuses to go on with one that has.
 template <int K, bool SPREAD = false>
 __device__ __forceinline__ void cq_lookup(const ChanParams<K>& cp, float edge, const float2* __restrict__ lut, CqLookup<K>& q) {
 #pragma unroll

@@ -20,7 +20,7 @@ for whatever the compiler lays out.
 
 A second check on the same assembly, for the decoder's flag that a band has given up: a wave sets it and every wave reads
 it in each step, and the waves leave their loops together only if a workgroup barrier lies between any write and any
-read."""
+read.  A third: the decoder reads its table at LDS address 0, so it must have no static LDS in front of the dynamic array."""
 import functools
 import os
 import re
@@ -296,3 +296,23 @@ def test_a_barrier_lies_between_writes_and_reads_of_the_decoders_flag():
     for name, body, labels in kernels:
         written, read = flag_races(body, labels)
         assert written and read and not written & read, "%s: written in %s, read in %s" % (name, written, read)
+
+
+def static_lds(asm_text):
+    """kernel -> bytes of static LDS, from the kernel descriptors."""
+    out, name = {}, None
+    for line in asm_text.split("\n"):
+        words = line.split()
+        if words[:1] == [".amdhsa_kernel"]:
+            name = words[1]
+        elif words[:1] == [".amdhsa_group_segment_fixed_size"]:
+            out[name] = int(words[1])
+    return out
+
+
+@needs_hipcc
+def test_decoders_have_no_static_lds():
+    sizes = static_lds(_assembly())
+    decoders = [k for k in sizes if "decode_kernel" in k]
+    assert len(decoders) == 18 and not any(sizes[k] for k in decoders), {k: sizes[k] for k in decoders}
+    assert any(sizes[k] for k in sizes if "rans_rows_kernel" in k)          # a kernel that has static LDS shows it here
