@@ -872,6 +872,15 @@ struct DecLds {
     // first, cheaper half of their jobs goes there (the fetch wave's request, the storing wave's read of the pixels).
     static constexpr bool kIdleInFirstLayer =
         kIdleSlack > 0 && kIdleLayer != 0 && wave_idles(0, kStoreWave) && wave_idles(0, kFetchWave);
+    // StepRole::kOwnsLast is one answer for all layers: the waves without a block in a layer's last round must be the same in
+    // every layer that has such a round, and each must have a role of its own (a third one would compute a block too many).
+    static constexpr bool same_waves_idle() {
+        for (int l = 0; l < Net::kLayers; ++l)
+            for (int w = 0; w <= kLastWave; ++w)
+                if (Net::ob(l) % 4 != 0 && wave_idles(l, w) != (w >= kFirstIdleWave)) return false;
+        return true;
+    }
+    static_assert(same_waves_idle() && kIdleWaves <= 2, "the roles of the decoder's waves do not fit the network's block counts");
     static_assert(kIdleLayer > 0 || kIdleSlack == 0, "the fetch must lie behind the barrier that follows the step's gather");
     static_assert(2 * Net::kDelay + 3 + kMaxReach <= Net::kRingCols, "ring too small for the neighbourhood");
     // what a row reads of the rows above must have been decoded in an earlier pass
@@ -1058,7 +1067,7 @@ struct WaveNet {
         rest.load(model, lds, lane, wave);
     }
     // OWNS_LAST: has this wave a block in the last round of the layers whose block count is no multiple of four?  (The
-    // same waves have in all of them.)  idle: what a wave that has none does in its place.
+    // same waves have in all of them: DecLds::same_waves_idle.)  idle: what a wave that has none does in its place.
     // settle: work of every wave that nothing waits for before the searches, in parts for the layers; it goes between the
     // MFMAs.
     template <bool OWNS_LAST, class Idle, class Settle>
