@@ -25,13 +25,14 @@ FLAGS = [
 ]
 
 
-def build(verbose: bool = False, extra=(), lib: str = LIB) -> str:
+def build(verbose: bool = False, extra=(), lib: str = LIB, src: str = SRC) -> str:
     """Compile the library to `lib` (default: libpcc.so next to the package).  `extra` are more hipcc flags, e.g.
-    -DPCC_PHASE_TIMING for the measurement build that counts the decode step's cycles per phase."""
+    -DPCC_PHASE_TIMING for the measurement build that counts the decode step's cycles per phase.  `src` is another HIP
+    source to compile with the library's flags."""
     LIB = lib
     os.makedirs(os.path.dirname(os.path.abspath(LIB)), exist_ok=True)
     tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [HIPCC] + FLAGS + list(extra) + ["-o", tmp, SRC]
+    cmd = [HIPCC] + FLAGS + list(extra) + ["-o", tmp, src]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -3,10 +3,17 @@
 // Encoder and decoder must derive bit-identical integer CDF values for every
 // pixel, otherwise decoding desynchronises.  Everything between "bytes of the
 // neighbourhood" and "Cq(e)" is therefore written once, here, and compiled
-// with floating-point contraction off: the same inputs go through the same
-// instruction sequence in both kernels.  An MFMA output element depends only
-// on its A row, its B column and the order of the k blocks, all of which are
-// fixed below, so it does not matter which other pixels share a tile.
+// with floating-point contraction off: the same inputs give the same bits in
+// both kernels.  They do so by the same instructions but for the split of an
+// activation into hi + lo, which has two forms (act_split_bf16 on the vector
+// ALU, act_split4_bf16 with the subtraction on the matrix core) and is chosen
+// per network and kernel: both are exact, and a test compares their bits.
+// Where an activation rounds to infinity their lo parts differ, but the pixel
+// is NaN from the next layer on in either form, and MFMA has one NaN
+// (0xFFC00000) for every product with a NaN, 0 x inf or inf - inf in it.
+// An MFMA output element depends only on its A row, its B column and the
+// order of the k blocks, all of which are fixed below, so it does not matter
+// which other pixels share a tile.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -252,7 +259,7 @@ __host__ __device__ constexpr int kslot_feature(int g, int i) { return 16 * (i >
 // instead of ~1e-2.  Each weight tile is multiplied with hi and then with lo.
 // ReLU as a signed integer maximum of the bit pattern (negative floats are negative
 // integers), LeakyReLU as the median of {a, 0.01 a, +inf}: one instruction each, where
-// fmaxf() would first re-canonicalise its operand.  Inputs are finite.
+// fmaxf() would first re-canonicalise its operand.  (MFMA's NaN is a negative integer: ReLU makes it 0.)
 template <bool LEAKY>
 __device__ __forceinline__ float activation(float a) {
     if constexpr (LEAKY) return __builtin_amdgcn_fmed3f(a, 0.01f * a, __builtin_inff());
