@@ -580,8 +580,9 @@ __device__ __forceinline__ void cq_fractions(CqLookup<K>& q) {
     for (int k = 0; k < K; ++k) q.t[k] = __builtin_amdgcn_fractf(q.t[k]);
 }
 
-// 65280 min(sum, 1), whose floor is Cq(e) - e.  The sum is at least 0 and exceeds 1 by rounding at most; limited to
-// [0, 1] it costs nothing (the result modifier of the last fma), and 65280 times it is what min(65280 sum, 65280) is.
+// 65280 min(sum, 1), whose floor is Cq(e) - e.  The sum is at least 0 and exceeds 1 by rounding at most, and 65280 times
+// the minimum is what min(65280 sum, 65280) is.  A sum that is NaN (logits that are, or are infinite) counts as 1: all of
+// the mass lies below bin 1 then.  (The result modifier of the last fma would limit the sum for nothing but make NaN 0.)
 template <int K>
 __device__ __forceinline__ float cq_scaled(const ChanParams<K>& cp, CqLookup<K>& q) {
     static_assert(K == 3 || K == 5 || K == 7, "the scheduling barrier below lists the table reads explicitly");
@@ -604,7 +605,7 @@ __device__ __forceinline__ float cq_scaled(const ChanParams<K>& cp, CqLookup<K>&
         const float phi = __builtin_fmaf(q.t[k], td[k].y, td[k].x);
         acc = __builtin_fmaf(cp.pi[k], phi, acc);
     }
-    return __builtin_amdgcn_fmed3f(acc, 0.0f, 1.0f) * 65280.0f;
+    return fminf(acc, 1.0f) * 65280.0f;
 }
 
 template <int K>

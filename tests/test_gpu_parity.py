@@ -215,6 +215,28 @@ def test_cdf_tables_against_oracle(codec, orc):
     assert worst <= CQ_ATOL
 
 
+def test_cdf_tables_of_logits_that_are_not_finite(codec):
+    """A channel whose logits are NaN, or infinite so that the softmax is, has all its mass in bin 0 (a stream coded with
+    such a model stays readable); means and log-sigmas that are not finite leave the table monotone."""
+    heads = np.zeros((8, 60), dtype=np.float32)
+    heads[0] = np.nan
+    heads[1, [0, 17, 34]] = np.nan
+    heads[2, [0, 17, 34]] = np.inf
+    for ch in range(3):
+        heads[3, 15 * ch:15 * ch + 5] = -np.inf
+    heads[4, [5, 20, 35]] = np.nan
+    heads[5, [5, 20, 35]], heads[5, [6, 21, 36]] = np.inf, -np.inf
+    heads[6, [10, 25, 40]], heads[6, [11, 26, 41]] = np.inf, -np.inf
+    heads[7, 45:] = np.inf
+    cq = codec.pcc_cdf_tables(_dev(heads), _dev(np.full((8, 2), 100, dtype=np.uint8)))
+    torch.cuda.synchronize()
+    cq = cq.cpu().numpy().astype(np.int64)
+    assert (cq[:, :, 0] == 0).all() and (cq[:, :, 256] == 65536).all() and (np.diff(cq, axis=2) >= 1).all()
+    e = np.arange(1, 256)
+    for i in range(4):
+        np.testing.assert_array_equal(cq[i, :, 1:256], np.broadcast_to(e + 65280, (3, 255)))
+
+
 # ----------------------------------------------------------------- logistic mixture (Eq. (8))
 
 def test_logistic_mixture(codec, codec_logistic, orc_logistic):
