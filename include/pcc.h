@@ -124,13 +124,15 @@ int pcc_encode_probs(pcc_ctx *ctx, const uint8_t *d_img, int n, int H, int W,
  * hip_stream is idle at the call and the job has at most 3072 rows, the row
  * coder and the stream assembly run on a stream the ctx owns, beside the
  * pixel kernel; both streams have been waited for when the call returns, so
- * the caller's view is the same.  That mode needs the two kernels to run at
- * the same time.  Where something runs a process's kernels one after the other
- * (a profiler collecting counters does; so does a chip another job fills), the
- * row coder finds no symbols, gives up after PCC_RANS_PATIENCE polls (a few
- * milliseconds with the default) and is launched again behind the pixel kernel:
- * the result is the same, but such a call pays that wait first, i.e. ten times
- * a 768 x 512 encode.  PCC_ENCODE_OVERLAP=0 avoids the mode altogether.
+ * the caller's view is the same.  The pixel kernel is queued first: where the
+ * two do not run at the same time (a profiler collecting counters runs a
+ * process's kernels one after the other; so do two streams that share one of the
+ * process's hardware queues), the row coder finds all symbols when it starts.
+ * Only where the pixel kernel is held up while the row coder already runs (by
+ * other work in front of it, or on a chip another job fills) does the row coder
+ * give up after PCC_RANS_PATIENCE polls (a few milliseconds with the default) and
+ * is launched again behind the pixel kernel: the result is the same, but such a
+ * call pays that wait.  PCC_ENCODE_OVERLAP=0 avoids the mode altogether.
  * One call at a time per ctx.  On an error return no kernel of the call is
  * still running on either stream. */
 int pcc_encode(pcc_ctx *ctx, const uint8_t *d_img, int n, int H, int W,

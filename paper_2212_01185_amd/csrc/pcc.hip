@@ -472,9 +472,8 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
             // ahead): the lane polls one of them, sleeping in between so that the polls of a coder that has
             // caught up do not load the memory system, and then loads its whole set again, all loads at once.
             // A running pixel kernel delivers a row's next strip within tens of microseconds.  A wait of
-            // `patience` polls (milliseconds) therefore means that it is not running beside this kernel
-            // (something runs the process's kernels one at a time, or the chip is taken): the row coder stands
-            // down, and the host launches it again after the pixel kernel.
+            // `patience` polls (milliseconds) therefore means that it is held up (other work is in front of it, or the
+            // chip is taken): the row coder stands down, and the host launches it again after the pixel kernel.
             uint32_t spins = 0;
             for (;;) {
                 size_t stale_at = 0;
@@ -2435,11 +2434,19 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         rc = finish(st);
         if (rc != PCC_OK) return rc;
     } else {
-        // An image of few rows: the row coder is the longer of the two, goes first and is in place when the pixel
-        // kernel's first symbols appear.  A tall image: the pixel kernel is the longer one; it does the first
-        // strips with the whole chip, and the row coder joins it (an event; the launch gap does not matter at
-        // this size) for a last part sized so that both end together.  The row coder takes about as long as the
-        // pixel kernel at kRansBalanceRows rows, both in proportion to the width.
+        // An image of few rows: the row coder follows the pixel kernel through the whole image.  A tall image: the
+        // pixel kernel is the longer one; it does the first strips with the whole chip, and the row coder joins it
+        // (an event; the launch gap does not matter at this size) for a last part sized so that both end together.
+        // The row coder takes about as long as the pixel kernel at kRansBalanceRows rows, both in proportion to the
+        // width.
+        //
+        // The pixel kernel is queued first.  Two streams may share one of the process's few hardware queues and then run
+        // their kernels in the order in which they were queued: a row coder in front of the pixel kernel that it waits
+        // for would hold it up until its patience is over (768x512: 2,250 us a call instead of 154, for about one pair
+        // of a codec and a caller's stream in six), behind it the call merely runs in sequence (201 us).  With queues of
+        // their own the order costs nothing (64x64 65.2 -> 62.9 us, 768x512 142.7 -> 139.6): the pixel kernel, the longer
+        // one, starts a launch earlier.  Since each call queues the kernel that waits for nothing first, calls of several
+        // threads cannot wait for each other in a circle either.
         //
         // Two streams carry work from here on.  Whatever fails, the branch leaves through `drain`: both streams
         // are waited for (a row coder without its pixel kernel stands down when its patience is over), so nothing
@@ -2455,29 +2462,25 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         };
         const double share = 1.1 * kRansBalanceRows / rows * (double)(cus - reserve) / cus;   // of the strips, beside
         const uint32_t strips_alone = share >= 1.0 ? 0u : (uint32_t)((1.0 - share) * strips);
-        if (strips_alone == 0) {
-            launch_rans(ctx->side);
-            prof_begin(ctx, PCC_T_ENCODE_PIXELS, st);
-        } else {
-            prof_begin(ctx, PCC_T_ENCODE_PIXELS, st);
+        prof_begin(ctx, PCC_T_ENCODE_PIXELS, st);
+        if (strips_alone != 0) {
             rc = launch_encode_any(ctx, d_img, n, H, W, nullptr, nullptr, nullptr, d_tagged, 0, 0, strips_alone, st);
             if (rc != PCC_OK) return drain(rc);
             if (hipEventRecord(ctx->ev_joined, st) != hipSuccess) return drain(PCC_E_HIP);
             if (hipStreamWaitEvent(ctx->side, ctx->ev_joined, 0) != hipSuccess) return drain(PCC_E_HIP);
-            launch_rans(ctx->side);
         }
         rc = launch_encode_any(ctx, d_img, n, H, W, nullptr, nullptr, nullptr, d_tagged, reserve, strips_alone,
                                strips - strips_alone, st);
         if (rc != PCC_OK) return drain(rc);
         prof_end(ctx, PCC_T_ENCODE_PIXELS, st);
+        launch_rans(ctx->side);
         rc = finish(ctx->side);
         if (rc != PCC_OK) return drain(rc);
         // the row coder ends after the pixel kernel's last store; the caller's stream is waited for as well, so
         // that the pixel kernel has retired when this returns
         if (hipStreamSynchronize(st) != hipSuccess) return drain(PCC_E_HIP);
         if (ctx->h_status[kStErr] == 0 && ctx->h_status[kStSide + kSideDefer] != 0) {
-            // The row coder saw nothing of the pixel kernel for a long time and stood down: the two did not run side
-            // by side.  The symbols are all there now; code them on the caller's stream.
+            // The row coder saw nothing of the pixel kernel for a long time and stood down.  The symbols are all there now; code them on the caller's stream.
             if (hipMemsetAsync(ctx->d_status, 0, kStCleared, st) != hipSuccess) return drain(PCC_E_HIP);
             launch_rans(st);
             rc = finish(st);
