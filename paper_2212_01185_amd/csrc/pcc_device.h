@@ -60,10 +60,19 @@ struct NetWorkload {
     static constexpr int kRingPad = 2;        // extra 16-bit elements per ring row
     static constexpr bool kLeaky = false;
     // Decoder with two workgroups per CU (256 registers per lane each): what of a wave's weight slices is then read
-    // from a copy in LDS instead of held in registers, chosen by measurement (batches of 24 and 48 images of 768x512;
-    // 24 images: none 8.39 ms, first layer 8.05, head 7.60, head and biases 7.49, first layer and head 7.23, all 7.51): LDS
-    // copies cost time too, so a few spilled registers can be the better deal.  1: the biases, 2: the first layer's
-    // weights, 4: the head's.
+    // from a copy in LDS instead of held in registers, chosen by measurement (1: the biases, 2: the first layer's
+    // weights, 4: the head's).  LDS copies cost time too, so a few spilled registers can be the better deal.  24 images of
+    // 768x512 with two per CU, ms (spilled registers):
+    //   copies             none         first layer   head         first and head   all
+    //   this network       7.85 (61)    7.15 (47)     6.98 (45)    6.38 (29)        6.49 (0)
+    //   the paper's        9.44 (42)    8.09 (27)     8.00 (29)    7.58 (16)        7.80 (0)
+    //   diagonal           6.84 (45)    6.31 (47)     6.21 (40)    5.24 (25)        5.41 (0)
+    //   five mixtures      10.85 (49)   9.47 (30)     9.87 (34)    8.57 (19)        8.95 (0)
+    //   seven mixtures     13.61 (104)  13.12 (87)    12.77 (80)   13.15 (87)       11.22 (44)
+    //   six layers         12.14 (93)   11.19 (75)    11.27 (62)   10.39 (47)       8.86 (8)
+    //   four layers        6.38 (11)    6.60 (0)      6.43 (0)     6.64 (0)         6.83 (0)
+    //   64 filters         5.65 (0)     5.69 (0)      5.63 (0)     5.73 (0)         5.89 (0)
+    // (Seven mixtures: the first layer and the head do not fit a CU twice, `all` is the biases and the first layer.)
     static constexpr int kEncodeVariant = 1;      // pixel kernel: two tiles per work item, 512 threads (index into the host's table)
     static constexpr int kSharedCuLds = 6;
     // Time of a decode step when both workgroups of a CU are busy, in percent of a step of a workgroup that has its
@@ -104,7 +113,7 @@ struct NetPaper {
     static constexpr int kRingPad = 4;
     static constexpr bool kLeaky = true;
     static constexpr int kEncodeVariant = 1;
-    static constexpr int kSharedCuLds = 4;      // 24 images of 768x512: none 8.04 ms, first layer 7.61, head 7.34, both 7.61
+    static constexpr int kSharedCuLds = 6;
     static constexpr unsigned kSharedStepPercent = 145;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
@@ -171,7 +180,7 @@ struct NetAblation : NetPaper {
     static constexpr int kLayers = LAYERS;
     static constexpr int K = MIXTURES;
     static constexpr int kEncodeVariant = 1;
-    static constexpr int kSharedCuLds = MIXTURES >= 7 ? 7 : (MIXTURES >= 5 || LAYERS >= 6) ? 6 : NetPaper::kSharedCuLds;
+    static constexpr int kSharedCuLds = MIXTURES >= 7 || LAYERS >= 6 ? 7 : MIXTURES >= 5 ? 6 : 4;
     // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch)
     static constexpr unsigned kSharedStepPercent = C > 128 ? 1000 : MIXTURES >= 7 ? 186 : MIXTURES >= 5 ? 153 : 147;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == LAYERS ? 12 * MIXTURES : C; }
