@@ -2178,21 +2178,29 @@ void launch_decode(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, 
     constexpr int kLds = DecLds<Net>::kBytes;
     const uint64_t bands = (uint64_t)n * nbands;                      // dims_ok: below 2^31
     const uint64_t cus = ctx->num_cus > 0 ? (uint64_t)ctx->num_cus : 256u;
-    // One workgroup per CU decodes a step in the shortest time; two per CU take Net::kSharedStepPercent / 100 as
-    // long per step when both are busy but decode twice as many bands at once.  An image is a chain of `chain`
-    // steps whatever the machine does; the job is `work` band-steps.  Estimates, in percent of a step alone, fitted to
-    // batches of 6 to 48 images of 768x512 in both shapes: one per CU takes the chain plus a tenth, or the work per CU
-    // plus a fifth (rounds of bands that do not fill the chip); two per CU take the chain stretched by the share of
-    // the time a unit's two workgroups are both busy (the work per CU over twice the chain, at most all of it), or the
-    // work per place at the shared pace.  Two per CU win from about 2.2 bands per CU on (18 images of 768x512).
-    const int band_rows = H < kBandRows ? H : kBandRows;
-    const uint64_t chain = (uint64_t)W + (uint64_t)Net::kDelay * (H - 1);
-    const uint64_t work = bands * ((uint64_t)W + (uint64_t)Net::kDelay * (band_rows - 1));
-    const uint64_t per_cu = (work + cus - 1) / cus, per_half_cu = (work + 2 * cus - 1) / (2 * cus);
-    const uint64_t alone = std::max(chain * 110u, per_cu * 120u);
-    const uint64_t stretch = (Net::kSharedStepPercent - 113u) * std::min(per_cu, 2 * chain) / (2 * chain);
-    const uint64_t shared = std::max(chain * (100u + stretch), per_half_cu * Net::kSharedStepPercent) * 103u / 100u;
-    const bool two = ctx->decode_variant == 2 || (ctx->decode_variant == 0 && DecLds<Net>::kTwoFit && bands > cus && shared < alone);
+    // One workgroup per CU decodes a step in the shortest time; two per CU decode twice as many bands at once, at
+    // Net::kSharedAlonePercent of that time per step while a unit's other workgroup waits and Net::kSharedStepPercent
+    // while both are busy.  The steps on a job's longest path follow from the order of the tickets (band-major): a band
+    // holds its place for `hold` steps and begins `stride` steps behind the band above, ticket k begins where ticket
+    // k - places ended, so the last ticket begins behind stride steps per band above it (the chain of an image), or
+    // behind whole rounds of the places and the bands of the last, partial one.  times alone / per step: within 3 % of the
+    // measured time with one workgroup per CU.  With two the time per step goes from one figure to the other with the
+    // share of the places that are busy on average, from a fifth of them to four fifths.
+    // Fitted per network to 57 jobs of 192 to 2,000 bands (6 to 48 images of 768x512, 65 to 500 of 64x64, 2 to 4 of
+    // 4096x2160, images of a few rows and of a few columns): the launch chosen takes 0.1 % longer than the better one on
+    // average and 3.6 % at most.  768x512, ms with one and with two per CU: 16 images 5.66 and 6.02, 18 images 6.56 and
+    // 5.96, 48 images 12.68 and 9.93; the paper's shape, 9 images 6.27 and 6.66, 24 images 7.53 and 7.51.
+    const uint64_t band_rows = H < kBandRows ? H : kBandRows;
+    const uint64_t hold = (uint64_t)W + (uint64_t)Net::kDelay * (band_rows - 1), stride = (uint64_t)Net::kDelay * kBandRows;
+    auto steps = [&](uint64_t places) {
+        const uint64_t last = bands - 1;
+        return hold + std::max(stride * (last / n), hold * (last / places) + stride * (last % places / n));
+    };
+    const double steps_two = (double)steps(2 * cus), busy = (double)(bands * hold) / (steps_two * (double)(2 * cus));
+    const double pace = Net::kSharedAlonePercent +
+                        ((double)Net::kSharedStepPercent - Net::kSharedAlonePercent) * std::min(std::max((busy - 0.2) / 0.6, 0.0), 1.0);
+    const bool two = ctx->decode_variant == 2 || (ctx->decode_variant == 0 && DecLds<Net>::kTwoFit && bands > cus &&
+                                                  steps_two * pace < 100.0 * (double)steps(cus));
     const uint32_t grid = (uint32_t)std::min(bands, two ? 2 * cus : cus);
     if (!two)
         hipLaunchKernelGGL((decode_kernel<Net, 1>), dim3(grid), dim3(kDecThreads), kLds, st, ctx->d_model, d_stream,

@@ -75,9 +75,9 @@ struct NetWorkload {
     // (Seven mixtures: the first layer and the head do not fit a CU twice, `all` is the biases and the first layer.)
     static constexpr int kEncodeVariant = 1;      // pixel kernel: two tiles per work item, 512 threads (index into the host's table)
     static constexpr int kSharedCuLds = 6;
-    // Time of a decode step when both workgroups of a CU are busy, in percent of a step of a workgroup that has its
-    // CU alone (measured the same way; the host chooses between the two launches with it).
-    static constexpr unsigned kSharedStepPercent = 150;
+    // Time of a decode step with two workgroups per CU, in percent of a step with one, while the other workgroup waits and
+    // while both are busy (fitted to whole jobs; the host chooses between the two launches with them: launch_decode).
+    static constexpr unsigned kSharedAlonePercent = 112, kSharedStepPercent = 138;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 30 : l == 1 ? 160 : l == 2 ? 160 : l == 3 ? 128 : 60; }
     __host__ __device__ static constexpr int ob(int l) { return l == 0 ? 10 : l == 1 ? 10 : l == 2 ? 8 : 4; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 1 : l == 1 ? 5 : l == 2 ? 5 : 4; }
@@ -114,7 +114,7 @@ struct NetPaper {
     static constexpr bool kLeaky = true;
     static constexpr int kEncodeVariant = 1;
     static constexpr int kSharedCuLds = 6;
-    static constexpr unsigned kSharedStepPercent = 145;
+    static constexpr unsigned kSharedAlonePercent = 108, kSharedStepPercent = 137;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 2 : 4; }
@@ -141,7 +141,7 @@ struct NetDiagonal : NetPaper {
     static constexpr int kReach1 = 0, kReach2 = 1;   // row r-1 is read up to column c, row r-2 up to c+1
     static constexpr int kRingCols = 8;
     static constexpr int kRingPad = 4;
-    static constexpr unsigned kSharedStepPercent = 138;
+    static constexpr unsigned kSharedAlonePercent = 118, kSharedStepPercent = 138;
     __host__ __device__ static constexpr bool run_desc(int kbi, int g, int half, int& dr, int& off) {
         if (kbi == 0) {
             if (g == 0) { dr = -2; off = 4 * half; }                          // row r-2, bytes 0..7
@@ -181,8 +181,9 @@ struct NetAblation : NetPaper {
     static constexpr int K = MIXTURES;
     static constexpr int kEncodeVariant = 1;
     static constexpr int kSharedCuLds = MIXTURES >= 7 || LAYERS >= 6 ? 7 : MIXTURES >= 5 ? 6 : 4;
-    // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch)
-    static constexpr unsigned kSharedStepPercent = C > 128 ? 1000 : MIXTURES >= 7 ? 186 : MIXTURES >= 5 ? 153 : 147;
+    // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch.)
+    static constexpr unsigned kSharedAlonePercent = C > 128 ? 1000 : MIXTURES >= 7 ? 126 : MIXTURES >= 5 ? 107 : LAYERS >= 6 ? 114 : LAYERS <= 4 ? 104 : 101;
+    static constexpr unsigned kSharedStepPercent = C > 128 ? 1000 : MIXTURES >= 7 ? 149 : MIXTURES >= 5 ? 135 : LAYERS >= 6 ? 141 : LAYERS <= 4 ? 130 : 123;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == LAYERS ? 12 * MIXTURES : C; }
     __host__ __device__ static constexpr int ob(int l) { return (dim(l + 1) + 15) / 16; }
     __host__ __device__ static constexpr int kb(int l) { return (dim(l) + 31) / 32; }
