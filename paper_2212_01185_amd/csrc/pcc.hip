@@ -867,8 +867,9 @@ struct DecLds {
     static constexpr int kFetchWave = kIdleWaves >= 2 ? kLastWave - 1 : kLastWave;
     // Does wave w have a round without an out-block in layer l?
     static constexpr bool wave_idles(int l, int w) { return w + 4 * ((Net::ob(l) + 3) / 4 - 1) >= Net::ob(l); }
-    // The idle waves also have a (short) round to spare in the first layer where that is not the layer above: the
-    // first, cheaper half of their jobs goes there (the fetch wave's request, the storing wave's read of the pixels).
+    // The idle waves also have a (short) round to spare in the first layer where that is not the layer above: the storing
+    // wave reads the pixels there that it stores in layer kIdleLayer.  (The fetch wave has then time enough for its whole job
+    // in that layer, and its request moves to the step's end: decode_kernel, fetch_request.)
     static constexpr bool kIdleInFirstLayer =
         kIdleSlack > 0 && kIdleLayer != 0 && wave_idles(0, kStoreWave) && wave_idles(0, kFetchWave);
     // StepRole::kOwnsLast is one answer for all layers: the waves without a block in a layer's last round must be the same in
@@ -1214,8 +1215,8 @@ struct StepRole {
 };
 
 // MINBLOCKS = 1: all registers to one workgroup per CU (lowest latency per step).  MINBLOCKS = 2: two
-// workgroups share a CU (some spills; a step takes about twice as long, so this only pays for jobs of
-// so many bands that the work per CU, not an image's chain of steps, sets the time: launch_decode).
+// workgroups share a CU (some spills; a step takes Net::kSharedAlonePercent to Net::kSharedStepPercent of the time, so
+// this only pays for jobs of so many bands that the work per CU, not an image's chain of steps, sets the time: launch_decode).
 template <class Net, int MINBLOCKS>
 __global__ void __launch_bounds__(kDecThreads, MINBLOCKS)
 decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ stream, uint64_t nbytes, int n, int H,
@@ -1443,13 +1444,13 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
 
     // Per step: the word of column (t - t_begin) + ahead + 1, requested in the step before, goes to the ring for the
     // next step's gather, and the column after it is requested; columns right of the image read as zero.  The fetch
-    // wave does this where it has no out-block to compute, in two halves when it has such a round in the first layer
-    // too: first the check of the word that has arrived and its conversion (fetch_check), then, behind the barrier
-    // that follows this step's gather and before the one that ends the step, the ring write (fetch_put).  With those
-    // two rounds the request (fetch_request) is issued at the very end of the step, after the pixel has been
+    // wave does this where it has no out-block to compute, in layer kIdleLayer (or at the step's end if there is no such
+    // layer): the check of the word that has arrived (fetch_check), then the ring write, which lies behind the barrier
+    // that follows this step's gather and before the one that ends the step (fetch_put).  Where the first layer has such a
+    // round too, the request (fetch_request) is issued at the very end of the step, after the pixel has been
     // published: the later a word is asked for, the closer the band can follow the band above (a word asked for
-    // before it is published is asked for again, which holds the fetch wave up), and the load is back when the next
-    // step's first layer checks it.  The request always loads (the row's last word again beyond the image): no
+    // before it is published is asked for again, which holds the fetch wave up), and the load is back when layer
+    // kIdleLayer of the next step checks it.  The request always loads (the row's last word again beyond the image): no
     // branch, the value is not used then.
     uint32_t fetched = 0;
     constexpr bool kLateRequest = D::kIdleInFirstLayer;
@@ -1481,7 +1482,8 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     // The pixels decoded in step t_done go from the ring (which holds a pixel for kRingCols steps, as three bf16 of
     // its bytes) to the image: by the 16 first lanes of the storing wave, a lane per row of the band, a step later,
     // where that wave has no out-block to compute, instead of by the lanes that decoded them at the end of their
-    // step, where all four waves would wait for it.  Again in two halves: the ring read, then the stores.  The image is
+    // step, where all four waves would wait for it.  In two halves: the ring read (in the first layer if that has such a
+    // round), then the stores.  The image is
     // addressed as a buffer: lanes and columns without a pixel store beyond its end, which the hardware drops.
     uint16_t held[3] = {0, 0, 0};
     const auto image = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, 3 * H * W, 0x00020000 /* untyped */);
