@@ -125,14 +125,14 @@ int pcc_encode_probs(pcc_ctx *ctx, const uint8_t *d_img, int n, int H, int W,
  * coder and the stream assembly run on a stream the ctx owns, beside the
  * pixel kernel; both streams have been waited for when the call returns, so
  * the caller's view is the same.  The pixel kernel is queued first: where the
- * two do not run at the same time (a profiler collecting counters runs a
- * process's kernels one after the other; so do two streams that share one of the
- * process's hardware queues), the row coder finds all symbols when it starts.
- * Only where the pixel kernel is held up while the row coder already runs (by
- * other work in front of it, or on a chip another job fills) does the row coder
- * give up after PCC_RANS_PATIENCE polls (a few milliseconds with the default) and
- * is launched again behind the pixel kernel: the result is the same, but such a
- * call pays that wait.  PCC_ENCODE_OVERLAP=0 avoids the mode altogether.
+ * two streams share one of the process's hardware queues, the row coder finds all
+ * symbols when it starts.  Where the pixel kernel is held up while the row coder
+ * already runs (by other work in front of it, on a chip another job fills, by a
+ * profiler that collects counters and runs the kernels one at a time in an order
+ * of its own), the row coder gives up after PCC_RANS_PATIENCE polls (a few
+ * milliseconds with the default) and is launched again behind the pixel kernel:
+ * the result is the same, but such a call pays that wait.  PCC_ENCODE_OVERLAP=0
+ * avoids the mode altogether.
  * One call at a time per ctx.  On an error return no kernel of the call is
  * still running on either stream. */
 int pcc_encode(pcc_ctx *ctx, const uint8_t *d_img, int n, int H, int W,

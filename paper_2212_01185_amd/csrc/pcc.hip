@@ -472,8 +472,8 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
             // ahead): the lane polls one of them, sleeping in between so that the polls of a coder that has
             // caught up do not load the memory system, and then loads its whole set again, all loads at once.
             // A running pixel kernel delivers a row's next strip within tens of microseconds.  A wait of
-            // `patience` polls (milliseconds) therefore means that it is held up (other work is in front of it, or the
-            // chip is taken): the row coder stands down, and the host launches it again after the pixel kernel.
+            // `patience` polls (milliseconds) therefore means that it is held up (other work is in front of it, the chip is
+            // taken, a profiler runs the kernels one at a time): the row coder stands down, and the host launches it again after the pixel kernel.
             uint32_t spins = 0;
             for (;;) {
                 size_t stale_at = 0;
