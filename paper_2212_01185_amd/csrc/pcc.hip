@@ -1509,7 +1509,7 @@ decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ str
     int t = t_begin;
     // The bookkeeping of a step's pixel that the symbols themselves do not wait for: the pops of G and B, the words the
     // next pixel may read, and where that pixel goes in the ring.  It is done a step later, in the shadow of the matrix
-    // instructions of the last hidden layer (settle); R's pop has to be done before B's search and is done during G's.
+    // instructions of the second layer and the head (settle); R's pop has to be done before B's search and is done during G's.
     // Two VALU instructions issue for free beside an MFMA of 16 cycles; done at the end of the step, as all three pops
     // once were, this was 500 of its 7,250 cycles.
     Found found_g = {0, 0, 0, 1, 0}, found_b = {0, 0, 0, 1, 0};
