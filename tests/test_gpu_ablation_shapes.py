@@ -173,3 +173,21 @@ def test_a_band_that_gives_up_ends_the_call_where_no_layer_has_an_idle_round(lau
     finally:
         good.close()
         hasty.close()
+
+
+@pytest.mark.parametrize("net", SHAPES + ["diagonal"])
+def test_roundtrip_with_two_workgroups_per_unit(net, monkeypatch):
+    """Every network's build with 256 registers a lane, whose weight slices are partly read from LDS: a few images that
+    share units (540 bands), of odd size."""
+    from paper_2212_01185_amd import binding
+    monkeypatch.setenv("PCC_DECODE_VARIANT", "2")
+    blob = synth.make_diagonal_blob(0) if net == "diagonal" else synth.make_ablation_blob(*synth.ABLATION_SHAPES[net])
+    c = binding.Codec(blob, 0)
+    try:
+        imgs = _dev(np.random.default_rng(65).integers(0, 256, (180, 37, 23, 3), dtype=np.uint8))
+        for n in (180, 3):
+            stream = c.pcc_encode(imgs[:n])
+            _log("%s: %d images with two workgroups per unit" % (net, n))
+            assert torch.equal(c.pcc_decode(stream, n, 37, 23), imgs[:n])
+    finally:
+        c.close()
