@@ -377,7 +377,7 @@ def main():
         result["cpu_baseline"] = cpu_baseline(blob, imgs, min(args.cpu_rows, h))
         result["cpu_baseline"]["host"] = host_description()
         if headline and not args.no_all_configs:
-            # the batch workload with the host's cores: one image per thread (16 threads is the GPU machine's CPU share)
+            # the batch workload with the host's cores: one image per thread (16 threads)
             result["cpu_baseline"]["batch"] = cpu_baseline_batch(blob, synth.make_batch(2), 16,
                                                                  min(16, os.cpu_count() or 1))
     print(json.dumps(result))
