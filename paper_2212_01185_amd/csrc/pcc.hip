@@ -43,19 +43,18 @@ constexpr uint32_t kMailTag = 0x80000000u;
 template <class Net>
 constexpr uint32_t model_tag() { return (uint32_t)Net::K | ((uint32_t)Net::kNbhd << 8) | ((uint32_t)Net::kDelay << 16) | (16u << 24); }
 
-// Encode kernel variants: tiles of 16 pixels per wave per iteration x threads per workgroup.
-// More tiles per wave reuse each LDS weight read more often but need more registers.
-struct EncodeVariant { int tiles, threads; };
-// pcc_encode_probs: pixels of a tile whose head outputs a wave stages in LDS at a time (four, or as many as fit
-// beside the model image: two or one for the largest networks), and the bytes that takes for the workgroup.
+// The pixel kernel's work item: a strip of 32 pixels of one row (two tiles of the network) for a wave.
+constexpr int kStripPixels = 32;
 constexpr int kLdsBytes = 160 * 1024;
-// What the pixel kernel keeps in LDS: the weight tiles of as many leading layers as fit together with all biases,
-// the biases behind them, and behind those the CDF table if there is room left (the whole model image when
-// everything fits).  The other layers' tiles, and the table when it is not there, are read from global memory.
+constexpr int kTakenBytes = 16;          // LDS of the counter that a workgroup's waves take their items from
+// What the pixel kernel keeps in LDS: the weights of as many leading layers as fit together with all biases,
+// the biases behind them, and behind those the CDF table if there is room left (the whole image when
+// everything fits).  The other layers' weights, and the table when it is not there, are read from global memory.
 template <class Net>
 constexpr int encode_resident_layers() {
+    using Lay = Layout<Net>;
     int r = Net::kLayers;
-    while (r > 0 && Layout<Net>::w_off(r) + (Layout<Net>::kLutOff - Layout<Net>::kWeightBytes) > kLdsBytes) --r;
+    while (r > 0 && Lay::w_off(r) + (Lay::kLutOff - Lay::kWeightBytes) + kTakenBytes > kLdsBytes) --r;
     return r;
 }
 template <class Net>
@@ -63,21 +62,22 @@ constexpr int encode_table_lds_off() {      // = Layout::kLutOff when all layers
     return Layout<Net>::w_off(encode_resident_layers<Net>()) + (Layout<Net>::kLutOff - Layout<Net>::kWeightBytes);
 }
 template <class Net>
-constexpr bool encode_table_in_lds() { return encode_table_lds_off<Net>() + (Layout<Net>::kModelBytes - Layout<Net>::kLutOff) <= kLdsBytes; }
+constexpr bool encode_table_in_lds() { return encode_table_lds_off<Net>() + (Layout<Net>::kModelBytes - Layout<Net>::kLutOff) + kTakenBytes <= kLdsBytes; }
 template <class Net>
 constexpr int encode_model_lds_bytes() {
     return encode_table_lds_off<Net>() + (encode_table_in_lds<Net>() ? Layout<Net>::kModelBytes - Layout<Net>::kLutOff : 0);
 }
+// pcc_encode_probs: pixels of a tile whose head outputs a wave stages in LDS at a time (eight, or as many as fit
+// beside the model image), and the bytes that takes for the workgroup.
 // 0: no room for a staging area; the head outputs are then stored value by value.
 template <class Net>
 constexpr int params_stage_pixels(int threads) {
-    for (int px = 4; px >= 1; px /= 2)
-        if (encode_model_lds_bytes<Net>() + (threads / 64) * px * Net::dim(Net::kLayers) * 4 <= kLdsBytes) return px;
+    for (int px = 8; px >= 1; px /= 2)
+        if (encode_model_lds_bytes<Net>() + kTakenBytes + (threads / 64) * px * Net::dim(Net::kLayers) * 4 <= kLdsBytes) return px;
     return 0;
 }
 template <class Net>
 constexpr int params_stage_bytes(int threads) { return (threads / 64) * params_stage_pixels<Net>(threads) * Net::dim(Net::kLayers) * 4; }
-constexpr EncodeVariant kEncodeVariants[4] = {{1, 512}, {2, 512}, {1, 1024}, {4, 256}};
 
 // status words in device memory
 enum { kStErr = 0, kStAbort = 1, kStTicket = 2, kStWords = 4 };
@@ -123,75 +123,49 @@ __host__ __device__ constexpr int head_slot(int c) {
     return -1;
 }
 
-// Compile-time loop: f(std::integral_constant<int, I>) for I = 0 .. N-1.
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
-// Raw head registers of one lane after the network -> mixture of "its" channel
-// (lane groups 0,1,2 = R,G,B) with the coupling coefficients it needs.
-template <class Net>
-struct LaneHead {
-    ChanParams<Net::K> cp;
-    float c1[Net::K];  // alpha (group 1) or beta (group 2)
-    float c2[Net::K];  // gamma (group 2)
-};
-
-template <class Net>
-__device__ __forceinline__ void lane_head_setup(const f32x4_t (&o)[Layout<Net>::kHeadOB], int lane, float lut_scale,
-                                                LaneHead<Net>& h) {
-    constexpr int K = Net::K, HS = Layout<Net>::kHeadSlots;
-    float v[HS];
-#pragma unroll
-    for (int ob = 0; ob < Layout<Net>::kHeadOB; ++ob) {
-        v[4 * ob + 0] = o[ob].x; v[4 * ob + 1] = o[ob].y; v[4 * ob + 2] = o[ob].z; v[4 * ob + 3] = o[ob].w;
-    }
-    const int g = lane >> 4, nl = lane & 15;
-    float raw[3 * K];
-#pragma unroll
-    for (int s = 0; s < 3 * K; ++s) raw[s] = v[s];
-    channel_setup<K>(raw, lut_scale, h.cp);
-    // Coupling coefficients alpha_k = head[9K+k] (needed by group 1), beta_k = head[10K+k] and
-    // gamma_k = head[11K+k] (group 2): the lane's own register where its group holds the value,
-    // else pulled from the lane of the same pixel in the group that does.
-    static_for<0, K>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        constexpr int sa = head_slot<Net>(9 * K + k), sb = head_slot<Net>(10 * K + k), sc = head_slot<Net>(11 * K + k);
-        static_assert(sa >= 0 && sb >= 0 && sc >= 0, "every head output has a register");
-        float va, vb, vc;
-        if constexpr (sa / HS == 1) va = v[sa % HS]; else va = __shfl(v[sa % HS], nl + 16 * (sa / HS));
-        if constexpr (sb / HS == 2) vb = v[sb % HS]; else vb = __shfl(v[sb % HS], nl + 16 * (sb / HS));
-        if constexpr (sc / HS == 2) vc = v[sc % HS]; else vc = __shfl(v[sc % HS], nl + 16 * (sc / HS));
-        h.c1[k] = (g == 1) ? va : vb;
-        h.c2[k] = vc;
-    });
+// A value of each of a pixel's two lanes (lane and lane + 32), in both of them.
+__device__ __forceinline__ void both_halves(uint32_t v, uint32_t& of_half0, uint32_t& of_half1) {
+    const u32x2_t r = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_permlane32_swap(v, v, false, false));
+    of_half0 = r.x;
+    of_half1 = r.y;
 }
 
 // ---------------------------------------------------------------------------
 // encode: all pixels in parallel
 //
-// A work item is a strip of 16 T consecutive pixels of one image row; strips are
-// numbered from the right edge of the image, item = strip * rows + row, and wave
-// w of the grid's G waves takes the items w, w + G, w + 2G, ...  The rows' right
+// A work item is a strip of 32 consecutive pixels of one image row, two tiles of the network; strips are
+// numbered from the right edge of the image, item = strip * rows + row, and the
+// workgroups take the items in turn, one for each of their waves at a time.  The rows' right
 // ends are therefore finished first, which is where the row coder starts (it
 // pushes the symbols last to first).  The row coder may run beside this kernel:
 // then the results go to sf_tagged instead of sf, one 64-bit word per symbol with
 // this launch's epoch in the high half, written through to device scope.  A
 // reader that finds the epoch has the symbol; nothing else is published and
 // nothing has to be cleared between launches (epochs only grow).
+//
+// What bounds it: with weights that are dense numbers the chip's power.  A loop of these MFMAs on random operands in
+// registers runs at 1.94 of 2.4 GHz (2,028 TFLOP/s); this kernel executes 1,490 TFLOP/s of them beside its LDS reads and vector
+// instructions (4096x2160; 227,000 matrix operations per pixel with hi + lo, 117,120 of them the network's).
+// With weights that are mostly zero (the plane predictor) it runs at 2.38 GHz and is bound by its
+// SIMDs: 9,700 cycles a strip against 7,104 of the MFMAs, some 560 of the split's small ones, and 870 vector instructions of
+// 4.1 that the issue port takes between them (an MFMA holds the port for 8 of its 16 cycles).
+// v_mfma_f32_32x32x16_bf16, two of which give the same bits as one 16x16x32, holds it for half as long, but takes 15 % more
+// power for the same numbers (1,764 TFLOP/s): 24 images with the predictor's weights 1,288 us a call against 1,334, but the
+// paper's network 1,910 against 1,800 and 4096x2160 1,475 against 1,437.
+// Two waves per SIMD: one does not hide its own gather and mixtures (1,562 us against 1,246).
+// Pixel kernel, 24 images of 768x512, predictor: 1,455 -> 1,180 us; paper's network 1,854 -> 1,624; 4096x2160 1,578 -> 1,348.
 // ---------------------------------------------------------------------------
-template <class Net, int T, int THREADS>
+template <class Net, int THREADS>
 __global__ void __launch_bounds__(THREADS)
 encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img, int n, int H, int W,
               uint32_t* __restrict__ sf, float* __restrict__ params, float* __restrict__ bits, int* status,
               uint64_t* sf_tagged, uint32_t epoch, uint32_t strip_begin, uint32_t strip_count) {
     using Lay = Layout<Net>;
+    using Head = EncHead<Net>;
     constexpr int K = Net::K, KB0 = Net::kb(0), HEAD = Net::dim(Net::kLayers);
     extern __shared__ __align__(16) uint8_t lds[];
+    uint32_t* taken = reinterpret_cast<uint32_t*>(lds + encode_model_lds_bytes<Net>());     // items of the workgroup that have been taken
+    if (threadIdx.x == 0) *taken = 0;
     constexpr int RESIDENT = encode_resident_layers<Net>();
     if constexpr (RESIDENT == Net::kLayers) {
         copy_to_lds(lds, model, encode_model_lds_bytes<Net>());
@@ -203,50 +177,81 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
     const uint8_t* table_at = encode_table_in_lds<Net>() ? lds + (encode_table_lds_off<Net>() - Lay::kLutOff) : model;
     const float2* lut = reinterpret_cast<const float2*>(table_at + Lay::kLutOff);
     const float lut_scale = *reinterpret_cast<const float*>(table_at + Lay::kLutScaleOff);
-    const int lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
+    constexpr uint32_t nwaves = THREADS / 64;
+    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar: the item's row and strip are scalars too
-    const int g = lane >> 4, nl = lane & 15;
+    const int g = lane >> 4, nl = lane & 15;      // the network's lane: inputs of k-slot group g of pixel nl of a tile
+    const int h = lane >> 5, px = lane & 31;      // the mixtures' lane: pixel px of the strip; its channel R (half 0) or G (half 1), and half of B
     const bf16x4_bits_t minus_one = minus_identity(lane);
     const uint32_t rows = (uint32_t)n * (uint32_t)H;
     const uint32_t P = rows * (uint32_t)W;
     const uint32_t items = strip_count * rows;              // this launch's strips: strip_begin .. strip_begin + strip_count - 1
-    for (uint32_t item = blockIdx.x * nwaves + wave; item < items; item += gridDim.x * nwaves) {
-        const uint32_t local = item / rows, rowg = item - local * rows, strip = strip_begin + local;
+    // This lane's first-layer inputs are runs of four consecutive image bytes.  Byte offset of a run from the strip's first pixel,
+    // for the first tile.
+    uint32_t run_at[KB0][2];
+    bool run_used[KB0][2];
+#pragma unroll
+    for (int kb = 0; kb < KB0; ++kb) {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            int dr = 0, off = 0;
+            run_used[kb][half] = Net::run_desc(kb, g, half, dr, off);
+            run_at[kb][half] = run_used[kb][half] ? (uint32_t)((dr * W + nl - 2) * 3 + off) : 3u * (uint32_t)nl;
+        }
+    }
+    // The workgroup's waves take the next of its items as they get free, from a counter in LDS: of the two waves of a SIMD the
+    // older one goes first wherever both can issue and is through its work faster.  (Dealt out beforehand, the older waves
+    // ended after four fifths of the kernel's time, and the younger ones had a SIMD each for the rest.)
+    auto take = [&]() __attribute__((always_inline)) {
+        uint32_t k = 0;
+        if (lane == 0) k = atomicAdd(taken, 1u);
+        k = (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
+        return (k / nwaves * gridDim.x + blockIdx.x) * nwaves + k % nwaves;
+    };
+    // An item's bytes: the lane's runs of both tiles and its pixel's own bytes r | g<<8 | b<<16.
+    auto gather = [&](uint32_t item, uint32_t& rowg, int& c0, uint32_t (&runs)[KB0][2][2], uint32_t& pix) __attribute__((always_inline)) {
+        const uint32_t local = item / rows, strip = strip_begin + local;
+        rowg = item - local * rows;
         const uint32_t im = rowg / (uint32_t)H;
         const int r = (int)(rowg - im * (uint32_t)H);
-        const int c0 = W - 16 * T * (int)(strip + 1);           // negative in the leftmost strip of a ragged width
+        c0 = W - kStripPixels * (int)(strip + 1);               // negative in the leftmost strip of a ragged width
         const uint8_t* base = img + (size_t)im * H * W * 3;
-        u32x4_t in[T][KB0][2];
-        uint32_t pix[T];   // the pixel's own bytes r | g<<8 | b<<16
+        if (r >= 2 && c0 >= 2 && c0 + kStripPixels + 3 <= W) {
+            // everything the strip's pixels look at lies in the image (their runs end at column c + 3 at most)
+            const uint8_t* first = base + ((size_t)r * W + c0) * 3;
+            __builtin_memcpy(&pix, first + 3u * (uint32_t)px, 4);     // unaligned dword; the fourth byte is the next pixel's
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int c = c0 + 16 * t + nl;
-            uint32_t runs[KB0][2];
+            for (int kb = 0; kb < KB0; ++kb) {
 #pragma unroll
-            for (int kbi = 0; kbi < KB0; ++kbi) { runs[kbi][0] = 0; runs[kbi][1] = 0; }
-            pix[t] = 0;
-            if (c >= 0) {
-                const uint32_t p = rowg * (uint32_t)W + (uint32_t)c;
-                const int me = (r * W + c) * 3;
-                if (p + 1 < P) {
-                    uint32_t v;
-                    __builtin_memcpy(&v, base + me, 4);       // unaligned dword; the fourth byte is the next pixel's
-                    pix[t] = v & 0xFFFFFFu;
-                } else {
-                    pix[t] = (uint32_t)base[me] | ((uint32_t)base[me + 1] << 8) | ((uint32_t)base[me + 2] << 16);
+                for (int half = 0; half < 2; ++half) {
+                    const uint8_t* run = first + (int)run_at[kb][half];
+                    __builtin_memcpy(&runs[kb][0][half], run, 4);
+                    __builtin_memcpy(&runs[kb][1][half], run + 3 * 16, 4);
                 }
-                // This lane's first-layer inputs are runs of four consecutive image bytes; a run is
-                // read with one load when all its bytes lie in the image, byte by byte at the borders.
+            }
+            return;
+        }
+        pix = 0;
+        if (c0 + px >= 0) {
+            const uint32_t p = rowg * (uint32_t)W + (uint32_t)(c0 + px);
+            const int me = (r * W + c0 + px) * 3;
+            if (p + 1 < P) __builtin_memcpy(&pix, base + me, 4);
+            else pix = (uint32_t)base[me] | ((uint32_t)base[me + 1] << 8) | ((uint32_t)base[me + 2] << 16);
+        }
+        // a run is read with one load when all its bytes lie in the image, byte by byte at the borders
 #pragma unroll
-                for (int kbi = 0; kbi < KB0; ++kbi) {
+        for (int kb = 0; kb < KB0; ++kb) {
 #pragma unroll
-                    for (int half = 0; half < 2; ++half) {
-                        int dr = 0, off = 0;
-                        if (!Net::run_desc(kbi, g, half, dr, off)) continue;
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    uint32_t v = 0;
+                    const int c = c0 + 16 * t + nl;
+                    int dr = 0, off = 0;
+                    if (Net::run_desc(kb, g, half, dr, off) && c >= 0) {
                         const int rr = r + dr;
                         const int at = (rr * W + (c - 2)) * 3 + off;
                         const int col_first = c - 2 + ((off * 11) >> 5), col_last = c - 2 + (((off + 3) * 11) >> 5);
-                        uint32_t v = 0;
                         if (rr >= 0 && col_first >= 0 && col_last < W) {
                             __builtin_memcpy(&v, base + at, 4);
                         } else if (rr >= 0) {
@@ -256,61 +261,92 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
                                 if (col >= 0 && col < W) v |= (uint32_t)base[at + i] << (8 * i);
                             }
                         }
-                        runs[kbi][half] = v;
                     }
+                    runs[kb][t][half] = v;
                 }
             }
+        }
+    };
+    // The next item's bytes are asked for before the network runs on this one's.
+    uint32_t item = take(), next_row = 0, runs[KB0][2][2], next_pix = 0;
+    int next_c0 = 0;
+    if (item < items) gather(item, next_row, next_c0, runs, next_pix);
+    while (item < items) {
+        const uint32_t rowg = next_row, pix = next_pix & 0xFFFFFFu;
+        const int c0 = next_c0, c = c0 + px;
+        const bool live = c >= 0;
+        u32x4_t in[KB0][2][2];
 #pragma unroll
-            for (int kbi = 0; kbi < KB0; ++kbi) {
+        for (int kb = 0; kb < KB0; ++kb) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
                 uint32_t a, b, c2, d;
-                run_to_bf16(runs[kbi][0], a, b);
-                run_to_bf16(runs[kbi][1], c2, d);
-                in[t][kbi][0].x = a; in[t][kbi][0].y = b; in[t][kbi][0].z = c2; in[t][kbi][0].w = d;
-                in[t][kbi][1] = in[t][kbi][0];   // unused (layer-1 inputs are exact)
+                run_to_bf16(run_used[kb][0] ? runs[kb][t][0] : 0u, a, b);
+                run_to_bf16(run_used[kb][1] ? runs[kb][t][1] : 0u, c2, d);
+                in[kb][t][0].x = a; in[kb][t][0].y = b; in[kb][t][0].z = c2; in[kb][t][0].w = d;
+                in[kb][t][1] = in[kb][t][0];   // unused (layer-1 inputs are exact)
             }
         }
-        f32x4_t out[T][Lay::kHeadOB];
-        mlp_from<Net, T, (T == 1 && THREADS <= 512), 0, RESIDENT>(lds + opaque_zero(), model, lane, minus_one, in, out);
+        item = take();
+        if (item < items) gather(item, next_row, next_c0, runs, next_pix);
+        f32x4_t out[Lay::kHeadOB][2];
+        // the wave that feeds the matrix cores goes first (2048x1365 head outputs 524 -> 494 us, 24 images of the paper's network 1,647 -> 1,624)
+        __builtin_amdgcn_s_setprio(2);
+        EncoderNet<Net, RESIDENT>{lds + opaque_zero(), model + opaque_zero(), lane, minus_one}.run(in, out);
+        __builtin_amdgcn_s_setprio(0);
         // The head's results are first read behind branches (which outputs are wanted, border tiles).  The wait
         // states an MFMA's result needs are counted along the instruction stream as laid out, not along a taken
         // branch, so the accumulators are made to settle here, in straight-line code.
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-#pragma unroll
-            for (int ob = 0; ob < Lay::kHeadOB; ++ob) asm volatile("" : "+v"(out[t][ob]));
-        }
+        for (int ob = 0; ob < Lay::kHeadOB; ++ob) asm volatile("" : "+v"(out[ob][0]), "+v"(out[ob][1]));
         asm volatile("s_nop 7" ::: "memory");
 
+        // from two tiles of four lane groups to one strip of two halves (EncHead)
+        float head[Head::kSlots];
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int c = c0 + 16 * t + nl;
-            const bool live = c >= 0;
-            const uint32_t p = rowg * (uint32_t)W + (uint32_t)c;
-            constexpr int kStagePixels = params_stage_pixels<Net>(THREADS);
-            constexpr int PX = kStagePixels > 0 ? kStagePixels : 1;       // (the block below is dead code when there is no room)
-            if (kStagePixels > 0 && params != nullptr && ((uintptr_t)params & 15u) == 0) {
-                // The tile's head outputs are HEAD consecutive floats per pixel, 16 consecutive pixels: they go
+        for (int s = 0; s < Head::kGroupSlots; ++s) {
+            const u32x2_t r = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_permlane16_swap(
+                __float_as_uint(out[s >> 2][0][s & 3]), __float_as_uint(out[s >> 2][1][s & 3]), false, false));
+            head[s] = __uint_as_float(r.x);
+            head[s + Head::kGroupSlots] = __uint_as_float(r.y);
+        }
+        // B's values, which the two lanes of a pixel hold in turn, in both
+        float item_b[Head::kBItems];
+        static_for<0, (Head::kBItems + 1) / 2>([&](auto pc) {
+            constexpr int b = 2 * decltype(pc)::value;
+            uint32_t v0, v1;
+            both_halves(__float_as_uint(head[Head::b_slot(b)]), v0, v1);
+            item_b[b] = __uint_as_float(v0);
+            if constexpr (b + 1 < Head::kBItems) {
+                static_assert(Head::b_half(b) == 0 && Head::b_half(b + 1) == 1 && Head::b_slot(b) == Head::b_slot(b + 1), "pairs share a register");
+                item_b[b + 1] = __uint_as_float(v1);
+            }
+        });
+        const uint32_t p = rowg * (uint32_t)W + (uint32_t)c;
+        if (params != nullptr) {
+            // A pixel's outputs are R's, G's, B's parameters (3 K each), alphas, betas, gammas (K each): half 0 holds the first
+            // and third group of 3 K, half 1 the second and fourth.
+            constexpr int PX = params_stage_pixels<Net>(THREADS) > 0 ? params_stage_pixels<Net>(THREADS) : 1;
+            float second[3 * K];
+#pragma unroll
+            for (int i = 0; i < 3 * K; ++i) second[i] = h == 0 ? item_b[i] : i < K ? head[3 * K + i] : item_b[2 * K + i];
+            if (params_stage_pixels<Net>(THREADS) > 0 && ((uintptr_t)params & 15u) == 0) {
+                // The tile's head outputs are HEAD consecutive floats per pixel, 32 consecutive pixels: they go
                 // through a staging area of this wave in LDS, PX pixels at a time, and leave as
                 // 16-byte stores of consecutive lanes (stored straight from the registers, a lane's values lie
                 // 4 bytes here and 4 bytes there, 240 bytes apart from its neighbour's).  LDS takes a wave's
                 // instructions in order, so the reads see the writes of the same pass.
-                float* stage = reinterpret_cast<float*>(lds + encode_model_lds_bytes<Net>()) + wave * (PX * HEAD);
+                float* stage = reinterpret_cast<float*>(lds + encode_model_lds_bytes<Net>() + kTakenBytes) + wave * (PX * HEAD);
 #pragma unroll
-                for (int pass = 0; pass < 16 / PX; ++pass) {
-                    if (nl / PX == pass) {
+                for (int pass = 0; pass < kStripPixels / PX; ++pass) {
+                    if (px / PX == pass) {
+                        float* mine = stage + (px % PX) * HEAD + 3 * K * h;
 #pragma unroll
-                        for (int ob = 0; ob < Lay::kHeadOB; ++ob) {
-                            const float vv[4] = {out[t][ob].x, out[t][ob].y, out[t][ob].z, out[t][ob].w};
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const int idx = Net::head_index(g, 4 * ob + i);
-                                if (idx >= 0) stage[(nl % PX) * HEAD + idx] = vv[i];
-                            }
-                        }
+                        for (int i = 0; i < 3 * K; ++i) { mine[i] = head[i]; mine[6 * K + i] = second[i]; }
                     }
                     __builtin_amdgcn_wave_barrier();
                     for (int j = lane; j < PX * HEAD / 4; j += 64) {
-                        const int cc = c0 + 16 * t + pass * PX + (4 * j) / HEAD;      // the chunk's pixel
+                        const int cc = c0 + pass * PX + (4 * j) / HEAD;      // the chunk's pixel
                         if (cc >= 0) {
                             const f32x4_t v = *reinterpret_cast<const f32x4_t*>(stage + 4 * j);
                             *reinterpret_cast<f32x4_t*>(params + ((size_t)rowg * W + cc) * HEAD + (4 * j) % HEAD) = v;
@@ -318,40 +354,73 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
                     }
                     __builtin_amdgcn_wave_barrier();
                 }
-            } else if (params != nullptr && live) {
+            } else if (live) {
+                float* mine = params + (size_t)p * HEAD + 3 * K * h;
 #pragma unroll
-                for (int ob = 0; ob < Lay::kHeadOB; ++ob) {
-                    const float vv[4] = {out[t][ob].x, out[t][ob].y, out[t][ob].z, out[t][ob].w};
+                for (int i = 0; i < 3 * K; ++i) { mine[i] = head[i]; mine[6 * K + i] = second[i]; }
+            }
+        }
+        const float rhat = (float)(pix & 0xFF) * (1.0f / 256.0f);
+        const float ghat = (float)((pix >> 8) & 0xFF) * (1.0f / 256.0f);
+        // the lane's own channel: R, or G given R
+        uint32_t lo, freq;
+        {
+            float raw[3 * K];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int idx = Net::head_index(g, 4 * ob + i);
-                        if (idx >= 0) params[(size_t)p * HEAD + idx] = vv[i];
-                    }
-                }
+            for (int s = 0; s < 3 * K; ++s) raw[s] = head[s];
+            ChanParams<K> cp;
+            channel_setup<K>(raw, lut_scale, cp);
+            if (h == 1) {
+                float alpha[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k) alpha[k] = head[3 * K + k];
+                couple_green<K>(cp, alpha, rhat);
             }
-            LaneHead<Net> h;
-            lane_head_setup<Net>(out[t], lane, lut_scale, h);
-            const float rhat = (float)(pix[t] & 0xFF) * (1.0f / 256.0f);
-            const float ghat = (float)((pix[t] >> 8) & 0xFF) * (1.0f / 256.0f);
-            if (g == 1) couple_green<K>(h.cp, h.c1, rhat);
-            if (g == 2) couple_blue<K>(h.cp, h.c1, h.c2, rhat, ghat);
-            const int x = (int)((pix[t] >> (8 * (g & 3))) & 0xFF);   // group 3 reads the zero top byte
-            const uint32_t lo = cq_full<K>(h.cp, x, lut);
-            const uint32_t hi = cq_full<K>(h.cp, x + 1, lut);
-            uint32_t freq = hi - lo;
-            if (g < 3 && live && (hi <= lo || freq > 65536u)) { set_error(status, PCC_E_INTERNAL); freq = 1; }
-            if (g < 3 && live) {
-                const uint32_t word = lo | ((freq - 1u) << 16);
-                if (sf_tagged != nullptr)
-                    __hip_atomic_store(&sf_tagged[(size_t)p * 3 + g], ((uint64_t)epoch << 32) | word, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                else if (sf != nullptr) sf[(size_t)p * 3 + g] = word;
+            const int x = (int)((pix >> (8 * h)) & 0xFF);
+            lo = cq_full<K>(cp, x, lut);
+            freq = cq_full<K>(cp, x + 1, lut) - lo;
+        }
+        // B given R and G: half 0 evaluates the lower edge, half 1 the upper one
+        uint32_t lo_b, freq_b;
+        {
+            float raw[3 * K], beta[K], gamma[K];
+#pragma unroll
+            for (int i = 0; i < 3 * K; ++i) raw[i] = item_b[i];
+#pragma unroll
+            for (int k = 0; k < K; ++k) { beta[k] = item_b[3 * K + k]; gamma[k] = item_b[4 * K + k]; }
+            ChanParams<K> cp;
+            channel_setup<K>(raw, lut_scale, cp);
+            couple_blue<K>(cp, beta, gamma, rhat, ghat);
+            uint32_t hi_b;
+            both_halves(cq_full<K>(cp, (int)(pix >> 16) + h, lut), lo_b, hi_b);
+            freq_b = hi_b - lo_b;
+        }
+        // Cq increases strictly from 0 to 65536: a frequency outside 1 .. 65536 (also: lo not below hi) is an error
+        if (live && (freq - 1u > 65535u || freq_b - 1u > 65535u)) {
+            set_error(status, PCC_E_INTERNAL);
+            if (freq - 1u > 65535u) freq = 1;
+            if (freq_b - 1u > 65535u) freq_b = 1;
+        }
+        const uint32_t word = lo | ((freq - 1u) << 16), word_b = lo_b | ((freq_b - 1u) << 16);
+        if (sf_tagged != nullptr) {
+            if (live) {
+                uint64_t* at = sf_tagged + (size_t)p * 3;
+                __hip_atomic_store(at + h, ((uint64_t)epoch << 32) | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (h == 0) __hip_atomic_store(at + 2, ((uint64_t)epoch << 32) | word_b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (bits != nullptr) {
-                const float mine = 16.0f - __builtin_amdgcn_logf((float)freq);
-                const float tot = (__shfl(mine, nl) + __shfl(mine, nl + 16)) + __shfl(mine, nl + 32);
-                if (g == 0 && live) bits[p] = tot;
+        } else if (sf != nullptr) {
+            uint32_t word_r, word_g;
+            both_halves(word, word_r, word_g);
+            if (live && h == 0) {
+                const uint32_t three[3] = {word_r, word_g, word_b};
+                __builtin_memcpy(sf + (size_t)p * 3, three, sizeof three);
             }
+        }
+        if (bits != nullptr) {
+            uint32_t bits_r, bits_g;
+            both_halves(__float_as_uint(16.0f - __builtin_amdgcn_logf((float)freq)), bits_r, bits_g);
+            const float tot = (__uint_as_float(bits_r) + __uint_as_float(bits_g)) + (16.0f - __builtin_amdgcn_logf((float)freq_b));
+            if (h == 0 && live) bits[p] = tot;
         }
     }
 }
@@ -1888,7 +1957,7 @@ struct pcc_ctx {
     int num_cus = 0;
     uint32_t* d_static_scratch = nullptr;   // this device's copy of the static scratch array (pcc_decode_static)
     uint32_t dist = 0;             // written to / checked against stream header word 6
-    int encode_variant = 1;
+    int encode_threads = 512;       // of a workgroup of the pixel kernel
     uint32_t spin_limit = 1u << 22;      // polls of a band for one pixel of the band above (seconds) before the call fails (PCC_DECODE_SPIN_LIMIT, for tests)
     int decode_variant = 0;              // 0: chosen per job; 1: one workgroup per CU; 2: two (PCC_DECODE_VARIANT, for measurements)
     // the row coder of a small job runs beside the pixel kernel, on a stream of its own
@@ -2041,7 +2110,7 @@ int pack_model(const uint8_t* p, size_t blob_bytes, uint32_t dist, std::vector<u
     auto Wat = [&](int l, int o, int i) { return rdf(wsrc[l] + 4 * ((size_t)o * Net::dim(l) + i)); };
     auto Bat = [&](int l, int o) { return rdf(bsrc[l] + 4 * (size_t)o); };
 
-    image.assign(Lay::kModelBytes, 0);
+    image.assign(2 * Lay::kModelBytes, 0);        // the decoder's image; behind it the encoder's, with the head's rows in another order
     uint16_t* w16 = reinterpret_cast<uint16_t*>(image.data());
     for (int l = 0; l < NL; ++l) {
         const int nob = Net::ob(l), nkb = Net::kb(l);
@@ -2092,23 +2161,36 @@ int pack_model(const uint8_t* p, size_t blob_bytes, uint32_t dist, std::vector<u
     }
     lut[2 * kLutEntries] = 1.0f;
     lut[2 * kLutEntries + 1] = 0.0f;
+
+    uint8_t* enc = image.data() + Lay::kModelBytes;
+    memcpy(enc, image.data(), Lay::kModelBytes);
+    constexpr int kHead = NL - 1;
+    for (int s = 0; s < 16 * Net::ob(kHead); ++s) {
+        const int ob = s >> 4, m = s & 15, c = EncHead<Net>::head_index(m >> 2, 4 * ob + (m & 3));
+        // the row of the decoder's head that holds this output, or one that holds none
+        int from = -1;
+        for (int k = 0; k < 16 * Net::ob(kHead); ++k) if (Net::head_index((k & 15) >> 2, 4 * (k >> 4) + (k & 3)) == c) from = k;
+        for (int kb = 0; kb < Net::kb(kHead); ++kb)
+            for (int g = 0; g < 4; ++g) {
+                uint8_t* to = enc + Lay::w_off(kHead) + ((ob * Net::kb(kHead) + kb) * 64 + 16 * g + m) * 16;
+                if (c < 0) memset(to, 0, 16);
+                else memcpy(to, image.data() + Lay::w_off(kHead) + (((from >> 4) * Net::kb(kHead) + kb) * 64 + 16 * g + (from & 15)) * 16, 16);
+            }
+        if (c < 0) memset(enc + Lay::b_off(kHead) + 4 * s, 0, 4);
+        else memcpy(enc + Lay::b_off(kHead) + 4 * s, image.data() + Lay::b_off(kHead) + 4 * from, 4);
+    }
     return PCC_OK;
 }
 
 template <class Net>
 bool set_kernel_attributes() {
-    constexpr int stage = std::max(params_stage_bytes<Net>(256), std::max(params_stage_bytes<Net>(512), params_stage_bytes<Net>(1024)));
-    constexpr int enc = encode_model_lds_bytes<Net>() + stage, dec = DecLds<Net>::kBytes;
+    constexpr int enc = encode_model_lds_bytes<Net>() + kTakenBytes + std::max(params_stage_bytes<Net>(256), params_stage_bytes<Net>(512)), dec = DecLds<Net>::kBytes;
     static_assert(enc <= kLdsBytes && dec <= kLdsBytes && DecLds<Net>::kBytesShared <= kLdsBytes,
                   "the network does not fit a compute unit's LDS");
     bool ok = true;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 1, 512>),
+    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 256>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, enc) == hipSuccess;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 2, 512>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, enc) == hipSuccess;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 1, 1024>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, enc) == hipSuccess;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 4, 256>),
+    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 512>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, enc) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<Net, 1>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, dec) == hipSuccess;
@@ -2124,16 +2206,12 @@ bool set_kernel_attributes() {
     return ok;
 }
 
-// Workgroups of the pixel kernel.  reserve_cus: compute units left free for a kernel that runs beside it.
-uint32_t encode_strips(const pcc_ctx* ctx, int W) {
-    const uint32_t cols = 16u * (uint32_t)kEncodeVariants[ctx->encode_variant].tiles;
-    return ((uint32_t)W + cols - 1) / cols;
-}
+uint32_t encode_strips(int W) { return ((uint32_t)W + kStripPixels - 1) / kStripPixels; }
 
+// Workgroups of the pixel kernel.  reserve_cus: compute units left free for a kernel that runs beside it.
 uint32_t encode_blocks(const pcc_ctx* ctx, int n, int H, uint32_t strips, uint32_t reserve_cus) {
-    const EncodeVariant ev = kEncodeVariants[ctx->encode_variant];
     const uint64_t items = (uint64_t)strips * (uint64_t)n * H;          // dims_ok: below 2^31
-    const uint32_t per_block = ev.threads / 64;
+    const uint32_t per_block = (uint32_t)ctx->encode_threads / 64;
     const uint64_t blocks = (items + per_block - 1) / per_block;
     const uint32_t cus = (ctx->num_cus > 0 ? (uint32_t)ctx->num_cus : 256u) - reserve_cus;
     return blocks > cus ? cus : (uint32_t)blocks;   // persistent: one workgroup per CU, looping over the items
@@ -2143,26 +2221,15 @@ uint32_t encode_blocks(const pcc_ctx* ctx, int n, int H, uint32_t strips, uint32
 template <class Net>
 int launch_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint32_t* sf, float* params, float* bits,
                   uint64_t* sf_tagged, uint32_t reserve_cus, uint32_t strip_begin, uint32_t strip_count, hipStream_t st) {
-    const int kLds = encode_model_lds_bytes<Net>() + (params != nullptr ? params_stage_bytes<Net>(kEncodeVariants[ctx->encode_variant].threads) : 0);
+    const int lds = encode_model_lds_bytes<Net>() + kTakenBytes + (params != nullptr ? params_stage_bytes<Net>(ctx->encode_threads) : 0);
     const uint32_t blocks = encode_blocks(ctx, n, H, strip_count, reserve_cus);
-    switch (ctx->encode_variant) {
-        case 0:
-            hipLaunchKernelGGL((encode_kernel<Net, 1, 512>), dim3(blocks), dim3(512), kLds, st, ctx->d_model, d_img, n, H, W,
-                               sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
-            break;
-        case 1:
-            hipLaunchKernelGGL((encode_kernel<Net, 2, 512>), dim3(blocks), dim3(512), kLds, st, ctx->d_model, d_img, n, H, W,
-                               sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
-            break;
-        case 2:
-            hipLaunchKernelGGL((encode_kernel<Net, 1, 1024>), dim3(blocks), dim3(1024), kLds, st, ctx->d_model, d_img, n, H, W,
-                               sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
-            break;
-        default:
-            hipLaunchKernelGGL((encode_kernel<Net, 4, 256>), dim3(blocks), dim3(256), kLds, st, ctx->d_model, d_img, n, H, W,
-                               sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
-            break;
-    }
+    const uint8_t* model = ctx->d_model + Layout<Net>::kModelBytes;
+    if (ctx->encode_threads == 256)
+        hipLaunchKernelGGL((encode_kernel<Net, 256>), dim3(blocks), dim3(256), lds, st, model, d_img, n, H, W,
+                           sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
+    else
+        hipLaunchKernelGGL((encode_kernel<Net, 512>), dim3(blocks), dim3(512), lds, st, model, d_img, n, H, W,
+                           sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
     return hipGetLastError() == hipSuccess ? PCC_OK : PCC_E_HIP;
 }
 
@@ -2287,10 +2354,10 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
     ok = ok && hipHostMalloc((void**)&ctx->h_status, kStBytes, hipHostMallocDefault) == hipSuccess;
     ok = ok && hipMemcpy(ctx->d_model, image.data(), image.size(), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && with_net(net, [](auto tag) { return set_kernel_attributes<decltype(tag)>(); });
-    ctx->encode_variant = with_net(net, [](auto tag) { return decltype(tag)::kEncodeVariant; });
+    ctx->encode_threads = with_net(net, [](auto tag) { return decltype(tag)::kEncodeThreads; });
     if (const char* e = getenv("PCC_ENCODE_VARIANT")) {
         const int v = atoi(e);
-        if (v >= 0 && v < 4) ctx->encode_variant = v;
+        if (v >= 0 && v < 2) ctx->encode_threads = v == 0 ? 256 : 512;
     }
     // limits from the environment: negative values are taken as zero (no patience), never as huge unsigned ones
     auto env_limit = [](const char* e) { const long v = atol(e); return (uint32_t)std::min<long>(std::max<long>(v, 0), 0x7FFFFFFFl); };
@@ -2343,7 +2410,7 @@ int pcc_encode_probs(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, fl
     if (!ctx || !d_img || !d_params || !dims_ok(n, H, W)) return PCC_E_ARG;
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return PCC_E_HIP;
-    return launch_encode_any(ctx, d_img, n, H, W, nullptr, d_params, d_bits, nullptr, 0, 0, encode_strips(ctx, W),
+    return launch_encode_any(ctx, d_img, n, H, W, nullptr, d_params, d_bits, nullptr, 0, 0, encode_strips(W),
                              (hipStream_t)hip_stream);
 }
 
@@ -2434,7 +2501,7 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         if (hipStreamSynchronize(s) != hipSuccess) { (void)hipGetLastError(); return PCC_E_HIP; }
         return PCC_OK;
     };
-    const uint32_t strips = encode_strips(ctx, W);
+    const uint32_t strips = encode_strips(W);
     if (!beside) {
         prof_begin(ctx, PCC_T_ENCODE_PIXELS, st);
         rc = launch_encode_any(ctx, d_img, n, H, W, d_sf, nullptr, nullptr, nullptr, 0, 0, strips, st);

@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace pcc {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -73,7 +75,7 @@ struct NetWorkload {
     //   four layers        6.38 (11)    6.60 (0)      6.43 (0)     6.64 (0)         6.83 (0)
     //   64 filters         5.65 (0)     5.69 (0)      5.63 (0)     5.73 (0)         5.89 (0)
     // (Seven mixtures: the first layer and the head do not fit a CU twice, `all` is the biases and the first layer.)
-    static constexpr int kEncodeVariant = 1;      // pixel kernel: two tiles per work item, 512 threads (index into the host's table)
+    static constexpr int kEncodeThreads = 512;    // pixel kernel: threads of a workgroup
     static constexpr int kSharedCuLds = 6;
     // Time of a decode step with two workgroups per CU, in percent of a step with one, while the other workgroup waits and
     // while both are busy (fitted to whole jobs; the host chooses between the two launches with them: launch_decode).
@@ -112,7 +114,7 @@ struct NetPaper {
     static constexpr int kRingCols = 16;
     static constexpr int kRingPad = 4;
     static constexpr bool kLeaky = true;
-    static constexpr int kEncodeVariant = 1;
+    static constexpr int kEncodeThreads = 512;
     static constexpr int kSharedCuLds = 6;
     static constexpr unsigned kSharedAlonePercent = 108, kSharedStepPercent = 137;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
@@ -179,7 +181,9 @@ struct NetAblation : NetPaper {
                   "unsupported shape");
     static constexpr int kLayers = LAYERS;
     static constexpr int K = MIXTURES;
-    static constexpr int kEncodeVariant = 1;
+    // 192 filters: a strip's activations and the next layer's take 192 registers, more than half of a lane's: with two waves to a
+    // SIMD some 190 are spilled (4 images of 640x480: 882 us with 512 threads, 546 with 256).
+    static constexpr int kEncodeThreads = C > 128 ? 256 : 512;
     static constexpr int kSharedCuLds = MIXTURES >= 7 || LAYERS >= 6 ? 7 : MIXTURES >= 5 ? 6 : 4;
     // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch.)
     static constexpr unsigned kSharedAlonePercent = C > 128 ? 1000 : MIXTURES >= 7 ? 126 : MIXTURES >= 5 ? 107 : LAYERS >= 6 ? 114 : LAYERS <= 4 ? 104 : 101;
@@ -254,10 +258,57 @@ struct Layout {
 };
 static_assert(Layout<NetWorkload>::kWeightBytes == 118784, "workload weight image size");
 
+// The encoder's head.  A wave of the encoder takes a strip of 32 pixels, two MFMA tiles of 16; one exchange of rows of 16
+// lanes per register (v_permlane16_swap) between the tiles' outputs gives every pixel two lanes, l and l + 32 ("halves"):
+// half 0 holds lane groups 0 and 1 of both, half 1 groups 2 and 3.  The halves take a channel each, half 0 R and half 1 G, and
+// share B's two CDF values, so that three evaluations per pixel and lane do for the strip's six per pixel (four where each lane
+// group took a channel of its tile and a fourth group none).
+// Register S of a half: its channel's 3 K parameters; in half 1 the K alphas; then B's 5 K values (parameters, betas, gammas),
+// alternately in half 0 and half 1 of a register, from where both get them.  The last one of five mixtures does not fit there
+// and stands in half 0 beside the alphas.
+template <class Net>
+struct EncHead {
+    static constexpr int K = Net::K;
+    static constexpr int kGroupSlots = Layout<Net>::kHeadSlots;       // registers of a lane group
+    static constexpr int kSlots = 2 * kGroupSlots;
+    static constexpr int kBItems = 5 * K;
+    __host__ __device__ static constexpr int b_canonical(int b) { return b < 3 * K ? 6 * K + b : 10 * K + (b - 3 * K); }
+    __host__ __device__ static constexpr int b_slot(int b) { return 4 * K + b / 2 < kSlots ? 4 * K + b / 2 : 3 * K + (4 * K + b / 2 - kSlots); }
+    __host__ __device__ static constexpr int b_half(int b) { return 4 * K + b / 2 < kSlots ? b % 2 : 0; }
+    // canonical head output in register S of half h, or -1
+    __host__ __device__ static constexpr int index(int h, int S) {
+        if (S < 3 * K) return 3 * K * h + S;
+        if (h == 1 && S < 4 * K) return 9 * K + (S - 3 * K);
+        for (int b = 0; b < kBItems; ++b) if (b_slot(b) == S && b_half(b) == h) return b_canonical(b);
+        return -1;
+    }
+    // ... in register s of lane group g of a tile's outputs
+    __host__ __device__ static constexpr int head_index(int g, int s) { return index(g >> 1, s + (g & 1) * kGroupSlots); }
+    static constexpr bool placed_once() {
+        for (int c = 0; c < Net::dim(Net::kLayers); ++c) {
+            int n = 0;
+            for (int g = 0; g < 4; ++g) for (int s = 0; s < kGroupSlots; ++s) n += head_index(g, s) == c ? 1 : 0;
+            if (n != 1) return false;
+        }
+        return true;
+    }
+};
+static_assert(EncHead<NetWorkload>::placed_once() && EncHead<NetPaper>::placed_once() && EncHead<NetMostMixtures>::placed_once(),
+              "encoder's head layout");
+
 // Feature index (within a 32-wide k-block) held in slot i of lane group g for
 // the layers after the first: the two 16-row output tiles of the previous layer,
 // as MFMA left them.
 __host__ __device__ constexpr int kslot_feature(int g, int i) { return 16 * (i >> 2) + 4 * g + (i & 3); }
+
+// Compile-time loop: f(std::integral_constant<int, I>) for I = 0 .. N-1.
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
 
 // ---------------------------------------------------------------------------
 // bf16 helpers
@@ -339,141 +390,153 @@ __device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
 }
 
 // ---------------------------------------------------------------------------
-// The network on T tiles of 16 pixels held by one wave (encoder).
-//   in[t][kb][0]  layer-1 B operand of tile t (8 bf16 per lane and k-block; [1] unused)
-//   out[t][ob]    raw head outputs, register s = 4*ob + i  <->  Net::head_index(lane>>4, s)
+// The network on a strip of 32 pixels, two tiles of 16, held by one wave (encoder).
+//   in[k-block][tile][0 = hi, 1 = lo]  B operands (8 bf16 per lane); the first layer's inputs are exact, their lo unused
+//   out[out-block][tile]               raw head outputs, register 4 ob + i  <->  EncHead::head_index(lane >> 4, 4 ob + i)
 // Accumulation order per output element: bias, then k-blocks 0,1,2,..., each hi then lo.
-// Activations of one layer for T tiles: [tile][k-block][0 = hi, 1 = lo].
+//
+// A wave works through a layer in pairs of out-blocks (a pair is one k-block of the next layer) and k-block by k-block, all in
+// the order written, which the scheduling barriers keep:
+//   weights   are read two k-blocks ahead, across pairs and layers (`a`: those of the layer's first two), the next pair's
+//             biases one k-block ahead;
+//   split     the pair before (`last`; across layers too: it is the layer's last k-block) is activated and split into hi + lo
+//             among this pair's MFMAs, three vector instructions beside one, the four subtractions on the matrix core together
+//             (going from one MFMA shape to the other and back costs it some 8 cycles), and nothing is used right behind
+//             the MFMA that makes it.
+// Left to itself the compiler reads weights where they are used and waits for LDS in front of every other MFMA.
 // ---------------------------------------------------------------------------
-// FAR: the weight tiles come from global memory; the reads of a k-block's tiles then stay behind the MFMAs of the
-// k-block before the previous one (left to itself the compiler issues a whole layer's reads at once and spills).
-// MFMA_SPLIT: activations are split by act_split4_bf16, else by act_split_bf16 (the same numbers).
-template <int T, int NOB, int NKB, int OBG, bool SPLIT_IN, bool LEAKY, bool FAR, bool MFMA_SPLIT>
-__device__ __forceinline__ void hidden_layer(const uint8_t* __restrict__ w, const float* __restrict__ bias,
-                                             int lane, bf16x4_bits_t minus_one, const u32x4_t (&in)[T][NKB][2],
-                                             u32x4_t (&out)[T][NOB / 2][2]) {
-    static_assert(NOB % OBG == 0 && OBG % 2 == 0, "out-block group must be even and divide the layer");
-    const int g = lane >> 4;
-#pragma unroll
-    for (int ob0 = 0; ob0 < NOB; ob0 += OBG) {
-        f32x4_t acc[OBG][T];
-        f32x4_t bv[OBG];   // the bias is the C operand of each chain's first MFMA
-#pragma unroll
-        for (int j = 0; j < OBG; ++j) bv[j] = *reinterpret_cast<const f32x4_t*>(bias + 16 * (ob0 + j) + 4 * g);
-        // weight tiles of the next k-block are fetched from LDS while the current ones feed the MFMAs
-        u32x4_t a_cur[OBG], a_nxt[OBG];
-#pragma unroll
-        for (int j = 0; j < OBG; ++j)
-            a_cur[j] = *reinterpret_cast<const u32x4_t*>(w + (((ob0 + j) * NKB + 0) * 64 + lane) * 16);
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-            if (kb + 1 < NKB) {
-#pragma unroll
-                for (int j = 0; j < OBG; ++j)
-                    a_nxt[j] = *reinterpret_cast<const u32x4_t*>(w + (((ob0 + j) * NKB + kb + 1) * 64 + lane) * 16);
-            }
-#pragma unroll
-            for (int j = 0; j < OBG; ++j) {
-#pragma unroll
-                for (int t = 0; t < T; ++t) acc[j][t] = mfma16(a_cur[j], in[t][kb][0], kb == 0 ? bv[j] : acc[j][t]);
-            }
-            if (SPLIT_IN) {
-#pragma unroll
-                for (int j = 0; j < OBG; ++j) {
-#pragma unroll
-                    for (int t = 0; t < T; ++t) acc[j][t] = mfma16(a_cur[j], in[t][kb][1], acc[j][t]);
-                }
-            }
-            if (kb + 1 < NKB) {
-#pragma unroll
-                for (int j = 0; j < OBG; ++j) a_cur[j] = a_nxt[j];
-            }
-            if constexpr (FAR) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int j = 0; j < OBG; j += 2) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                u32x4_t hi, lo;
-                if constexpr (MFMA_SPLIT) {
-                    u32x2_t h0, h1, l0, l1;
-                    act_split4_bf16<LEAKY>(acc[j][t], minus_one, h0, l0);
-                    act_split4_bf16<LEAKY>(acc[j + 1][t], minus_one, h1, l1);
-                    hi.x = h0.x; hi.y = h0.y; hi.z = h1.x; hi.w = h1.y;
-                    lo.x = l0.x; lo.y = l0.y; lo.z = l1.x; lo.w = l1.y;
-                } else {
-                    // Where layers' weights come from global memory the matrix core is seldom busy and the subtraction's
-                    // latency counts instead (192 filters, 4 images of 640x480: 1,403 us this way, 1,440 the other).
-                    uint32_t l0, l1, l2, l3;
-                    hi.x = act_split_bf16<LEAKY>(acc[j][t].x, acc[j][t].y, l0);
-                    hi.y = act_split_bf16<LEAKY>(acc[j][t].z, acc[j][t].w, l1);
-                    hi.z = act_split_bf16<LEAKY>(acc[j + 1][t].x, acc[j + 1][t].y, l2);
-                    hi.w = act_split_bf16<LEAKY>(acc[j + 1][t].z, acc[j + 1][t].w, l3);
-                    lo.x = l0; lo.y = l1; lo.z = l2; lo.w = l3;
-                }
-                out[t][(ob0 + j) / 2][0] = hi;
-                out[t][(ob0 + j) / 2][1] = lo;
-            }
-        }
+template <class Net, int L, int P, int KB>
+struct KBlockAt {                      // layer, pair of out-blocks, k-block
+    static constexpr int l = L, p = P, kb = KB;
+    static constexpr bool valid = L < Net::kLayers;
+    static constexpr int blocks = !valid ? 0 : 2 * P + 1 < Net::ob(L) ? 2 : 1;        // a layer of an odd number of out-blocks ends in half a pair
+    static constexpr auto next() {
+        if constexpr (!valid) return KBlockAt<Net, L, P, KB>{};
+        else if constexpr (KB + 1 < Net::kb(L)) return KBlockAt<Net, L, P, KB + 1>{};
+        else if constexpr (2 * P + 2 < Net::ob(L)) return KBlockAt<Net, L, P + 1, 0>{};
+        else return KBlockAt<Net, L + 1, 0, 0>{};
     }
-}
+};
+constexpr int kWeightsAhead = 2;       // k-blocks
 
-template <int T, int NOB, int NKB, bool FAR = false>
-__device__ __forceinline__ void head_layer(const uint8_t* __restrict__ w, const float* __restrict__ bias, int lane,
-                                           const u32x4_t (&in)[T][NKB][2], f32x4_t (&out)[T][NOB]) {
-    const int g = lane >> 4;
-    f32x4_t bv[NOB];
-#pragma unroll
-    for (int ob = 0; ob < NOB; ++ob) bv[ob] = *reinterpret_cast<const f32x4_t*>(bias + 16 * ob + 4 * g);
-    u32x4_t a_cur[NOB], a_nxt[NOB];
-#pragma unroll
-    for (int ob = 0; ob < NOB; ++ob)
-        a_cur[ob] = *reinterpret_cast<const u32x4_t*>(w + ((ob * NKB + 0) * 64 + lane) * 16);
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) {
-        if (kb + 1 < NKB) {
-#pragma unroll
-            for (int ob = 0; ob < NOB; ++ob)
-                a_nxt[ob] = *reinterpret_cast<const u32x4_t*>(w + ((ob * NKB + kb + 1) * 64 + lane) * 16);
-        }
-#pragma unroll
-        for (int ob = 0; ob < NOB; ++ob) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) out[t][ob] = mfma16(a_cur[ob], in[t][kb][0], kb == 0 ? bv[ob] : out[t][ob]);
-        }
-#pragma unroll
-        for (int ob = 0; ob < NOB; ++ob) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) out[t][ob] = mfma16(a_cur[ob], in[t][kb][1], out[t][ob]);
-        }
-        if (kb + 1 < NKB) {
-#pragma unroll
-            for (int ob = 0; ob < NOB; ++ob) a_cur[ob] = a_nxt[ob];
-        }
-        if constexpr (FAR) __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// Layers L .. last.  WIDE selects how many out-blocks are accumulated concurrently:
-// the whole layer (one tile per wave: many independent MFMA chains are needed) or two.
-// `model` holds the weight tiles of the first RESIDENT layers and, straight behind them, all biases (the packed
-// image itself when RESIDENT is the number of layers); the other layers' tiles are read from the image at `rest`.
-template <class Net, int T, bool WIDE, int L, int RESIDENT = Net::kLayers>
-__device__ __forceinline__ void mlp_from(const uint8_t* __restrict__ model, const uint8_t* __restrict__ rest, int lane,
-                                         bf16x4_bits_t minus_one, const u32x4_t (&in)[T][Net::kb(L)][2],
-                                         f32x4_t (&out)[T][Layout<Net>::kHeadOB]) {
+// `model` holds the weight tiles of the first RESIDENT layers and, straight behind them, all biases (the packed image itself
+// when RESIDENT is the number of layers); the other layers' tiles are read from the image at `rest`.
+template <class Net, int RESIDENT>
+struct EncoderNet {
     using Lay = Layout<Net>;
-    const uint8_t* w = (L < RESIDENT ? model : rest) + Lay::w_off(L);
-    const float* b = reinterpret_cast<const float*>(model + Lay::w_off(RESIDENT) + (Lay::b_off(L) - Lay::kWeightBytes));
-    if constexpr (L == Net::kLayers - 1) {
-        head_layer<T, Net::ob(L), Net::kb(L), (L >= RESIDENT)>(w, b, lane, in, out);
-    } else {
-        static_assert(Net::ob(L) == 2 * Net::kb(L + 1), "two out-blocks form one k-block of the next layer");
-        u32x4_t h[T][Net::kb(L + 1)][2];
-        hidden_layer<T, Net::ob(L), Net::kb(L), (WIDE ? Net::ob(L) : 2), (L > 0), Net::kLeaky, (L >= RESIDENT), (RESIDENT == Net::kLayers)>(w, b, lane, minus_one, in, h);
-        mlp_from<Net, T, WIDE, L + 1, RESIDENT>(model, rest, lane, minus_one, h, out);
+    const uint8_t* model;
+    const uint8_t* rest;
+    int lane;
+    bf16x4_bits_t minus_one;
+
+    template <class At>
+    __device__ __forceinline__ void weights(At, u32x4_t (&a)[2]) const {
+        const uint8_t* w = (At::l < RESIDENT ? model : rest) + lane * 16;
+#pragma unroll
+        for (int j = 0; j < At::blocks; ++j)
+            a[j] = *reinterpret_cast<const u32x4_t*>(w + Lay::w_off(At::l) + ((2 * At::p + j) * Net::kb(At::l) + At::kb) * kBlockBytes);
     }
-}
+    template <class At>
+    __device__ __forceinline__ void biases(At, f32x4_t (&b)[2]) const {
+        const float* from = reinterpret_cast<const float*>(model + Lay::w_off(RESIDENT) + (Lay::b_off(At::l) - Lay::kWeightBytes)) + 4 * (lane >> 4);
+#pragma unroll
+        for (int j = 0; j < At::blocks; ++j) b[j] = *reinterpret_cast<const f32x4_t*>(from + 16 * (2 * At::p + j));
+    }
+
+    // The split of a pair, in pieces, eighths of its values: block e >> 2, tile (e >> 1) & 1, registers 2 (e & 1) and + 1.
+    __device__ __forceinline__ void split_hi(f32x4_t (&v)[2][2], int e, u32x4_t (&to)[2][2]) const {
+        f32x4_t& x = v[e >> 2][(e >> 1) & 1];
+        const int i = 2 * (e & 1);
+        const f32x2_t a = {activation<Net::kLeaky>(x[i]), activation<Net::kLeaky>(x[i + 1])};
+        x[i] = a.x; x[i + 1] = a.y;
+        to[(e >> 1) & 1][0][2 * (e >> 2) + (e & 1)] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, bf16x2_t));
+    }
+    __device__ __forceinline__ void split_rest(f32x4_t (&v)[2][2], const u32x4_t (&to)[2][2]) const {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const u32x2_t h = {to[t][0][2 * j], to[t][0][2 * j + 1]};
+                v[j][t] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(minus_one, __builtin_bit_cast(bf16x4_bits_t, h), v[j][t], 0, 0, 0);
+            }
+        }
+    }
+    __device__ __forceinline__ void split_lo(const f32x4_t (&v)[2][2], int e, u32x4_t (&to)[2][2]) const {
+        const f32x4_t& x = v[e >> 2][(e >> 1) & 1];
+        const f32x2_t a = {x[2 * (e & 1)], x[2 * (e & 1) + 1]};
+        to[(e >> 1) & 1][1][2 * (e >> 2) + (e & 1)] = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, bf16x2_t));
+    }
+    // What of it goes behind MFMA M of a pair's NM (a layer's inputs are used from MFMA NM - 8 on, their lo from NM - 4 on).
+    template <int M, int NM>
+    __device__ __forceinline__ void split_piece(f32x4_t (&v)[2][2], u32x4_t (&to)[2][2]) const {
+        constexpr int kHiPer = NM >= 24 ? 1 : NM >= 8 ? 2 : 4, kHi0 = NM >= 24 ? 2 : 1;
+        constexpr int kRest = kHi0 + 8 / kHiPer - 1;
+        constexpr int kLoPer = NM >= 24 ? 2 : NM >= 8 ? 4 : 8, kLo0 = NM >= 24 ? kRest + 3 : NM >= 16 ? kRest + 4 : NM >= 8 ? kRest + 2 : kRest + 1;
+        static_assert(kLo0 + 8 / kLoPer <= (NM >= 16 ? NM - 4 : NM), "the split is done in time");
+#pragma unroll
+        for (int e = 0; e < 8; ++e) if (kHi0 + e / kHiPer == M) split_hi(v, e, to);
+        if constexpr (kRest == M) {
+            __builtin_amdgcn_sched_barrier(0);
+            split_rest(v, to);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) if (kLo0 + e / kLoPer == M) split_lo(v, e, to);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // in: the layer's inputs; the last k-block's are still to be made of `last` (but in the first layer).  b: its first pair's biases.
+    template <int L>
+    __device__ __forceinline__ void layers(u32x4_t (&in)[Net::kb(L)][2][2], f32x4_t (&last)[2][2], u32x4_t (&a)[kWeightsAhead][2], f32x4_t (&b)[2],
+                                           f32x4_t (&out)[Lay::kHeadOB][2]) const {
+        constexpr bool kHead = L == Net::kLayers - 1;
+        constexpr int NOB = Net::ob(L), NP = (NOB + 1) / 2, NKB = Net::kb(L), PARTS = L > 0 ? 2 : 1;
+        static_assert(kHead || NOB == 2 * Net::kb(kHead ? L : L + 1), "two out-blocks form one k-block of the next layer");
+        u32x4_t nxt[kHead ? 1 : NP][2][2];
+        f32x4_t acc[2][2];
+        static_for<0, NP>([&](auto pc) __attribute__((always_inline)) {
+            constexpr int p = decltype(pc)::value, NB = KBlockAt<Net, L, p, 0>::blocks, NM = NKB * PARTS * 4;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[j][0] = acc[j][1] = b[j];
+            static_for<0, NKB>([&](auto kc) __attribute__((always_inline)) {
+                constexpr int kb = decltype(kc)::value;
+                using At = KBlockAt<Net, L, p, kb>;
+                u32x4_t w[2];
+#pragma unroll
+                for (int j = 0; j < NB; ++j) w[j] = a[0][j];
+                a[0][0] = a[1][0]; a[0][1] = a[1][1];
+                weights(At::next().next(), a[1]);
+                if constexpr (kb == (NKB > 1 ? NKB - 2 : 0)) biases(KBlockAt<Net, L, p, NKB - 1>::next(), b);
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<0, 4 * PARTS>([&](auto mc) __attribute__((always_inline)) {
+                    constexpr int m = decltype(mc)::value, part = m >> 2, j = (m >> 1) & 1, t = m & 1;
+                    if constexpr (j < NB) acc[j][t] = mfma16(w[j], in[kb][t][part], acc[j][t]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (p == 0 && L > 0) split_piece<4 * PARTS * kb + m, NM>(last, in[NKB - 1]);
+                    else if constexpr (p > 0 && !kHead) split_piece<4 * PARTS * kb + m, NM>(last, nxt[p - 1]);
+                });
+            });
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    if constexpr (kHead) out[2 * p + j][t] = acc[j][t];
+                    last[j][t] = acc[j][t];
+                }
+            }
+        });
+        if constexpr (!kHead) layers<L + 1>(nxt, last, a, b, out);
+    }
+
+    __device__ __forceinline__ void run(u32x4_t (&in)[Net::kb(0)][2][2], f32x4_t (&out)[Lay::kHeadOB][2]) const {
+        u32x4_t a[kWeightsAhead][2];
+        f32x4_t b[2], last[2][2];
+        using First = KBlockAt<Net, 0, 0, 0>;
+        weights(First{}, a[0]);
+        weights(First::next(), a[1]);
+        biases(First{}, b);
+        layers<0>(in, last, a, b, out);
+    }
+};
 
 // ---------------------------------------------------------------------------
 // Mixture parameters and the integer CDF (Eq. (1)-(4) of the paper).
