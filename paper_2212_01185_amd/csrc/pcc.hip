@@ -470,10 +470,18 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// (v << 1) | bit, in one instruction: the bit is the carry into v + v.
+__device__ __forceinline__ uint32_t shift_in(uint32_t v, bool bit) {
+    const uint64_t carry = __ballot(bit);
+    uint64_t out;
+    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(v), "=s"(out) : "s"(carry));
+    return v;
+}
+
 // BESIDE: the pixel kernel is running; the symbols are read from sf_tagged, past the caches that are not
 // coherent with the pixel kernel's stores, and each is waited for until it carries this launch's epoch.
 template <bool BESIDE>
-__global__ void __launch_bounds__(kRansThreads)
+__global__ void __launch_bounds__(kRansThreads, 2 /* waves per SIMD: two workgroups per compute unit */)
 rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uint32_t epoch, int W, uint32_t rows,
                  uint32_t* __restrict__ slabs, uint32_t* __restrict__ row_words, int* status, uint32_t patience) {
     constexpr int kPerState = kRansChunk / 2;   // symbols of a chunk that one state (one coding lane) takes
@@ -484,8 +492,9 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
     // [buffer][state][row][step]: the low state word before each of the lane's symbols of the chunk, in the order
     // coded; it is one of the stream's words where the lane's flag for that step is set
     __shared__ uint32_t outw[2][2][kRansRows][kPerState + 1];
-    // [buffer][row][state]: the flags, the first step's in bit 31
-    __shared__ uint32_t outflags[2][kRansRows][2];
+    // [buffer][row][state]: the flags, the first step's in bit 31, and [2 + state] the words the state emitted in all rounds
+    // before: whoever stores the round's words has their places from these alone
+    __shared__ __align__(16) uint32_t outflags[2][kRansRows][4];
     __shared__ uint32_t final_state[kRansRows][4];   // xl, xh of state 0, xl, xh of state 1 after the row's first symbol
     __shared__ uint32_t abandon;                // set by a loader whose wait ran out: every wave leaves after the round
     const int tid = threadIdx.x, lane = tid & 63;
@@ -498,9 +507,7 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
     // coding lane: row of the workgroup lane & 31, state lane >> 5 (symbol i of the row is coded on state i mod 2)
     const int crow = lane & (kRansRows - 1), cstate = lane >> 5;
     uint32_t xl = (uint32_t)kRansL, xh = (uint32_t)(kRansL >> 32);     // the lane's state x = xh 2^32 + xl
-    // storing lanes keep the slab position of row lane & 31: slabs fill from the end, the decoder reads the words in
-    // reverse order of production
-    uint32_t wp = (uint32_t)sw;
+    uint32_t emitted = 0;            // coding lane: words of the rounds so far
 
     // Wave 0 codes; waves 2 and 3 load (symbols from global memory, reciprocals, both to LDS); wave 1 stores (the
     // words the coding wave produced, from LDS to the rows' slabs).  Loads and stores are kept in different waves
@@ -581,31 +588,51 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
             rcp[b][r][i] = rans_recip_below((v >> 16) + 1u);
         }
     };
-    // Wave 1: the words of a finished chunk from buffer b to the rows' slabs, one row per iteration.  Lane p stands
+    // Wave 1: the words of a finished chunk from buffer b to the rows' slabs, one row per iteration.  Slabs fill from the end:
+    // the decoder reads the words in reverse order of production.  Lane p stands
     // for the p-th symbol coded in the round (symbol kRansChunk - 1 - p of the chunk: state 1 when p is even, the
     // state's step p / 2).  Where that symbol's flag is set, its word goes behind the words of the symbols coded
-    // before it, from either state: the flags set among the first ceil(p / 2) steps of state 1 and the first
-    // floor(p / 2) steps of state 0.  All LDS reads are issued before the first store.
+    // before it, from either state: those of the rounds before, the flags set among the first ceil(p / 2) steps of state 1 and
+    // the first floor(p / 2) steps of state 0.  Lanes without a word store beyond the slabs' end, which the hardware drops:
+    // with a branch around each row's store, positions read from other lanes and 64-bit addresses this wave took 3,900
+    // cycles a round where the coding wave takes 3,200.  All LDS reads are issued before the first store.
+    const auto slab_rows = __builtin_amdgcn_make_buffer_rsrc(slabs + (size_t)row0 * sw, 0, (int)(uint32_t)(live_rows * sw * 4),
+                                                             0x00020000 /* untyped dwords */);
     auto flush = [&](int b) __attribute__((always_inline)) {
         const uint32_t p = (uint32_t)lane, step = p >> 1, state = 1u - (p & 1u);
         auto first_steps = [](uint32_t nsteps) { return nsteps == 0 ? 0u : 0xFFFFFFFFu << (32u - nsteps); };   // their flag bits
-        const uint32_t before1 = first_steps((p + 1) >> 1), before0 = first_steps(p >> 1), mine = 0x80000000u >> step;
-        uint32_t word[kRansRows], f0[kRansRows], f1[kRansRows];
+        const uint32_t before1 = first_steps((p + 1) >> 1), before0 = first_steps(p >> 1);
+        // in batches of rows; the next batch's LDS reads are issued before this one's stores
+        constexpr int kBatch = 8;
+        uint32_t word[2][kBatch], own[2][kBatch];
+        u32x4_t f[2][kBatch];
+        auto read = [&](int n) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < kRansRows; ++r) {
-            word[r] = outw[b][state][r][step];
-            f0[r] = outflags[b][r][0];
-            f1[r] = outflags[b][r][1];
-        }
-        const uint32_t own0 = outflags[b][lane & (kRansRows - 1)][0], own1 = outflags[b][lane & (kRansRows - 1)][1];
+            for (int i = 0; i < kBatch; ++i) {
+                const int r = n * kBatch + i;
+                word[n & 1][i] = outw[b][state][r][step];
+                own[n & 1][i] = outflags[b][r][state];
+                f[n & 1][i] = *reinterpret_cast<const u32x4_t*>(outflags[b][r]);
+            }
+        };
+        read(0);
+        uint32_t row_at = 0;                                        // the row's slab, from the first one's
 #pragma unroll
-        for (int r = 0; r < kRansRows; ++r) {
-            const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)wp, r);     // the row's position before this chunk
-            const uint32_t ahead = (uint32_t)__popc(f1[r] & before1) + (uint32_t)__popc(f0[r] & before0);
-            const bool emitted = ((state ? f1[r] : f0[r]) & mine) != 0;
-            if ((uint32_t)r < live_rows && emitted) slabs[(size_t)(row0 + r) * sw + (at - 1u - ahead)] = word[r];
+        for (int n = 0; n < kRansRows / kBatch; ++n) {
+            if (n + 1 < kRansRows / kBatch) read(n + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                const u32x4_t v = f[n & 1][i];
+                const uint32_t ahead = (uint32_t)__popc(v.y & before1) + v.w + ((uint32_t)__popc(v.x & before0) + v.z);
+                uint32_t at = 4u * ((uint32_t)sw - 1u - ahead);
+                asm volatile("" : "+v"(at));                        // no branch round its computation
+                at = (int)(own[n & 1][i] << step) < 0 ? at : 0xFFFFFFF0u;
+                __builtin_amdgcn_raw_buffer_store_b32(word[n & 1][i], slab_rows, (int)at, (int)row_at, 0);
+                row_at += 4u * (uint32_t)sw;
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        wp -= (uint32_t)__popc(own0) + (uint32_t)__popc(own1);
     };
     if (tid == 0) abandon = 0;
     lds_barrier();
@@ -649,13 +676,15 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
                     // serial chain
                     const bool emit = (xh >> 15) >= f;
                     my_out[n * kU + u] = xl;
-                    flags = (flags << 1) | (emit ? 1u : 0u);
+                    flags = shift_in(flags, emit);
                     xl = emit ? xh : xl;
                     xh = emit ? 0u : xh;
                     rans_push(xl, xh, f, start, rf[n & 1][u]);
                 }
             }
             outflags[b][crow][cstate] = flags;
+            outflags[b][crow][2 + cstate] = emitted;
+            emitted += (uint32_t)__popc(flags);
         }
         lds_barrier();   // all that crosses threads here is in LDS; the loaders' global loads stay in flight
         return !BESIDE || abandon == 0;
@@ -670,9 +699,11 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
     if (coder) {
         final_state[crow][2 * cstate] = xl;
         final_state[crow][2 * cstate + 1] = xh;
+        outflags[0][crow][cstate] = emitted;                        // (the last words have been stored)
     }
     lds_barrier();
     if (storer && lane < kRansRows && row0 + lane < rows) {
+        const uint32_t wp = (uint32_t)sw - (outflags[0][lane][0] + outflags[0][lane][1]);
         // the four state words end the slab's data: the decoder reads them first
         uint32_t* slab = slabs + (size_t)(row0 + lane) * sw;
         slab[wp - 1] = final_state[lane][3];
