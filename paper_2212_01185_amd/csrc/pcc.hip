@@ -8,9 +8,8 @@
 //                      first into a per-row slab, written backwards; for a small
 //                      job it runs beside encode_kernel, taking the symbols as
 //                      they appear
-//   scan_kernel        exclusive prefix sum of row payload sizes, header, offsets
-//   compact_kernel     slabs -> contiguous stream
-//   compact_scan_kernel  both of the above in one launch, for jobs of few rows
+//   compact_kernel     slabs -> contiguous stream, with header and offsets
+//   scan_kernel        exclusive prefix sum of row payload sizes in front of it, for jobs of very many rows
 //   decode_kernel      persistent wavefront decoder: one workgroup (4 waves) per
 //                      band of 16 rows, step t handles pixel (r, t - delay*r) of each row
 //   cdf_tables_kernel  test hook: full integer CDF tables from given parameters
@@ -79,16 +78,19 @@ constexpr int params_stage_pixels(int threads) {
 template <class Net>
 constexpr int params_stage_bytes(int threads) { return (threads / 64) * params_stage_pixels<Net>(threads) * Net::dim(Net::kLayers) * 4; }
 
-// status words in device memory
-enum { kStErr = 0, kStAbort = 1, kStTicket = 2, kStWords = 4 };
-// The status block: kStWords ints that every call clears on its stream before its kernels, the 64-bit stream
-// size, and two ints that only a row coder running beside the pixel kernel writes (stood down; spare).
-// That row coder runs on another stream than the clearing, so its words are cleared after they have been read,
-// at the end of the call, and are zero whenever a call begins.
-constexpr size_t kStCleared = kStWords * sizeof(int) + sizeof(uint64_t);
-constexpr int kStSide = (int)(kStCleared / sizeof(int));     // index of the first of the two side words
-enum { kSideDefer = 0 };
-constexpr size_t kStBytes = kStCleared + 2 * sizeof(int);
+// Status words in device memory, one block for the decoder, one for the encoder, one that nobody reads (pcc_encode_probs,
+// which does not wait for its kernel).  The decoder's is cleared on its stream before each call.
+// The encoder's is zero whenever a call begins: the last workgroup of the compaction leaves what the call has to say in pinned
+// host memory (EncodeResult) and clears it for the next call, so that a call needs no clearing, no copy and no second clearing
+// around its kernels (64x64 59.7 -> 45.7 us a call, 768x512 124 -> 113); a call that fails clears it from the host.
+enum { kStErr = 0, kStAbort = 1, kStTicket = 2, kStDefer = 3, kStWords = 4 };
+enum { kStDone = kStTicket };                 // encoder: workgroups of the compaction that have ended
+enum { kBlockDecode = 0, kBlockEncode = 1, kBlockProbs = 2, kStBlocks = 3 };
+constexpr size_t kStBytes = kStWords * sizeof(int);
+struct EncodeResult {                         // of a call, in pinned host memory
+    uint64_t total_bytes;
+    int err, defer;
+};
 
 // Most 32-bit words a row's payload can have: four of the two final coder states, and one per two symbols plus two.
 __host__ __device__ inline size_t slab_words(int W) { return (6 * (size_t)W + 24) / 4 + 1; }
@@ -398,6 +400,7 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
         // Cq increases strictly from 0 to 65536: a frequency outside 1 .. 65536 (also: lo not below hi) is an error
         if (live && (freq - 1u > 65535u || freq_b - 1u > 65535u)) {
             set_error(status, PCC_E_INTERNAL);
+            __threadfence();                 // known before the symbols are: whoever has those reads the status
             if (freq - 1u > 65535u) freq = 1;
             if (freq_b - 1u > 65535u) freq_b = 1;
         }
@@ -483,7 +486,8 @@ __device__ __forceinline__ uint32_t shift_in(uint32_t v, bool bit) {
 template <bool BESIDE>
 __global__ void __launch_bounds__(kRansThreads, 2 /* waves per SIMD: two workgroups per compute unit */)
 rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uint32_t epoch, int W, uint32_t rows,
-                 uint32_t* __restrict__ slabs, uint32_t* __restrict__ row_words, int* status, uint32_t patience) {
+                 uint32_t* __restrict__ slabs, uint32_t* __restrict__ row_words, uint32_t* __restrict__ group_words, int* status,
+                 uint32_t patience) {
     constexpr int kPerState = kRansChunk / 2;   // symbols of a chunk that one state (one coding lane) takes
     static_assert(kPerState == 32, "a coding lane's emission flags of a round fill one 32-bit word");
     // [buffer][row][symbol of the chunk]; the odd row strides keep the coding wave's column accesses off shared banks
@@ -571,7 +575,7 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
                     __builtin_amdgcn_s_sleep(32);
                 }
                 if (gave_up) {
-                    __hip_atomic_store(&status[kStSide + kSideDefer], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&status[kStDefer], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     abandon = 1;
                     break;
                 }
@@ -693,6 +697,7 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
     for (int k = nchunks + 2 + (nchunks & 1); k >= 0; k -= 2) {
         if (!round(k, std::integral_constant<int, 0>()) || !round(k - 1, std::integral_constant<int, 1>())) {
             if (tid < kRansRows && row0 + tid < rows) row_words[row0 + tid] = 0;    // stood down: nothing for the compaction to copy
+            if (tid == 0) group_words[blockIdx.x] = 0;
             return;
         }
     }
@@ -702,35 +707,36 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
         outflags[0][crow][cstate] = emitted;                        // (the last words have been stored)
     }
     lds_barrier();
+    uint32_t words = 0;
     if (storer && lane < kRansRows && row0 + lane < rows) {
         const uint32_t wp = (uint32_t)sw - (outflags[0][lane][0] + outflags[0][lane][1]);
+        words = (uint32_t)sw - (wp - 4u);
         // the four state words end the slab's data: the decoder reads them first
         uint32_t* slab = slabs + (size_t)(row0 + lane) * sw;
         slab[wp - 1] = final_state[lane][3];
         slab[wp - 2] = final_state[lane][2];
         slab[wp - 3] = final_state[lane][1];
         slab[wp - 4] = final_state[lane][0];
-        row_words[row0 + lane] = (uint32_t)sw - (wp - 4u);
+        row_words[row0 + lane] = words;
+    }
+    if (storer) {                                // the group's sum (at most 32 times 100 MB in words)
+        for (int d = 32; d >= 1; d >>= 1) words += __shfl_xor(words, d);
+        if (lane == 0) group_words[blockIdx.x] = words;
     }
 }
 
-// Single workgroup: offsets[k] = 4 * sum_{j<k} row_words[j]; header; total size.
+// Single workgroup: before[k] = sum_{j<k} group_words[j], for jobs of so many groups that the compaction's workgroups cannot
+// each add up those before their own.
+constexpr uint32_t kSumGroupsMax = 4096;
 __global__ void __launch_bounds__(1024)
-scan_kernel(const uint32_t* __restrict__ row_words, uint32_t rows, int n, int H, int W, uint32_t tag, uint32_t dist,
-            uint8_t* __restrict__ stream, uint64_t* __restrict__ total_bytes) {
+scan_kernel(const uint32_t* __restrict__ group_words, uint32_t groups, uint64_t* __restrict__ before) {
     __shared__ uint64_t part[1024];
     __shared__ uint64_t carry;
-    uint64_t* offsets = reinterpret_cast<uint64_t*>(stream + kStreamHeader);
-    if (threadIdx.x == 0) {
-        carry = 0;
-        uint32_t* hdr = reinterpret_cast<uint32_t*>(stream);
-        hdr[0] = kStreamMagic; hdr[1] = kStreamVersion; hdr[2] = (uint32_t)n; hdr[3] = (uint32_t)H; hdr[4] = (uint32_t)W;
-        hdr[5] = tag; hdr[6] = dist; hdr[7] = 0;
-    }
+    if (threadIdx.x == 0) carry = 0;
     __syncthreads();
-    for (uint32_t base = 0; base < rows; base += 1024) {
+    for (uint32_t base = 0; base < groups; base += 1024) {
         const uint32_t k = base + threadIdx.x;
-        const uint64_t mine = k < rows ? 4ull * row_words[k] : 0ull;
+        const uint64_t mine = k < groups ? (uint64_t)group_words[k] : 0ull;
         part[threadIdx.x] = mine;
         __syncthreads();
         for (int d = 1; d < 1024; d <<= 1) {
@@ -739,93 +745,112 @@ scan_kernel(const uint32_t* __restrict__ row_words, uint32_t rows, int n, int H,
             part[threadIdx.x] += add;
             __syncthreads();
         }
-        if (k < rows) offsets[k] = carry + part[threadIdx.x] - mine;
+        if (k < groups) before[k] = carry + part[threadIdx.x] - mine;
         __syncthreads();
         if (threadIdx.x == 1023) carry += part[1023];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        offsets[rows] = carry;
-        *total_bytes = (uint64_t)kStreamHeader + 8ull * (rows + 1) + carry;
-    }
 }
 
-__global__ void __launch_bounds__(64)
-compact_kernel(const uint32_t* __restrict__ slabs, const uint32_t* __restrict__ row_words, int W, uint32_t rows,
-               uint8_t* __restrict__ stream, uint64_t cap_bytes, int* status) {
-    const uint32_t row = blockIdx.x;
+// Header, offsets and the rows' payloads to their places in the stream.  A workgroup takes `chunk` consecutive rows (a multiple
+// of four), four at a time, a wave per row.  The words before its first row are those
+// of the row coder's groups before (added up by every workgroup, from L2: no launch for a scan; or from scan_kernel)
+// and of the group's rows before it.  The last workgroup to end leaves the call's result in host memory and the status block
+// clear: the workgroups count in one word, some 10 ns each, so there are at most kCompactBlocks of them.
+// (With an offset per row from a scan by one workgroup, 24 images of 768x512 took 25 us for the scan and 9 for the copy.)
+constexpr int kCompactRows = 4, kCompactThreads = 64 * kCompactRows;
+constexpr uint32_t kCompactBlocks = 512;
+
+__global__ void __launch_bounds__(kCompactThreads)
+compact_kernel(const uint32_t* __restrict__ slabs, const uint32_t* __restrict__ row_words, const uint32_t* __restrict__ group_words,
+               const uint64_t* __restrict__ before, int n, int H, int W, uint32_t rows, uint32_t chunk, uint32_t tag, uint32_t dist,
+               uint8_t* __restrict__ stream, uint64_t cap_bytes, int* status, uint64_t* total_bytes, EncodeResult* result) {
+    __shared__ unsigned long long part[kCompactRows];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t first = blockIdx.x * chunk, end = min(first + chunk, rows), group = first / kRansRows;      // first < rows
     const size_t sw = slab_words(W);
-    const uint64_t table = (uint64_t)kStreamHeader + 8ull * (rows + 1);
-    const uint64_t off = reinterpret_cast<const uint64_t*>(stream + kStreamHeader)[row];
-    const uint32_t nw = row_words[row];
-    if (nw > sw) {                                // not a row coder's count: never read outside the slab
-        if (threadIdx.x == 0) set_error(status, PCC_E_INTERNAL);
-        return;
+    const uint64_t table = (uint64_t)kStreamHeader + 8ull * ((uint64_t)rows + 1);
+    uint32_t nw[kCompactRows];                 // the words of the next four rows
+    auto sizes = [&](uint32_t row0) __attribute__((always_inline)) {
+#pragma unroll
+        for (uint32_t w = 0; w < kCompactRows; ++w) nw[w] = row0 + w < end ? row_words[row0 + w] : 0u;
+    };
+    sizes(first);
+    unsigned long long words_before = 0;
+    if (before != nullptr) {
+        if (threadIdx.x == 0) words_before = before[group];
+    } else {
+        for (uint32_t j = threadIdx.x; j < group; j += kCompactThreads) words_before += group_words[j];
     }
-    if (table + off + 4ull * nw > cap_bytes) {
-        if (threadIdx.x == 0) set_error(status, PCC_E_CAP);
-        return;
+    if (threadIdx.x < first - group * kRansRows) words_before += row_words[group * kRansRows + threadIdx.x];
+    for (int d = 32; d >= 1; d >>= 1) words_before += __shfl_xor(words_before, d);
+    if (lane == 0) part[wave] = words_before;
+    __syncthreads();
+    words_before = 0;
+    for (int w = 0; w < kCompactRows; ++w) words_before += part[w];
+
+    uint64_t* offsets = reinterpret_cast<uint64_t*>(stream + kStreamHeader);
+    for (uint32_t row0 = first; row0 < end; row0 += kCompactRows) {
+        unsigned long long mine = words_before;
+        uint32_t words = nw[0];
+#pragma unroll
+        for (int w = 0; w < kCompactRows; ++w) {
+            if (w < wave) mine += nw[w];
+            if (w == wave) words = nw[w];
+            words_before += nw[w];
+        }
+        const uint32_t row = row0 + wave;
+        if (row0 + kCompactRows < end) sizes(row0 + kCompactRows);
+        if (row >= rows) break;
+        const uint64_t off = 4ull * mine;
+        // header, this row's offset and, from the last row, the end offset and the total: all inside the table,
+        // which the host has checked against the capacity
+        if (lane == 0) {
+            offsets[row] = off;
+            if (row == 0) {
+                uint32_t* hdr = reinterpret_cast<uint32_t*>(stream);
+                hdr[0] = kStreamMagic; hdr[1] = kStreamVersion; hdr[2] = (uint32_t)n; hdr[3] = (uint32_t)H; hdr[4] = (uint32_t)W;
+                hdr[5] = tag; hdr[6] = dist; hdr[7] = 0;
+            }
+            if (row + 1 == rows) {
+                offsets[rows] = off + 4ull * words;
+                __hip_atomic_store(total_bytes, table + off + 4ull * words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (words > sw) {                             // not a row coder's count: never read outside the slab
+            if (lane == 0) set_error(status, PCC_E_INTERNAL);
+        } else if (table + off + 4ull * words > cap_bytes) {
+            if (lane == 0) set_error(status, PCC_E_CAP);
+        } else {
+            const uint32_t* src = slabs + (size_t)row * sw + (sw - words);
+            uint32_t* dst = reinterpret_cast<uint32_t*>(stream + table + off);
+            constexpr uint32_t kUnroll = 8;           // loads in flight
+            for (uint32_t i = lane; i < words; i += 64 * kUnroll) {
+                uint32_t v[kUnroll];
+#pragma unroll
+                for (uint32_t u = 0; u < kUnroll; ++u) if (i + 64 * u < words) v[u] = src[i + 64 * u];
+#pragma unroll
+                for (uint32_t u = 0; u < kUnroll; ++u) if (i + 64 * u < words) dst[i + 64 * u] = v[u];
+            }
+        }
     }
-    const uint32_t* src = slabs + (size_t)row * sw + (sw - nw);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(stream + table + off);
-    for (uint32_t i = threadIdx.x; i < nw; i += blockDim.x) dst[i] = src[i];
+    // This workgroup's errors, and the total if it is here, before its count: all are atomic accesses at device scope, so that
+    // they have been made when the wave's counter of outstanding ones is zero.  (A fence would write the die's L2 back, in every
+    // workgroup: 254 us for 24 images of 768x512.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0 && (uint32_t)atomicAdd(&status[kStDone], 1) + 1u == gridDim.x) {
+        result->total_bytes = __hip_atomic_load(total_bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        result->err = atomicExch(&status[kStErr], 0);
+        result->defer = atomicExch(&status[kStDefer], 0);
+        atomicExch(&status[kStDone], 0);
+    }
 }
 
 // test hook: the symbols of a tagged buffer without their epochs
 __global__ void __launch_bounds__(256)
 untag_kernel(const uint64_t* __restrict__ tagged, size_t count, uint32_t* __restrict__ out) {
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) out[i] = (uint32_t)tagged[i];
-}
-
-// scan_kernel and compact_kernel in one launch for jobs of few rows: every workgroup sums the sizes of the rows
-// before its own (the sizes stay in L2), so nothing has to wait for a scan.  Quadratic in the rows.
-constexpr uint32_t kCompactScanMaxRows = 4096;
-constexpr int kCompactScanThreads = 256;
-
-__global__ void __launch_bounds__(kCompactScanThreads)
-compact_scan_kernel(const uint32_t* __restrict__ slabs, const uint32_t* __restrict__ row_words, int n, int H, int W,
-                    uint32_t rows, uint32_t tag, uint32_t dist, uint8_t* __restrict__ stream, uint64_t cap_bytes,
-                    uint64_t* __restrict__ total_bytes, int* status) {
-    __shared__ unsigned long long part[kCompactScanThreads / 64];
-    const uint32_t row = blockIdx.x;
-    unsigned long long words_before = 0;
-    for (uint32_t j = threadIdx.x; j < row; j += kCompactScanThreads) words_before += row_words[j];
-    for (int d = 32; d >= 1; d >>= 1) words_before += __shfl_xor(words_before, d);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = words_before;
-    __syncthreads();
-    words_before = 0;
-    for (int w = 0; w < kCompactScanThreads / 64; ++w) words_before += part[w];
-
-    const size_t sw = slab_words(W);
-    const uint64_t table = (uint64_t)kStreamHeader + 8ull * (rows + 1);
-    const uint64_t off = 4ull * words_before;
-    const uint32_t nw = row_words[row];
-    // header, this row's offset and, from the last row, the end offset and the total: all inside the table,
-    // which the host has checked against the capacity
-    uint64_t* offsets = reinterpret_cast<uint64_t*>(stream + kStreamHeader);
-    if (threadIdx.x == 0) {
-        offsets[row] = off;
-        if (row == 0) {
-            uint32_t* hdr = reinterpret_cast<uint32_t*>(stream);
-            hdr[0] = kStreamMagic; hdr[1] = kStreamVersion; hdr[2] = (uint32_t)n; hdr[3] = (uint32_t)H; hdr[4] = (uint32_t)W;
-            hdr[5] = tag; hdr[6] = dist; hdr[7] = 0;
-        }
-        if (row + 1 == rows) {
-            offsets[rows] = off + 4ull * nw;
-            *total_bytes = table + off + 4ull * nw;
-        }
-    }
-    if (nw > sw) {                                // not a row coder's count: never read outside the slab
-        if (threadIdx.x == 0) set_error(status, PCC_E_INTERNAL);
-        return;
-    }
-    if (table + off + 4ull * nw > cap_bytes) {
-        if (threadIdx.x == 0) set_error(status, PCC_E_CAP);
-        return;
-    }
-    const uint32_t* src = slabs + (size_t)row * sw + (sw - nw);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(stream + table + off);
-    for (uint32_t i = threadIdx.x; i < nw; i += kCompactScanThreads) dst[i] = src[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1979,9 +2004,12 @@ struct pcc_ctx {
     // workspace (grown on demand)
     uint8_t* d_ws = nullptr;
     size_t ws_bytes = 0;
-    int* d_status = nullptr;       // kStWords ints
+    int* d_status = nullptr;       // the status blocks, and the encoder's stream size behind them
     uint64_t* d_total = nullptr;
-    int* h_status = nullptr;       // pinned, kStWords ints + 2 for the total
+    int* h_status = nullptr;       // pinned: the decoder's block after a call, the encoder's result behind it
+    EncodeResult* h_result = nullptr;
+    EncodeResult* d_result = nullptr;         // the same, as kernels see it
+    int* status(int block) const { return d_status + block * kStWords; }
     // layout of the last encode inside the workspace
     uint32_t* d_sf = nullptr;
     size_t sf_count = 0;
@@ -2245,7 +2273,7 @@ uint32_t encode_blocks(const pcc_ctx* ctx, int n, int H, uint32_t strips, uint32
     const uint32_t per_block = (uint32_t)ctx->encode_threads / 64;
     const uint64_t blocks = (items + per_block - 1) / per_block;
     const uint32_t cus = (ctx->num_cus > 0 ? (uint32_t)ctx->num_cus : 256u) - reserve_cus;
-    return blocks > cus ? cus : (uint32_t)blocks;   // persistent: one workgroup per CU, looping over the items
+    return blocks > cus ? cus : (uint32_t)blocks;   // persistent: one workgroup per CU, whose waves take its items
 }
 
 // sf_tagged: see encode_kernel
@@ -2257,10 +2285,10 @@ int launch_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint3
     const uint8_t* model = ctx->d_model + Layout<Net>::kModelBytes;
     if (ctx->encode_threads == 256)
         hipLaunchKernelGGL((encode_kernel<Net, 256>), dim3(blocks), dim3(256), lds, st, model, d_img, n, H, W,
-                           sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
+                           sf, params, bits, ctx->status(params != nullptr ? kBlockProbs : kBlockEncode), sf_tagged, ctx->epoch, strip_begin, strip_count);
     else
         hipLaunchKernelGGL((encode_kernel<Net, 512>), dim3(blocks), dim3(512), lds, st, model, d_img, n, H, W,
-                           sf, params, bits, ctx->d_status, sf_tagged, ctx->epoch, strip_begin, strip_count);
+                           sf, params, bits, ctx->status(params != nullptr ? kBlockProbs : kBlockEncode), sf_tagged, ctx->epoch, strip_begin, strip_count);
     return hipGetLastError() == hipSuccess ? PCC_OK : PCC_E_HIP;
 }
 
@@ -2304,10 +2332,10 @@ void launch_decode(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, 
     const uint32_t grid = (uint32_t)std::min(bands, two ? 2 * cus : cus);
     if (!two)
         hipLaunchKernelGGL((decode_kernel<Net, 1>), dim3(grid), dim3(kDecThreads), kLds, st, ctx->d_model, d_stream,
-                           (uint64_t)nbytes, n, H, W, nbands, ctx->dist, d_img_out, d_mail, ctx->d_status, spin_limit);
+                           (uint64_t)nbytes, n, H, W, nbands, ctx->dist, d_img_out, d_mail, ctx->status(kBlockDecode), spin_limit);
     else
         hipLaunchKernelGGL((decode_kernel<Net, 2>), dim3(grid), dim3(kDecThreads), DecLds<Net>::kBytesShared, st, ctx->d_model, d_stream,
-                           (uint64_t)nbytes, n, H, W, nbands, ctx->dist, d_img_out, d_mail, ctx->d_status, spin_limit);
+                           (uint64_t)nbytes, n, H, W, nbands, ctx->dist, d_img_out, d_mail, ctx->status(kBlockDecode), spin_limit);
 }
 
 inline int head_outputs(const pcc_ctx* ctx) {
@@ -2380,9 +2408,15 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
     ctx->d_static_scratch = static_scratch(hip_device);
     ok = ok && ctx->d_static_scratch != nullptr;
     ok = ok && hipMalloc((void**)&ctx->d_model, image.size()) == hipSuccess;
-    ok = ok && hipMalloc((void**)&ctx->d_status, kStBytes) == hipSuccess;
-    ok = ok && hipMemset(ctx->d_status, 0, kStBytes) == hipSuccess;
-    ok = ok && hipHostMalloc((void**)&ctx->h_status, kStBytes, hipHostMallocDefault) == hipSuccess;
+    constexpr size_t kBlocksBytes = kStBlocks * kStBytes;
+    static_assert(kBlocksBytes % sizeof(uint64_t) == 0 && kStBytes % alignof(EncodeResult) == 0, "alignment");
+    ok = ok && hipMalloc((void**)&ctx->d_status, kBlocksBytes + sizeof(uint64_t)) == hipSuccess;
+    ok = ok && hipMemset(ctx->d_status, 0, kBlocksBytes + sizeof(uint64_t)) == hipSuccess;
+    ok = ok && hipHostMalloc((void**)&ctx->h_status, kStBytes + sizeof(EncodeResult), hipHostMallocDefault) == hipSuccess;
+    if (ok) {
+        ctx->h_result = reinterpret_cast<EncodeResult*>(ctx->h_status + kStWords);
+        ok = hipHostGetDevicePointer((void**)&ctx->d_result, ctx->h_result, 0) == hipSuccess;
+    }
     ok = ok && hipMemcpy(ctx->d_model, image.data(), image.size(), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && with_net(net, [](auto tag) { return set_kernel_attributes<decltype(tag)>(); });
     ctx->encode_threads = with_net(net, [](auto tag) { return decltype(tag)::kEncodeThreads; });
@@ -2402,7 +2436,7 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
     ok = ok && hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->ev_joined, hipEventDisableTiming) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); pcc_destroy(ctx); return PCC_E_HIP; }
-    ctx->d_total = reinterpret_cast<uint64_t*>(ctx->d_status + kStWords);
+    ctx->d_total = reinterpret_cast<uint64_t*>(ctx->d_status + kStBlocks * kStWords);
     *out = ctx;
     return PCC_OK;
 }
@@ -2459,12 +2493,16 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
 
     const size_t sf_bytes = align_up(P * 3 * sizeof(uint32_t), 256);
     const size_t slab_bytes = align_up((size_t)rows * slab_words(W) * 4, 256);
-    const size_t rw_bytes = align_up((size_t)rows * 4, 256);
-    int rc = ensure_workspace(ctx, sf_bytes + slab_bytes + rw_bytes);
+    const uint32_t groups = (rows + kRansRows - 1) / kRansRows;
+    const bool scan = groups > kSumGroupsMax;
+    const size_t rw_bytes = align_up((size_t)rows * 4, 256), gw_bytes = align_up((size_t)groups * 4, 256);
+    int rc = ensure_workspace(ctx, sf_bytes + slab_bytes + rw_bytes + gw_bytes + (scan ? (size_t)groups * 8 : 0));
     if (rc != PCC_OK) return rc;
     uint32_t* d_sf = reinterpret_cast<uint32_t*>(ctx->d_ws);
     uint32_t* d_slabs = reinterpret_cast<uint32_t*>(ctx->d_ws + sf_bytes);
     uint32_t* d_rw = reinterpret_cast<uint32_t*>(ctx->d_ws + sf_bytes + slab_bytes);
+    uint32_t* d_gw = reinterpret_cast<uint32_t*>(ctx->d_ws + sf_bytes + slab_bytes + rw_bytes);
+    uint64_t* d_before = scan ? reinterpret_cast<uint64_t*>(ctx->d_ws + sf_bytes + slab_bytes + rw_bytes + gw_bytes) : nullptr;
     ctx->d_sf = d_sf;
     ctx->sf_count = (size_t)P * 3;
 
@@ -2475,7 +2513,6 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
     // the context's own; nothing orders that stream after the caller's, so this is only done when the caller's
     // stream is idle and the pixel kernel starts at once.  A large job's row coder needs the whole chip and
     // runs after the pixel kernel, on the caller's stream.
-    const uint32_t groups = (rows + kRansRows - 1) / kRansRows;
     const uint32_t cus = ctx->num_cus > 0 ? (uint32_t)ctx->num_cus : 256u;
     bool beside = ctx->overlap && groups <= kRansBesideMaxGroups && cus >= 2 * kRansBesideMaxGroups;
     if (beside) {
@@ -2497,50 +2534,59 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
     // through its share of the items alone.
     const uint32_t reserve = beside ? kXcds * ((groups + kXcds - 1) / kXcds) : 0u;
 
-    if (hipMemsetAsync(ctx->d_status, 0, kStCleared, st) != hipSuccess) return PCC_E_HIP;
     prof_reset(ctx);
+    int* d_status = ctx->status(kBlockEncode);
     const uint32_t tag = with_net(ctx->net, [](auto net) { return model_tag<decltype(net)>(); });
     auto launch_rans = [&](hipStream_t s) {
         prof_begin(ctx, PCC_T_ENCODE_RANS, s);
         if (beside)
             hipLaunchKernelGGL(rans_rows_kernel<true>, dim3(groups), dim3(kRansThreads), 0, s, d_sf, d_tagged, ctx->epoch, W,
-                               rows, d_slabs, d_rw, ctx->d_status, ctx->patience);
+                               rows, d_slabs, d_rw, d_gw, d_status, ctx->patience);
         else
             hipLaunchKernelGGL(rans_rows_kernel<false>, dim3(groups), dim3(kRansThreads), 0, s, d_sf, d_tagged, ctx->epoch, W,
-                               rows, d_slabs, d_rw, ctx->d_status, 0u);
+                               rows, d_slabs, d_rw, d_gw, d_status, 0u);
         prof_end(ctx, PCC_T_ENCODE_RANS, s);
     };
     // what follows the row coder, and the wait for it
     auto finish = [&](hipStream_t s) -> int {
-        if (rows <= kCompactScanMaxRows) {
-            prof_begin(ctx, PCC_T_ENCODE_COMPACT, s);
-            hipLaunchKernelGGL(compact_scan_kernel, dim3(rows), dim3(kCompactScanThreads), 0, s, d_slabs, d_rw, n, H, W, rows,
-                               tag, ctx->dist, d_stream, (uint64_t)cap_bytes, ctx->d_total, ctx->d_status);
-            prof_end(ctx, PCC_T_ENCODE_COMPACT, s);
-        } else {
+        if (scan) {
             prof_begin(ctx, PCC_T_ENCODE_SCAN, s);
-            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, d_rw, rows, n, H, W, tag, ctx->dist, d_stream, ctx->d_total);
+            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, d_gw, groups, d_before);
             prof_end(ctx, PCC_T_ENCODE_SCAN, s);
-            prof_begin(ctx, PCC_T_ENCODE_COMPACT, s);
-            hipLaunchKernelGGL(compact_kernel, dim3(rows), dim3(64), 0, s, d_slabs, d_rw, W, rows, d_stream,
-                               (uint64_t)cap_bytes, ctx->d_status);
-            prof_end(ctx, PCC_T_ENCODE_COMPACT, s);
         }
+        prof_begin(ctx, PCC_T_ENCODE_COMPACT, s);
+        const uint32_t chunk = kCompactRows * (uint32_t)(((uint64_t)rows + kCompactRows * kCompactBlocks - 1) / (kCompactRows * kCompactBlocks));
+        hipLaunchKernelGGL(compact_kernel, dim3((rows + chunk - 1) / chunk), dim3(kCompactThreads), 0, s, d_slabs, d_rw,
+                           d_gw, d_before, n, H, W, rows, chunk, tag, ctx->dist, d_stream, (uint64_t)cap_bytes, d_status, ctx->d_total,
+                           ctx->d_result);
+        prof_end(ctx, PCC_T_ENCODE_COMPACT, s);
         if (hipGetLastError() != hipSuccess) return PCC_E_HIP;
-        if (hipMemcpyAsync(ctx->h_status, ctx->d_status, kStBytes, hipMemcpyDeviceToHost, s) != hipSuccess) return PCC_E_HIP;
-        if (beside && hipMemsetAsync(ctx->d_status + kStSide, 0, 2 * sizeof(int), s) != hipSuccess) return PCC_E_HIP;
+        // The pixel kernel, on the caller's stream, ends before the row coder: waiting for it first costs nothing, waiting for it
+        // after the compaction 8.6 us, and an event for the compaction to wait for holds the host up for 20.
+        if (s != st && hipStreamSynchronize(st) != hipSuccess) { (void)hipGetLastError(); return PCC_E_HIP; }
         if (hipStreamSynchronize(s) != hipSuccess) { (void)hipGetLastError(); return PCC_E_HIP; }
         return PCC_OK;
+    };
+    // Whatever fails, the call leaves through `drain`: its streams are waited for (a row coder without its pixel kernel stands
+    // down when its patience is over), so nothing still writes the caller's stream buffer or the workspace after the return, and
+    // the status block is clear again for the next call.
+    auto drain = [&](int code) -> int {
+        if (beside) (void)hipStreamSynchronize(ctx->side);
+        (void)hipStreamSynchronize(st);
+        (void)hipMemsetAsync(d_status, 0, kStBytes, st);
+        (void)hipStreamSynchronize(st);
+        (void)hipGetLastError();
+        return code;
     };
     const uint32_t strips = encode_strips(W);
     if (!beside) {
         prof_begin(ctx, PCC_T_ENCODE_PIXELS, st);
         rc = launch_encode_any(ctx, d_img, n, H, W, d_sf, nullptr, nullptr, nullptr, 0, 0, strips, st);
-        if (rc != PCC_OK) return rc;
+        if (rc != PCC_OK) return drain(rc);
         prof_end(ctx, PCC_T_ENCODE_PIXELS, st);
         launch_rans(st);
         rc = finish(st);
-        if (rc != PCC_OK) return rc;
+        if (rc != PCC_OK) return drain(rc);
     } else {
         // An image of few rows: the row coder follows the pixel kernel through the whole image.  A tall image: the
         // pixel kernel is the longer one; it does the first strips with the whole chip, and the row coder joins it
@@ -2555,19 +2601,6 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         // their own the order costs nothing (64x64 65.2 -> 62.9 us, 768x512 142.7 -> 139.6): the pixel kernel, the longer
         // one, starts a launch earlier.  Since each call queues the kernel that waits for nothing first, calls of several
         // threads cannot wait for each other in a circle either.
-        //
-        // Two streams carry work from here on.  Whatever fails, the branch leaves through `drain`: both streams
-        // are waited for (a row coder without its pixel kernel stands down when its patience is over), so nothing
-        // still writes the caller's stream buffer or the workspace after the return, and the side status words
-        // are zero again for the next call.
-        auto drain = [&](int code) -> int {
-            (void)hipStreamSynchronize(ctx->side);
-            (void)hipStreamSynchronize(st);
-            (void)hipMemsetAsync(ctx->d_status + kStSide, 0, 2 * sizeof(int), st);
-            (void)hipStreamSynchronize(st);
-            (void)hipGetLastError();
-            return code;
-        };
         const double share = 1.1 * kRansBalanceRows / rows * (double)(cus - reserve) / cus;   // of the strips, beside
         const uint32_t strips_alone = share >= 1.0 ? 0u : (uint32_t)((1.0 - share) * strips);
         prof_begin(ctx, PCC_T_ENCODE_PIXELS, st);
@@ -2584,22 +2617,17 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         launch_rans(ctx->side);
         rc = finish(ctx->side);
         if (rc != PCC_OK) return drain(rc);
-        // the row coder ends after the pixel kernel's last store; the caller's stream is waited for as well, so
-        // that the pixel kernel has retired when this returns
-        if (hipStreamSynchronize(st) != hipSuccess) return drain(PCC_E_HIP);
-        if (ctx->h_status[kStErr] == 0 && ctx->h_status[kStSide + kSideDefer] != 0) {
+        if (ctx->h_result->err == 0 && ctx->h_result->defer != 0) {
             // The row coder saw nothing of the pixel kernel for a long time and stood down.  The symbols are all there now; code them on the caller's stream.
-            if (hipMemsetAsync(ctx->d_status, 0, kStCleared, st) != hipSuccess) return drain(PCC_E_HIP);
             launch_rans(st);
             rc = finish(st);
             if (rc != PCC_OK) return drain(rc);
-            if (ctx->h_status[kStSide + kSideDefer] != 0) return PCC_E_INTERNAL;   // a symbol was never written
+            if (ctx->h_result->defer != 0) return drain(PCC_E_INTERNAL);   // a symbol was never written
         }
     }
     prof_collect(ctx);
-    if (ctx->h_status[kStErr] != 0) return ctx->h_status[kStErr];
-    uint64_t total;
-    memcpy(&total, ctx->h_status + kStWords, sizeof(total));
+    if (ctx->h_result->err != 0) return drain(ctx->h_result->err);
+    const uint64_t total = ctx->h_result->total_bytes;
     if (total > cap_bytes) return PCC_E_CAP;
     *h_nbytes_out = (size_t)total;
     return PCC_OK;
@@ -2610,13 +2638,13 @@ static int decode_with_mailbox(pcc_ctx* ctx, const uint8_t* d_stream, size_t nby
                                uint8_t* d_img_out, uint32_t* d_mail, size_t mail_bytes, bool clear_by_kernel, hipStream_t st) {
     if (clear_by_kernel) {
         const size_t words = mail_bytes / 4;
-        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ctx->d_status),
-                           kStCleared / 4);
+        hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ctx->status(kBlockDecode)),
+                           (size_t)kStWords);
         hipLaunchKernelGGL(clear_words_kernel, dim3((uint32_t)std::min<size_t>((words + 255) / 256, 1024)), dim3(256), 0, st,
                            d_mail, words);
         if (hipGetLastError() != hipSuccess) return PCC_E_HIP;
     } else {
-        if (hipMemsetAsync(ctx->d_status, 0, kStCleared, st) != hipSuccess) return PCC_E_HIP;
+        if (hipMemsetAsync(ctx->status(kBlockDecode), 0, kStBytes, st) != hipSuccess) return PCC_E_HIP;
         if (hipMemsetAsync(d_mail, 0, mail_bytes, st) != hipSuccess) return PCC_E_HIP;
     }
     const uint32_t spin_limit = ctx->spin_limit;
@@ -2628,7 +2656,7 @@ static int decode_with_mailbox(pcc_ctx* ctx, const uint8_t* d_stream, size_t nby
     });
     prof_end(ctx, PCC_T_DECODE, st);
     if (hipGetLastError() != hipSuccess) return PCC_E_HIP;
-    if (hipMemcpyAsync(ctx->h_status, ctx->d_status, kStWords * sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess)
+    if (hipMemcpyAsync(ctx->h_status, ctx->status(kBlockDecode), kStBytes, hipMemcpyDeviceToHost, st) != hipSuccess)
         return PCC_E_HIP;
     if (hipStreamSynchronize(st) != hipSuccess) { (void)hipGetLastError(); return PCC_E_HIP; }
     prof_collect(ctx);

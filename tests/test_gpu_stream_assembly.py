@@ -1,0 +1,70 @@
+"""The compaction (rows to their places in the stream, the call's result to the host): numbers of rows where its workgroups take
+more than four of them, end in a ragged one or leave the sums to a scan, and calls that fail in between.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+from oracle import pcc_oracle as po
+from paper_2212_01185_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def codec():
+    from paper_2212_01185_amd import binding
+    c = binding.Codec(synth.make_blob(0), 0)
+    yield c
+    c.close()
+
+
+# 512 workgroups of four rows each; of eight (2,049 rows: the last workgroup has one); of a number that is no divisor of a row
+# coder's 32; beyond 4,096 groups of 32, where a scan adds the groups up (131,105 rows: the last group has one)
+@pytest.mark.parametrize("n,h,w", [(1, 2048, 1), (1, 2049, 5), (3, 2051, 2), (23, 1111, 1), (5, 26221, 1)])
+def test_rows_and_offsets(codec, n, h, w):
+    rng = np.random.default_rng(n * h + w)
+    imgs = torch.from_numpy(rng.integers(0, 256, (n, h, w, 3), dtype=np.uint8)).cuda()
+    stream = codec.pcc_encode(imgs)
+    rows = n * h
+    raw = stream.cpu().numpy()
+    offsets = raw[32:32 + 8 * (rows + 1)].view(np.uint64).astype(np.int64)
+    sizes = np.diff(offsets)
+    assert offsets[0] == 0 and (sizes >= 16).all() and (sizes % 4 == 0).all()
+    assert offsets[-1] == raw.size - 32 - 8 * (rows + 1)
+    # every row's payload, from the intervals the pixel kernel made: the oracle's coder gives the same bytes
+    sf = codec.pcc_copy_intervals(n, h, w).cpu().numpy().reshape(rows, 3 * w).astype(np.uint32)
+    for r in sorted({0, 1, 31, 32, rows // 2, rows - 2, rows - 1} | set(rng.integers(0, rows, 40).tolist())):
+        want = po.rans_encode(sf[r] & 0xFFFF, (sf[r] >> 16) + 1)
+        at = 32 + 8 * (rows + 1) + offsets[r]
+        assert raw[at:at + sizes[r]].tobytes() == want, r
+    assert torch.equal(codec.pcc_decode(stream, n, h, w), imgs)
+
+
+def test_a_call_that_fails_leaves_no_trace(codec):
+    from paper_2212_01185_amd import binding
+    rng = np.random.default_rng(5)
+    imgs = torch.from_numpy(rng.integers(0, 256, (1, 70, 40, 3), dtype=np.uint8)).cuda()
+    want = codec.pcc_encode(imgs).clone()
+    for size in (want.numel() - 8, 32 + 8 * 71 + 64):
+        for _ in range(2):
+            with pytest.raises(binding.PccError) as e:
+                codec.pcc_encode(imgs, out=torch.zeros(size // 8 * 8, dtype=torch.uint8, device="cuda"))
+            assert e.value.code == binding.PCC_E_CAP
+            assert torch.equal(codec.pcc_encode(imgs), want)
+
+
+@pytest.mark.parametrize("env", [{"PCC_RANS_PATIENCE": "0"}, {"PCC_ENCODE_OVERLAP": "0"}])
+def test_sequence_does_not_matter(codec, env, monkeypatch):
+    from paper_2212_01185_amd import binding
+    rng = np.random.default_rng(6)
+    imgs = torch.from_numpy(rng.integers(0, 256, (2, 33, 300, 3), dtype=np.uint8)).cuda()
+    want = codec.pcc_encode(imgs).clone()
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    other = binding.Codec(synth.make_blob(0), 0)
+    try:
+        for _ in range(3):
+            assert torch.equal(other.pcc_encode(imgs), want)
+    finally:
+        other.close()
