@@ -110,10 +110,20 @@ __device__ __forceinline__ uint32_t opaque_zero() {
     return z;
 }
 
+// 16 bytes a thread at a time, kUnroll of them in flight.
 __device__ __forceinline__ void copy_to_lds(uint8_t* lds, const uint8_t* __restrict__ src, int bytes) {
-    const uint4* s = reinterpret_cast<const uint4*>(src);
-    uint4* d = reinterpret_cast<uint4*>(lds);
-    for (int i = threadIdx.x; i < bytes / 16; i += blockDim.x) d[i] = s[i];
+    constexpr int kUnroll = 17;
+    const u32x4_t* s = reinterpret_cast<const u32x4_t*>(src);
+    u32x4_t* d = reinterpret_cast<u32x4_t*>(lds);
+    const int n = bytes / 16, step = (int)blockDim.x;
+    for (int i = threadIdx.x; i < n; i += kUnroll * step) {
+        u32x4_t v[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) v[u] = s[min(i + u * step, n - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) if (i + u * step < n) d[i + u * step] = v[u];
+    }
 }
 
 // Lane group and register (g * kHeadSlots + s) that hold canonical head output c.
@@ -167,18 +177,7 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
     constexpr int K = Net::K, KB0 = Net::kb(0), HEAD = Net::dim(Net::kLayers);
     extern __shared__ __align__(16) uint8_t lds[];
     uint32_t* taken = reinterpret_cast<uint32_t*>(lds + encode_model_lds_bytes<Net>());     // items of the workgroup that have been taken
-    if (threadIdx.x == 0) *taken = 0;
     constexpr int RESIDENT = encode_resident_layers<Net>();
-    if constexpr (RESIDENT == Net::kLayers) {
-        copy_to_lds(lds, model, encode_model_lds_bytes<Net>());
-    } else {
-        copy_to_lds(lds, model, Lay::w_off(RESIDENT));
-        copy_to_lds(lds + Lay::w_off(RESIDENT), model + Lay::kWeightBytes, encode_model_lds_bytes<Net>() - Lay::w_off(RESIDENT));
-    }
-    __syncthreads();
-    const uint8_t* table_at = encode_table_in_lds<Net>() ? lds + (encode_table_lds_off<Net>() - Lay::kLutOff) : model;
-    const float2* lut = reinterpret_cast<const float2*>(table_at + Lay::kLutOff);
-    const float lut_scale = *reinterpret_cast<const float*>(table_at + Lay::kLutScaleOff);
     constexpr uint32_t nwaves = THREADS / 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar: the item's row and strip are scalars too
@@ -270,9 +269,21 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
         }
     };
     // The next item's bytes are asked for before the network runs on this one's.
-    uint32_t item = take(), next_row = 0, runs[KB0][2][2], next_pix = 0;
+    // (A wave's first item is dealt by its number, and its bytes are asked for before the model is.)
+    uint32_t item = wave * gridDim.x + blockIdx.x, next_row = 0, runs[KB0][2][2], next_pix = 0;
     int next_c0 = 0;
     if (item < items) gather(item, next_row, next_c0, runs, next_pix);
+    if (threadIdx.x == 0) *taken = nwaves;
+    if constexpr (RESIDENT == Net::kLayers) {
+        copy_to_lds(lds, model, encode_model_lds_bytes<Net>());
+    } else {
+        copy_to_lds(lds, model, Lay::w_off(RESIDENT));
+        copy_to_lds(lds + Lay::w_off(RESIDENT), model + Lay::kWeightBytes, encode_model_lds_bytes<Net>() - Lay::w_off(RESIDENT));
+    }
+    __syncthreads();
+    const uint8_t* table_at = encode_table_in_lds<Net>() ? lds + (encode_table_lds_off<Net>() - Lay::kLutOff) : model;
+    const float2* lut = reinterpret_cast<const float2*>(table_at + Lay::kLutOff);
+    const float lut_scale = *reinterpret_cast<const float*>(table_at + Lay::kLutScaleOff);
     while (item < items) {
         const uint32_t rowg = next_row, pix = next_pix & 0xFFFFFFu;
         const int c0 = next_c0, c = c0 + px;
