@@ -89,7 +89,8 @@ typedef struct pcc_ctx pcc_ctx;
  * workgroup of the pixel kernel), PCC_ENCODE_OVERLAP (0: the row coder
  * always runs after the pixel kernel), PCC_RANS_PATIENCE (polls before a row
  * coder running beside the pixel kernel stands down), PCC_DECODE_VARIANT (1, 2:
- * decoder workgroups per compute unit; 0: chosen per job), PCC_DECODE_SPIN_LIMIT
+ * decoder workgroups per compute unit; 3: one, with bands of eight rows where
+ * the network has such a kernel; 0: chosen per job), PCC_DECODE_SPIN_LIMIT
  * (polls of a band for the band above before pcc_decode fails with
  * PCC_E_INTERNAL). */
 int pcc_create(pcc_ctx **out, const void *h_blob, size_t blob_bytes, int hip_device);
@@ -150,7 +151,8 @@ int pcc_decode(pcc_ctx *ctx, const uint8_t *d_stream, size_t nbytes, int n, int 
  * hipMalloc.  Same arguments, same result and same errors as pcc_decode, but the
  * decoder's only scratch buffer -- the mailbox through which a band of 16 rows
  * hands its last two rows to the band below, 8 bytes per pixel column and band:
- * pcc_decode_static_scratch_bytes(n, H, W) -- lives in an array of
+ * pcc_decode_static_scratch_bytes(n, H, W), or twice that for bands of eight
+ * rows, which are only used where they fit -- lives in an array of
  * PCC_STATIC_SCRATCH_BYTES that is part of the library's device code (every GPU
  * the library runs on holds it until the process ends) instead of the ctx's
  * workspace.  The call allocates and frees nothing, and clears what it uses of

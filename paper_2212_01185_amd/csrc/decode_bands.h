@@ -1,8 +1,9 @@
-// The body of the decoders' kernels (pcc.hip), included into each: template parameters Net and MINBLOCKS and the kernel's
-// parameters are in scope.  (As a function inlined into the kernels the compiler allots their registers differently: the
+// The body of the decoders' kernels (pcc.hip), included into each: Net, MINBLOCKS, ROWS and the kernel's parameters
+// are in scope.  (As a function inlined into the kernels the compiler allots their registers differently: the
 // paper's shape with two workgroups per compute unit then spills 20 instead of 16.)
     using Lay = Layout<Net>;
-    using D = DecLds<Net>;
+    using D = DecLds<Net, ROWS>;
+    constexpr int PK = D::kPartK, LP = D::kLanes;
     constexpr int K = Net::K, HS = Lay::kHeadSlots, RC = Net::kRingCols, KB0 = Net::kb(0);
     constexpr int kDelay = Net::kDelay, kMaxReach = D::kMaxReach;
     extern __shared__ __align__(16) uint8_t lds[];
@@ -21,18 +22,21 @@
     // network role: pixel nl of the tile, k-slot group g
     const int g = lane >> 4, nl = lane & 15;
     const bf16x4_bits_t minus_one = minus_identity(lane);
-    // search role: pixel q of the band, lane j of its group
-    const int q = 4 * wave + (lane >> 4), j = lane & 15;
+    // search role: pixel q of the band, lane j of its LP lanes, which is edge e and takes part `part` of the components
+    const int q = LP == 16 ? 4 * wave + (lane >> 4) : 2 * wave + (lane >> 5), j = LP == 16 ? lane & 15 : lane & 31, part = LP == 16 ? 0 : (lane >> 4) & 1;
     SearchLane sl;
-    sl.j = j; sl.shift = lane & 48; sl.base4 = 4 * (lane & 48);
-    sl.edge1 = (float)(32 * j - 1) * (1.0f / 512.0f);
-    sl.edge2 = (float)(2 * j - 1) * (1.0f / 512.0f);
-    sl.e1 = j == 0 ? -__builtin_inff() : (float)(16 * j);
-    sl.e2 = j == 0 ? -__builtin_inff() : (float)j;
+    sl.e = LP == 16 ? j : lane & 15; sl.shift = LP == 16 ? lane & 48 : (lane & 32) + 16; sl.base4 = LP == 16 ? 4 * (lane & 48) : 4 * ((lane & 32) + 16);
+    sl.edge1 = (float)(32 * sl.e - 1) * (1.0f / 512.0f);
+    sl.edge2 = (float)(2 * sl.e - 1) * (1.0f / 512.0f);
+    sl.e1 = sl.e == 0 ? -__builtin_inff() : (float)(16 * sl.e);
+    sl.e2 = sl.e == 0 ? -__builtin_inff() : (float)sl.e;
 
     {
         const float2* src = reinterpret_cast<const float2*>(model + Lay::kLutOff);
         for (int i = tid; i < kLutEntries + 1; i += kDecThreads) *reinterpret_cast<float2*>(lds + D::kLutOff + spread_at((uint32_t)i)) = src[i];
+    }
+    if constexpr (D::kParts * PK > K) {      // the component that the second part has too few: looked up, never summed
+        for (int i = tid; i < ROWS * 3 * D::kCpStride; i += kDecThreads) cpbuf[i] = 0.0f;
     }
     if constexpr (MINBLOCKS > 1) {
         auto stage = [&](int dst_off, int src_off, int bytes) {
@@ -61,7 +65,7 @@
         for (int half = 0; half < 2; ++half) {
             int dr = 0, off = 0;
             run_used[kbi][half] = Net::run_desc(kbi, g, half, dr, off);
-            run_at[kbi][half] = D::kRingOff + 2u * ((nl + 2 + dr) * D::kRingRowElems + off);
+            run_at[kbi][half] = D::kRingOff + 2u * (((ROWS == 16 ? nl : nl & (ROWS - 1)) + 2 + dr) * D::kRingRowElems + off);
             run_odd[kbi][half] = has_odd_runs<Net>() && (off & 1) != 0;
         }
     }
@@ -97,14 +101,14 @@
                        : (kIndexTickets ? (int)gridDim.x : 0) + atomicAdd(&status[kStTicket], 1);
         misc[1] = 0;
     }
-    for (int i = tid; i < 18 * D::kRingRowElems; i += kDecThreads) ring[i] = 0;
+    for (int i = tid; i < (ROWS + 2) * D::kRingRowElems; i += kDecThreads) ring[i] = 0;
     __syncthreads();
     const int ticket = __builtin_amdgcn_readfirstlane(misc[0]);
     first_band = false;
     if (ticket >= total_bands) break;
     const int band = ticket / n, im = ticket - band * n;
 
-    const int r0 = band * kBandRows;
+    const int r0 = band * ROWS;
     const uint64_t rows_total = (uint64_t)n * H;
     const uint64_t table = (uint64_t)kStreamHeader + 8ull * (rows_total + 1);
     const uint64_t payload_bytes = nbytes - table;   // host guarantees nbytes >= table
@@ -161,7 +165,7 @@
     const uint32_t* mail_in = mailbox + ((size_t)im * nbands + (band > 0 ? band - 1 : 0)) * 2 * (size_t)W;
     uint32_t* mail_out = mailbox + ((size_t)im * nbands + band) * 2 * (size_t)W;
 
-    const int last_row = min(r0 + kBandRows - 1, H - 1);
+    const int last_row = min(r0 + ROWS - 1, H - 1);
     const int t_begin = kDelay * r0, t_end = kDelay * last_row + W - 1;
     // The first eight lanes of the fetch wave bring in the rows above the band: even lanes row r0-2 -> ring row 0, odd
     // lanes row r0-1 -> ring row 1, each pair to one of a pixel's four places.  That wave has a round without an out-block in one of the layers (DecLds::kIdleLayer)
@@ -266,8 +270,8 @@
     // addressed as a buffer: lanes and columns without a pixel store beyond its end, which the hardware drops.
     uint16_t held[3] = {0, 0, 0};
     const auto image = __builtin_amdgcn_make_buffer_rsrc(out_img, 0, 3 * H * W, 0x00020000 /* untyped */);
-    const uint16_t* held_at = ring + ((lane & 15) + 2) * D::kRingRowElems;
-    const uint32_t store_end = lane < kBandRows && r0 + lane < H ? (uint32_t)W : 0u;
+    const uint16_t* held_at = ring + ((lane & (ROWS - 1)) + 2) * D::kRingRowElems;
+    const uint32_t store_end = lane < ROWS && r0 + lane < H ? (uint32_t)W : 0u;
     auto store_read = [&](int t_done) __attribute__((always_inline)) {
         const int cc = t_done - kDelay * (r0 + lane);
         const uint16_t* e = held_at + (cc & (RC - 1)) * 3;
@@ -301,7 +305,7 @@
     // where a step's gather reads: the window's offset for runs that start at an even element of it and at an odd one
     uint32_t window_at[2];
     auto gather_window = [&](int at) __attribute__((always_inline)) {
-        const uint32_t slot = (uint32_t)(at - kDelay * (r0 + nl) - 2) & (RC - 1);
+        const uint32_t slot = (uint32_t)(at - kDelay * (r0 + (ROWS == 16 ? nl : nl & (ROWS - 1))) - 2) & (RC - 1);
         const uint32_t second = (slot & 1u) * (2u * D::kRingCopyElems);
         window_at[0] = 6u * slot + second;
         window_at[1] = 6u * slot + 2u * D::kRingCopyElems - second;
@@ -363,8 +367,8 @@
     };
     // the last step's pixel of the band's last two rows, for the band below
     auto mail = [&](int t_done) __attribute__((always_inline)) {
-        if (j == 0 && q >= kBandRows - 2 && settle_active != 0)
-            __hip_atomic_store(mail_out + (size_t)(q - (kBandRows - 2)) * W + (t_done - kDelay * qrow), mail_px, __ATOMIC_RELAXED,
+        if (j == 0 && q >= ROWS - 2 && settle_active != 0)
+            __hip_atomic_store(mail_out + (size_t)(q - (ROWS - 2)) * W + (t_done - kDelay * qrow), mail_px, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
     };
 
@@ -433,7 +437,7 @@
         // ---- network, layers meeting in LDS
         net.template run<Role::kOwnsLast>(in1, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
 
-        // ---- mixtures: lane j < 3K of pixel q prepares component j % K of channel j / K
+        // ---- mixtures: lane jj < 3K of pixel q prepares component jj % K of channel jj / K
         auto prepare = [&](int jj) __attribute__((always_inline)) {
             const int ch = jj / K, k = jj - K * ch;
             const float* hc = headout + q * D::kHeadStride + ch * HS;
@@ -465,14 +469,15 @@
 #pragma unroll
                 for (int kk = 1; kk < K; ++kk) if (k == kk) { pk = all.pi[kk]; mk = all.mu[kk]; ak = all.a[kk]; }
             }
-            float* dst = jj < 3 * K ? cpbuf + (q * 3 + ch) * D::kCpStride + k : reinterpret_cast<float*>(lds + D::kSinkOff + 4 * lane);
-            dst[0] = pk; dst[K] = mk; dst[2 * K] = ak;
+            float* dst = jj < 3 * K ? cpbuf + (q * 3 + ch) * D::kCpStride + (D::kParts > 1 ? k / PK * D::kPartStride + k % PK : k)
+                                    : reinterpret_cast<float*>(lds + D::kSinkOff + 4 * lane);
+            dst[0] = pk; dst[PK] = mk; dst[2 * PK] = ak;
         };
-        if constexpr (3 * K <= 16) {
+        if constexpr (3 * K <= LP) {
             prepare(j);        // (lanes without a component prepare what nobody reads: no branch)
         } else {
             prepare(j);
-            prepare(j + 16);
+            prepare(j + LP);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
         __builtin_amdgcn_wave_barrier();
@@ -481,36 +486,44 @@
         // What the three searches need, channel by channel: R's mixture now, G's and B's (with their coupling
         // coefficients) while the search before them waits for its last table reads.  Requested all at once, the reads
         // of the four waves keep LDS busy for hundreds of cycles in front of R's first table reads.
-        ChanParams<K> cpr, cpg, cpb;
-        float alpha[K], beta[K], gamma[K];
+        ChanParams<PK> cpr, cpg, cpb;
+        float alpha[PK], beta[PK], gamma[PK];
         const float* hq = headout + q * D::kHeadStride;
         // `tail` receives the last vector read, padding included: the caller keeps it in use until the values are
         // consumed (register allocation only: a padding register that is free at once is handed to the next read,
         // which then has to wait for this one)
-        auto load_cp = [&](int ch, ChanParams<K>& cp, f32x4_t& tail) __attribute__((always_inline)) {
-            constexpr int NV = (3 * K + 3) / 4;
-            const f32x4_t* src = reinterpret_cast<const f32x4_t*>(cpbuf + (q * 3 + ch) * D::kCpStride);
+        auto load_cp = [&](int ch, ChanParams<PK>& cp, f32x4_t& tail) __attribute__((always_inline)) {
+            constexpr int NV = (3 * PK + 3) / 4;
+            const f32x4_t* src = reinterpret_cast<const f32x4_t*>(cpbuf + (q * 3 + ch) * D::kCpStride + (D::kParts > 1 ? part * D::kPartStride : 0));
             f32x4_t vv[NV];
 #pragma unroll
             for (int i = 0; i < NV; ++i) vv[i] = src[i];
             tail = vv[NV - 1];
             auto at = [&](int i) { const f32x4_t w = vv[i >> 2]; return (i & 3) == 0 ? w.x : (i & 3) == 1 ? w.y : (i & 3) == 2 ? w.z : w.w; };
 #pragma unroll
-            for (int k = 0; k < K; ++k) { cp.pi[k] = at(k); cp.mu[k] = at(K + k); cp.a[k] = at(2 * K + k); }
+            for (int k = 0; k < PK; ++k) { cp.pi[k] = at(k); cp.mu[k] = at(PK + k); cp.a[k] = at(2 * PK + k); }
         };
         f32x4_t tail_r, tail_g, tail_b;
         // coupling coefficients: canonical head outputs 9K.. (alpha), 10K.. (beta), 11K.. (gamma), wherever the head's
-        // (group, register) layout put them
+        // (group, register) layout put them; a component that the lane's part does not have reads the first part's last one
+        auto coupling = [&](auto first, auto kc) __attribute__((always_inline)) {
+            constexpr int c = decltype(first)::value, k = decltype(kc)::value, mine = head_slot<Net>(c + k);
+            if constexpr (D::kParts == 1) return hq[mine];
+            else {
+                constexpr int other = PK + k < K ? head_slot<Net>(c + PK + k) : mine;
+                return hq[mine + part * (other - mine)];
+            }
+        };
         auto load_g = [&]() __attribute__((always_inline)) {
             load_cp(1, cpg, tail_g);
-            static_for<0, K>([&](auto kc) { alpha[decltype(kc)::value] = hq[head_slot<Net>(9 * K + decltype(kc)::value)]; });
+            static_for<0, PK>([&](auto kc) { alpha[decltype(kc)::value] = coupling(std::integral_constant<int, 9 * K>{}, kc); });
         };
         auto load_b = [&]() __attribute__((always_inline)) {
             load_cp(2, cpb, tail_b);
-            static_for<0, K>([&](auto kc) {
+            static_for<0, PK>([&](auto kc) {
                 constexpr int k = decltype(kc)::value;
-                beta[k] = hq[head_slot<Net>(10 * K + k)];
-                gamma[k] = hq[head_slot<Net>(11 * K + k)];
+                beta[k] = coupling(std::integral_constant<int, 10 * K>{}, kc);
+                gamma[k] = coupling(std::integral_constant<int, 11 * K>{}, kc);
             });
         };
         auto load_nothing = [&]() __attribute__((always_inline)) {};
@@ -522,7 +535,7 @@
         uint32_t start, freq;
         Found found_r;
         // R
-        const int sr = group_search<K>(cpr, slot1_x, lut, sl, found_r, load_nothing, load_g);
+        const int sr = group_search<K, PK>(cpr, slot1_x, lut, sl, found_r, load_nothing, load_g);
         float rhat = (float)sr;
         ring_elem[0] = bf16_bits(rhat) & active;
         Interval iv_r;
@@ -531,7 +544,7 @@
         clk.mark(kPhR);
         // G given R; meanwhile R's pop, whose state B is coded on
         asm volatile("" : "+v"(rhat) : "v"(tail_r), "v"(tail_g));    // (tied to a value known only now: stays here)
-        couple_green<K>(cpg, alpha, rhat);
+        couple_green<PK>(cpg, alpha, rhat);
         auto pick_r_upper = [&]() __attribute__((always_inline)) { interval_pick_upper(found_r, sl, iv_r); };
         auto pop_r = [&]() __attribute__((always_inline)) {
             load_b();
@@ -539,15 +552,15 @@
             reader_pop(rd, rd.x, start, freq, active);
             asm volatile("" : "+v"(rd.x), "+v"(rd.w[0]), "+v"(rd.w[1]), "+v"(rd.pos));     // scheduling only: done here
         };
-        const int sg = group_search<K>(cpg, slot1_y, lut, sl, found_g, pick_r_upper, pop_r);
+        const int sg = group_search<K, PK>(cpg, slot1_y, lut, sl, found_g, pick_r_upper, pop_r);
         float ghat = (float)sg;
         ring_elem[1] = bf16_bits(ghat) & active;
         ghat = ghat * (1.0f / 256.0f);
         clk.mark(kPhG);
         // B given R, G
         asm volatile("" : "+v"(ghat) : "v"(tail_b));
-        couple_blue<K>(cpb, beta, gamma, rhat, ghat);
-        const int sb = group_search<K>(cpb, (float)(((uint32_t)rd.x & 0xFFFFu) + 1u), lut, sl, found_b, load_stop, load_nothing);
+        couple_blue<PK>(cpb, beta, gamma, rhat, ghat);
+        const int sb = group_search<K, PK>(cpb, (float)(((uint32_t)rd.x & 0xFFFFu) + 1u), lut, sl, found_b, load_stop, load_nothing);
         ring_elem[2] = bf16_bits((float)sb) & active;
         clk.mark(kPhB);
 

@@ -12,6 +12,7 @@
 //   scan_kernel        exclusive prefix sum of row payload sizes in front of it, for jobs of very many rows
 //   decode_kernel      persistent wavefront decoder: one workgroup (4 waves) per
 //                      band of 16 rows, step t handles pixel (r, t - delay*r) of each row
+//   decode_narrow_kernel  the same with bands of eight rows
 //   cdf_tables_kernel  test hook: full integer CDF tables from given parameters
 #include <hip/hip_runtime.h>
 
@@ -36,7 +37,7 @@ constexpr uint32_t kBlobMagic = 0x57434350u;    // "PCCW"
 constexpr uint32_t kStreamMagic = 0x31434350u;  // "PCC1"
 constexpr int kStreamHeader = 32;
 constexpr uint32_t kStreamVersion = 2;          // two coder states per row (1: one)
-constexpr int kBandRows = 16;
+constexpr int kBandRows = 16, kNarrowRows = 8;      // rows of a band (decode_kernel, decode_narrow_kernel)
 constexpr uint32_t kMailTag = 0x80000000u;
 
 template <class Net>
@@ -923,8 +924,11 @@ constexpr bool has_odd_runs() {
 }
 
 // decode LDS: the CDF table, two activation buffers, head outputs, mixtures, ring
-template <class Net>
+template <class Net, int ROWS = kBandRows>
 struct DecLds {
+    static constexpr int kLanes = kDecThreads / ROWS;                  // lanes of a pixel
+    static constexpr int kParts = kLanes / 16;                         // ... in rows of 16, which take a part of the components each
+    static constexpr int kPartK = (Net::K + kParts - 1) / kParts;      // components of a part (the last part may have fewer)
     static constexpr int max_kb() {
         int m = 0;
         for (int l = 1; l < Net::kLayers; ++l) m = Net::kb(l) > m ? Net::kb(l) : m;
@@ -938,10 +942,12 @@ struct DecLds {
     // Strides in floats, padded by one 16-byte vector: consecutive pixels (and channels) then start
     // four LDS banks apart instead of on the same bank.
     static constexpr int kHeadStride = 4 * kHS + 4;                    // head outputs of one pixel: [4 groups][kHS]
-    static constexpr int kCpStride = 3 * Net::K <= 16 ? 20 : 24;       // mixture of one (pixel, channel): pi[K], mu[K], a[K]
+    // mixture of one (pixel, channel): for each part of the components pi[kPartK], mu[kPartK], a[kPartK]
+    static constexpr int kPartStride = kParts > 1 ? (3 * kPartK + 3) / 4 * 4 : 3 * Net::K <= 16 ? 20 : 24;
+    static constexpr int kCpStride = kParts * kPartStride;
     static constexpr int kHeadOff = kAct1Off + kActBytes;              // [16 pixels][kHeadStride] fp32, (group, register) layout
     static constexpr int kCpOff = kHeadOff + 16 * kHeadStride * 4;     // [16 pixels][3 channels][kCpStride] fp32
-    // Ring of recently decoded pixels as first-layer inputs, bf16: [18 rows][2 copies][2 * kRingCols columns][3].
+    // Ring of recently decoded pixels as first-layer inputs, bf16: [ROWS + 2 rows][2 copies][2 * kRingCols columns][3].
     // Rows 0,1 are the two rows above the band.  Column c lives at slots c mod kRingCols and that + kRingCols, so the
     // values of a run of neighbour columns are always contiguous.  The second copy is one element further on, so
     // that a run of four values, which may start at any element, is two aligned dwords in one of the copies: LDS takes
@@ -949,7 +955,7 @@ struct DecLds {
     static constexpr int kRingCopyElems = 2 * Net::kRingCols * 3 + 1;  // from an element to the same one in the second copy
     static constexpr int kRingRowElems = 2 * kRingCopyElems + Net::kRingPad;
     static constexpr int kRingOff = kCpOff + 16 * 3 * kCpStride * 4;
-    static constexpr int kMiscOff = kRingOff + 18 * kRingRowElems * 2; // ticket, abort flag
+    static constexpr int kMiscOff = kRingOff + (ROWS + 2) * kRingRowElems * 2; // ticket, abort flag
     static constexpr int kSinkOff = kMiscOff + 16;                     // where lanes with no ring element to write write
     static constexpr int kBytes = (kSinkOff + 64 * 4 + 8 * Net::K + 15) / 16 * 16;
     // Two workgroups per CU have 256 registers per lane each, too few for the whole of a wave's weight slices: there
@@ -1256,21 +1262,24 @@ struct WaveNet<Net, SHARED, L, true> {
     __device__ __forceinline__ void load(const uint8_t* __restrict__, const uint8_t* __restrict__, int, int) {}
 };
 
-// Symbol search by the 16 lanes (j = 0..15) of one pixel: two sweeps of 16 evaluations, Cq(16 j) and, in the
-// block b found, Cq(16 b + j).  The search compares 65280 F(edge) with slot + 1 - e in floating point, both exact:
-// floor(v) + e <= slot exactly when v < slot + 1 - e.  Lane 0 always passes (Cq(0) = 0; in the second sweep Cq(16 b)
-// is known to pass): its own constants are minus infinity.  What the symbol's interval needs is left in `found`, for
+// Symbol search by the lanes of one pixel: two sweeps of 16 evaluations, Cq(16 e) and, in the
+// block b found, Cq(16 b + e), e = 0..15.  The search compares 65280 F(edge) with slot + 1 - e in floating point, both exact:
+// floor(v) + e <= slot exactly when v < slot + 1 - e.  Edge 0 always passes (Cq(0) = 0; in the second sweep Cq(16 b)
+// is known to pass): its lanes' constants are minus infinity.  What the symbol's interval needs is left in `found`, for
 // group_interval, which is off the path from symbol to symbol.
+// With 32 lanes to a pixel two rows of 16 lanes share an edge's components: the first row looks up the first kPartK of them and
+// sums them, the second row looks up the others meanwhile and goes on with the first row's sum, so that the sum is made in
+// the order of the components as everywhere; what a sweep finds is in the second row.
 struct SearchLane {            // a lane's constants
-    float edge1, edge2;        // (2 (16 j) - 1) / 512 and (2 j - 1) / 512
-    float e1, e2;              // 16 j and j; minus infinity in lane 0
-    int j, shift;              // lane of the group; position of the group's 16 bits in a ballot
-    int base4;                 // 4 x first lane of the group
+    float edge1, edge2;        // (2 (16 e) - 1) / 512 and (2 e - 1) / 512
+    float e1, e2;              // 16 e and e; minus infinity for e = 0
+    int e, shift;              // the lane's edge; position in a ballot of the 16 bits of the pixel's row that has the sums
+    int base4;                 // 4 x first lane of that row
 };
 struct Found {
-    uint32_t next1;            // Cq(16 j + 16), 65536 in lane 15
-    uint32_t c2;               // Cq(16 b + j), but for b = j = 0
-    int b, count, x;           // block, lanes that passed in the second sweep, the symbol 16 b + count - 1
+    uint32_t next1;            // Cq(16 e + 16), 65536 for e = 15
+    uint32_t c2;               // Cq(16 b + e), but for b = e = 0
+    int b, count, x;           // block, edges that passed in the second sweep, the symbol 16 b + count - 1
 };
 
 // Scheduling only: the fractions are computed here.
@@ -1280,36 +1289,68 @@ __device__ __forceinline__ void pin(CqLookup<K>& q) {
     for (int k = 0; k < K; ++k) asm volatile("" : "+v"(q.t[k]));
 }
 
+// cq_scaled for components that two rows share: K in all, the lane's are PK (the first row's) or the K - PK behind them.
+template <int K, int PK>
+__device__ __forceinline__ float cq_scaled_shared(const ChanParams<PK>& cp, CqLookup<PK>& q) {
+    float2 (&td)[PK] = q.td;
+    // Scheduling only: all table reads are in flight before the first is used.
+    if constexpr (PK == 4) {
+        asm volatile("" : "+v"(td[0].x), "+v"(td[0].y), "+v"(td[1].x), "+v"(td[1].y), "+v"(td[2].x), "+v"(td[2].y), "+v"(td[3].x), "+v"(td[3].y));
+    } else if constexpr (PK == 3) {
+        asm volatile("" : "+v"(td[0].x), "+v"(td[0].y), "+v"(td[1].x), "+v"(td[1].y), "+v"(td[2].x), "+v"(td[2].y));
+    } else {
+        static_assert(PK == 2, "three, five or seven components");
+        asm volatile("" : "+v"(td[0].x), "+v"(td[0].y), "+v"(td[1].x), "+v"(td[1].y));
+    }
+    float acc = 0.0f, phi[PK];
+#pragma unroll
+    for (int k = 0; k < PK; ++k) {
+        phi[k] = __builtin_fmaf(q.t[k], td[k].y, td[k].x);
+        acc = __builtin_fmaf(cp.pi[k], phi[k], acc);
+    }
+    // the first row's sum in the second row
+    const u32x2_t swapped = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_permlane16_swap(__float_as_uint(acc), __float_as_uint(acc), false, false));
+    acc = __uint_as_float(swapped.x);
+#pragma unroll
+    for (int k = 0; k < K - PK; ++k) acc = __builtin_fmaf(cp.pi[k], phi[k], acc);
+    return fminf(acc, 1.0f) * 65280.0f;
+}
+
 // during1(), during2(): called when a sweep's table reads are issued; memory requests made there queue behind them.
-template <int K, class During1, class During2>
-__device__ __forceinline__ int group_search(const ChanParams<K>& cp, float slot1, const float2* __restrict__ lut, const SearchLane& sl,
+// K components in all, PK of them (or the rest) the lane's own.
+template <int K, int PK, class During1, class During2>
+__device__ __forceinline__ int group_search(const ChanParams<PK>& cp, float slot1, const float2* __restrict__ lut, const SearchLane& sl,
                                             Found& found, During1&& during1, During2&& during2) {
-    CqLookup<K> q1, q2;
-    cq_lookup<K, true>(cp, sl.edge1, lut, q1);
+    auto scaled = [&](CqLookup<PK>& q) __attribute__((always_inline)) {
+        if constexpr (PK < K) return cq_scaled_shared<K, PK>(cp, q);
+        else return cq_scaled<K>(cp, q);
+    };
+    CqLookup<PK> q1, q2;
+    cq_lookup<PK, true>(cp, sl.edge1, lut, q1);
     __builtin_amdgcn_sched_barrier(0);       // scheduling only: the table reads first, then what they leave time for
     during1();
-    cq_fractions<K>(q1);
+    cq_fractions<PK>(q1);
     float limit1 = slot1 - sl.e1;
     asm volatile("" : "+v"(limit1) :: "memory");
-    pin<K>(q1);
-    const float v1 = cq_scaled<K>(cp, q1);
+    pin<PK>(q1);
+    const float v1 = scaled(q1);
     const int b = __popcll((__ballot(v1 < limit1) >> sl.shift) & 0xFFFFull) - 1;
     const float bf = (float)b;
-    cq_lookup<K, true>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2);
+    cq_lookup<PK, true>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2);
     __builtin_amdgcn_sched_barrier(0);
     during2();
-    cq_fractions<K>(q2);
+    cq_fractions<PK>(q2);
     float limit2 = __builtin_fmaf(bf, -16.0f, slot1 - sl.e2);
-    found.next1 = (uint32_t)__builtin_amdgcn_update_dpp(65536, (int)((uint32_t)v1 + 16u * (uint32_t)sl.j), 0x101 /* row_shl:1 */,
+    found.next1 = (uint32_t)__builtin_amdgcn_update_dpp(65536, (int)((uint32_t)v1 + 16u * (uint32_t)sl.e), 0x101 /* row_shl:1 */,
                                                         0xF, 0xF, false);
     int first = 16 * b - 1;
     asm volatile("" : "+v"(limit2), "+v"(found.next1), "+v"(first) :: "memory");
-    pin<K>(q2);
-    const float v2 = cq_scaled<K>(cp, q2);
+    pin<PK>(q2);
+    const float v2 = scaled(q2);
     found.count = __popcll((__ballot(v2 < limit2) >> sl.shift) & 0xFFFFull);
     found.b = b;
     found.x = first + found.count;
-    found.c2 = (uint32_t)v2 + (uint32_t)(first + 1 + sl.j);
+    found.c2 = (uint32_t)v2 + (uint32_t)(first + 1 + sl.e);
     return found.x;
 }
 
@@ -1321,8 +1362,8 @@ __device__ __forceinline__ void interval_pick(const Found& f, const SearchLane& 
     v.lower = (uint32_t)__builtin_amdgcn_ds_bpermute(sl.base4 + 4 * f.count - 4, (int)f.c2);
 }
 __device__ __forceinline__ void interval_pick_upper(const Found& f, const SearchLane& sl, Interval& v) {
-    // lane 0 is nobody's upper end: it stands in for the block's end
-    v.upper = (uint32_t)__builtin_amdgcn_ds_bpermute(sl.base4 + 4 * (f.count & 15), (int)(sl.j == 0 ? v.up : f.c2));
+    // edge 0 is nobody's upper end: it stands in for the block's end
+    v.upper = (uint32_t)__builtin_amdgcn_ds_bpermute(sl.base4 + 4 * (f.count & 15), (int)(sl.e == 0 ? v.up : f.c2));
 }
 __device__ __forceinline__ void interval_of(const Found& f, const Interval& v, uint32_t& start, uint32_t& freq) {
     start = f.x == 0 ? 0u : v.lower;
@@ -1353,11 +1394,23 @@ struct StepRole {
 // MINBLOCKS = 1: all registers to one workgroup per CU (lowest latency per step).  MINBLOCKS = 2: two
 // workgroups share a CU (some spills; a step takes Net::kSharedAlonePercent to Net::kSharedStepPercent of the time, so
 // this only pays for jobs of so many bands that the work per CU, not an image's chain of steps, sets the time: launch_decode).
+// ROWS = 16: 16 lanes to a pixel.  ROWS = 8 (half of a tile's columns are copies): 32 lanes, which share the mixture components
+// in two halves, and half the pixels to a wave, so that the searches, more than half of a step's instructions, have a fifth
+// fewer of them (437 -> 349 vector instructions with five components).
 template <class Net, int MINBLOCKS>
 __global__ void __launch_bounds__(kDecThreads, MINBLOCKS)
 decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ stream, uint64_t nbytes, int n, int H,
               int W, int nbands, uint32_t dist, uint8_t* __restrict__ img_out, uint32_t* mailbox, int* status,
               uint32_t spin_limit) {
+    constexpr int ROWS = kBandRows;
+#include "decode_bands.h"
+}
+template <class Net>
+__global__ void __launch_bounds__(kDecThreads, 1)
+decode_narrow_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ stream, uint64_t nbytes, int n, int H,
+                     int W, int nbands, uint32_t dist, uint8_t* __restrict__ img_out, uint32_t* mailbox, int* status,
+                     uint32_t spin_limit) {
+    constexpr int MINBLOCKS = 1, ROWS = kNarrowRows;
 #include "decode_bands.h"
 }
 
@@ -1437,7 +1490,7 @@ struct pcc_ctx {
     uint32_t dist = 0;             // written to / checked against stream header word 6
     int encode_threads = 512;       // of a workgroup of the pixel kernel
     uint32_t spin_limit = 1u << 22;      // polls of a band for one pixel of the band above (seconds) before the call fails (PCC_DECODE_SPIN_LIMIT, for tests)
-    int decode_variant = 0;              // 0: chosen per job; 1: one workgroup per CU; 2: two (PCC_DECODE_VARIANT, for measurements)
+    int decode_variant = 0;              // 0: chosen per job; 1: one workgroup per CU; 2: two; 3: one, bands of eight rows where the network has them (PCC_DECODE_VARIANT, for measurements)
     // the row coder of a small job runs beside the pixel kernel, on a stream of its own
     bool overlap = true;
     uint32_t patience = kRansPatience;        // polls before a row coder beside the pixel kernel stands down
@@ -1674,10 +1727,15 @@ bool set_kernel_attributes() {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, dec) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<Net, 2>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net>::kBytesShared) == hipSuccess;
+    if constexpr (Net::kNarrowBands)
+        ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net, kNarrowRows>::kBytes) == hipSuccess;
     // The decoders read the CDF table at LDS address 0 (cq_lookup<K, true>): their dynamic array must begin there, that is,
     // they must have no static one in front of it.
     static_assert(DecLds<Net>::kLutOff == 0, "the table's LDS address is a literal in cq_lookup");
-    for (const void* decoder : {reinterpret_cast<const void*>(&decode_kernel<Net, 1>), reinterpret_cast<const void*>(&decode_kernel<Net, 2>)}) {
+    std::vector<const void*> decoders = {reinterpret_cast<const void*>(&decode_kernel<Net, 1>), reinterpret_cast<const void*>(&decode_kernel<Net, 2>)};
+    if constexpr (Net::kNarrowBands) decoders.push_back(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>));
+    for (const void* decoder : decoders) {
         hipFuncAttributes attr;
         ok = ok && hipFuncGetAttributes(&attr, decoder) == hipSuccess && attr.sharedSizeBytes == 0;
     }
@@ -1717,10 +1775,19 @@ int launch_encode_any(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, u
     });
 }
 
+// How a job is decoded: the kernel, its bands to an image and its workgroups.
+struct DecodeLaunch {
+    enum { kOne = 1, kTwo = 2, kNarrow = 3 } kernel;       // one or two workgroups per compute unit; one, bands of eight rows
+    int nbands;
+    uint32_t grid;
+};
+
+size_t mailbox_bytes(int n, int nbands, int W) { return align_up((size_t)n * nbands * 2 * (size_t)W * 4, 256); }
+
+// most_bytes: what there is for the mailbox, if that is limited (bands of eight rows need twice as much of it)
 template <class Net>
-void launch_decode(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, int H, int W, int nbands,
-                   uint8_t* d_img_out, uint32_t* d_mail, uint32_t spin_limit, hipStream_t st) {
-    constexpr int kLds = DecLds<Net>::kBytes;
+DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_bytes) {
+    const int nbands = (H + kBandRows - 1) / kBandRows, narrow_bands = (H + kNarrowRows - 1) / kNarrowRows;
     const uint64_t bands = (uint64_t)n * nbands;                      // dims_ok: below 2^31
     const uint64_t cus = ctx->num_cus > 0 ? (uint64_t)ctx->num_cus : 256u;
     // One workgroup per CU decodes a step in the shortest time; two per CU decode twice as many bands at once, at
@@ -1735,24 +1802,52 @@ void launch_decode(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, 
     // 4096x2160, images of a few rows and of a few columns): the launch chosen takes 0.1 % longer than the better one on
     // average and 3.6 % at most.  768x512, ms with one and with two per CU: 16 images 5.66 and 6.02, 18 images 6.56 and
     // 5.96, 48 images 12.68 and 9.93; the paper's shape, 9 images 6.27 and 6.66, 24 images 7.53 and 7.51.
-    const uint64_t band_rows = H < kBandRows ? H : kBandRows;
-    const uint64_t hold = (uint64_t)W + (uint64_t)Net::kDelay * (band_rows - 1), stride = (uint64_t)Net::kDelay * kBandRows;
-    auto steps = [&](uint64_t places) {
-        const uint64_t last = bands - 1;
+    // Bands of eight rows take Net::kNarrowPercent of the time of a step, and are twice as many: they are for jobs whose chain of
+    // steps, not whose work per CU, sets the time.  768x512, ms with bands of 16 and of 8 rows: 1 image 4.65 and 4.53, 4 images
+    // 4.66 and 4.63, 8 images 4.73 and 5.15 (the hand-overs of 500 bands), 10 images 4.74 and 6.27; 4096x2160 21.8 and 21.3, two
+    // of them 21.8 and 29.9; 512x512 with seven mixtures 7.01 and 6.20, 12 images 7.26 and 6.40, 16 images 7.28 and 7.40.  Of 53 such
+    // jobs the launch chosen takes 0.2 % longer than the best of the three on average and 1.5 % at most.
+    auto steps = [&](uint64_t places, int rows, int per_image) {
+        const uint64_t hold = (uint64_t)W + (uint64_t)Net::kDelay * ((H < rows ? H : rows) - 1), stride = (uint64_t)Net::kDelay * rows;
+        const uint64_t last = (uint64_t)n * per_image - 1;
         return hold + std::max(stride * (last / n), hold * (last / places) + stride * (last % places / n));
     };
-    const double steps_two = (double)steps(2 * cus), busy = (double)(bands * hold) / (steps_two * (double)(2 * cus));
+    const uint64_t hold = (uint64_t)W + (uint64_t)Net::kDelay * ((H < kBandRows ? H : kBandRows) - 1);
+    const double steps_two = (double)steps(2 * cus, kBandRows, nbands), busy = (double)(bands * hold) / (steps_two * (double)(2 * cus));
     const double pace = Net::kSharedAlonePercent +
                         ((double)Net::kSharedStepPercent - Net::kSharedAlonePercent) * std::min(std::max((busy - 0.2) / 0.6, 0.0), 1.0);
-    const bool two = ctx->decode_variant == 2 || (ctx->decode_variant == 0 && DecLds<Net>::kTwoFit && bands > cus &&
-                                                  steps_two * pace < 100.0 * (double)steps(cus));
-    const uint32_t grid = (uint32_t)std::min(bands, two ? 2 * cus : cus);
-    if (!two)
-        hipLaunchKernelGGL((decode_kernel<Net, 1>), dim3(grid), dim3(kDecThreads), kLds, st, ctx->d_model, d_stream,
-                           (uint64_t)nbytes, n, H, W, nbands, ctx->dist, d_img_out, d_mail, ctx->status(kBlockDecode), spin_limit);
-    else
-        hipLaunchKernelGGL((decode_kernel<Net, 2>), dim3(grid), dim3(kDecThreads), DecLds<Net>::kBytesShared, st, ctx->d_model, d_stream,
-                           (uint64_t)nbytes, n, H, W, nbands, ctx->dist, d_img_out, d_mail, ctx->status(kBlockDecode), spin_limit);
+    double best = 100.0 * (double)steps(cus, kBandRows, nbands);
+    auto kernel = DecodeLaunch::kOne;
+    if (DecLds<Net>::kTwoFit && bands > cus && steps_two * pace < best) { kernel = DecodeLaunch::kTwo; best = steps_two * pace; }
+    const bool narrow_fits = Net::kNarrowBands && mailbox_bytes(n, narrow_bands, W) <= most_bytes;
+    if (narrow_fits && (double)Net::kNarrowPercent * (double)steps(cus, kNarrowRows, narrow_bands) < best) kernel = DecodeLaunch::kNarrow;
+    if (ctx->decode_variant == 1) kernel = DecodeLaunch::kOne;
+    if (ctx->decode_variant == 2) kernel = DecodeLaunch::kTwo;
+    if (ctx->decode_variant == 3) kernel = narrow_fits ? DecodeLaunch::kNarrow : DecodeLaunch::kOne;
+    const int per_image = kernel == DecodeLaunch::kNarrow ? narrow_bands : nbands;
+    return {kernel, per_image, (uint32_t)std::min((uint64_t)n * per_image, kernel == DecodeLaunch::kTwo ? 2 * cus : cus)};
+}
+
+template <class Net>
+void launch_decode(pcc_ctx* ctx, const DecodeLaunch& how, const uint8_t* d_stream, size_t nbytes, int n, int H, int W,
+                   uint8_t* d_img_out, uint32_t* d_mail, uint32_t spin_limit, hipStream_t st) {
+    constexpr int kLds = DecLds<Net>::kBytes, kLdsShared = DecLds<Net>::kBytesShared;
+    int* status = ctx->status(kBlockDecode);
+    if (how.kernel == DecodeLaunch::kOne)
+        hipLaunchKernelGGL((decode_kernel<Net, 1>), dim3(how.grid), dim3(kDecThreads), kLds, st, ctx->d_model, d_stream,
+                           (uint64_t)nbytes, n, H, W, how.nbands, ctx->dist, d_img_out, d_mail, status, spin_limit);
+    else if (how.kernel == DecodeLaunch::kTwo)
+        hipLaunchKernelGGL((decode_kernel<Net, 2>), dim3(how.grid), dim3(kDecThreads), kLdsShared, st, ctx->d_model, d_stream,
+                           (uint64_t)nbytes, n, H, W, how.nbands, ctx->dist, d_img_out, d_mail, status, spin_limit);
+    else if constexpr (Net::kNarrowBands) {
+        constexpr int kLdsNarrow = DecLds<Net, kNarrowRows>::kBytes;
+        hipLaunchKernelGGL((decode_narrow_kernel<Net>), dim3(how.grid), dim3(kDecThreads), kLdsNarrow, st, ctx->d_model, d_stream,
+                           (uint64_t)nbytes, n, H, W, how.nbands, ctx->dist, d_img_out, d_mail, status, spin_limit);
+    }
+}
+
+DecodeLaunch choose_decode_any(const pcc_ctx* ctx, int n, int H, int W, size_t most_bytes) {
+    return with_net(ctx->net, [&](auto net) { return choose_decode<decltype(net)>(ctx, n, H, W, most_bytes); });
 }
 
 inline int head_outputs(const pcc_ctx* ctx) {
@@ -1846,7 +1941,7 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
     if (const char* e = getenv("PCC_DECODE_SPIN_LIMIT")) ctx->spin_limit = env_limit(e);
     if (const char* e = getenv("PCC_DECODE_VARIANT")) {
         const int v = atoi(e);
-        if (v >= 0 && v <= 2) ctx->decode_variant = v;
+        if (v >= 0 && v <= 3) ctx->decode_variant = v;
     }
     if (const char* e = getenv("PCC_ENCODE_OVERLAP")) ctx->overlap = atoi(e) != 0;
     if (const char* e = getenv("PCC_RANS_PATIENCE")) ctx->patience = env_limit(e);
@@ -2051,7 +2146,7 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
 }
 
 // Both decoders: `d_mail` is the mailbox (zeroed here), big enough for the job.
-static int decode_with_mailbox(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, int H, int W, int nbands,
+static int decode_with_mailbox(pcc_ctx* ctx, const DecodeLaunch& how, const uint8_t* d_stream, size_t nbytes, int n, int H, int W,
                                uint8_t* d_img_out, uint32_t* d_mail, size_t mail_bytes, bool clear_by_kernel, hipStream_t st) {
     if (clear_by_kernel) {
         const size_t words = mail_bytes / 4;
@@ -2068,7 +2163,7 @@ static int decode_with_mailbox(pcc_ctx* ctx, const uint8_t* d_stream, size_t nby
     prof_reset(ctx);
     prof_begin(ctx, PCC_T_DECODE, st);
     with_net(ctx->net, [&](auto net) {
-        launch_decode<decltype(net)>(ctx, d_stream, nbytes, n, H, W, nbands, d_img_out, d_mail, spin_limit, st);
+        launch_decode<decltype(net)>(ctx, how, d_stream, nbytes, n, H, W, d_img_out, d_mail, spin_limit, st);
         return 0;
     });
     prof_end(ctx, PCC_T_DECODE, st);
@@ -2089,35 +2184,40 @@ int pcc_decode(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, int 
     const uint64_t rows = (uint64_t)n * H;
     const uint64_t table = (uint64_t)kStreamHeader + 8 * (rows + 1);
     if (nbytes < table + 16 * rows) return PCC_E_STREAM;   // every row payload holds at least its two 8-byte states
-    const int nbands = (H + kBandRows - 1) / kBandRows;
-    const size_t mail_bytes = align_up((size_t)n * nbands * 2 * (size_t)W * 4, 256);
+    DecodeLaunch how = choose_decode_any(ctx, n, H, W, SIZE_MAX);
+    size_t mail_bytes = mailbox_bytes(n, how.nbands, W);
     int rc = ensure_workspace(ctx, mail_bytes);
+    if (rc != PCC_OK && how.kernel == DecodeLaunch::kNarrow) {        // no memory for twice as many bands
+        how = choose_decode_any(ctx, n, H, W, mail_bytes - 1);
+        mail_bytes = mailbox_bytes(n, how.nbands, W);
+        rc = ensure_workspace(ctx, mail_bytes);
+    }
     if (rc != PCC_OK) return rc;
     ctx->d_sf = nullptr; ctx->sf_count = 0;
-    return decode_with_mailbox(ctx, d_stream, nbytes, n, H, W, nbands, d_img_out, reinterpret_cast<uint32_t*>(ctx->d_ws),
+    return decode_with_mailbox(ctx, how, d_stream, nbytes, n, H, W, d_img_out, reinterpret_cast<uint32_t*>(ctx->d_ws),
                                mail_bytes, false, (hipStream_t)hip_stream);
 }
 
 size_t pcc_decode_static_scratch_bytes(int n, int H, int W) {
     if (!dims_ok(n, H, W)) return 0;
-    const int nbands = (H + kBandRows - 1) / kBandRows;
-    return align_up((size_t)n * nbands * 2 * (size_t)W * 4, 256);
+    return mailbox_bytes(n, (H + kBandRows - 1) / kBandRows, W);
 }
 
 int pcc_decode_static(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, int H, int W, uint8_t* d_img_out,
                       void* hip_stream) {
     if (!ctx || !d_stream || !d_img_out || !dims_ok(n, H, W)) return PCC_E_ARG;
     if (((uintptr_t)d_stream & 7u) != 0) return PCC_E_ARG;
-    const size_t mail_bytes = pcc_decode_static_scratch_bytes(n, H, W);
-    if (mail_bytes > kStaticScratchBytes) return PCC_E_SCRATCH;
+    if (pcc_decode_static_scratch_bytes(n, H, W) > kStaticScratchBytes) return PCC_E_SCRATCH;
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return PCC_E_HIP;
     const uint64_t rows = (uint64_t)n * H;
     const uint64_t table = (uint64_t)kStreamHeader + 8 * (rows + 1);
     if (nbytes < table + 16 * rows) return PCC_E_STREAM;
-    const int nbands = (H + kBandRows - 1) / kBandRows;
+    // bands of eight rows where the array is large enough for them
+    const DecodeLaunch how = choose_decode_any(ctx, n, H, W, kStaticScratchBytes);
+    const size_t mail_bytes = mailbox_bytes(n, how.nbands, W);
     // the array keeps the last call's words (tagged pixels of another image): the part this job uses is cleared
-    return decode_with_mailbox(ctx, d_stream, nbytes, n, H, W, nbands, d_img_out, ctx->d_static_scratch, mail_bytes, true,
+    return decode_with_mailbox(ctx, how, d_stream, nbytes, n, H, W, d_img_out, ctx->d_static_scratch, mail_bytes, true,
                                (hipStream_t)hip_stream);
 }
 

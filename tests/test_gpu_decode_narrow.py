@@ -1,0 +1,50 @@
+"""The decoder with bands of eight rows: heights around whole bands of 8 and of 16 rows, widths from one pixel on, networks whose two
+halves of the components are equal in number and not, several images, and the limit of the static scratch.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+from paper_2212_01185_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+BLOBS = {"workload": synth.make_blob, "paper": synth.make_paper_blob}
+BLOBS.update({name: lambda seed, name=name: synth.make_ablation_blob(*synth.ABLATION_SHAPES[name], seed=seed) for name in ("more_mixtures", "most_mixtures")})
+SIZES = [(1, 1, 1), (2, 7, 5), (1, 8, 33), (3, 9, 2), (1, 15, 40), (1, 16, 3), (2, 17, 18), (1, 23, 1), (5, 24, 31), (1, 25, 64), (1, 33, 17)]
+
+
+@pytest.mark.parametrize("launch", ["0", "3"])
+@pytest.mark.parametrize("net", sorted(BLOBS))
+def test_bands_of_eight_rows_decode_exactly(net, launch, monkeypatch):
+    """Chosen by the rule and forced (the paper's network has no such kernel: the other one runs): the images exactly."""
+    from paper_2212_01185_amd import binding
+    monkeypatch.setenv("PCC_DECODE_VARIANT", launch)
+    codec = binding.Codec(BLOBS[net](0), 0)
+    rng = np.random.default_rng(11)
+    try:
+        for n, h, w in SIZES:
+            print("%s %dx%dx%d" % (net, n, h, w), flush=True)
+            imgs = torch.from_numpy(rng.integers(0, 256, (n, h, w, 3), dtype=np.uint8)).cuda()
+            stream = codec.pcc_encode(imgs)
+            assert torch.equal(codec.pcc_decode(stream, n, h, w), imgs)
+            out = torch.zeros_like(imgs)
+            assert torch.equal(codec.pcc_decode_static(stream, n, h, w, out), imgs)
+    finally:
+        codec.close()
+
+
+@pytest.mark.parametrize("launch", ["0", "3"])
+def test_static_scratch_too_small_for_twice_the_bands(launch, monkeypatch):
+    """270 bands of eight rows of 4096 pixels would need 8.4 MiB of the 8 MiB, the 135 bands of 16 rows fit: accepted as ever."""
+    from paper_2212_01185_amd import binding
+    monkeypatch.setenv("PCC_DECODE_VARIANT", launch)
+    h, w = 2160, 4096
+    assert binding.load().pcc_decode_static_scratch_bytes(1, h, w) <= 8 << 20 < 2 * 8 * 135 * w
+    imgs = torch.from_numpy(synth.make_image(5, synth.ImageSpec(w, h, 12, 8.0, 64.0))).cuda()[None]
+    codec = binding.Codec(synth.make_blob(0), 0)
+    try:
+        stream = codec.pcc_encode(imgs)
+        assert torch.equal(codec.pcc_decode_static(stream, 1, h, w, torch.zeros_like(imgs)), imgs)
+    finally:
+        codec.close()
