@@ -1177,12 +1177,18 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
     if constexpr (kBlocks < SLOTS && RUN_IDLE) idle();
 }
 
-template <int NKB>
+// ORDERED (scheduling only): the reads are issued in the order in which the MFMAs take them.  Left to itself the compiler issues
+// them in another, and the first MFMA waits for the last read.  us in 512x512, before and after: the paper's network 5,320 and
+// 5,265, diagonal 2,722 and 2,696, six layers 5,984 and 5,912, seven mixtures 6,222 and 6,180; 768x512 4,558 and 4,527.  With five
+// k-blocks as well 768x512 takes 4,565: those are left to the compiler.
+template <int NKB, bool ORDERED>
 __device__ __forceinline__ void dec_load_act(const uint8_t* __restrict__ act, int lane, u32x4_t (&in)[NKB][2]) {
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
         in[kb][0] = *reinterpret_cast<const u32x4_t*>(act + ((kb * 2 + 0) * 64 + lane) * 16);
+        if constexpr (ORDERED) __builtin_amdgcn_sched_barrier(0);
         in[kb][1] = *reinterpret_cast<const u32x4_t*>(act + ((kb * 2 + 1) * 64 + lane) * 16);
+        if constexpr (ORDERED) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -1248,7 +1254,7 @@ struct WaveNet {
             lds_barrier();
             clk.mark(kPhLayer0 + L);
             u32x4_t nxt[Net::kb(L + 1)][2];
-            dec_load_act<Net::kb(L + 1)>(out, lane, nxt);
+            dec_load_act<Net::kb(L + 1), !SHARED && Net::kb(L + 1) <= 4>(out, lane, nxt);
             // scheduling only: every read of the layer's input is issued before its first MFMA, so
             // the LDS latency is paid once per layer and not once per k-block.  With two workgroups per CU the other one
             // hides the latency, and the registers of 40 values are better spent otherwise (24 images 7.23 -> 7.06 ms).
