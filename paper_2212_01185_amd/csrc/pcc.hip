@@ -1406,7 +1406,7 @@ struct StepRole {
 
 // MINBLOCKS = 1: all registers to one workgroup per CU (lowest latency per step).  MINBLOCKS = 2: two
 // workgroups share a CU (some spills; a step takes Net::kSharedAlonePercent to Net::kSharedStepPercent of the time, so
-// this only pays for jobs of so many bands that the work per CU, not an image's chain of steps, sets the time: launch_decode).
+// this only pays for jobs of so many bands that the work per CU, not an image's chain of steps, sets the time: choose_decode).
 // ROWS = 16: 16 lanes to a pixel.  ROWS = 8 (half of a tile's columns are copies): 32 lanes, which share the mixture components
 // in two halves, and half the pixels to a wave, so that the searches, more than half of a step's instructions, have a fifth
 // fewer of them (437 -> 349 vector instructions with five components).

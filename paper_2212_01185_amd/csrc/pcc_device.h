@@ -78,7 +78,7 @@ struct NetWorkload {
     static constexpr int kEncodeThreads = 512;    // pixel kernel: threads of a workgroup
     static constexpr int kSharedCuLds = 6;
     // Time of a decode step with two workgroups per CU, in percent of a step with one, while the other workgroup waits and
-    // while both are busy (fitted to whole jobs; the host chooses between the two launches with them: launch_decode).
+    // while both are busy (fitted to whole jobs; the host chooses between the launches with them: choose_decode).
     static constexpr unsigned kSharedAlonePercent = 112, kSharedStepPercent = 138;
     // Bands of eight rows with 32 lanes to a pixel (decode_narrow_kernel): is there such a kernel, and its time for a single image in
     // percent of the time with bands of 16 rows, the hand-overs of twice as many bands included.  768x512: this network 4,675 ->
