@@ -1187,7 +1187,8 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
 // ORDERED (scheduling only): the reads are issued in the order in which the MFMAs take them.  Left to itself the compiler issues
 // them in another, and the first MFMA waits for the last read.  us in 512x512, before and after: the paper's network 5,320 and
 // 5,265, diagonal 2,722 and 2,696, six layers 5,984 and 5,912, seven mixtures 6,222 and 6,180; 768x512 4,558 and 4,527.  With five
-// k-blocks as well 768x512 takes 4,565: those are left to the compiler.
+// k-blocks as well 768x512 takes 4,565: those are left to the compiler.  With two workgroups per CU fewer registers are live at a time:
+// the paper's network spills 2 instead of 16 and 24 images of 768x512 take 7,360 us instead of 7,485, diagonal 6 for 25 and 5,050 for 5,140.
 template <int NKB, bool ORDERED>
 __device__ __forceinline__ void dec_load_act(const uint8_t* __restrict__ act, int lane, u32x4_t (&in)[NKB][2]) {
 #pragma unroll
@@ -1261,7 +1262,7 @@ struct WaveNet {
             lds_barrier();
             clk.mark(kPhLayer0 + L);
             u32x4_t nxt[Net::kb(L + 1)][2];
-            dec_load_act<Net::kb(L + 1), !SHARED && Net::kb(L + 1) <= 4>(out, lane, nxt);
+            dec_load_act<Net::kb(L + 1), Net::kb(L + 1) <= 4>(out, lane, nxt);
             // scheduling only: every read of the layer's input is issued before its first MFMA, so
             // the LDS latency is paid once per layer and not once per k-block.  With two workgroups per CU the other one
             // hides the latency, and the registers of 40 values are better spent otherwise (24 images 7.23 -> 7.06 ms).

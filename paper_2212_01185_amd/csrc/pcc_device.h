@@ -74,6 +74,8 @@ struct NetWorkload {
     //   six layers         12.14 (93)   11.19 (75)    11.27 (62)   10.39 (47)       8.86 (8)
     //   four layers        6.38 (11)    6.60 (0)      6.43 (0)     6.64 (0)         6.83 (0)
     //   64 filters         5.65 (0)     5.69 (0)      5.63 (0)     5.73 (0)         5.89 (0)
+    // (The paper's and diagonal before a layer's input was read in order, dec_load_act; since then first layer 7.41 and 5.18, head
+    // 7.37 and 5.40, first and head 7.37 (2) and 5.05 (6).)
     // (Seven mixtures: the first layer and the head do not fit a CU twice, `all` is the biases and the first layer.)
     static constexpr int kEncodeThreads = 512;    // pixel kernel: threads of a workgroup
     static constexpr int kSharedCuLds = 6;
