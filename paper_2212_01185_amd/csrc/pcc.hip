@@ -67,14 +67,14 @@ template <class Net>
 constexpr int encode_model_lds_bytes() {
     return encode_table_lds_off<Net>() + (encode_table_in_lds<Net>() ? Layout<Net>::kModelBytes - Layout<Net>::kLutOff : 0);
 }
-// pcc_encode_probs: pixels of a tile whose head outputs a wave stages in LDS at a time (eight, or as many as fit
-// beside the model image), and the bytes that takes for the workgroup.
-// 0: no room for a staging area; the head outputs are then stored value by value.
+// pcc_encode_probs: pixels whose head outputs a wave stages in LDS at a time, where there is room for that beside the model image.
+// 0: a lane stores its outputs from its registers, runs of 3 K floats.  Smaller stages cost more than they save, in passes of one LDS
+// round trip each: 1403x1021, us, with one pixel at a time, two and from the registers: six layers 462, 411, 405; two, four and from the
+// registers: seven mixtures 446, 388, 375.  With eight, staged and from the registers: 30-160-160-128-60 284 and 293, four layers 247 and 257,
+// five mixtures 356 and 361, the paper's network 330 and 338.
 template <class Net>
 constexpr int params_stage_pixels(int threads) {
-    for (int px = 8; px >= 1; px /= 2)
-        if (encode_model_lds_bytes<Net>() + kTakenBytes + (threads / 64) * px * Net::dim(Net::kLayers) * 4 <= kLdsBytes) return px;
-    return 0;
+    return encode_model_lds_bytes<Net>() + kTakenBytes + (threads / 64) * 8 * Net::dim(Net::kLayers) * 4 <= kLdsBytes ? 8 : 0;
 }
 template <class Net>
 constexpr int params_stage_bytes(int threads) { return (threads / 64) * params_stage_pixels<Net>(threads) * Net::dim(Net::kLayers) * 4; }
@@ -347,8 +347,8 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
             if (params_stage_pixels<Net>(THREADS) > 0 && ((uintptr_t)params & 15u) == 0) {
                 // The tile's head outputs are HEAD consecutive floats per pixel, 32 consecutive pixels: they go
                 // through a staging area of this wave in LDS, PX pixels at a time, and leave as
-                // 16-byte stores of consecutive lanes (stored straight from the registers, a lane's values lie
-                // 4 bytes here and 4 bytes there, 240 bytes apart from its neighbour's).  LDS takes a wave's
+                // 16-byte stores of consecutive lanes (stored straight from the registers, a lane's values are
+                // two runs of 3 K floats, HEAD floats apart from its neighbour's).  LDS takes a wave's
                 // instructions in order, so the reads see the writes of the same pass.  All reads of a pass before its
                 // stores, whose addresses are one base and constants: 2048x1365 490 -> 470 us (432 without any outputs; they
                 // are 670 MB).
