@@ -492,11 +492,15 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// (v << 1) | bit, in one instruction: the bit is the carry into v + v.
-__device__ __forceinline__ uint32_t shift_in(uint32_t v, bool bit) {
+// (v << 1) | bit, in one instruction: the bit is the carry into v + v.  The carry may be read only two wait states after
+// the compare that made it, and the compiler, which sees to that in its own instructions, does not look into this one.
+// So it takes `selected`, which has to be a value that a select on the same bit has made: the compiler puts the select
+// two wait states behind the compare, and this behind the select.
+// (Of the compiler's own making this takes two instructions, a select of 0 or 1 and a shift with an or.)
+__device__ __forceinline__ uint32_t shift_in(uint32_t v, bool bit, uint32_t selected) {
     const uint64_t carry = __ballot(bit);
     uint64_t out;
-    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(v), "=s"(out) : "s"(carry));
+    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(v), "=s"(out) : "s"(carry), "v"(selected));
     return v;
 }
 
@@ -699,9 +703,9 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
                     // serial chain
                     const bool emit = (xh >> 15) >= f;
                     my_out[n * kU + u] = xl;
-                    flags = shift_in(flags, emit);
                     xl = emit ? xh : xl;
                     xh = emit ? 0u : xh;
+                    flags = shift_in(flags, emit, xl);
                     rans_push(xl, xh, f, start, rf[n & 1][u]);
                 }
             }

@@ -20,7 +20,12 @@ for whatever the compiler lays out.
 
 A second check on the same assembly, for the decoder's flag that a band has given up: a wave sets it and every wave reads
 it in each step, and the waves leave their loops together only if a workgroup barrier lies between any write and any
-read.  A third: the decoder reads its table at LDS address 0, so it must have no static LDS in front of the dynamic array."""
+read.  A third: the decoder reads its table at LDS address 0, so it must have no static LDS in front of the dynamic array.
+
+A fourth, the same walk for scalar registers: a vector instruction that writes an SGPR or VCC (a compare, a carry, a lane
+read) may be followed by a vector instruction that reads it (as a condition, a carry or an operand) only some wait states
+later.  The compiler sees to that in its own code but not for instructions inside `asm`.  The number is again the one it
+leaves itself."""
 import functools
 import os
 import re
@@ -202,6 +207,99 @@ def test_no_mfma_result_is_touched_early_on_any_path():
     print("wait states the compiler leaves in straight-line code:", need)
     assert need.get("v_mfma_f32_16x16x32_bf16", 0) >= 4, need     # calibration cases exist for the shape the kernels use
     assert not found, "MFMA results touched too soon:\n" + "\n".join("%d of %d wait states: %s" % f for f in sorted(found)[:10])
+
+
+def _scalars(tok):
+    """Scalar registers named by one operand; VCC is 200 and 201."""
+    tok = tok.strip()
+    m = re.match(r"s\[(\d+):(\d+)\]$", tok)
+    if m:
+        return set(range(int(m.group(1)), int(m.group(2)) + 1))
+    m = re.match(r"s(\d+)$", tok)
+    if m:
+        return {int(m.group(1))}
+    return {"vcc": {200, 201}, "vcc_lo": {200}, "vcc_hi": {201}}.get(tok, set())
+
+
+def _scalar_access(ins):
+    """(scalar registers a vector-ALU instruction writes, reads); two empty sets for any other instruction."""
+    op, _, rest = ins.partition(" ")
+    if not op.startswith("v_") or op.startswith(("v_mfma", "v_nop")):
+        return set(), set()
+    operands = [o.split()[0] for o in rest.split(",") if o.split()]
+    # a destination in front; a second one, the carry or the scale's flag, behind it
+    second = re.match(r"v_(addc?_co|subb?(rev)?_co|div_scale|mad_[ui]64)_", op)
+    dests = operands[:2] if second else operands[:1]
+    writes = set().union(*map(_scalars, dests))
+    reads = set().union(*map(_scalars, operands[len(dests):]))
+    return writes, reads | ({200, 201} if op.startswith("v_div_fmas") else set())
+
+
+def early_scalar_reads(asm_text, needed=None):
+    """([(wait states, needed, description)] for every path on which a vector instruction reads a scalar register too
+    soon after a vector instruction has written it, the number needed).  That number is the smallest one the compiler
+    leaves where nothing but s_nop stands between the two."""
+    near = 5                                          # as far as a path is followed
+    pairs, left = [], []
+    for name, body, labels in _functions(asm_text.split("\n")):
+        access = [_scalar_access(ins) for ins in body]
+        for i, (writes, _) in enumerate(access):
+            if not writes:
+                continue
+            best, stack = {}, [(i + 1, 0, writes, True)]
+            while stack:
+                pc, st, live, only_nops = stack.pop()
+                while pc < len(body) and st < near and live:
+                    if best.get((pc, frozenset(live)), 1 << 30) <= st:
+                        break
+                    best[(pc, frozenset(live))] = st
+                    cur = body[pc]
+                    if access[pc][1] & live:
+                        if only_nops and st:
+                            left.append(st)
+                        pairs.append((st, "%s: %s ... %s" % (name[:70], body[i], cur)))
+                    live = live - access[pc][0]       # written anew: that write's own window
+                    if cur.startswith(("s_endpgm", "s_setpc", "s_swappc", "s_call")):
+                        break
+                    if cur.startswith(("s_branch", "s_cbranch")):
+                        stack.append((labels[cur.split()[-1]], st + 1, live, False))
+                        if cur.startswith("s_branch"):
+                            break
+                    only_nops = only_nops and cur.startswith("s_nop")
+                    st += _states(cur)
+                    pc += 1
+    if needed is None:
+        needed = min(left, default=0)
+    return [(st, needed, what) for st, what in pairs if st < needed], needed
+
+
+def test_scalar_scanner_finds_planted_cases():
+    def kernel(*body):
+        return "\n".join(["_Z6kernelv: ; @_Z6kernelv"] + ["\t" + i if i[0] != "." else i for i in body] + ["\ts_endpgm", ".Lfunc_end0:"])
+    compare, between = "v_cmp_gt_u32_sdwa s[6:7], v4, v145 src0_sel:DWORD src1_sel:WORD_1", "v_not_b32_sdwa v5, v145 dst_sel:DWORD"
+    shift = "v_addc_co_u32_e64 v152, s[20:21], v152, v152, s[6:7]"
+    assert [f[0] for f in early_scalar_reads(kernel(compare, shift), 2)[0]] == [0]
+    assert [f[0] for f in early_scalar_reads(kernel(compare, between, shift), 2)[0]] == [1]
+    assert not early_scalar_reads(kernel(compare, between, "v_mov_b32_e32 v1, v2", shift), 2)[0]
+    assert not early_scalar_reads(kernel(compare, "s_nop 1", shift), 2)[0]
+    # a carry out that nobody reads is no read; a register written anew starts again; VCC, implicit and named
+    assert not early_scalar_reads(kernel("v_cmp_lt_u32_e64 s[20:21], v1, v2", shift), 2)[0]
+    assert len(early_scalar_reads(kernel(compare, compare, shift), 2)[0]) == 1
+    assert early_scalar_reads(kernel("v_add_co_u32_e32 v0, vcc, v1, v2", "v_addc_co_u32_e32 v1, vcc, v3, v4, vcc"), 2)[0]
+    assert early_scalar_reads(kernel("v_div_scale_f32 v0, vcc, v1, v2, v1", "v_div_fmas_f32 v0, v1, v2, v3"), 2)[0]
+    assert early_scalar_reads(kernel("v_readfirstlane_b32 s6, v0", "v_add_u32_e32 v1, s6, v1"), 2)[0]
+    # over a branch and over a back-edge
+    assert early_scalar_reads(kernel(compare, "s_cbranch_scc1 .LBB0_1", "s_nop 3", ".LBB0_1:", shift), 2)[0]
+    assert early_scalar_reads(kernel(".LBB0_1:", shift, "s_nop 3", compare, "s_cbranch_scc1 .LBB0_1", "s_nop 3"), 2)[0]
+    # the number the compiler leaves
+    assert early_scalar_reads(kernel(compare, "s_nop 1", shift, compare, between, "s_nop 0", shift))[1] == 2
+
+
+@needs_hipcc
+def test_no_scalar_result_of_the_vector_alu_is_read_early_on_any_path():
+    found, needed = early_scalar_reads(_assembly())
+    assert needed >= 2, needed                        # calibration cases exist
+    assert not found, "%d scalar results read too soon:\n" % len(found) + "\n".join("%d of %d wait states: %s" % f for f in sorted(found)[:10])
 
 
 def _successors(body, labels):
