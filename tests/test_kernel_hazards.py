@@ -387,11 +387,22 @@ def test_flag_race_is_found_where_planted():
     assert flag_races(body, labels) == ({0}, {0})
 
 
+# The decoders: nine networks with one and two workgroups per unit, and three of them with bands of eight rows.
+DECODERS = {"decode_kernel": 18, "decode_narrow_kernel": 3}
+
+
+def _decoders(names):
+    found = [n for n in names if any(kind in n for kind in DECODERS)]
+    for kind, count in DECODERS.items():
+        assert sum(kind in n for n in found) == count, (kind, found)
+    return found
+
+
 @needs_hipcc
 def test_a_barrier_lies_between_writes_and_reads_of_the_decoders_flag():
-    kernels = [(name, body, labels) for name, body, labels in _functions(_assembly().split("\n")) if "decode_kernel" in name]
-    assert len(kernels) == 18                                       # nine networks, one and two workgroups per unit
-    for name, body, labels in kernels:
+    kernels = {name: (body, labels) for name, body, labels in _functions(_assembly().split("\n"))}
+    for name in _decoders(kernels):
+        body, labels = kernels[name]
         written, read = flag_races(body, labels)
         assert written and read and not written & read, "%s: written in %s, read in %s" % (name, written, read)
 
@@ -411,8 +422,8 @@ def static_lds(asm_text):
 @needs_hipcc
 def test_decoders_have_no_static_lds():
     sizes = static_lds(_assembly())
-    decoders = [k for k in sizes if "decode_kernel" in k]
-    assert len(decoders) == 18 and not any(sizes[k] for k in decoders), {k: sizes[k] for k in decoders}
+    decoders = _decoders(sizes)
+    assert not any(sizes[k] for k in decoders), {k: sizes[k] for k in decoders}
     assert any(sizes[k] for k in sizes if "rans_rows_kernel" in k)          # a kernel that has static LDS shows it here
 
 
