@@ -84,18 +84,21 @@ def _overflowing(dims, layer):
     return layers, plain
 
 
-NETS = {"workload": (synth.DEFAULT_DIMS, {}),
-        "paper": (synth.PAPER_DIMS, dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY)),
-        "more_filters": (synth.ablation_dims(3, 192, 5), dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY))}
+# network: layer widths, header, launches of its decoder (one and two workgroups per unit; 3: bands of eight rows)
+NETS = {"workload": (synth.DEFAULT_DIMS, {}, "123"),
+        "paper": (synth.PAPER_DIMS, dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY), "12"),
+        "more_filters": (synth.ablation_dims(3, 192, 5), dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY), "12"),
+        "more_mixtures": (synth.ablation_dims(5, 128, 5), dict(k=5, nbhd=12, delay=3, act=synth.ACT_LEAKY), "3"),
+        "most_mixtures": (synth.ablation_dims(7, 128, 5), dict(k=7, nbhd=12, delay=3, act=synth.ACT_LEAKY), "3")}
 
 
 @pytest.mark.parametrize("net", sorted(NETS))
 def test_roundtrip_where_activations_pass_the_range_of_bf16(net, monkeypatch):
     """An activation that rounds to infinity has different lo parts in the two forms (the matrix core multiplies it with zero
     for its three neighbours), and the pixel is NaN from the next layer on: the same NaN in both, whose products are all
-    0xFFC00000.  Both decoders must return the image."""
+    0xFFC00000.  All decoders must return the image."""
     from paper_2212_01185_amd import binding
-    dims, header = NETS[net]
+    dims, header, launches = NETS[net]
     rng = np.random.default_rng(91)
     imgs = torch.from_numpy(rng.integers(0, 256, (2, 37, 50, 3), dtype=np.uint8)).cuda()
     for layer in range(len(dims) - 2):
@@ -103,7 +106,7 @@ def test_roundtrip_where_activations_pass_the_range_of_bf16(net, monkeypatch):
         c = binding.Codec(plain, 0)
         want = c.pcc_encode_probs(imgs)[0]
         c.close()
-        for launch in ("1", "2"):
+        for launch in launches:
             monkeypatch.setenv("PCC_DECODE_VARIANT", launch)
             c = binding.Codec(layers, 0)
             try:

@@ -9,6 +9,9 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+NARROW = {"workload": (synth.DEFAULT_DIMS, {})}       # the networks that have such a kernel
+NARROW.update({name: (synth.ablation_dims(*synth.ABLATION_SHAPES[name]), dict(k=synth.ABLATION_SHAPES[name][0], nbhd=12, delay=3, act=synth.ACT_LEAKY))
+               for name in ("more_mixtures", "most_mixtures")})
 BLOBS = {"workload": synth.make_blob, "paper": synth.make_paper_blob}
 BLOBS.update({name: lambda seed, name=name: synth.make_ablation_blob(*synth.ABLATION_SHAPES[name], seed=seed) for name in ("more_mixtures", "most_mixtures")})
 SIZES = [(1, 1, 1), (2, 7, 5), (1, 8, 33), (3, 9, 2), (1, 15, 40), (1, 16, 3), (2, 17, 18), (1, 23, 1), (5, 24, 31), (1, 25, 64), (1, 33, 17)]
@@ -48,3 +51,51 @@ def test_static_scratch_too_small_for_twice_the_bands(launch, monkeypatch):
         assert torch.equal(codec.pcc_decode_static(stream, 1, h, w, torch.zeros_like(imgs)), imgs)
     finally:
         codec.close()
+
+
+@pytest.mark.parametrize("net", sorted(NARROW))
+def test_a_band_that_gives_up_ends_the_call(net, monkeypatch):
+    """With the limit of a band's polls set to zero from the host the call returns an error, and the next one works: for jobs of
+    more bands than the chip holds at once and of a few, with the flag read in B's search (the workload's network) and in the next
+    step's head (no layer leaves a wave spare time)."""
+    from paper_2212_01185_amd import binding
+    monkeypatch.setenv("PCC_DECODE_VARIANT", "3")
+    good = binding.Codec(BLOBS[net](0), 0)
+    monkeypatch.setenv("PCC_DECODE_SPIN_LIMIT", "0")
+    hasty = binding.Codec(BLOBS[net](0), 0)
+    try:
+        imgs = torch.from_numpy(np.random.default_rng(79).integers(0, 256, (120, 40, 24, 3), dtype=np.uint8)).cuda()       # 600 bands
+        for n in (120, 1):
+            print("%s: decode without patience, %d images" % (net, n), flush=True)
+            stream = good.pcc_encode(imgs[:n])
+            for decode in (hasty.pcc_decode, lambda *a: hasty.pcc_decode_static(*a, torch.zeros_like(imgs[:n]))):
+                with pytest.raises(binding.PccError) as e:
+                    decode(stream, n, 40, 24)
+                assert e.value.code == binding.PCC_E_INTERNAL
+            assert torch.equal(good.pcc_decode(stream, n, 40, 24), imgs[:n])
+    finally:
+        good.close()
+        hasty.close()
+
+
+@pytest.mark.parametrize("net", sorted(NARROW))
+def test_mixture_sums_that_are_not_numbers(net, monkeypatch):
+    """A logit that is infinite or NaN makes the softmax and with it a channel's mixture sums NaN, which count as 1.  The second
+    half of a pixel's lanes goes on with the first half's sum: logits of either half, in each channel."""
+    from paper_2212_01185_amd import binding
+    monkeypatch.setenv("PCC_DECODE_VARIANT", "3")
+    dims, header = NARROW[net]
+    k = header.get("k", 5)
+    imgs = torch.from_numpy(np.random.default_rng(83).integers(0, 256, (2, 19, 24, 3), dtype=np.uint8)).cuda()
+    for channel, component, value in [(0, 0, np.inf), (0, k - 1, np.nan), (1, k - 1, np.inf), (2, 0, np.nan), (2, k - 1, np.inf)]:
+        layers = [[w, b.copy()] for w, b in synth.make_weights(0, dims)]
+        layers[-1][1][3 * k * channel + component] = value
+        codec = binding.Codec(synth.pack_blob(layers, **header), 0)
+        print("%s: channel %d, component %d: %s" % (net, channel, component, value), flush=True)
+        try:
+            params, _ = codec.pcc_encode_probs(imgs)
+            assert not torch.isfinite(params[..., 3 * k * channel + component]).any()
+            stream = codec.pcc_encode(imgs)
+            assert torch.equal(codec.pcc_decode(stream, 2, 19, 24), imgs)
+        finally:
+            codec.close()
