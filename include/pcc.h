@@ -85,8 +85,7 @@ typedef struct pcc_ctx pcc_ctx;
 /* Parse and pack the weight blob (host pointer) for device `hip_device`.
  * On success *out owns device memory until pcc_destroy.
  * Reads these environment variables, which exist for tests and measurements and
- * never change a result: PCC_ENCODE_VARIANT (0, 1: 256 or 512 threads to a
- * workgroup of the pixel kernel), PCC_ENCODE_OVERLAP (0: the row coder
+ * never change a result: PCC_ENCODE_OVERLAP (0: the row coder
  * always runs after the pixel kernel), PCC_RANS_PATIENCE (polls before a row
  * coder running beside the pixel kernel stands down), PCC_DECODE_VARIANT (1, 2:
  * decoder workgroups per compute unit; 3: one, with bands of eight rows where

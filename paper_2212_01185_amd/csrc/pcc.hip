@@ -73,11 +73,11 @@ constexpr int encode_model_lds_bytes() {
 // registers: seven mixtures 446, 388, 375.  With eight, staged and from the registers: 30-160-160-128-60 284 and 293, four layers 247 and 257,
 // five mixtures 356 and 361, the paper's network 330 and 338.
 template <class Net>
-constexpr int params_stage_pixels(int threads) {
-    return encode_model_lds_bytes<Net>() + kTakenBytes + (threads / 64) * 8 * Net::dim(Net::kLayers) * 4 <= kLdsBytes ? 8 : 0;
+constexpr int params_stage_pixels() {
+    return encode_model_lds_bytes<Net>() + kTakenBytes + (Net::kEncodeThreads / 64) * 8 * Net::dim(Net::kLayers) * 4 <= kLdsBytes ? 8 : 0;
 }
 template <class Net>
-constexpr int params_stage_bytes(int threads) { return (threads / 64) * params_stage_pixels<Net>(threads) * Net::dim(Net::kLayers) * 4; }
+constexpr int params_stage_bytes() { return (Net::kEncodeThreads / 64) * params_stage_pixels<Net>() * Net::dim(Net::kLayers) * 4; }
 
 // Status words in device memory, one block for the decoder, one for the encoder, one that nobody reads (pcc_encode_probs,
 // which does not wait for its kernel).  The decoder's is cleared on its stream before each call.
@@ -168,8 +168,8 @@ __device__ __forceinline__ void both_halves(uint32_t v, uint32_t& of_half0, uint
 // Two waves per SIMD: one does not hide its own gather and mixtures (1,562 us against 1,246).
 // Pixel kernel, 24 images of 768x512, predictor: 1,455 -> 1,180 us; paper's network 1,854 -> 1,624; 4096x2160 1,578 -> 1,348.
 // ---------------------------------------------------------------------------
-template <class Net, int THREADS>
-__global__ void __launch_bounds__(THREADS)
+template <class Net>
+__global__ void __launch_bounds__(Net::kEncodeThreads)
 encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img, int n, int H, int W,
               uint32_t* __restrict__ sf, float* __restrict__ params, float* __restrict__ bits, int* status,
               uint64_t* sf_tagged, uint32_t epoch, uint32_t strip_begin, uint32_t strip_count) {
@@ -179,7 +179,7 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
     extern __shared__ __align__(16) uint8_t lds[];
     uint32_t* taken = reinterpret_cast<uint32_t*>(lds + encode_model_lds_bytes<Net>());     // items of the workgroup that have been taken
     constexpr int RESIDENT = encode_resident_layers<Net>();
-    constexpr uint32_t nwaves = THREADS / 64;
+    constexpr uint32_t nwaves = Net::kEncodeThreads / 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar: the item's row and strip are scalars too
     const int g = lane >> 4, nl = lane & 15;      // the network's lane: inputs of k-slot group g of pixel nl of a tile
@@ -340,11 +340,11 @@ encode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ img
         if (params != nullptr) {
             // A pixel's outputs are R's, G's, B's parameters (3 K each), alphas, betas, gammas (K each): half 0 holds the first
             // and third group of 3 K, half 1 the second and fourth.
-            constexpr int PX = params_stage_pixels<Net>(THREADS) > 0 ? params_stage_pixels<Net>(THREADS) : 1;
+            constexpr int PX = params_stage_pixels<Net>() > 0 ? params_stage_pixels<Net>() : 1;
             float second[3 * K];
 #pragma unroll
             for (int i = 0; i < 3 * K; ++i) second[i] = h == 0 ? item_b[i] : i < K ? head[3 * K + i] : item_b[2 * K + i];
-            if (params_stage_pixels<Net>(THREADS) > 0 && ((uintptr_t)params & 15u) == 0) {
+            if (params_stage_pixels<Net>() > 0 && ((uintptr_t)params & 15u) == 0) {
                 // The tile's head outputs are HEAD consecutive floats per pixel, 32 consecutive pixels: they go
                 // through a staging area of this wave in LDS, PX pixels at a time, and leave as
                 // 16-byte stores of consecutive lanes (stored straight from the registers, a lane's values are
@@ -1506,7 +1506,6 @@ struct pcc_ctx {
     int num_cus = 0;
     uint32_t* d_static_scratch = nullptr;   // this device's copy of the static scratch array (pcc_decode_static)
     uint32_t dist = 0;             // written to / checked against stream header word 6
-    int encode_threads = 512;       // of a workgroup of the pixel kernel
     uint32_t spin_limit = 1u << 22;      // polls of a band for one pixel of the band above (seconds) before the call fails (PCC_DECODE_SPIN_LIMIT, for tests)
     int decode_variant = 0;              // 0: chosen per job; 1: one workgroup per CU; 2: two; 3: one, bands of eight rows where the network has them (PCC_DECODE_VARIANT, for measurements)
     // the row coder of a small job runs beside the pixel kernel, on a stream of its own
@@ -1733,13 +1732,11 @@ int pack_model(const uint8_t* p, size_t blob_bytes, uint32_t dist, std::vector<u
 
 template <class Net>
 bool set_kernel_attributes() {
-    constexpr int enc = encode_model_lds_bytes<Net>() + kTakenBytes + std::max(params_stage_bytes<Net>(256), params_stage_bytes<Net>(512)), dec = DecLds<Net>::kBytes;
+    constexpr int enc = encode_model_lds_bytes<Net>() + kTakenBytes + params_stage_bytes<Net>(), dec = DecLds<Net>::kBytes;
     static_assert(enc <= kLdsBytes && dec <= kLdsBytes && DecLds<Net>::kBytesShared <= kLdsBytes,
                   "the network does not fit a compute unit's LDS");
     bool ok = true;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 256>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, enc) == hipSuccess;
-    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net, 512>),
+    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, enc) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<Net, 1>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, dec) == hipSuccess;
@@ -1773,15 +1770,11 @@ uint32_t encode_blocks(const pcc_ctx* ctx, int n, int H, uint32_t strips, uint32
 template <class Net>
 int launch_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint32_t* sf, float* params, float* bits,
                   uint64_t* sf_tagged, uint32_t reserve_cus, uint32_t strip_begin, uint32_t strip_count, hipStream_t st) {
-    const int lds = encode_model_lds_bytes<Net>() + kTakenBytes + (params != nullptr ? params_stage_bytes<Net>(ctx->encode_threads) : 0);
+    const int lds = encode_model_lds_bytes<Net>() + kTakenBytes + (params != nullptr ? params_stage_bytes<Net>() : 0);
     const uint32_t blocks = encode_blocks(ctx, n, H, strip_count, reserve_cus);
     const uint8_t* model = ctx->d_model + Layout<Net>::kModelBytes;
-    if (ctx->encode_threads == 256)
-        hipLaunchKernelGGL((encode_kernel<Net, 256>), dim3(blocks), dim3(256), lds, st, model, d_img, n, H, W,
-                           sf, params, bits, ctx->status(params != nullptr ? kBlockProbs : kBlockEncode), sf_tagged, ctx->epoch, strip_begin, strip_count);
-    else
-        hipLaunchKernelGGL((encode_kernel<Net, 512>), dim3(blocks), dim3(512), lds, st, model, d_img, n, H, W,
-                           sf, params, bits, ctx->status(params != nullptr ? kBlockProbs : kBlockEncode), sf_tagged, ctx->epoch, strip_begin, strip_count);
+    hipLaunchKernelGGL((encode_kernel<Net>), dim3(blocks), dim3(Net::kEncodeThreads), lds, st, model, d_img, n, H, W,
+                       sf, params, bits, ctx->status(params != nullptr ? kBlockProbs : kBlockEncode), sf_tagged, ctx->epoch, strip_begin, strip_count);
     return hipGetLastError() == hipSuccess ? PCC_OK : PCC_E_HIP;
 }
 
@@ -1949,11 +1942,6 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
     }
     ok = ok && hipMemcpy(ctx->d_model, image.data(), image.size(), hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && with_net(net, [](auto tag) { return set_kernel_attributes<decltype(tag)>(); });
-    ctx->encode_threads = with_net(net, [](auto tag) { return decltype(tag)::kEncodeThreads; });
-    if (const char* e = getenv("PCC_ENCODE_VARIANT")) {
-        const int v = atoi(e);
-        if (v >= 0 && v < 2) ctx->encode_threads = v == 0 ? 256 : 512;
-    }
     // limits from the environment: negative values are taken as zero (no patience), never as huge unsigned ones
     auto env_limit = [](const char* e) { const long v = atol(e); return (uint32_t)std::min<long>(std::max<long>(v, 0), 0x7FFFFFFFl); };
     if (const char* e = getenv("PCC_DECODE_SPIN_LIMIT")) ctx->spin_limit = env_limit(e);
