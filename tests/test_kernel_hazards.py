@@ -429,15 +429,34 @@ def test_decoders_have_no_static_lds():
 
 # Vector registers that the decoder with two workgroups per compute unit keeps in scratch memory (256 per lane are too few
 # for a wave's weight slices): the copies of weights in LDS are chosen with these counts in view, and a change to the step
-# that raises one calls for choosing them again.
-SPILLED_AT_MOST = {"11NetWorkload": 29, "8NetPaper": 16, "11NetDiagonal": 25, "11NetAblationILi5ELi128ELi5EE": 19,
+# that raises one calls for choosing them again.  They are what the build has: the gain of reading a layer's input in order
+# (24 images with the paper's network 7.49 -> 7.36 ms) was that 2 are left of 16 and 6 of 25.
+SPILLED_AT_MOST = {"11NetWorkload": 29, "8NetPaper": 2, "11NetDiagonal": 6, "11NetAblationILi5ELi128ELi5EE": 19,
                    "11NetAblationILi7ELi128ELi5EE": 44, "11NetAblationILi3ELi128ELi6EE": 8, "11NetAblationILi3ELi128ELi4EE": 0,
                    "11NetAblationILi3ELi64ELi5EE": 0}
 
 
+def _spilled():
+    return {k: int(n) for k, n in re.findall(r"\.name:\s+(\S+)\n(?:(?!\.name:).)*?\.vgpr_spill_count: (\d+)", _assembly(), flags=re.S)}
+
+
 @needs_hipcc
 def test_spilled_registers_of_the_shared_decoder():
-    spilled = dict(re.findall(r"\.name:\s+(\S+)\n(?:(?!\.name:).)*?\.vgpr_spill_count: (\d+)", _assembly(), flags=re.S))
+    spilled = _spilled()
     for net, most in SPILLED_AT_MOST.items():
-        got = [int(n) for k, n in spilled.items() if "decode_kernelINS_%sELi2E" % net in k]
+        got = [n for k, n in spilled.items() if "decode_kernelINS_%sELi2E" % net in k]
         assert len(got) == 1 and got[0] <= most, (net, got, most)
+
+
+@needs_hipcc
+def test_no_other_kernel_spills_registers():
+    """The decoder with 192 filters and two workgroups per unit, which no rule chooses, aside.  The row coder that runs by itself
+    keeps one register in scratch, which it stores ahead of its rounds and reads again behind them."""
+    spilled = {k: n for k, n in _spilled().items() if not re.search(r"decode_kernelINS_\w+ELi2E", k)}
+    assert spilled and sum("encode_kernel" in k for k in spilled) == 9 and len(_decoders(_spilled())) == 21
+    coder = [k for k in spilled if "rans_rows_kernelILb0E" in k]
+    assert len(coder) == 1 and spilled.pop(coder[0]) <= 1
+    assert not any(spilled.values()), {k: n for k, n in spilled.items() if n}
+    (body, labels), = [(b, l) for name, b, l in _functions(_assembly().split("\n")) if name == coder[0]]
+    rounds = [passed for _, passed in _barrier_loops(body, labels)]
+    assert rounds and not any(body[i].startswith("scratch_") for passed in rounds for i in passed)
