@@ -5,11 +5,12 @@
 // neighbourhood" and "Cq(e)" is therefore written once, here, and compiled
 // with floating-point contraction off: the same inputs give the same bits in
 // both kernels.  They do so by the same instructions but for the split of an
-// activation into hi + lo, which has two forms (act_split_bf16 on the vector
-// ALU, act_split4_bf16 with the subtraction on the matrix core) and is chosen
-// per network and kernel: both are exact, and a test compares their bits.
+// activation into hi + lo, which has three forms: act_split_bf16 on the vector
+// ALU and act_split4_bf16 with the subtraction on the matrix core, of which the
+// decoder has one per network and launch, and EncoderNet's, which is the second
+// in pieces.  All are exact, and a test compares their bits.
 // Where an activation rounds to infinity their lo parts differ, but the pixel
-// is NaN from the next layer on in either form, and MFMA has one NaN
+// is NaN from the next layer on in each form, and MFMA has one NaN
 // (0xFFC00000) for every product with a NaN, 0 x inf or inf - inf in it.
 // An MFMA output element depends only on its A row, its B column and the
 // order of the k blocks, all of which are fixed below, so it does not matter
@@ -341,7 +342,7 @@ __device__ __forceinline__ float activation(float a) {
 
 typedef short bf16x4_bits_t __attribute__((ext_vector_type(4)));
 
-// This lane's row of minus the 4x4 identity (rows repeat every four lanes), as bf16: the A operand of act_split4_bf16.
+// This lane's row of minus the 4x4 identity (rows repeat every four lanes), as bf16: the A operand of the split's subtraction.
 __device__ __forceinline__ bf16x4_bits_t minus_identity(int lane) {
     const uint32_t one = 0xBF80u;                                    // -1
     u32x2_t v = {(lane & 2) ? 0u : ((lane & 1) ? one << 16 : one), (lane & 2) ? ((lane & 1) ? one << 16 : one) : 0u};

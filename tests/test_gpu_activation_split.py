@@ -1,5 +1,6 @@
-"""Encoder and decoder split activations by two forms, on the matrix core and by the vector ALU, which differ from network to
-network and from launch to launch: both must give the same bits, or a stream could not be decoded.  Needs an MI355X."""
+"""The decoder splits activations by two forms, on the matrix core and by the vector ALU, which differ from network to
+network and from launch to launch, the encoder by a third, in pieces between its MFMAs: all must give the same bits, or a
+stream could not be decoded.  Needs an MI355X."""
 import ctypes as C
 import os
 
@@ -13,6 +14,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 LIB = os.path.join(os.path.dirname(os.path.abspath(__file__)), "device_checks", "libact_split_check.so")
+FORMS = 6                                     # of act_split_check: matrix core, vector ALU, the encoder's four schedules
 LARGEST_BF16 = np.uint32(0x7F7F7FFF)          # the largest float whose nearest bf16 is finite
 
 
@@ -41,6 +43,7 @@ def _values():
 
 @pytest.mark.parametrize("leaky", [False, True])
 def test_both_forms_of_the_split_give_the_same_bits(leaky):
+    """The decoder's two forms, and the encoder's pieces in each of their four schedules."""
     if not os.path.exists(LIB):
         import __graft_entry__
         __graft_entry__.build_device_checks()
@@ -48,11 +51,12 @@ def test_both_forms_of_the_split_give_the_same_bits(leaky):
     lib.act_split_check.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.c_void_p, C.c_void_p]
     v = _values()
     d = torch.from_numpy(v).cuda()
-    out = torch.zeros((len(v), 8), dtype=torch.int32, device="cuda")
+    out = torch.zeros((len(v), FORMS * 4), dtype=torch.int32, device="cuda")
     rc = lib.act_split_check(d.data_ptr(), len(v), int(leaky), out.data_ptr(), torch.cuda.current_stream().cuda_stream)
     assert rc == 0
-    got = out.cpu().numpy().view(np.uint32).reshape(-1, 2, 4)
-    np.testing.assert_array_equal(got[:, 0], got[:, 1])
+    got = out.cpu().numpy().view(np.uint32).reshape(-1, FORMS, 4)
+    for form in range(1, FORMS):
+        np.testing.assert_array_equal(got[:, 0], got[:, form], err_msg="form %d" % form)
     # and they are what the split is defined as: hi the nearest bf16 of the activation, lo of what hi leaves
     act = np.where(v > 0, v, (np.float32(0.01) * v if leaky else np.float32(0))).astype(np.float32)
     hi = _bf16(act)
