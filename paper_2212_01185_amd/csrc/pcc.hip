@@ -4,8 +4,8 @@
 //   encode_kernel      gather + network (MFMA) + mixture -> (start,freq) of the
 //                      true sub-pixels, all pixels in parallel, the rows' right
 //                      ends first
-//   rans_rows_kernel   one lane per image row: push the row's symbols last to
-//                      first into a per-row slab, written backwards; for a small
+//   rans_rows_kernel   two lanes per image row, one per coder state: push the row's
+//                      symbols last to first into a per-row slab, written backwards; for a small
 //                      job it runs beside encode_kernel, taking the symbols as
 //                      they appear
 //   compact_kernel     slabs -> contiguous stream, with header and offsets
@@ -466,9 +466,12 @@ constexpr int kRansThreads = 256;
 constexpr uint32_t kRansBesideMaxGroups = 96;      // row-coder workgroups that may run beside the pixel kernel
 constexpr uint32_t kXcds = 8;
 constexpr uint32_t kRansPatience = 2048;            // polls for one symbol before a row coder beside the pixel kernel stands down (a few ms)
-// Rows at which the row coder of an image takes as long as the pixel kernel with the whole chip (both times are
-// proportional to the width; measured with the 30-160-160-128-60 network, 768x512 to 4096x2160): decides how much of
-// a tall image the pixel kernel does before the row coder joins it.
+// Decides how much of a tall image the pixel kernel does before the row coder joins it: the share of its strips that is left for
+// that is 1.1 times this over the rows.  (Alone, the row coder takes as long as the pixel kernel with the whole chip at
+// some 390 rows: 55 us at any number of rows of 768 pixels against 73 at 512 rows.  Beside each other both are slower.)  Whole calls, us, with
+// 300, 400, 500, 600 and 700: 2048x1365 524, 501, 488, 491, 491; 4096x2160 1,475, 1,437, 1,401, 1,422, 1,430; 800x640 154, 142,
+// 141, 143, 129 (no split any more); nine shapes from 800x640 on, with the paper's network too, take 4.5, 1.8, 1.2, 2.3 and 1.7 % longer
+// than with the best of the five on average.
 constexpr uint32_t kRansBalanceRows = 600;
 // Padding symbol (start 0, frequency 2^16): pushing it leaves the state unchanged
 // and never renormalises, so every chunk can be coded as a full one.
@@ -879,10 +882,11 @@ untag_kernel(const uint64_t* __restrict__ tagged, size_t count, uint32_t* __rest
 // ---------------------------------------------------------------------------
 // wavefront decode
 //
-// One workgroup of 4 waves owns a band of 16 image rows; step t decodes pixel
+// One workgroup of 4 waves owns a band of 16 image rows (or eight, with twice as
+// many lanes to a pixel, see decode_narrow_kernel); step t decodes pixel
 // (r, t - delay * r) of each row (delay = right reach of the neighbourhood + 1).
 // Per step:
-//   network   the 16 pixels form one MFMA tile; each wave computes a quarter
+//   network   the pixels form one MFMA tile of 16; each wave computes a quarter
 //             of every layer's out-blocks with its weight slices held in
 //             registers for the whole kernel, and the layers meet in LDS
 //   search    16 lanes per pixel find the symbol with two 16-way sweeps of
@@ -1040,7 +1044,7 @@ struct DecLds {
     static_assert(Net::kReach1 <= Net::kDelay - 1 && Net::kReach2 <= 2 * Net::kDelay - 1, "schedule is not causal");
 };
 
-// rANS reader of one row, replicated in the 16 lanes of the pixel's group.  A pixel consumes at most three of the
+// rANS reader of one row, replicated in the pixel's lanes (16, or 32 with bands of eight rows).  A pixel consumes at most three of the
 // row's 32-bit words; the next three, w[0..2], are requested at the end of a step's bookkeeping (settle, in
 // decode_kernel) and wanted a third of a step later, so a renormalisation never waits for memory.
 struct RowReader {
@@ -1120,7 +1124,7 @@ struct WaveLayer {
 };
 
 // One hidden layer on this wave's out-blocks.  Same arithmetic per output element
-// as hidden_layer<> in pcc_device.h: bias, then k-blocks in order, each hi then
+// as EncoderNet::layers in pcc_device.h: bias, then k-blocks in order, each hi then
 // lo; activation; split into hi + lo.  The out-blocks are taken one after the
 // other (an accumulation chain of MFMAs issues back to back at full rate).
 // In a layer's last round some waves may have no block (OWNS_LAST is false): such a wave skips the round and calls
@@ -2109,8 +2113,7 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         // An image of few rows: the row coder follows the pixel kernel through the whole image.  A tall image: the
         // pixel kernel is the longer one; it does the first strips with the whole chip, and the row coder joins it
         // (an event; the launch gap does not matter at this size) for a last part sized so that both end together.
-        // The row coder takes about as long as the pixel kernel at kRansBalanceRows rows, both in proportion to the
-        // width.
+        // Both times are in proportion to the width, the pixel kernel's to the rows as well.
         //
         // The pixel kernel is queued first.  Two streams may share one of the process's few hardware queues and then run
         // their kernels in the order in which they were queued: a row coder in front of the pixel kernel that it waits

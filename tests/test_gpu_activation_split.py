@@ -98,7 +98,7 @@ NETS = {"workload": (synth.DEFAULT_DIMS, {}, "123"),
 
 @pytest.mark.parametrize("net", sorted(NETS))
 def test_roundtrip_where_activations_pass_the_range_of_bf16(net, monkeypatch):
-    """An activation that rounds to infinity has different lo parts in the two forms (the matrix core multiplies it with zero
+    """An activation that rounds to infinity has different lo parts in the forms (the matrix core multiplies it with zero
     for its three neighbours), and the pixel is NaN from the next layer on: the same NaN in both, whose products are all
     0xFFC00000.  All decoders must return the image."""
     from paper_2212_01185_amd import binding
