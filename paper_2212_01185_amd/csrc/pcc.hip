@@ -1564,14 +1564,27 @@ int ensure_workspace(pcc_ctx* ctx, size_t bytes) {
     return PCC_OK;
 }
 
-int ensure_tagged(pcc_ctx* ctx, size_t count) {
+// Zeros in all of d_tagged, waited for: neither the caller's stream, where the pixel kernel writes it, nor the context's, where the
+// row coder reads it, is ordered after the null stream, whose hipMemset returns before it has begun.  A late one wiped
+// symbols that had been written, and until then a row coder could find those of a freed context with its own epoch.
+int clear_tagged(pcc_ctx* ctx, hipStream_t st) {
+    if (hipMemsetAsync(ctx->d_tagged, 0, ctx->tagged_count * sizeof(uint64_t), st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+        (void)hipGetLastError();
+        return PCC_E_HIP;
+    }
+    return PCC_OK;
+}
+
+// `st` is idle.
+int ensure_tagged(pcc_ctx* ctx, size_t count, hipStream_t st) {
     if (count <= ctx->tagged_count) return PCC_OK;
     if (ctx->d_tagged) { (void)hipFree(ctx->d_tagged); ctx->d_tagged = nullptr; ctx->tagged_count = 0; }
     const size_t want = count + count / 8 + 512;
     if (hipMalloc((void**)&ctx->d_tagged, want * sizeof(uint64_t)) != hipSuccess) { (void)hipGetLastError(); return PCC_E_HIP; }
-    if (hipMemset(ctx->d_tagged, 0, want * sizeof(uint64_t)) != hipSuccess) { (void)hipGetLastError(); return PCC_E_HIP; }
     ctx->tagged_count = want;
-    return PCC_OK;
+    const int rc = clear_tagged(ctx, st);
+    if (rc != PCC_OK) ctx->tagged_count = 0;
+    return rc;
 }
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -2042,10 +2055,11 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         if (busy != hipSuccess) { (void)hipGetLastError(); beside = false; }
     }
     if (beside) {
-        rc = ensure_tagged(ctx, (size_t)P * 3);
+        rc = ensure_tagged(ctx, (size_t)P * 3, st);
         if (rc != PCC_OK) return rc;
         if (++ctx->epoch == 0) {      // wrapped: the words of old launches would pass for new ones
-            if (hipMemset(ctx->d_tagged, 0, ctx->tagged_count * sizeof(uint64_t)) != hipSuccess) return PCC_E_HIP;
+            rc = clear_tagged(ctx, st);
+            if (rc != PCC_OK) { --ctx->epoch; return rc; }
             ctx->epoch = 1;
         }
     }

@@ -51,3 +51,27 @@ def test_no_encode_waits_out_the_row_coders_patience(blob, monkeypatch):
     finally:
         for c in codecs:
             c.close()
+
+
+def test_a_busy_null_stream_does_not_matter(blob):
+    """A codec's first encode clears the buffer through which the row coder gets its symbols.  On the null stream, which other
+    streams do not wait for, the clearing came behind whatever was queued there: after the pixel kernel, whose symbols it wiped."""
+    from paper_2212_01185_amd import binding
+    imgs = torch.from_numpy(np.random.default_rng(96).integers(0, 256, (1, 128, 128, 3), dtype=np.uint8)).cuda()
+    known = binding.Codec(blob, 0)
+    want = known.pcc_encode(imgs).clone()
+    intervals = known.pcc_copy_intervals(1, 128, 128)
+    known.close()
+    out = torch.empty(binding.pcc_stream_bound(1, 128, 128), dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        codec, s = binding.Codec(blob, 0), torch.cuda.Stream()
+        try:
+            torch.cuda.synchronize()
+            torch.cuda._sleep(100_000_000)           # some 40 ms
+            with torch.cuda.stream(s):
+                got = codec.pcc_encode(imgs, out=out)
+            torch.cuda.synchronize()
+            assert torch.equal(got, want)
+            assert torch.equal(codec.pcc_copy_intervals(1, 128, 128), intervals)
+        finally:
+            codec.close()
