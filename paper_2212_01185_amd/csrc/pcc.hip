@@ -22,6 +22,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <new>
 #include <type_traits>
@@ -1803,6 +1804,19 @@ int launch_encode_any(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, u
     });
 }
 
+// A decode that is running, in any context of the process; both entry points return when theirs is done.
+struct RunningDecode {
+    std::atomic<int>& running;
+    const int sharers;                            // that run on this GPU at this one's begin, itself included
+    static std::atomic<int>& on(int device) {     // (pcc_create takes no other devices: static_scratch)
+        static std::atomic<int> count[kMaxDevices];
+        return count[device];
+    }
+    explicit RunningDecode(int device) : running(on(device)), sharers(running.fetch_add(1, std::memory_order_relaxed) + 1) {}
+    ~RunningDecode() { running.fetch_sub(1, std::memory_order_relaxed); }
+    RunningDecode(const RunningDecode&) = delete;
+};
+
 // How a job is decoded: the kernel, its bands to an image and its workgroups.
 struct DecodeLaunch {
     enum { kOne = 1, kTwo = 2, kNarrow = 3 } kernel;       // one or two workgroups per compute unit; one, bands of eight rows
@@ -1813,8 +1827,9 @@ struct DecodeLaunch {
 size_t mailbox_bytes(int n, int nbands, int W) { return align_up((size_t)n * nbands * 2 * (size_t)W * 4, 256); }
 
 // most_bytes: what there is for the mailbox, if that is limited (bands of eight rows need twice as much of it)
+// sharers: decodes that run on the GPU, this one included
 template <class Net>
-DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_bytes) {
+DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_bytes, int sharers) {
     const int nbands = (H + kBandRows - 1) / kBandRows, narrow_bands = (H + kNarrowRows - 1) / kNarrowRows;
     const uint64_t bands = (uint64_t)n * nbands;                      // dims_ok: below 2^31
     const uint64_t cus = ctx->num_cus > 0 ? (uint64_t)ctx->num_cus : 256u;
@@ -1835,6 +1850,10 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     // 4.66 and 4.63, 8 images 4.73 and 5.15 (the hand-overs of 500 bands), 10 images 4.74 and 6.27; 4096x2160 21.8 and 21.3, two
     // of them 21.8 and 29.9; 512x512 with seven mixtures 7.01 and 6.20, 12 images 7.26 and 6.40, 16 images 7.28 and 7.40.  Of 53 such
     // jobs the launch chosen takes 0.2 % longer than the best of the three on average and 1.5 % at most.
+    // They hold twice the places for it, which other decodes then wait for: beside another decode (threads with a context and a stream
+    // each) they are for jobs of which four, the hardware queues of a process, keep three quarters of the chip busy at most.  ms until each
+    // thread has decoded an image, with 16 rows and with 8: 4096x2160, two threads 22.5 and 24.3, three 24.6 and 34.4, four 26.0
+    // and 45.2; 2048x1365, two 12.7 and 12.7, three 12.8 and 13.3, four 13.4 and 15.0; 1024x1024, four 8.55 and 8.51.
     auto steps = [&](uint64_t places, int rows, int per_image) {
         const uint64_t hold = (uint64_t)W + (uint64_t)Net::kDelay * ((H < rows ? H : rows) - 1), stride = (uint64_t)Net::kDelay * rows;
         const uint64_t last = (uint64_t)n * per_image - 1;
@@ -1848,7 +1867,10 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     auto kernel = DecodeLaunch::kOne;
     if (DecLds<Net>::kTwoFit && bands > cus && steps_two * pace < best) { kernel = DecodeLaunch::kTwo; best = steps_two * pace; }
     const bool narrow_fits = Net::kNarrowBands && mailbox_bytes(n, narrow_bands, W) <= most_bytes;
-    if (narrow_fits && (double)Net::kNarrowPercent * (double)steps(cus, kNarrowRows, narrow_bands) < best) kernel = DecodeLaunch::kNarrow;
+    const double steps_narrow = (double)steps(cus, kNarrowRows, narrow_bands);
+    const double narrow_busy = (double)n * narrow_bands * (W + (double)Net::kDelay * ((H < kNarrowRows ? H : kNarrowRows) - 1)) / steps_narrow;    // places, on average
+    const bool narrow_room = sharers <= 1 || 4.0 * narrow_busy <= 0.75 * (double)cus;
+    if (narrow_fits && narrow_room && (double)Net::kNarrowPercent * steps_narrow < best) kernel = DecodeLaunch::kNarrow;
     if (ctx->decode_variant == 1) kernel = DecodeLaunch::kOne;
     if (ctx->decode_variant == 2) kernel = DecodeLaunch::kTwo;
     if (ctx->decode_variant == 3) kernel = narrow_fits ? DecodeLaunch::kNarrow : DecodeLaunch::kOne;
@@ -1874,8 +1896,8 @@ void launch_decode(pcc_ctx* ctx, const DecodeLaunch& how, const uint8_t* d_strea
     }
 }
 
-DecodeLaunch choose_decode_any(const pcc_ctx* ctx, int n, int H, int W, size_t most_bytes) {
-    return with_net(ctx->net, [&](auto net) { return choose_decode<decltype(net)>(ctx, n, H, W, most_bytes); });
+DecodeLaunch choose_decode_any(const pcc_ctx* ctx, int n, int H, int W, size_t most_bytes, int sharers) {
+    return with_net(ctx->net, [&](auto net) { return choose_decode<decltype(net)>(ctx, n, H, W, most_bytes, sharers); });
 }
 
 inline int head_outputs(const pcc_ctx* ctx) {
@@ -2207,11 +2229,12 @@ int pcc_decode(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int n, int 
     const uint64_t rows = (uint64_t)n * H;
     const uint64_t table = (uint64_t)kStreamHeader + 8 * (rows + 1);
     if (nbytes < table + 16 * rows) return PCC_E_STREAM;   // every row payload holds at least its two 8-byte states
-    DecodeLaunch how = choose_decode_any(ctx, n, H, W, SIZE_MAX);
+    const RunningDecode self(ctx->device);
+    DecodeLaunch how = choose_decode_any(ctx, n, H, W, SIZE_MAX, self.sharers);
     size_t mail_bytes = mailbox_bytes(n, how.nbands, W);
     int rc = ensure_workspace(ctx, mail_bytes);
     if (rc != PCC_OK && how.kernel == DecodeLaunch::kNarrow) {        // no memory for twice as many bands
-        how = choose_decode_any(ctx, n, H, W, mail_bytes - 1);
+        how = choose_decode_any(ctx, n, H, W, mail_bytes - 1, self.sharers);
         mail_bytes = mailbox_bytes(n, how.nbands, W);
         rc = ensure_workspace(ctx, mail_bytes);
     }
@@ -2237,7 +2260,8 @@ int pcc_decode_static(pcc_ctx* ctx, const uint8_t* d_stream, size_t nbytes, int 
     const uint64_t table = (uint64_t)kStreamHeader + 8 * (rows + 1);
     if (nbytes < table + 16 * rows) return PCC_E_STREAM;
     // bands of eight rows where the array is large enough for them
-    const DecodeLaunch how = choose_decode_any(ctx, n, H, W, kStaticScratchBytes);
+    const RunningDecode self(ctx->device);
+    const DecodeLaunch how = choose_decode_any(ctx, n, H, W, kStaticScratchBytes, self.sharers);
     const size_t mail_bytes = mailbox_bytes(n, how.nbands, W);
     // the array keeps the last call's words (tagged pixels of another image): the part this job uses is cleared
     return decode_with_mailbox(ctx, how, d_stream, nbytes, n, H, W, d_img_out, ctx->d_static_scratch, mail_bytes, true,

@@ -1,5 +1,8 @@
 """The decoder with bands of eight rows: heights around whole bands of 8 and of 16 rows, widths from one pixel on, networks whose two
 halves of the components are equal in number and not, several images, and the limit of the static scratch.  Needs an MI355X."""
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -99,3 +102,50 @@ def test_mixture_sums_that_are_not_numbers(net, monkeypatch):
             assert torch.equal(codec.pcc_decode(stream, 2, 19, 24), imgs)
         finally:
             codec.close()
+
+
+@pytest.mark.parametrize("h, w, threads", [(2160, 4096, 3), (217, 333, 4)])
+def test_decodes_that_run_at_once_share_the_chip(h, w, threads, monkeypatch):
+    """Several threads decode, each with a codec and a stream of its own.  Bands of eight rows hold twice the places: where that
+    many such jobs fill the chip they would wait for each other (three of 4096x2160: 1.4 times as long as with bands of
+    16 rows), so the rule leaves them out.  Best of five with other streams each, of which two may share a hardware queue."""
+    from paper_2212_01185_amd import binding
+    one = torch.from_numpy(synth.make_image(7, synth.ImageSpec(w, h, 12, 8.0, 64.0))).cuda()[None]
+    seconds = {}
+    for variant in ("1", "0"):
+        monkeypatch.setenv("PCC_DECODE_VARIANT", variant)
+        codecs = [binding.Codec(synth.make_blob(0), 0) for _ in range(threads)]
+        outs = [torch.empty_like(one) for _ in codecs]
+        try:
+            stream = codecs[0].pcc_encode(one)
+            for c, out in zip(codecs, outs):
+                c.pcc_decode(stream, 1, h, w, out=out)
+            seconds[variant] = 1e9
+            for _ in range(5):
+                for out in outs:
+                    out.zero_()
+                torch.cuda.synchronize()
+                wrong = []
+
+                def work(c, s, out):
+                    with torch.cuda.stream(s):
+                        try:
+                            for _ in range(4):
+                                c.pcc_decode(stream, 1, h, w, out=out)
+                        except binding.PccError as e:
+                            wrong.append(e)
+                workers = [threading.Thread(target=work, args=(c, torch.cuda.Stream(), out)) for c, out in zip(codecs, outs)]
+                start = time.perf_counter()
+                for t in workers:
+                    t.start()
+                for t in workers:
+                    t.join()
+                seconds[variant] = min(seconds[variant], time.perf_counter() - start)
+                torch.cuda.synchronize()
+                assert not wrong and all(torch.equal(out, one) for out in outs)
+        finally:
+            for c in codecs:
+                c.close()
+    print("%d threads, %dx%d: bands of 16 rows %.1f ms, chosen %.1f" % (threads, w, h, 1e3 * seconds["1"], 1e3 * seconds["0"]), flush=True)
+    if h * w > 1 << 20:                # (the small ones take a few ms: only their images are looked at)
+        assert seconds["0"] <= 1.15 * seconds["1"]
