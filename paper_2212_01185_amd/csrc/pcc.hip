@@ -1567,7 +1567,8 @@ int ensure_workspace(pcc_ctx* ctx, size_t bytes) {
 
 // Zeros in all of d_tagged, waited for: neither the caller's stream, where the pixel kernel writes it, nor the context's, where the
 // row coder reads it, is ordered after the null stream, whose hipMemset returns before it has begun.  A late one wiped
-// symbols that had been written, and until then a row coder could find those of a freed context with its own epoch.
+// symbols that had been written, and until then a row coder could find those of a freed context with its own epoch.  (A context's
+// first encode takes 10 us longer for the wait, with an event for the second stream in its place or a kernel that clears as well.)
 int clear_tagged(pcc_ctx* ctx, hipStream_t st) {
     if (hipMemsetAsync(ctx->d_tagged, 0, ctx->tagged_count * sizeof(uint64_t), st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
         (void)hipGetLastError();

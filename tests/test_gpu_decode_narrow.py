@@ -108,20 +108,23 @@ def test_mixture_sums_that_are_not_numbers(net, monkeypatch):
 def test_decodes_that_run_at_once_share_the_chip(h, w, threads, monkeypatch):
     """Several threads decode, each with a codec and a stream of its own.  Bands of eight rows hold twice the places: where that
     many such jobs fill the chip they would wait for each other (three of 4096x2160: 1.4 times as long as with bands of
-    16 rows), so the rule leaves them out.  Best of five with other streams each, of which two may share a hardware queue."""
+    16 rows), so the rule leaves them out.  Both ways take the same streams, others each time (two may share a hardware queue)."""
     from paper_2212_01185_amd import binding
     one = torch.from_numpy(synth.make_image(7, synth.ImageSpec(w, h, 12, 8.0, 64.0))).cuda()[None]
-    seconds = {}
+    codecs = {}
     for variant in ("1", "0"):
         monkeypatch.setenv("PCC_DECODE_VARIANT", variant)
-        codecs = [binding.Codec(synth.make_blob(0), 0) for _ in range(threads)]
-        outs = [torch.empty_like(one) for _ in codecs]
-        try:
-            stream = codecs[0].pcc_encode(one)
-            for c, out in zip(codecs, outs):
+        codecs[variant] = [binding.Codec(synth.make_blob(0), 0) for _ in range(threads)]
+    outs = [torch.empty_like(one) for _ in range(threads)]
+    ratios = []
+    try:
+        stream = codecs["0"][0].pcc_encode(one)
+        for cs in codecs.values():
+            for c, out in zip(cs, outs):
                 c.pcc_decode(stream, 1, h, w, out=out)
-            seconds[variant] = 1e9
-            for _ in range(5):
+        for _ in range(5):
+            streams, seconds = [torch.cuda.Stream() for _ in outs], {}
+            for variant, cs in codecs.items():
                 for out in outs:
                     out.zero_()
                 torch.cuda.synchronize()
@@ -134,18 +137,19 @@ def test_decodes_that_run_at_once_share_the_chip(h, w, threads, monkeypatch):
                                 c.pcc_decode(stream, 1, h, w, out=out)
                         except binding.PccError as e:
                             wrong.append(e)
-                workers = [threading.Thread(target=work, args=(c, torch.cuda.Stream(), out)) for c, out in zip(codecs, outs)]
+                workers = [threading.Thread(target=work, args=a) for a in zip(cs, streams, outs)]
                 start = time.perf_counter()
                 for t in workers:
                     t.start()
                 for t in workers:
                     t.join()
-                seconds[variant] = min(seconds[variant], time.perf_counter() - start)
+                seconds[variant] = time.perf_counter() - start
                 torch.cuda.synchronize()
                 assert not wrong and all(torch.equal(out, one) for out in outs)
-        finally:
-            for c in codecs:
-                c.close()
-    print("%d threads, %dx%d: bands of 16 rows %.1f ms, chosen %.1f" % (threads, w, h, 1e3 * seconds["1"], 1e3 * seconds["0"]), flush=True)
+            ratios.append(seconds["0"] / seconds["1"])
+    finally:
+        for c in sum(codecs.values(), []):
+            c.close()
+    print("%d threads, %dx%d: chosen against bands of 16 rows %s" % (threads, w, h, " ".join("%.3f" % r for r in ratios)), flush=True)
     if h * w > 1 << 20:                # (the small ones take a few ms: only their images are looked at)
-        assert seconds["0"] <= 1.15 * seconds["1"]
+        assert sorted(ratios)[2] <= 1.15
