@@ -469,7 +469,7 @@ constexpr uint32_t kXcds = 8;
 constexpr uint32_t kRansPatience = 2048;            // polls for one symbol before a row coder beside the pixel kernel stands down (a few ms)
 // Decides how much of a tall image the pixel kernel does before the row coder joins it: the share of its strips that is left for
 // that is 1.1 times this over the rows.  (Alone, the row coder takes as long as the pixel kernel with the whole chip at
-// some 390 rows: 55 us at any number of rows of 768 pixels against 73 at 512 rows.  Beside each other both are slower.)  Whole calls, us, with
+// some 390 rows: 56 us at any number of rows of 768 pixels against 73 at 512 rows.  Beside each other both are slower.)  Whole calls, us, with
 // 300, 400, 500, 600 and 700: 2048x1365 524, 501, 488, 491, 491; 4096x2160 1,475, 1,437, 1,401, 1,422, 1,430; 800x640 154, 142,
 // 141, 143, 129 (no split any more); nine shapes from 800x640 on, with the paper's network too, take 4.5, 1.8, 1.2, 2.3 and 1.7 % longer
 // than with the best of the five on average.
