@@ -88,8 +88,8 @@ typedef struct pcc_ctx pcc_ctx;
  * never change a result: PCC_ENCODE_OVERLAP (0: the row coder
  * always runs after the pixel kernel), PCC_RANS_PATIENCE (polls before a row
  * coder running beside the pixel kernel stands down), PCC_DECODE_VARIANT (1, 2:
- * decoder workgroups per compute unit; 3: one, with bands of eight rows where
- * the network has such a kernel; 0: chosen per job), PCC_DECODE_SPIN_LIMIT
+ * decoder workgroups per compute unit; 3: one, with bands of eight rows;
+ * 0: chosen per job), PCC_DECODE_SPIN_LIMIT
  * (polls of a band for the band above before pcc_decode fails with
  * PCC_E_INTERNAL). */
 int pcc_create(pcc_ctx **out, const void *h_blob, size_t blob_bytes, int hip_device);

@@ -436,7 +436,7 @@
 
         clk.mark(kPhGather);
         // ---- network, layers meeting in LDS
-        net.template run<Role::kOwnsLast>(in1, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
+        net.template run<ActLds<ROWS>, Role::kOwnsLast>(in1, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
 
         // ---- mixtures: lane jj < 3K of pixel q prepares component jj % K of channel jj / K
         auto prepare = [&](int jj) __attribute__((always_inline)) {

@@ -1124,18 +1124,48 @@ struct WaveLayer {
     }
 };
 
+// A layer's activations in LDS: [k-block][hi, lo] in MFMA's B layout.  With bands of eight rows a tile's columns 8 to 15 are copies of
+// columns 0 to 7, which are stored once, and of a block's four values in a lane the column's lane splits and stores the first
+// two, its copy's lane the others.  A hand-over between layers is a chain of its own (the last block's split, its way through LDS and
+// a barrier, the first read), and this halves the split (16 vector instructions to 10) and the bytes written (two 8-byte writes of
+// four waves and a barrier take 136 cycles, two 4-byte ones some 85): 768x512 4,530 -> 4,317 us, and bands of eight rows pay for
+// networks of three mixtures too (the paper's in 512x512 5,272 -> 4,988, 16 rows before).
+template <int ROWS>
+struct ActLds {
+    static constexpr bool kHalved = ROWS == 8;
+    static constexpr int kPartBytes = kHalved ? 32 * 16 : 64 * 16;
+    __device__ __forceinline__ static int read_at(int lane) { return kHalved ? ((lane >> 4) * 8 + (lane & 7)) * 16 : lane * 16; }
+    // registers i and i + 2 of a column and its copy become one register with a value each (no condition: bank_mask names the lanes)
+    __device__ __forceinline__ static float share(float mine, float copys) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp((int)__float_as_uint(mine), (int)__float_as_uint(copys), 0xE4 /* quad_perm 0 1 2 3 */,
+                                                                     0xF, 0xC /* lanes 8 to 15 of a row */, false));
+    }
+    template <bool LEAKY>
+    __device__ __forceinline__ static void finish(const f32x4_t& acc, uint8_t* __restrict__ act, int ob, int lane) {
+        uint32_t lo;
+        const uint32_t hi = act_split_bf16<LEAKY>(share(acc.x, acc.z), share(acc.y, acc.w), lo);
+        uint8_t* dst = act + (ob >> 1) * 2 * kPartBytes + read_at(lane) + 8 * (ob & 1) + ((lane & 8) >> 1);
+        *reinterpret_cast<uint32_t*>(dst) = hi;
+        *reinterpret_cast<uint32_t*>(dst + kPartBytes) = lo;
+    }
+};
+
 // One hidden layer on this wave's out-blocks.  Same arithmetic per output element
 // as EncoderNet::layers in pcc_device.h: bias, then k-blocks in order, each hi then
 // lo; activation; split into hi + lo.  The out-blocks are taken one after the
 // other (an accumulation chain of MFMAs issues back to back at full rate).
 // In a layer's last round some waves may have no block (OWNS_LAST is false): such a wave skips the round and calls
 // idle() instead, if RUN_IDLE.
-template <int NOB, int NKB, int SLOTS, bool W_LDS, bool B_LDS, bool SPLIT_IN, bool LEAKY, bool ONE_BY_ONE, bool OWNS_LAST, bool RUN_IDLE,
+template <class Act, int NOB, int NKB, int SLOTS, bool W_LDS, bool B_LDS, bool SPLIT_IN, bool LEAKY, bool ONE_BY_ONE, bool OWNS_LAST, bool RUN_IDLE,
           class Idle>
 __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS, W_LDS, B_LDS>& wl, int lane, int wave,
                                                  bf16x4_bits_t minus_one, const u32x4_t (&in)[NKB][2], uint8_t* __restrict__ act_out, Idle& idle) {
     auto finish = [&](int s, const f32x4_t& acc) {
         const int ob = wave + 4 * s;
+        if constexpr (Act::kHalved) {
+            Act::template finish<LEAKY>(acc, act_out, ob, lane);
+            return;
+        }
         u32x2_t hi, lo;
         // The matrix core's subtraction saves issue slots and adds its latency to the step.  It is the faster one where two
         // workgroups share the slots (24 images of 768x512 6.30 -> 6.23 ms) and with LeakyReLU (512x512 of the paper's shape
@@ -1149,9 +1179,9 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
             lo.x = l0; lo.y = l1;
         }
         // out-block ob is half (ob & 1) of k-block ob/2 of the next layer's operand
-        uint8_t* dst = act_out + (((ob >> 1) * 2) * 64 + lane) * 16 + 8 * (ob & 1);
+        uint8_t* dst = act_out + (ob >> 1) * 2 * Act::kPartBytes + lane * 16 + 8 * (ob & 1);
         *reinterpret_cast<u32x2_t*>(dst) = hi;
-        *reinterpret_cast<u32x2_t*>(dst + 64 * 16) = lo;
+        *reinterpret_cast<u32x2_t*>(dst + Act::kPartBytes) = lo;
     };
     auto chain = [&](int s, f32x4_t& acc) {
         acc = wl.B(s, wave);
@@ -1198,13 +1228,14 @@ __device__ __forceinline__ void dec_hidden_layer(const WaveLayer<NOB, NKB, SLOTS
 // 5,265, diagonal 2,722 and 2,696, six layers 5,984 and 5,912, seven mixtures 6,222 and 6,180; 768x512 4,558 and 4,527.  With five
 // k-blocks as well 768x512 takes 4,565: those are left to the compiler.  With two workgroups per CU fewer registers are live at a time:
 // the paper's network spills 2 instead of 16 and 24 images of 768x512 take 7,360 us instead of 7,485, diagonal 6 for 25 and 5,050 for 5,140.
-template <int NKB, bool ORDERED>
+template <class Act, int NKB, bool ORDERED>
 __device__ __forceinline__ void dec_load_act(const uint8_t* __restrict__ act, int lane, u32x4_t (&in)[NKB][2]) {
+    act += Act::read_at(lane);
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
-        in[kb][0] = *reinterpret_cast<const u32x4_t*>(act + ((kb * 2 + 0) * 64 + lane) * 16);
+        in[kb][0] = *reinterpret_cast<const u32x4_t*>(act + (kb * 2 + 0) * Act::kPartBytes);
         if constexpr (ORDERED) __builtin_amdgcn_sched_barrier(0);
-        in[kb][1] = *reinterpret_cast<const u32x4_t*>(act + ((kb * 2 + 1) * 64 + lane) * 16);
+        in[kb][1] = *reinterpret_cast<const u32x4_t*>(act + (kb * 2 + 1) * Act::kPartBytes);
         if constexpr (ORDERED) __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -1235,7 +1266,7 @@ struct WaveNet {
     // same waves have in all of them: DecLds::same_waves_idle.)  idle: what a wave that has none does in its place.
     // settle: work of every wave that nothing waits for before the searches, in parts for the layers; it goes between the
     // MFMAs.
-    template <bool OWNS_LAST, class Idle, class Settle>
+    template <class Act, bool OWNS_LAST, class Idle, class Settle>
     __device__ __forceinline__ void run(const u32x4_t (&in)[NKB][2], int lane, int wave, bf16x4_bits_t minus_one, uint8_t* __restrict__ act0, uint8_t* __restrict__ act1,
                                         float* __restrict__ headout, Idle& idle, Settle& settle, PhaseClock& clk) const {
         // what waves without an out-block in this layer's last round do instead (decode_kernel says what)
@@ -1256,7 +1287,12 @@ struct WaveNet {
                     acc = mfma16(a, in[kb][1], acc);
                 }
                 const int ob = wave + 4 * slot;
-                *reinterpret_cast<f32x4_t*>(headout + (lane & 15) * DecLds<Net>::kHeadStride + (lane >> 4) * HS + 4 * ob) = acc;
+                if constexpr (Act::kHalved) {
+                    const f32x2_t half = {Act::share(acc.x, acc.z), Act::share(acc.y, acc.w)};
+                    *reinterpret_cast<f32x2_t*>(headout + (lane & 7) * DecLds<Net>::kHeadStride + (lane >> 4) * HS + 4 * ob + ((lane & 8) >> 2)) = half;
+                } else {
+                    *reinterpret_cast<f32x4_t*>(headout + (lane & 15) * DecLds<Net>::kHeadStride + (lane >> 4) * HS + 4 * ob) = acc;
+                }
                 if constexpr (SHARED) __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (kBlocks < SLOTS && kRunIdle) idle_here();
@@ -1266,17 +1302,17 @@ struct WaveNet {
         } else {
             uint8_t* out = (L & 1) ? act1 : act0;
             settle(std::integral_constant<int, L>());
-            dec_hidden_layer<NOB, NKB, SLOTS, kWLds, kBLds, (L > 0), Net::kLeaky, SHARED, OWNS_LAST, kRunIdle>(wl, lane, wave, minus_one, in, out,
+            dec_hidden_layer<Act, NOB, NKB, SLOTS, kWLds, kBLds, (L > 0), Net::kLeaky, SHARED, OWNS_LAST, kRunIdle>(wl, lane, wave, minus_one, in, out,
                                                                                                                idle_here);
             lds_barrier();
             clk.mark(kPhLayer0 + L);
             u32x4_t nxt[Net::kb(L + 1)][2];
-            dec_load_act<Net::kb(L + 1), Net::kb(L + 1) <= 4>(out, lane, nxt);
+            dec_load_act<Act, Net::kb(L + 1), Net::kb(L + 1) <= 4>(out, lane, nxt);
             // scheduling only: every read of the layer's input is issued before its first MFMA, so
             // the LDS latency is paid once per layer and not once per k-block.  With two workgroups per CU the other one
             // hides the latency, and the registers of 40 values are better spent otherwise (24 images 7.23 -> 7.06 ms).
             if constexpr (!SHARED) __builtin_amdgcn_sched_barrier(0);
-            rest.template run<OWNS_LAST>(nxt, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
+            rest.template run<Act, OWNS_LAST>(nxt, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
         }
     }
 };
@@ -1419,7 +1455,7 @@ struct StepRole {
 // this only pays for jobs of so many bands that the work per CU, not an image's chain of steps, sets the time: choose_decode).
 // ROWS = 16: 16 lanes to a pixel.  ROWS = 8 (half of a tile's columns are copies): 32 lanes, which share the mixture components
 // in two halves, and half the pixels to a wave, so that the searches, more than half of a step's instructions, have a fifth
-// fewer of them (437 -> 349 vector instructions with five components).
+// fewer of them (437 -> 349 vector instructions with five components); and a column and its copy share the activation split (ActLds).
 template <class Net, int MINBLOCKS>
 __global__ void __launch_bounds__(kDecThreads, MINBLOCKS)
 decode_kernel(const uint8_t* __restrict__ model, const uint8_t* __restrict__ stream, uint64_t nbytes, int n, int H,
@@ -1512,7 +1548,7 @@ struct pcc_ctx {
     uint32_t* d_static_scratch = nullptr;   // this device's copy of the static scratch array (pcc_decode_static)
     uint32_t dist = 0;             // written to / checked against stream header word 6
     uint32_t spin_limit = 1u << 22;      // polls of a band for one pixel of the band above (seconds) before the call fails (PCC_DECODE_SPIN_LIMIT, for tests)
-    int decode_variant = 0;              // 0: chosen per job; 1: one workgroup per CU; 2: two; 3: one, bands of eight rows where the network has them (PCC_DECODE_VARIANT, for measurements)
+    int decode_variant = 0;              // 0: chosen per job; 1: one workgroup per CU; 2: two; 3: one, bands of eight rows (PCC_DECODE_VARIANT, for measurements)
     // the row coder of a small job runs beside the pixel kernel, on a stream of its own
     bool overlap = true;
     uint32_t patience = kRansPatience;        // polls before a row coder beside the pixel kernel stands down
@@ -1761,14 +1797,13 @@ bool set_kernel_attributes() {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, dec) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<Net, 2>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net>::kBytesShared) == hipSuccess;
-    if constexpr (Net::kNarrowBands)
-        ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net, kNarrowRows>::kBytes) == hipSuccess;
+    ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net, kNarrowRows>::kBytes) == hipSuccess;
     // The decoders read the CDF table at LDS address 0 (cq_lookup<K, true>): their dynamic array must begin there, that is,
     // they must have no static one in front of it.
     static_assert(DecLds<Net>::kLutOff == 0, "the table's LDS address is a literal in cq_lookup");
     std::vector<const void*> decoders = {reinterpret_cast<const void*>(&decode_kernel<Net, 1>), reinterpret_cast<const void*>(&decode_kernel<Net, 2>)};
-    if constexpr (Net::kNarrowBands) decoders.push_back(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>));
+    decoders.push_back(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>));
     for (const void* decoder : decoders) {
         hipFuncAttributes attr;
         ok = ok && hipFuncGetAttributes(&attr, decoder) == hipSuccess && attr.sharedSizeBytes == 0;
@@ -1847,10 +1882,9 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     // average and 3.6 % at most.  768x512, ms with one and with two per CU: 16 images 5.66 and 6.02, 18 images 6.56 and
     // 5.96, 48 images 12.68 and 9.93; the paper's shape, 9 images 6.27 and 6.66, 24 images 7.53 and 7.51.
     // Bands of eight rows take Net::kNarrowPercent of the time of a step, and are twice as many: they are for jobs whose chain of
-    // steps, not whose work per CU, sets the time.  768x512, ms with bands of 16 and of 8 rows: 1 image 4.65 and 4.53, 4 images
-    // 4.66 and 4.63, 8 images 4.73 and 5.15 (the hand-overs of 500 bands), 10 images 4.74 and 6.27; 4096x2160 21.8 and 21.3, two
-    // of them 21.8 and 29.9; 512x512 with seven mixtures 7.01 and 6.20, 12 images 7.26 and 6.40, 16 images 7.28 and 7.40.  Of 53 such
-    // jobs the launch chosen takes 0.2 % longer than the best of the three on average and 1.5 % at most.
+    // steps, not whose work per CU, sets the time.  768x512, ms with bands of 16 and of 8 rows: 1 image 4.67 and 4.32, 4 images
+    // 4.73 and 4.44, 6 images 4.78 and 4.60, 8 images 4.80 and 4.98 (the hand-overs of 500 bands), 10 images 4.89 and 6.01;
+    // 4096x2160 22.0 and 20.5; 768x512 with seven mixtures, 8 images 8.11 and 6.76, 10 images 8.24 and 7.40.
     // They hold twice the places for it, which other decodes then wait for: beside another decode (threads with a context and a stream
     // each) they are for jobs of which four, the hardware queues of a process, keep three quarters of the chip busy at most.  ms until each
     // thread has decoded an image, with 16 rows and with 8: 4096x2160, two threads 22.5 and 24.3, three 24.6 and 34.4, four 26.0
@@ -1867,7 +1901,7 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     double best = 100.0 * (double)steps(cus, kBandRows, nbands);
     auto kernel = DecodeLaunch::kOne;
     if (DecLds<Net>::kTwoFit && bands > cus && steps_two * pace < best) { kernel = DecodeLaunch::kTwo; best = steps_two * pace; }
-    const bool narrow_fits = Net::kNarrowBands && mailbox_bytes(n, narrow_bands, W) <= most_bytes;
+    const bool narrow_fits = mailbox_bytes(n, narrow_bands, W) <= most_bytes;
     const double steps_narrow = (double)steps(cus, kNarrowRows, narrow_bands);
     const double narrow_busy = (double)n * narrow_bands * (W + (double)Net::kDelay * ((H < kNarrowRows ? H : kNarrowRows) - 1)) / steps_narrow;    // places, on average
     const bool narrow_room = sharers <= 1 || 4.0 * narrow_busy <= 0.75 * (double)cus;
@@ -1890,7 +1924,7 @@ void launch_decode(pcc_ctx* ctx, const DecodeLaunch& how, const uint8_t* d_strea
     else if (how.kernel == DecodeLaunch::kTwo)
         hipLaunchKernelGGL((decode_kernel<Net, 2>), dim3(how.grid), dim3(kDecThreads), kLdsShared, st, ctx->d_model, d_stream,
                            (uint64_t)nbytes, n, H, W, how.nbands, ctx->dist, d_img_out, d_mail, status, spin_limit);
-    else if constexpr (Net::kNarrowBands) {
+    else {
         constexpr int kLdsNarrow = DecLds<Net, kNarrowRows>::kBytes;
         hipLaunchKernelGGL((decode_narrow_kernel<Net>), dim3(how.grid), dim3(kDecThreads), kLdsNarrow, st, ctx->d_model, d_stream,
                            (uint64_t)nbytes, n, H, W, how.nbands, ctx->dist, d_img_out, d_mail, status, spin_limit);

@@ -83,12 +83,11 @@ struct NetWorkload {
     // Time of a decode step with two workgroups per CU, in percent of a step with one, while the other workgroup waits and
     // while both are busy (fitted to whole jobs; the host chooses between the launches with them: choose_decode).
     static constexpr unsigned kSharedAlonePercent = 112, kSharedStepPercent = 138;
-    // Bands of eight rows with 32 lanes to a pixel (decode_narrow_kernel): is there such a kernel, and its time for a single image in
-    // percent of the time with bands of 16 rows, the hand-overs of twice as many bands included.  768x512: this network 4,675 ->
-    // 4,511 us; 512x512: five mixtures 6,090 -> 5,863, seven 7,022 -> 6,171; three mixtures have too little to share
-    // (the paper's 5,319 -> 5,341, diagonal 2,723 -> 2,828).
-    static constexpr bool kNarrowBands = true;
-    static constexpr unsigned kNarrowPercent = 97;
+    // Bands of eight rows with 32 lanes to a pixel (decode_narrow_kernel): the time for a single image in percent of the time with
+    // bands of 16 rows, the hand-overs of twice as many bands included.  512x512, us: this network 4,032 and 3,724, the paper's 5,261
+    // and 4,988, diagonal 2,705 and 2,701 (a boundary between bands every 8 of its passes), five mixtures 6,108 and 5,500, seven
+    // 7,072 and 5,730, four layers 4,615 and 4,415, six 5,891 and 5,651, 64 filters 4,416 and 4,094, 192 6,868 and 6,249.
+    static constexpr unsigned kNarrowPercent = 93;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 30 : l == 1 ? 160 : l == 2 ? 160 : l == 3 ? 128 : 60; }
     __host__ __device__ static constexpr int ob(int l) { return l == 0 ? 10 : l == 1 ? 10 : l == 2 ? 8 : 4; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 1 : l == 1 ? 5 : l == 2 ? 5 : 4; }
@@ -126,8 +125,7 @@ struct NetPaper {
     static constexpr int kEncodeThreads = 512;
     static constexpr int kSharedCuLds = 6;
     static constexpr unsigned kSharedAlonePercent = 108, kSharedStepPercent = 137;
-    static constexpr bool kNarrowBands = false;
-    static constexpr unsigned kNarrowPercent = 100;
+    static constexpr unsigned kNarrowPercent = 95;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 2 : 4; }
@@ -155,6 +153,7 @@ struct NetDiagonal : NetPaper {
     static constexpr int kRingCols = 8;
     static constexpr int kRingPad = 4;
     static constexpr unsigned kSharedAlonePercent = 118, kSharedStepPercent = 138;
+    static constexpr unsigned kNarrowPercent = 100;
     __host__ __device__ static constexpr bool run_desc(int kbi, int g, int half, int& dr, int& off) {
         if (kbi == 0) {
             if (g == 0) { dr = -2; off = 4 * half; }                          // row r-2, bytes 0..7
@@ -196,8 +195,7 @@ struct NetAblation : NetPaper {
     // SIMD some 190 are spilled (4 images of 640x480: 882 us with 512 threads, 546 with 256).
     static constexpr int kEncodeThreads = C > 128 ? 256 : 512;
     static constexpr int kSharedCuLds = MIXTURES >= 7 || LAYERS >= 6 ? 7 : MIXTURES >= 5 ? 6 : 4;
-    static constexpr bool kNarrowBands = MIXTURES >= 5;
-    static constexpr unsigned kNarrowPercent = MIXTURES >= 7 ? 88 : 97;
+    static constexpr unsigned kNarrowPercent = MIXTURES >= 7 ? 82 : MIXTURES >= 5 ? 91 : C > 128 ? 92 : C < 128 ? 93 : 96;
     // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch.)
     static constexpr unsigned kSharedAlonePercent = C > 128 ? 1000 : MIXTURES >= 7 ? 126 : MIXTURES >= 5 ? 107 : LAYERS >= 6 ? 114 : LAYERS <= 4 ? 104 : 101;
     static constexpr unsigned kSharedStepPercent = C > 128 ? 1000 : MIXTURES >= 7 ? 149 : MIXTURES >= 5 ? 135 : LAYERS >= 6 ? 141 : LAYERS <= 4 ? 130 : 123;

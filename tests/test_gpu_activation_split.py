@@ -90,8 +90,8 @@ def _overflowing(dims, layer):
 
 # network: layer widths, header, launches of its decoder (one and two workgroups per unit; 3: bands of eight rows)
 NETS = {"workload": (synth.DEFAULT_DIMS, {}, "123"),
-        "paper": (synth.PAPER_DIMS, dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY), "12"),
-        "more_filters": (synth.ablation_dims(3, 192, 5), dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY), "12"),
+        "paper": (synth.PAPER_DIMS, dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY), "123"),
+        "more_filters": (synth.ablation_dims(3, 192, 5), dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY), "123"),
         "more_mixtures": (synth.ablation_dims(5, 128, 5), dict(k=5, nbhd=12, delay=3, act=synth.ACT_LEAKY), "3"),
         "most_mixtures": (synth.ablation_dims(7, 128, 5), dict(k=7, nbhd=12, delay=3, act=synth.ACT_LEAKY), "3")}
 

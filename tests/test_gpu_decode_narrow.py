@@ -12,18 +12,17 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-NARROW = {"workload": (synth.DEFAULT_DIMS, {})}       # the networks that have such a kernel
-NARROW.update({name: (synth.ablation_dims(*synth.ABLATION_SHAPES[name]), dict(k=synth.ABLATION_SHAPES[name][0], nbhd=12, delay=3, act=synth.ACT_LEAKY))
-               for name in ("more_mixtures", "most_mixtures")})
-BLOBS = {"workload": synth.make_blob, "paper": synth.make_paper_blob}
-BLOBS.update({name: lambda seed, name=name: synth.make_ablation_blob(*synth.ABLATION_SHAPES[name], seed=seed) for name in ("more_mixtures", "most_mixtures")})
+NARROW = {"workload": (synth.DEFAULT_DIMS, {}), "paper": (synth.PAPER_DIMS, dict(k=3, nbhd=12, delay=3, act=synth.ACT_LEAKY))}
+NARROW.update({name: (synth.ablation_dims(*shape), dict(k=shape[0], nbhd=12, delay=3, act=synth.ACT_LEAKY)) for name, shape in synth.ABLATION_SHAPES.items()})
+BLOBS = {"workload": synth.make_blob, "paper": synth.make_paper_blob, "diagonal": synth.make_diagonal_blob}
+BLOBS.update({name: lambda seed, name=name: synth.make_ablation_blob(*synth.ABLATION_SHAPES[name], seed=seed) for name in synth.ABLATION_SHAPES})
 SIZES = [(1, 1, 1), (2, 7, 5), (1, 8, 33), (3, 9, 2), (1, 15, 40), (1, 16, 3), (2, 17, 18), (1, 23, 1), (5, 24, 31), (1, 25, 64), (1, 33, 17)]
 
 
 @pytest.mark.parametrize("launch", ["0", "3"])
 @pytest.mark.parametrize("net", sorted(BLOBS))
 def test_bands_of_eight_rows_decode_exactly(net, launch, monkeypatch):
-    """Chosen by the rule and forced (the paper's network has no such kernel: the other one runs): the images exactly."""
+    """Chosen by the rule and forced: the images exactly."""
     from paper_2212_01185_amd import binding
     monkeypatch.setenv("PCC_DECODE_VARIANT", launch)
     codec = binding.Codec(BLOBS[net](0), 0)

@@ -511,7 +511,7 @@ def test_roundtrip_random_shapes(codec, codec_sharp, paper_blob, diagonal_blob):
 
 def test_more_bands_than_resident_workgroups(blob, paper_blob, monkeypatch):
     """540 bands of 16 rows: more than the chip holds workgroups, with one and with two per compute unit, so every
-    workgroup decodes several bands one after the other; 900 of eight rows, where the network has that kernel.  All launch
+    workgroup decodes several bands one after the other; 900 of eight rows.  All launch
     choices return the images."""
     from paper_2212_01185_amd import binding
     rng = np.random.default_rng(77)
@@ -550,7 +550,7 @@ def test_the_faster_launch_of_the_decoder_is_chosen(net, n, h, w, monkeypatch):
     one = torch.from_numpy(synth.make_image(110, synth.ImageSpec(w, h, 12, 8.0, 64.0))).cuda()
     imgs = one[None].repeat(n, 1, 1, 1)
     ms = {}
-    for variant in ("1", "2", "3", "0"):        # (3 is 1 where the network has no kernel with bands of eight rows)
+    for variant in ("1", "2", "3", "0"):
         monkeypatch.setenv("PCC_DECODE_VARIANT", variant)
         c = binding.Codec(which, 0)
         try:
