@@ -26,15 +26,20 @@
     // search role: pixel q of the band, lane j of its LP lanes, which is edge e and takes part `part` of the components
     const int q = LP == 16 ? 4 * wave + (lane >> 4) : 2 * wave + (lane >> 5), j = LP == 16 ? lane & 15 : lane & 31, part = LP == 16 ? 0 : (lane >> 4) & 1;
     SearchLane sl;
-    sl.e = LP == 16 ? j : lane & 15; sl.shift = LP == 16 ? lane & 48 : (lane & 32) + 16; sl.base4 = LP == 16 ? 4 * (lane & 48) : 4 * ((lane & 32) + 16);
+    sl.e = LP == 16 ? j : lane & 15; sl.shift = LP == 16 ? lane & 48 : lane & 32; sl.base4 = LP == 16 ? 4 * (lane & 48) : 4 * ((lane & 32) + 16);
     sl.edge1 = (float)(32 * sl.e - 1) * (1.0f / 512.0f);
     sl.edge2 = (float)(2 * sl.e - 1) * (1.0f / 512.0f);
-    sl.e1 = sl.e == 0 ? -__builtin_inff() : (float)(16 * sl.e);
-    sl.e2 = sl.e == 0 ? -__builtin_inff() : (float)sl.e;
+    const bool no_sums = D::kParts > 1 && part == 0;
+    sl.e1 = no_sums ? __builtin_inff() : sl.e == 0 ? -__builtin_inff() : (float)(16 * sl.e);
+    sl.e2 = no_sums ? __builtin_inff() : sl.e == 0 ? -__builtin_inff() : (float)sl.e;
+    sl.table = (uint32_t)(sl.e >> 2) * kLutCopyBytes;
 
     {
         const float2* src = reinterpret_cast<const float2*>(model + Lay::kLutOff);
-        for (int i = tid; i < kLutEntries + 1; i += kDecThreads) *reinterpret_cast<float2*>(lds + D::kLutOff + spread_at((uint32_t)i)) = src[i];
+        for (int i = tid; i < kLutEntries + 1; i += kDecThreads) {
+            if constexpr (D::kTable == Table::kSpread) *reinterpret_cast<float2*>(lds + D::kLutOff + spread_at((uint32_t)i)) = src[i];
+            else for (int c = 0; c < kLutCopies; ++c) *reinterpret_cast<float2*>(lds + D::kLutOff + c * kLutCopyBytes + 8 * i) = src[i];
+        }
     }
     if constexpr (D::kParts * PK > K) {      // the component that the second part has too few: looked up, never summed
         for (int i = tid; i < ROWS * 3 * D::kCpStride; i += kDecThreads) cpbuf[i] = 0.0f;

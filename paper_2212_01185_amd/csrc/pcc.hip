@@ -953,7 +953,8 @@ struct DecLds {
     static constexpr int kHS = Layout<Net>::kHeadSlots;
     static constexpr int kActBytes = max_kb() * 2 * 64 * 16;           // one layer's activations: [k-block][hi,lo][lane][16 B]
     static constexpr int kLutOff = 0;
-    static constexpr int kAct0Off = (kSpreadLutBytes + 15) / 16 * 16;
+    static constexpr Table kTable = kParts > 1 ? Table::kCopies : Table::kSpread;
+    static constexpr int kAct0Off = ((kTable == Table::kCopies ? kLutCopies * kLutCopyBytes : kSpreadLutBytes) + 15) / 16 * 16;
     static constexpr int kAct1Off = kAct0Off + kActBytes;
     // Strides in floats, padded by one 16-byte vector: consecutive pixels (and channels) then start
     // four LDS banks apart instead of on the same bank.
@@ -1328,12 +1329,17 @@ struct WaveNet<Net, SHARED, L, true> {
 // group_interval, which is off the path from symbol to symbol.
 // With 32 lanes to a pixel two rows of 16 lanes share an edge's components: the first row looks up the first kPartK of them and
 // sums them, the second row looks up the others meanwhile and goes on with the first row's sum, so that the sum is made in
-// the order of the components as everywhere; what a sweep finds is in the second row.
+// the order of the components as everywhere; what a sweep finds is in the second row.  A vector instruction in a search costs more
+// than its 4 cycles: behind a gap (a look-up's wait) the four SIMDs of a unit share one issue slot for some 140 cycles (ten
+// instructions of each take 95 cycles longer).  So the forms with fewest of them: plain copies of the table instead of spread entries (one a look-up),
+// no copy of the sum before the lane swap, and rows without sums that never pass instead of a mask on the ballot: 768x512 4,318 -> 4,210 us,
+// the paper's network in 512x512 4,987 -> 4,899.
 struct SearchLane {            // a lane's constants
     float edge1, edge2;        // (2 (16 e) - 1) / 512 and (2 e - 1) / 512
-    float e1, e2;              // 16 e and e; minus infinity for e = 0
-    int e, shift;              // the lane's edge; position in a ballot of the 16 bits of the pixel's row that has the sums
+    float e1, e2;              // 16 e and e; minus infinity for e = 0; infinity in lanes that have no sums
+    int e, shift;              // the lane's edge; position in a ballot of the pixel's lanes
     int base4;                 // 4 x first lane of that row
+    uint32_t table;            // LDS address of the table's copy that the lane reads (Table::kCopies)
 };
 struct Found {
     uint32_t next1;            // Cq(16 e + 16), 65536 for e = 15
@@ -1367,8 +1373,10 @@ __device__ __forceinline__ float cq_scaled_shared(const ChanParams<PK>& cp, CqLo
         phi[k] = __builtin_fmaf(q.t[k], td[k].y, td[k].x);
         acc = __builtin_fmaf(cp.pi[k], phi[k], acc);
     }
-    // the first row's sum in the second row
-    const u32x2_t swapped = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_permlane16_swap(__float_as_uint(acc), __float_as_uint(acc), false, false));
+    // the first row's sum in the second row (the first row goes on with anything: its lanes never pass, SearchLane::e1)
+    uint32_t any;
+    asm("" : "=v"(any));
+    const u32x2_t swapped = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_permlane16_swap(any, __float_as_uint(acc), false, false));
     acc = __uint_as_float(swapped.x);
 #pragma unroll
     for (int k = 0; k < K - PK; ++k) acc = __builtin_fmaf(cp.pi[k], phi[k], acc);
@@ -1384,8 +1392,15 @@ __device__ __forceinline__ int group_search(const ChanParams<PK>& cp, float slot
         if constexpr (PK < K) return cq_scaled_shared<K, PK>(cp, q);
         else return cq_scaled<K>(cp, q);
     };
+    constexpr bool kShared = PK < K;            // two rows share an edge's components
+    constexpr Table kTable = kShared ? Table::kCopies : Table::kSpread;
+    // the edges of the pixel that have passed
+    auto passed = [&](bool pass) __attribute__((always_inline)) {
+        const uint64_t all = __ballot(pass) >> sl.shift;
+        return kShared ? __popc((uint32_t)all) : __popcll(all & 0xFFFFull);
+    };
     CqLookup<PK> q1, q2;
-    cq_lookup<PK, true>(cp, sl.edge1, lut, q1);
+    cq_lookup<PK, kTable>(cp, sl.edge1, lut, q1, sl.table);
     __builtin_amdgcn_sched_barrier(0);       // scheduling only: the table reads first, then what they leave time for
     during1();
     cq_fractions<PK>(q1);
@@ -1393,9 +1408,9 @@ __device__ __forceinline__ int group_search(const ChanParams<PK>& cp, float slot
     asm volatile("" : "+v"(limit1) :: "memory");
     pin<PK>(q1);
     const float v1 = scaled(q1);
-    const int b = __popcll((__ballot(v1 < limit1) >> sl.shift) & 0xFFFFull) - 1;
+    const int b = passed(v1 < limit1) - 1;
     const float bf = (float)b;
-    cq_lookup<PK, true>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2);
+    cq_lookup<PK, kTable>(cp, __builtin_fmaf(bf, 1.0f / 16.0f, sl.edge2), lut, q2, sl.table);
     __builtin_amdgcn_sched_barrier(0);
     during2();
     cq_fractions<PK>(q2);
@@ -1406,7 +1421,7 @@ __device__ __forceinline__ int group_search(const ChanParams<PK>& cp, float slot
     asm volatile("" : "+v"(limit2), "+v"(found.next1), "+v"(first) :: "memory");
     pin<PK>(q2);
     const float v2 = scaled(q2);
-    found.count = __popcll((__ballot(v2 < limit2) >> sl.shift) & 0xFFFFull);
+    found.count = passed(v2 < limit2);
     found.b = b;
     found.x = first + found.count;
     found.c2 = (uint32_t)v2 + (uint32_t)(first + 1 + sl.e);

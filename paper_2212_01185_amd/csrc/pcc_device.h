@@ -638,18 +638,23 @@ struct CqLookup {
 // sigma = 1, the first sweep), four LDS banks would serve all of them.
 __host__ __device__ constexpr uint32_t spread_at(uint32_t i) { return 8u * i + (i & ~15u); }
 constexpr int kSpreadLutBytes = (int)spread_at(kLutEntries) + 8;
+// Or four plain copies, a bank pair further on each, of which lanes 0 to 3 of the 16 read the first, lanes 4 to 7 the second and so on:
+// entries that lie 8 / 2^k apart are then 2^k lanes apart on one bank in one copy at most.  One instruction a look-up less, for 49 KB.
+constexpr int kLutCopies = 4, kLutCopyBytes = (((kLutEntries + 1) * 8 + 255) / 256) * 256 + 8;
 
-// edge: the bin edge's position (2 e - 1) / 512, exact for every e.  SPREAD: the table is such a copy, at LDS address 0
-// (an address the compiler knows: two instructions a look-up, a base it does not know would make it three).  The kernel
-// that uses it has no static LDS, which would move its dynamic array: pcc_create refuses to go on with one that has.
-template <int K, bool SPREAD = false>
-__device__ __forceinline__ void cq_lookup(const ChanParams<K>& cp, float edge, const float2* __restrict__ lut, CqLookup<K>& q) {
+// edge: the bin edge's position (2 e - 1) / 512, exact for every e.  TABLE: where the table is: at `lut`; a copy with free banks at LDS
+// address 0 (an address the compiler knows: two instructions a look-up, a base it does not know would make it three); or a plain copy at
+// LDS address `copy`.  The kernel that uses one in LDS has no static LDS, which would move its dynamic array: pcc_create refuses to
+// go on with one that has.
+enum class Table { kPlain, kSpread, kCopies };
+template <int K, Table TABLE = Table::kPlain>
+__device__ __forceinline__ void cq_lookup(const ChanParams<K>& cp, float edge, const float2* __restrict__ lut, CqLookup<K>& q, uint32_t copy = 0) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         q.t[k] = __builtin_amdgcn_fmed3f(__builtin_fmaf(edge - cp.mu[k], cp.a[k], kLutBias), 0.0f, kLutMax);
         const uint32_t i = (uint32_t)(int)q.t[k];                  // t >= 0: truncation is floor
-        if constexpr (SPREAD) {
-            const f32x2_t v = *(const __attribute__((address_space(3))) f32x2_t*)(spread_at(i));
+        if constexpr (TABLE != Table::kPlain) {
+            const f32x2_t v = *(const __attribute__((address_space(3))) f32x2_t*)(TABLE == Table::kSpread ? spread_at(i) : (i << 3) + copy);
             q.td[k].x = v.x; q.td[k].y = v.y;
         } else {
             q.td[k] = lut[i];
