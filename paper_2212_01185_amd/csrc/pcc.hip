@@ -954,7 +954,9 @@ struct DecLds {
     static constexpr int kActBytes = max_kb() * 2 * 64 * 16;           // one layer's activations: [k-block][hi,lo][lane][16 B]
     static constexpr int kLutOff = 0;
     static constexpr Table kTable = kParts > 1 ? Table::kCopies : Table::kSpread;
-    static constexpr int kAct0Off = ((kTable == Table::kCopies ? kLutCopies * kLutCopyBytes : kSpreadLutBytes) + 15) / 16 * 16;
+    static constexpr int kLutEnd = ((kTable == Table::kCopies ? kLutCopies * kLutCopyBytes : kSpreadLutBytes) + 15) / 16 * 16;
+    static constexpr bool kMiscFirst = kTable == Table::kCopies;       // (the 64 KB that an instruction's offset reaches end in front of the ring then)
+    static constexpr int kAct0Off = kLutEnd + (kMiscFirst ? 16 : 0);
     static constexpr int kAct1Off = kAct0Off + kActBytes;
     // Strides in floats, padded by one 16-byte vector: consecutive pixels (and channels) then start
     // four LDS banks apart instead of on the same bank.
@@ -972,8 +974,9 @@ struct DecLds {
     static constexpr int kRingCopyElems = 2 * Net::kRingCols * 3 + 1;  // from an element to the same one in the second copy
     static constexpr int kRingRowElems = 2 * kRingCopyElems + Net::kRingPad;
     static constexpr int kRingOff = kCpOff + 16 * 3 * kCpStride * 4;
-    static constexpr int kMiscOff = kRingOff + (ROWS + 2) * kRingRowElems * 2; // ticket, abort flag
-    static constexpr int kSinkOff = kMiscOff + 16;                     // where lanes with no ring element to write write
+    static constexpr int kRingEnd = kRingOff + (ROWS + 2) * kRingRowElems * 2;
+    static constexpr int kMiscOff = kMiscFirst ? kLutEnd : kRingEnd;   // ticket, abort flag
+    static constexpr int kSinkOff = kRingEnd + (kMiscFirst ? 0 : 16);  // where lanes with no ring element to write write
     static constexpr int kBytes = (kSinkOff + 64 * 4 + 8 * Net::K + 15) / 16 * 16;
     // Two workgroups per CU have 256 registers per lane each, too few for the whole of a wave's weight slices: there
     // the biases, and the weights of the first layer and of the head where two workgroups' LDS then still fits a CU,
