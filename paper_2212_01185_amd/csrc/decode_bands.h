@@ -317,6 +317,7 @@
         window_at[1] = 6u * slot + 2u * D::kRingCopyElems - second;
     };
     gather_window(t);
+    const float* coupling_at = headout + q * D::kHeadStride + (D::kParts > 1 ? 3 * PK * part : 0);
     // The lane picks come first, in two stages, each where the next wait for LDS is one of the network's own.
     Interval settle_g = {0, 0, 0}, settle_b = {0, 0, 0};
     auto settle_pick = [&]() __attribute__((always_inline)) {
@@ -494,7 +495,6 @@
         // of the four waves keep LDS busy for hundreds of cycles in front of R's first table reads.
         ChanParams<PK> cpr, cpg, cpb;
         float alpha[PK], beta[PK], gamma[PK];
-        const float* hq = headout + q * D::kHeadStride;
         // `tail` receives the last vector read, padding included: the caller keeps it in use until the values are
         // consumed (register allocation only: a padding register that is free at once is handed to the next read,
         // which then has to wait for this one)
@@ -511,14 +511,12 @@
         };
         f32x4_t tail_r, tail_g, tail_b;
         // coupling coefficients: canonical head outputs 9K.. (alpha), 10K.. (beta), 11K.. (gamma), wherever the head's
-        // (group, register) layout put them; a component that the lane's part does not have reads the first part's last one
+        // (group, register) layout put them; for a component that the lane's part does not have it is the padding behind them
         auto coupling = [&](auto first, auto kc) __attribute__((always_inline)) {
             constexpr int c = decltype(first)::value, k = decltype(kc)::value, mine = head_slot<Net>(c + k);
-            if constexpr (D::kParts == 1) return hq[mine];
-            else {
-                constexpr int other = PK + k < K ? head_slot<Net>(c + PK + k) : mine;
-                return hq[mine + part * (other - mine)];
-            }
+            static_assert(D::kParts == 1 || head_slot<Net>(c + K - 1) == mine + 3 * (K - 1 - k), "one distance between the parts");
+            static_assert(head_slot<Net>(c) + 3 * (D::kParts * PK - 1) < D::kHeadStride, "the padding is there");
+            return coupling_at[mine];
         };
         auto load_g = [&]() __attribute__((always_inline)) {
             load_cp(1, cpg, tail_g);
@@ -571,7 +569,7 @@
         clk.mark(kPhB);
 
         // ---- publish
-        mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
+        if constexpr (Role::kStores) mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
         settle_active = active;
         asm volatile("" : "+v"(found_b.c2), "+v"(mail_px), "+v"(settle_active));   // scheduling only: while the ring is written
         if constexpr (!kStoreInIdle) {

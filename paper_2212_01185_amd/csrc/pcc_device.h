@@ -51,6 +51,14 @@ __host__ __device__ constexpr int run_in_index(int kbi, int g, int i) {
     return (dr == -2 ? 0 : dr == -1 ? Net::kUpBytes : 2 * Net::kUpBytes) + b;
 }
 
+// The decoder's head: canonical output in register s of lane group g after the last layer, or -1.  Groups 0..2 hold their
+// channel's 3 K parameters, group 3 the coupling coefficients component by component (alpha, beta, gamma), so that two parts of the
+// components are read at one distance from each other, whichever the coefficient.
+template <int K>
+__host__ __device__ constexpr int decoder_head_index(int g, int s) {
+    return s >= 3 * K ? -1 : g < 3 ? 3 * K * g + s : 9 * K + K * (s % 3) + s / 3;
+}
+
 // The measured workloads' network: 30 -> 160 -> 160 -> 128 -> 60, ReLU, K = 5,
 // neighbourhood {rows r-2, r-1 at columns c-2..c+1; row r at c-2, c-1}, wavefront delay 2.
 struct NetWorkload {
@@ -92,12 +100,8 @@ struct NetWorkload {
     __host__ __device__ static constexpr int ob(int l) { return l == 0 ? 10 : l == 1 ? 10 : l == 2 ? 8 : 4; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 1 : l == 1 ? 5 : l == 2 ? 5 : 4; }
     // Head output held by lane group g in register s = 4*out_block + i after the
-    // last layer: groups 0..2 hold their channel's 15 parameters plus one coupling
-    // coefficient, group 3 holds the other coupling coefficients.
-    __host__ __device__ static constexpr int head_index(int g, int s) {
-        return g < 3 ? (s < 15 ? 15 * g + s : (g == 1 ? 45 : (g == 2 ? 50 : -1)))
-                     : (s < 4 ? 46 + s : (s < 8 ? 51 + (s - 4) : (s < 13 ? 55 + (s - 8) : -1)));
-    }
+    // last layer: groups 0..2 hold their channel's 15 parameters, group 3 the coupling coefficients.
+    __host__ __device__ static constexpr int head_index(int g, int s) { return decoder_head_index<K>(g, s); }
     // First-layer operand: slots 0-3 (half 0) and 4-7 (half 1) of lane group g in k-block
     // kbi are four consecutive neighbour bytes of one row: row offset dr, first byte off
     // within the row's run that starts at column c-2.  Returns false for an unused half.
@@ -129,12 +133,7 @@ struct NetPaper {
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 2 : 4; }
-    // groups 0..2: the channel's 9 parameters in registers 0..8; group 1 also holds the
-    // alphas and group 2 the betas in registers 9..11; group 3 holds the gammas in 0..2.
-    __host__ __device__ static constexpr int head_index(int g, int s) {
-        return g < 3 ? (s < 9 ? 9 * g + s : (g == 1 ? 27 + (s - 9) : (g == 2 ? 30 + (s - 9) : -1)))
-                     : (s < 3 ? 33 + s : -1);
-    }
+    __host__ __device__ static constexpr int head_index(int g, int s) { return decoder_head_index<K>(g, s); }
     __host__ __device__ static constexpr bool run_desc(int kbi, int g, int half, int& dr, int& off) {
         if (kbi == 0) { dr = g < 2 ? -2 : -1; off = ((g & 1) ? 8 : 0) + 4 * half; return true; }
         dr = 0; off = 4 * half;
@@ -183,8 +182,6 @@ struct NetDiagonal : NetPaper {
 // (the head layouts above) or 7, C a multiple of 32.  The encoder keeps in LDS what fits of the packed model: six
 // layers of 128 filters fit without the CDF table, of 192 filters the first two layers (the other layers' weight
 // tiles and, there, the table are read from global memory).
-// K = 7 (six out-blocks, 24 registers): groups 0..2 hold their channel's 21 parameters, group 3 the
-// 21 coupling coefficients.
 template <int MIXTURES, int C, int LAYERS>
 struct NetAblation : NetPaper {
     static_assert((MIXTURES == 3 || MIXTURES == 5 || MIXTURES == 7) && C % 32 == 0 && C <= 192 && LAYERS >= 3 && LAYERS <= 7,
@@ -202,11 +199,7 @@ struct NetAblation : NetPaper {
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == LAYERS ? 12 * MIXTURES : C; }
     __host__ __device__ static constexpr int ob(int l) { return (dim(l + 1) + 15) / 16; }
     __host__ __device__ static constexpr int kb(int l) { return (dim(l) + 31) / 32; }
-    __host__ __device__ static constexpr int head_index(int g, int s) {
-        return MIXTURES == 3 ? NetPaper::head_index(g, s)
-             : MIXTURES == 5 ? NetWorkload::head_index(g, s)
-                             : (s < 21 ? 21 * g + s : -1);
-    }
+    __host__ __device__ static constexpr int head_index(int g, int s) { return decoder_head_index<K>(g, s); }
 };
 using NetFewerLayers = NetAblation<3, 128, 4>;
 using NetFewerFilters = NetAblation<3, 64, 5>;
@@ -561,6 +554,10 @@ struct ChanParams {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// sigma = exp(clamp(log sigma, -8, 4)); a NaN counts as -8.  One instruction (fminf and fmaxf take three): the median of a NaN and two
+// numbers is the smaller of the two.
+__device__ __forceinline__ float clamp_log_sigma(float ls) { return __builtin_amdgcn_fmed3f(ls, -8.0f, 4.0f); }
+
 // raw[0..K) logits, raw[K..2K) means, raw[2K..3K) log-sigmas of one channel.
 template <int K>
 __device__ __forceinline__ void channel_setup(const float (&raw)[3 * K], float lut_scale, ChanParams<K>& cp) {
@@ -578,7 +575,7 @@ __device__ __forceinline__ void channel_setup(const float (&raw)[3 * K], float l
     for (int k = 0; k < K; ++k) {
         cp.pi[k] = e[k] * inv;
         cp.mu[k] = raw[K + k];
-        const float ls = fminf(fmaxf(raw[2 * K + k], -8.0f), 4.0f);   // sigma = exp(clamp(log sigma, -8, 4))
+        const float ls = clamp_log_sigma(raw[2 * K + k]);
         cp.a[k] = __builtin_amdgcn_exp2f(-(ls * kLog2e)) * lut_scale;
     }
 }
@@ -601,7 +598,7 @@ __device__ __forceinline__ void channel_setup_one(const float (&logits)[K], floa
     const float inv = __builtin_amdgcn_rcpf(sum);
     pi = __builtin_amdgcn_exp2f((logit_k - m) * kLog2e) * inv;
     mu = mu_k;
-    const float ls = fminf(fmaxf(ls_k, -8.0f), 4.0f);
+    const float ls = clamp_log_sigma(ls_k);
     a = __builtin_amdgcn_exp2f(-(ls * kLog2e)) * lut_scale;
 }
 
