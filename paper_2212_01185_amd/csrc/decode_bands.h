@@ -56,6 +56,8 @@
     // this wave's weights stay in registers (all that is not staged above), for every band the workgroup decodes
     WaveNet<Net, (MINBLOCKS > 1), 0> net;
     net.load(model, lds, lane, wave);
+    using KeepAwake = Awake<(MINBLOCKS == 1 && Net::kKeepAwake)>;
+    KeepAwake awake;
     const float lut_scale = *reinterpret_cast<const float*>(model + Lay::kLutScaleOff);
     const int total_bands = n * nbands;
 
@@ -317,7 +319,7 @@
         window_at[1] = 6u * slot + 2u * D::kRingCopyElems - second;
     };
     gather_window(t);
-    const float* coupling_at = headout + q * D::kHeadStride + (D::kParts > 1 ? 3 * PK * part : 0);
+    const float* coupling_base = headout + q * D::kHeadStride + (D::kParts > 1 ? 3 * PK * part : 0);
     // The lane picks come first, in two stages, each where the next wait for LDS is one of the network's own.
     Interval settle_g = {0, 0, 0}, settle_b = {0, 0, 0};
     auto settle_pick = [&]() __attribute__((always_inline)) {
@@ -442,7 +444,7 @@
 
         clk.mark(kPhGather);
         // ---- network, layers meeting in LDS
-        net.template run<ActLds<ROWS>, Role::kOwnsLast>(in1, lane, wave, minus_one, act0, act1, headout, idle, settle, clk);
+        net.template run<ActLds<ROWS>, Role::kOwnsLast>(in1, lane, wave, minus_one, act0, act1, headout, idle, settle, awake, clk);
 
         // ---- mixtures: lane jj < 3K of pixel q prepares component jj % K of channel jj / K
         auto prepare = [&](int jj) __attribute__((always_inline)) {
@@ -457,6 +459,7 @@
 #pragma unroll
                 for (int i = 0; i < NV; ++i) lv[i] = reinterpret_cast<const f32x4_t*>(hc)[i];
                 float logit_k = hc[k], mu_k = hc[K + k], ls_k = hc[2 * K + k];
+                awake.template keep<KeepAwake::kBehindHeadReads>();
                 // scheduling only: all reads are issued before the first is used (whole vectors, so that the registers of
                 // the padding are not wanted for the next read's address)
                 asm volatile("" : "+v"(lv[0]), "+v"(lv[NV - 1]), "+v"(logit_k), "+v"(mu_k), "+v"(ls_k));
@@ -495,6 +498,8 @@
         // of the four waves keep LDS busy for hundreds of cycles in front of R's first table reads.
         ChanParams<PK> cpr, cpg, cpb;
         float alpha[PK], beta[PK], gamma[PK];
+        // (with two workgroups per unit the address is made again in every step, and every wave makes mail_px: 29 spilled registers, not 41)
+        const float* coupling_at = MINBLOCKS > 1 ? headout + q * D::kHeadStride : coupling_base;
         // `tail` receives the last vector read, padding included: the caller keeps it in use until the values are
         // consumed (register allocation only: a padding register that is free at once is handed to the next read,
         // which then has to wait for this one)
@@ -534,6 +539,7 @@
         auto load_stop = [&]() __attribute__((always_inline)) { if constexpr (kStopInSearch) stop = misc[1]; };
         load_cp(0, cpr, tail_r);
         asm volatile("" ::: "memory");
+        awake.template keep<KeepAwake::kBehindMixtureReads>();
 
         clk.mark(kPhMixture);
         uint32_t start, freq;
@@ -569,7 +575,7 @@
         clk.mark(kPhB);
 
         // ---- publish
-        if constexpr (Role::kStores) mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
+        if constexpr (MINBLOCKS > 1 || Role::kStores) mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
         settle_active = active;
         asm volatile("" : "+v"(found_b.c2), "+v"(mail_px), "+v"(settle_active));   // scheduling only: while the ring is written
         if constexpr (!kStoreInIdle) {
@@ -596,6 +602,7 @@
         else if (wave_s == D::kFetchWave) steps(StepRole<true, false, false>());
         else steps(StepRole<false, true, false>());
     }
+    awake.used();
 #ifdef PCC_PHASE_TIMING
     if (ticket == min(kPhaseTicket, total_bands - 1) && lane == 0) {
         for (int i = 0; i < kPhCount; ++i) phase_cycles[wave][i] = clk.acc[i];

@@ -92,10 +92,14 @@ struct NetWorkload {
     // while both are busy (fitted to whole jobs; the host chooses between the launches with them: choose_decode).
     static constexpr unsigned kSharedAlonePercent = 112, kSharedStepPercent = 138;
     // Bands of eight rows with 32 lanes to a pixel (decode_narrow_kernel): the time for a single image in percent of the time with
-    // bands of 16 rows, the hand-overs of twice as many bands included.  512x512, us: this network 4,032 and 3,724, the paper's 5,261
-    // and 4,988, diagonal 2,705 and 2,701 (a boundary between bands every 8 of its passes), five mixtures 6,108 and 5,500, seven
-    // 7,072 and 5,730, four layers 4,615 and 4,415, six 5,891 and 5,651, 64 filters 4,416 and 4,094, 192 6,868 and 6,249.
-    static constexpr unsigned kNarrowPercent = 93;
+    // bands of 16 rows, the hand-overs of twice as many bands included.  512x512, us with 16 and with eight: this network 3,946 and 3,520,
+    // the paper's 5,181 and 4,730, diagonal 2,734 and 2,587, five mixtures 6,003 and 5,313, seven 6,814 and 5,560, four layers 4,688 and
+    // 4,281, six 5,773 and 5,261, 64 filters 4,383 and 3,989, 192 6,738 and 6,132.
+    static constexpr unsigned kNarrowPercent = 89;
+    // Decoder with one workgroup per unit: are the waits for LDS filled with MFMAs (Awake)?  512x512 with bands of eight rows, us without and
+    // with: this network 3,600 and 3,500, the paper's 4,905 and 4,734, six layers (256x256) 2,643 and 2,621, four 2,155 and 2,140, 192 filters
+    // 3,094 and 3,060, five mixtures 2,672 and 2,650, seven 2,770 and 2,772; not with 64 filters 3,980 and 4,005 and in diagonal order (768x512) 3,168 and 3,238.
+    static constexpr bool kKeepAwake = true;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 30 : l == 1 ? 160 : l == 2 ? 160 : l == 3 ? 128 : 60; }
     __host__ __device__ static constexpr int ob(int l) { return l == 0 ? 10 : l == 1 ? 10 : l == 2 ? 8 : 4; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 1 : l == 1 ? 5 : l == 2 ? 5 : 4; }
@@ -129,7 +133,8 @@ struct NetPaper {
     static constexpr int kEncodeThreads = 512;
     static constexpr int kSharedCuLds = 6;
     static constexpr unsigned kSharedAlonePercent = 108, kSharedStepPercent = 137;
-    static constexpr unsigned kNarrowPercent = 95;
+    static constexpr unsigned kNarrowPercent = 91;
+    static constexpr bool kKeepAwake = true;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 2 : 4; }
@@ -152,7 +157,8 @@ struct NetDiagonal : NetPaper {
     static constexpr int kRingCols = 8;
     static constexpr int kRingPad = 4;
     static constexpr unsigned kSharedAlonePercent = 118, kSharedStepPercent = 138;
-    static constexpr unsigned kNarrowPercent = 100;
+    static constexpr unsigned kNarrowPercent = 95;
+    static constexpr bool kKeepAwake = false;
     __host__ __device__ static constexpr bool run_desc(int kbi, int g, int half, int& dr, int& off) {
         if (kbi == 0) {
             if (g == 0) { dr = -2; off = 4 * half; }                          // row r-2, bytes 0..7
@@ -192,7 +198,8 @@ struct NetAblation : NetPaper {
     // SIMD some 190 are spilled (4 images of 640x480: 882 us with 512 threads, 546 with 256).
     static constexpr int kEncodeThreads = C > 128 ? 256 : 512;
     static constexpr int kSharedCuLds = MIXTURES >= 7 || LAYERS >= 6 ? 7 : MIXTURES >= 5 ? 6 : 4;
-    static constexpr unsigned kNarrowPercent = MIXTURES >= 7 ? 82 : MIXTURES >= 5 ? 91 : C > 128 ? 92 : C < 128 ? 93 : 96;
+    static constexpr unsigned kNarrowPercent = MIXTURES >= 7 ? 82 : MIXTURES >= 5 ? 88 : 91;
+    static constexpr bool kKeepAwake = C >= 128;
     // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch.)
     static constexpr unsigned kSharedAlonePercent = C > 128 ? 1000 : MIXTURES >= 7 ? 126 : MIXTURES >= 5 ? 107 : LAYERS >= 6 ? 114 : LAYERS <= 4 ? 104 : 101;
     static constexpr unsigned kSharedStepPercent = C > 128 ? 1000 : MIXTURES >= 7 ? 149 : MIXTURES >= 5 ? 135 : LAYERS >= 6 ? 141 : LAYERS <= 4 ? 130 : 123;
