@@ -7,8 +7,8 @@
 //   rans_rows_kernel   two lanes per image row, one per coder state: push the row's
 //                      symbols last to first into a per-row slab, written backwards; for a small
 //                      job it runs beside encode_kernel, taking the symbols as
-//                      they appear
-//   compact_kernel     slabs -> contiguous stream, with header and offsets
+//                      they appear, and with narrow images takes the rows to their places in the stream itself
+//   compact_kernel     otherwise: slabs -> contiguous stream, with header and offsets
 //   scan_kernel        exclusive prefix sum of row payload sizes in front of it, for jobs of very many rows
 //   decode_kernel      persistent wavefront decoder: one workgroup (4 waves) per
 //                      band of 16 rows, step t handles pixel (r, t - delay*r) of each row
@@ -474,6 +474,11 @@ constexpr uint32_t kRansPatience = 2048;            // polls for one symbol befo
 // 141, 143, 129 (no split any more); nine shapes from 800x640 on, with the paper's network too, take 4.5, 1.8, 1.2, 2.3 and 1.7 % longer
 // than with the best of the five on average.
 constexpr uint32_t kRansBalanceRows = 600;
+// Widest image whose rows the row coder takes to their places in the stream itself where it runs beside the pixel kernel.  A
+// workgroup does so with one compute unit, the compaction with the whole chip.  Whole calls, us, with the compaction and
+// without: 256x256 58.3, 57.0; three of 768x512 228.7, 224.4; 1000x3000 510.2, 505.4; 1024x1024 204.4, 203.6; 1536x800 236.4,
+// 236.8; 2048x640 249.0, 250.8; 4096x512 366, 372; 6000x300 490, 502.
+constexpr int kRansAssembleWidth = 1024;
 // Padding symbol (start 0, frequency 2^16): pushing it leaves the state unchanged
 // and never renormalises, so every chunk can be coded as a full one.
 constexpr uint32_t kRansNop = 0xFFFF0000u;
@@ -544,13 +549,49 @@ __device__ __forceinline__ uint32_t shift_in(uint32_t v, bool bit, uint32_t sele
     return v;
 }
 
+// Where a call's stream goes, and what describes it.
+struct StreamOut {
+    uint8_t* stream;
+    uint64_t cap_bytes;
+    int n, H;
+    uint32_t tag, dist;
+    uint64_t* total_bytes;
+    EncodeResult* result;
+    uint64_t* sums;            // of the row coder's groups: epoch << 32 | words (kSumStoodDown: none)
+};
+constexpr uint32_t kSumStoodDown = 0xFFFFFFFFu;
+
+__device__ __forceinline__ void write_header(const StreamOut& out, int W) {
+    uint32_t* hdr = reinterpret_cast<uint32_t*>(out.stream);
+    hdr[0] = kStreamMagic; hdr[1] = kStreamVersion; hdr[2] = (uint32_t)out.n; hdr[3] = (uint32_t)out.H; hdr[4] = (uint32_t)W;
+    hdr[5] = out.tag; hdr[6] = out.dist; hdr[7] = 0;
+}
+
+// The last of a kernel's workgroups to end leaves the call's result in host memory and the status block clear.
+// This workgroup's errors, and the total if it is here, before its count: all are atomic accesses at device scope, so that
+// they have been made when the wave's counter of outstanding ones is zero.  (A fence would write the die's L2 back, in every
+// workgroup: 254 us for 24 images of 768x512.)
+__device__ __forceinline__ void leave_result(const StreamOut& out, int* status) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0 && (uint32_t)atomicAdd(&status[kStDone], 1) + 1u == gridDim.x) {
+        out.result->total_bytes = __hip_atomic_load(out.total_bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        out.result->err = atomicExch(&status[kStErr], 0);
+        out.result->defer = atomicExch(&status[kStDefer], 0);
+        atomicExch(&status[kStDone], 0);
+    }
+}
+
 // BESIDE: the pixel kernel is running; the symbols are read from sf_tagged, past the caches that are not
 // coherent with the pixel kernel's stores, and each is waited for until it carries this launch's epoch.
-template <bool BESIDE>
+// ASSEMBLES: the workgroups (at most kRansBesideMaxGroups) take their rows to their places in the stream themselves and there is
+// no compaction behind them: each publishes its words and waits for those of the groups before it.
+template <bool BESIDE, bool ASSEMBLES>
 __global__ void __launch_bounds__(kRansThreads, 2 /* waves per SIMD: two workgroups per compute unit */)
 rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uint32_t epoch, int W, uint32_t rows,
                  uint32_t* __restrict__ slabs, uint32_t* __restrict__ row_words, uint32_t* __restrict__ group_words, int* status,
-                 uint32_t patience) {
+                 uint32_t patience, StreamOut out) {
+    static_assert(BESIDE || !ASSEMBLES, "the sums carry the epoch of the symbols");
     constexpr int kPerState = kRansChunk / 2;   // symbols of a chunk that one state (one coding lane) takes
     static_assert(kPerState == 32, "a coding lane's emission flags of a round fill one 32-bit word");
     // [buffer][row][symbol of the chunk]; the odd row strides keep the coding wave's column accesses off shared banks
@@ -639,6 +680,7 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
                 }
                 if (gave_up) {
                     __hip_atomic_store(&status[kStDefer], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if constexpr (ASSEMBLES) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // before this workgroup counts as ended
                     abandon = 1;
                     break;
                 }
@@ -759,8 +801,14 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
     // rounds nchunks + 2 (or + 3, for an even number of rounds) down to -1, where chunk 0's words are stored
     for (int k = nchunks + 2 + (nchunks & 1); k >= 0; k -= 2) {
         if (!round(k, std::integral_constant<int, 0>()) || !round(k - 1, std::integral_constant<int, 1>())) {
-            if (tid < kRansRows && row0 + tid < rows) row_words[row0 + tid] = 0;    // stood down: nothing for the compaction to copy
-            if (tid == 0) group_words[blockIdx.x] = 0;
+            if constexpr (ASSEMBLES) {
+                if (tid == 0)
+                    __hip_atomic_store(&out.sums[blockIdx.x], (uint64_t)epoch << 32 | kSumStoodDown, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                leave_result(out, status);
+            } else {
+                if (tid < kRansRows && row0 + tid < rows) row_words[row0 + tid] = 0;    // stood down: nothing for the compaction to copy
+                if (tid == 0) group_words[blockIdx.x] = 0;
+            }
             return;
         }
     }
@@ -780,11 +828,112 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
         slab[wp - 2] = final_state[lane][2];
         slab[wp - 3] = final_state[lane][1];
         slab[wp - 4] = final_state[lane][0];
-        row_words[row0 + lane] = words;
+        if constexpr (!ASSEMBLES) row_words[row0 + lane] = words;
     }
-    if (storer) {                                // the group's sum (at most 32 times 100 MB in words)
-        for (int d = 32; d >= 1; d >>= 1) words += __shfl_xor(words, d);
-        if (lane == 0) group_words[blockIdx.x] = words;
+    if constexpr (!ASSEMBLES) {
+        if (storer) {                            // the group's sum (at most 32 times 100 MB in words)
+            for (int d = 32; d >= 1; d >>= 1) words += __shfl_xor(words, d);
+            if (lane == 0) group_words[blockIdx.x] = words;
+        }
+    } else {
+        // The compaction's work in the row coder: a launch, its gap and the way from one die's L2 to another's less (us a call,
+        // before and after: 64x64 41.5, 39.7; 768x512 102.5, 101.2; five of 333x217 with seven mixtures 132.8, 129.8).  What bounds
+        // it is latency: the sums' way between the dies, one batch of loads and stores for rows of up to 256 words, the count.
+        __shared__ uint32_t row_at[kRansRows], row_len[kRansRows], group_len, good;    // words in front of a row within the group, and in it
+        __shared__ uint64_t words_before;
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        if (storer) {
+            uint32_t upto = words;               // lanes beyond the rows have none
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t v = __shfl_up(upto, d);
+                upto += lane >= d ? v : 0u;
+            }
+            if (lane == 63)
+                __hip_atomic_store(&out.sums[blockIdx.x], (uint64_t)epoch << 32 | upto, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool over = __any(words > (uint32_t)sw) != 0;           // not a coder's count: never read outside the slab
+            if (over && lane == 0) set_error(status, PCC_E_INTERNAL);
+            if (lane < kRansRows) { row_at[lane] = upto - words; row_len[lane] = words; }
+            if (lane == 63) { group_len = upto; good = over ? 0u : 1u; }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // the slabs are written: all waves read them next
+        } else if (wave == 2) {
+            // The sums of the groups before, two to a lane.  All groups end within a few us of each other, and those before
+            // this one were started before it; should one not come (the chip is taken), this one stands down as from a missing symbol.
+            static_assert(kRansBesideMaxGroups <= 128, "two sums to a lane");
+            uint64_t before = 0, spins = 0;
+            bool waiting = true, down = false;
+            while (waiting) {
+                waiting = false;
+                before = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < 2; ++i) {
+                    const uint32_t k = (uint32_t)lane + 64 * i;
+                    if (k >= blockIdx.x) continue;
+                    const uint64_t v = __hip_atomic_load(&out.sums[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((uint32_t)(v >> 32) != epoch) waiting = true;
+                    else if ((uint32_t)v == kSumStoodDown) down = true;
+                    else before += (uint32_t)v;
+                }
+                down = __any(down) != 0;
+                waiting = __any(waiting) != 0 && !down;
+                if (waiting) {
+                    if (++spins > 4ull * patience) { down = true; break; }
+                    __builtin_amdgcn_s_sleep(2);
+                }
+            }
+            for (int d = 32; d >= 1; d >>= 1) before += __shfl_xor((unsigned long long)before, d);
+            if (lane == 0) {
+                words_before = before;
+                if (down) {
+                    __hip_atomic_store(&status[kStDefer], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    abandon = 1;
+                }
+            }
+        }
+        lds_barrier();
+        if (abandon == 0) {
+            const uint64_t table = (uint64_t)kStreamHeader + 8ull * ((uint64_t)rows + 1), first = words_before;
+            uint64_t* offsets = reinterpret_cast<uint64_t*>(out.stream + kStreamHeader);
+            // header, offsets and, from the last group, the end offset and the total: all inside the table, which the host has
+            // checked against the capacity
+            if (storer && (uint32_t)lane < live_rows) offsets[row0 + lane] = 4ull * (first + row_at[lane]);
+            const uint64_t end = table + 4ull * (first + group_len);
+            if (tid == 0) {
+                if (row0 == 0) write_header(out, W);
+                if (blockIdx.x + 1 == gridDim.x) {
+                    offsets[rows] = end - table;
+                    __hip_atomic_store(out.total_bytes, end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (end > out.cap_bytes) set_error(status, PCC_E_CAP);
+            }
+            if (end <= out.cap_bytes && good != 0 && (uint32_t)wave < live_rows) {
+                // A wave per four rows apart, eight of them at a time, 16 bytes a lane and row (words lie at multiples of four
+                // bytes, which such loads and stores allow).  A row has four words at least; lanes beyond its end take its last
+                // four again, and places beyond the group's rows the wave's first: no branch between the loads.
+                typedef uint32_t words4_t __attribute__((ext_vector_type(4), aligned(4)));
+                constexpr int kRowsOfWave = kRansRows / (kRansThreads / 64);
+                const uint32_t* src[kRowsOfWave];
+                uint32_t* dst[kRowsOfWave];
+                uint32_t last[kRowsOfWave], most = 0;
+#pragma unroll
+                for (int k = 0; k < kRowsOfWave; ++k) {
+                    const uint32_t r = (uint32_t)(wave + 4 * k) < live_rows ? (uint32_t)(wave + 4 * k) : (uint32_t)wave;
+                    const uint32_t len = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_len[r]);
+                    const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_at[r]);
+                    src[k] = slabs + (size_t)(row0 + r) * sw + (sw - len);
+                    dst[k] = reinterpret_cast<uint32_t*>(out.stream + table) + first + at;
+                    last[k] = len - 4u;
+                    most = max(most, len);
+                }
+                for (uint32_t i = 4u * (uint32_t)lane; i - 4u * (uint32_t)lane < most; i += 256) {
+                    words4_t v[kRowsOfWave];
+#pragma unroll
+                    for (int k = 0; k < kRowsOfWave; ++k) v[k] = *reinterpret_cast<const words4_t*>(src[k] + min(i, last[k]));
+#pragma unroll
+                    for (int k = 0; k < kRowsOfWave; ++k) *reinterpret_cast<words4_t*>(dst[k] + min(i, last[k])) = v[k];
+                }
+            }
+        }
+        leave_result(out, status);
     }
 }
 
@@ -826,8 +975,8 @@ constexpr uint32_t kCompactBlocks = 512;
 
 __global__ void __launch_bounds__(kCompactThreads)
 compact_kernel(const uint32_t* __restrict__ slabs, const uint32_t* __restrict__ row_words, const uint32_t* __restrict__ group_words,
-               const uint64_t* __restrict__ before, int n, int H, int W, uint32_t rows, uint32_t chunk, uint32_t tag, uint32_t dist,
-               uint8_t* __restrict__ stream, uint64_t cap_bytes, int* status, uint64_t* total_bytes, EncodeResult* result) {
+               const uint64_t* __restrict__ before, int W, uint32_t rows, uint32_t chunk, int* status, StreamOut out) {
+    uint8_t* const __restrict__ stream = out.stream;
     __shared__ unsigned long long part[kCompactRows];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t first = blockIdx.x * chunk, end = min(first + chunk, rows), group = first / kRansRows;      // first < rows
@@ -870,19 +1019,15 @@ compact_kernel(const uint32_t* __restrict__ slabs, const uint32_t* __restrict__ 
         // which the host has checked against the capacity
         if (lane == 0) {
             offsets[row] = off;
-            if (row == 0) {
-                uint32_t* hdr = reinterpret_cast<uint32_t*>(stream);
-                hdr[0] = kStreamMagic; hdr[1] = kStreamVersion; hdr[2] = (uint32_t)n; hdr[3] = (uint32_t)H; hdr[4] = (uint32_t)W;
-                hdr[5] = tag; hdr[6] = dist; hdr[7] = 0;
-            }
+            if (row == 0) write_header(out, W);
             if (row + 1 == rows) {
                 offsets[rows] = off + 4ull * words;
-                __hip_atomic_store(total_bytes, table + off + 4ull * words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(out.total_bytes, table + off + 4ull * words, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         if (words > sw) {                             // not a row coder's count: never read outside the slab
             if (lane == 0) set_error(status, PCC_E_INTERNAL);
-        } else if (table + off + 4ull * words > cap_bytes) {
+        } else if (table + off + 4ull * words > out.cap_bytes) {
             if (lane == 0) set_error(status, PCC_E_CAP);
         } else {
             const uint32_t* src = slabs + (size_t)row * sw + (sw - words);
@@ -897,17 +1042,7 @@ compact_kernel(const uint32_t* __restrict__ slabs, const uint32_t* __restrict__ 
             }
         }
     }
-    // This workgroup's errors, and the total if it is here, before its count: all are atomic accesses at device scope, so that
-    // they have been made when the wave's counter of outstanding ones is zero.  (A fence would write the die's L2 back, in every
-    // workgroup: 254 us for 24 images of 768x512.)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0 && (uint32_t)atomicAdd(&status[kStDone], 1) + 1u == gridDim.x) {
-        result->total_bytes = __hip_atomic_load(total_bytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        result->err = atomicExch(&status[kStErr], 0);
-        result->defer = atomicExch(&status[kStDefer], 0);
-        atomicExch(&status[kStDone], 0);
-    }
+    leave_result(out, status);
 }
 
 // test hook: the symbols of a tagged buffer without their epochs
@@ -1592,6 +1727,7 @@ struct pcc_ctx {
     size_t ws_bytes = 0;
     int* d_status = nullptr;       // the status blocks, and the encoder's stream size behind them
     uint64_t* d_total = nullptr;
+    uint64_t* d_sums = nullptr;    // behind it: words of the row coder's groups, tagged with the epoch
     int* h_status = nullptr;       // pinned: the decoder's block after a call, the encoder's result behind it
     EncodeResult* h_result = nullptr;
     EncodeResult* d_result = nullptr;         // the same, as kernels see it
@@ -2060,10 +2196,10 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
     ctx->d_static_scratch = static_scratch(hip_device);
     ok = ok && ctx->d_static_scratch != nullptr;
     ok = ok && hipMalloc((void**)&ctx->d_model, image.size()) == hipSuccess;
-    constexpr size_t kBlocksBytes = kStBlocks * kStBytes;
+    constexpr size_t kBlocksBytes = kStBlocks * kStBytes, kStatusBytes = kBlocksBytes + (1 + kRansBesideMaxGroups) * sizeof(uint64_t);
     static_assert(kBlocksBytes % sizeof(uint64_t) == 0 && kStBytes % alignof(EncodeResult) == 0, "alignment");
-    ok = ok && hipMalloc((void**)&ctx->d_status, kBlocksBytes + sizeof(uint64_t)) == hipSuccess;
-    ok = ok && hipMemset(ctx->d_status, 0, kBlocksBytes + sizeof(uint64_t)) == hipSuccess;
+    ok = ok && hipMalloc((void**)&ctx->d_status, kStatusBytes) == hipSuccess;
+    ok = ok && hipMemset(ctx->d_status, 0, kStatusBytes) == hipSuccess;
     ok = ok && hipHostMalloc((void**)&ctx->h_status, kStBytes + sizeof(EncodeResult), hipHostMallocDefault) == hipSuccess;
     if (ok) {
         ctx->h_result = reinterpret_cast<EncodeResult*>(ctx->h_status + kStWords);
@@ -2084,6 +2220,7 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
     ok = ok && hipEventCreateWithFlags(&ctx->ev_joined, hipEventDisableTiming) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); pcc_destroy(ctx); return PCC_E_HIP; }
     ctx->d_total = reinterpret_cast<uint64_t*>(ctx->d_status + kStBlocks * kStWords);
+    ctx->d_sums = ctx->d_total + 1;
     *out = ctx;
     return PCC_OK;
 }
@@ -2171,7 +2308,9 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         if (rc != PCC_OK) return rc;
         if (++ctx->epoch == 0) {      // wrapped: the words of old launches would pass for new ones
             rc = clear_tagged(ctx, st);
-            if (rc != PCC_OK) { --ctx->epoch; return rc; }
+            if (rc == PCC_OK && hipMemsetAsync(ctx->d_sums, 0, kRansBesideMaxGroups * sizeof(uint64_t), st) != hipSuccess) rc = PCC_E_HIP;
+            if (rc == PCC_OK && hipStreamSynchronize(st) != hipSuccess) rc = PCC_E_HIP;
+            if (rc != PCC_OK) { (void)hipGetLastError(); --ctx->epoch; return rc; }
             ctx->epoch = 1;
         }
     }
@@ -2185,29 +2324,29 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
     prof_reset(ctx);
     int* d_status = ctx->status(kBlockEncode);
     const uint32_t tag = with_net(ctx->net, [](auto net) { return model_tag<decltype(net)>(); });
+    const StreamOut out = {d_stream, (uint64_t)cap_bytes, n, H, tag, ctx->dist, ctx->d_total, ctx->d_result, ctx->d_sums};
+    bool assembles = beside && W <= kRansAssembleWidth;
     auto launch_rans = [&](hipStream_t s) {
         prof_begin(ctx, PCC_T_ENCODE_RANS, s);
-        if (beside)
-            hipLaunchKernelGGL(rans_rows_kernel<true>, dim3(groups), dim3(kRansThreads), 0, s, d_sf, d_tagged, ctx->epoch, W,
-                               rows, d_slabs, d_rw, d_gw, d_status, ctx->patience);
-        else
-            hipLaunchKernelGGL(rans_rows_kernel<false>, dim3(groups), dim3(kRansThreads), 0, s, d_sf, d_tagged, ctx->epoch, W,
-                               rows, d_slabs, d_rw, d_gw, d_status, 0u);
+        const auto kernel = !beside ? rans_rows_kernel<false, false> : assembles ? rans_rows_kernel<true, true> : rans_rows_kernel<true, false>;
+        hipLaunchKernelGGL(kernel, dim3(groups), dim3(kRansThreads), 0, s, d_sf, d_tagged, ctx->epoch, W,
+                           rows, d_slabs, d_rw, d_gw, d_status, beside ? ctx->patience : 0u, out);
         prof_end(ctx, PCC_T_ENCODE_RANS, s);
     };
     // what follows the row coder, and the wait for it
     auto finish = [&](hipStream_t s) -> int {
-        if (scan) {
-            prof_begin(ctx, PCC_T_ENCODE_SCAN, s);
-            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, d_gw, groups, d_before);
-            prof_end(ctx, PCC_T_ENCODE_SCAN, s);
+        if (!assembles) {
+            if (scan) {
+                prof_begin(ctx, PCC_T_ENCODE_SCAN, s);
+                hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, d_gw, groups, d_before);
+                prof_end(ctx, PCC_T_ENCODE_SCAN, s);
+            }
+            prof_begin(ctx, PCC_T_ENCODE_COMPACT, s);
+            const uint32_t chunk = kCompactRows * (uint32_t)(((uint64_t)rows + kCompactRows * kCompactBlocks - 1) / (kCompactRows * kCompactBlocks));
+            hipLaunchKernelGGL(compact_kernel, dim3((rows + chunk - 1) / chunk), dim3(kCompactThreads), 0, s, d_slabs, d_rw,
+                               d_gw, d_before, W, rows, chunk, d_status, out);
+            prof_end(ctx, PCC_T_ENCODE_COMPACT, s);
         }
-        prof_begin(ctx, PCC_T_ENCODE_COMPACT, s);
-        const uint32_t chunk = kCompactRows * (uint32_t)(((uint64_t)rows + kCompactRows * kCompactBlocks - 1) / (kCompactRows * kCompactBlocks));
-        hipLaunchKernelGGL(compact_kernel, dim3((rows + chunk - 1) / chunk), dim3(kCompactThreads), 0, s, d_slabs, d_rw,
-                           d_gw, d_before, n, H, W, rows, chunk, tag, ctx->dist, d_stream, (uint64_t)cap_bytes, d_status, ctx->d_total,
-                           ctx->d_result);
-        prof_end(ctx, PCC_T_ENCODE_COMPACT, s);
         if (hipGetLastError() != hipSuccess) return PCC_E_HIP;
         // The pixel kernel, on the caller's stream, ends before the row coder: waiting for it first costs nothing, waiting for it
         // after the compaction 8.6 us, and an event for the compaction to wait for holds the host up for 20.
@@ -2266,6 +2405,7 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         if (rc != PCC_OK) return drain(rc);
         if (ctx->h_result->err == 0 && ctx->h_result->defer != 0) {
             // The row coder saw nothing of the pixel kernel for a long time and stood down.  The symbols are all there now; code them on the caller's stream.
+            assembles = false;           // (the groups that stood down have said so in this epoch's sums)
             launch_rans(st);
             rc = finish(st);
             if (rc != PCC_OK) return drain(rc);

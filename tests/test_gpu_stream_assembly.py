@@ -1,5 +1,6 @@
-"""The compaction (rows to their places in the stream, the call's result to the host): numbers of rows where its workgroups take
-more than four of them, end in a ragged one or leave the sums to a scan, and calls that fail in between.  Needs an MI355X."""
+"""Rows to their places in the stream, and the call's result to the host: by the compaction (numbers of rows where its workgroups
+take more than four of them, end in a ragged one or leave the sums to a scan) and by the row coder itself, and calls that fail
+in between.  Needs an MI355X."""
 import numpy as np
 import pytest
 
@@ -66,5 +67,33 @@ def test_sequence_does_not_matter(codec, env, monkeypatch):
     try:
         for _ in range(3):
             assert torch.equal(other.pcc_encode(imgs), want)
+    finally:
+        other.close()
+
+
+# The row coder places the rows of images of up to 1,024 columns itself where it has at most 96 groups of 32 rows: one group with
+# a single row, with a row less than its waves, full and one row more; rows of fewer words than a wave's 256 and of several times
+# as many; the most groups and one more; the widest image and one column more.  The compaction gives the same bytes.
+@pytest.mark.parametrize("n,h,w", [(1, 1, 1), (1, 3, 40), (1, 32, 7), (1, 33, 300), (2, 37, 1024), (1, 34, 1025), (1, 3072, 9), (1, 3073, 9)])
+def test_row_coder_places_rows_as_the_compaction_does(codec, n, h, w, monkeypatch):
+    from paper_2212_01185_amd import binding
+    monkeypatch.setenv("PCC_ENCODE_OVERLAP", "0")
+    other = binding.Codec(synth.make_blob(0), 0)
+    rng = np.random.default_rng(3 * h + w)
+    # noise (long rows) in the first half of the rows, an even grey (short ones) in the second
+    imgs = rng.integers(0, 256, (n, h, w, 3), dtype=np.uint8)
+    imgs[:, h // 2:] = 77
+    imgs = torch.from_numpy(imgs).cuda()
+    try:
+        want = other.pcc_encode(imgs).clone()
+        for _ in range(3):
+            out = torch.full((binding.pcc_stream_bound(n, h, w),), 0xA5, dtype=torch.uint8, device="cuda")
+            got = codec.pcc_encode(imgs, out=out)
+            assert torch.equal(got, want)
+            assert bool((out[want.numel():] == 0xA5).all())           # nothing behind the stream
+        with pytest.raises(binding.PccError) as e:                    # and nothing behind a buffer that is too small
+            codec.pcc_encode(imgs, out=out.fill_(0xA5)[:(want.numel() - 4) // 8 * 8])
+        assert e.value.code == binding.PCC_E_CAP and bool((out[(want.numel() - 4) // 8 * 8:] == 0xA5).all())
+        assert torch.equal(codec.pcc_encode(imgs), want)
     finally:
         other.close()
