@@ -184,7 +184,7 @@ int pcc_copy_intervals(pcc_ctx *ctx, uint32_t *d_out, size_t count, void *hip_st
 #define PCC_T_ENCODE_PIXELS 0 /* gather + network + mixture -> (start,freq), all pixels */
 #define PCC_T_ENCODE_RANS 1   /* row-wise rANS */
 #define PCC_T_ENCODE_SCAN 2   /* offsets */
-#define PCC_T_ENCODE_COMPACT 3
+#define PCC_T_ENCODE_COMPACT 3 /* rows to the stream (0 where the row coder does it) */
 #define PCC_T_DECODE 4        /* wavefront decode kernel */
 #define PCC_N_TIMINGS 5
 int pcc_set_profiling(pcc_ctx *ctx, int enabled);
