@@ -1685,7 +1685,7 @@ cdf_tables_kernel(const uint8_t* __restrict__ model, const float* __restrict__ p
     const int ch = (int)(idx - p * 3);
     const float* o = params + p * HEAD;
     float raw[3 * K];
-    for (int s = 0; s < 3 * K; ++s) raw[s] = o[3 * K * ch + s];
+    for (int s = 0; s < 3 * K; ++s) raw[s] = s < 2 * K ? o[3 * K * ch + s] : __builtin_canonicalizef(o[3 * K * ch + s]);     // clamp_log_sigma
     ChanParams<K> cp;
     channel_setup<K>(raw, *reinterpret_cast<const float*>(model + Layout<Net>::kLutScaleOff), cp);
     const float rhat = (float)rg[2 * p] * (1.0f / 256.0f), ghat = (float)rg[2 * p + 1] * (1.0f / 256.0f);

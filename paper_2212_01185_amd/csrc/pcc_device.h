@@ -562,7 +562,8 @@ struct ChanParams {
 constexpr float kLog2e = 1.4426950408889634f;
 
 // sigma = exp(clamp(log sigma, -8, 4)); a NaN counts as -8.  One instruction (fminf and fmaxf take three): the median of a NaN and two
-// numbers is the smaller of the two.
+// numbers is the smaller of the two, if the NaN is quiet (a signalling one counts as 4).  The matrix cores' results are: a head bias
+// that is a signalling NaN arrives here as 0xFFC00000.  Values from elsewhere are made quiet first (cdf_tables_kernel).
 __device__ __forceinline__ float clamp_log_sigma(float ls) { return __builtin_amdgcn_fmed3f(ls, -8.0f, 4.0f); }
 
 // raw[0..K) logits, raw[K..2K) means, raw[2K..3K) log-sigmas of one channel.

@@ -237,6 +237,28 @@ def test_cdf_tables_of_logits_that_are_not_finite(codec):
         np.testing.assert_array_equal(cq[i, :, 1:256], np.broadcast_to(e + 65280, (3, 255)))
 
 
+@pytest.mark.parametrize("bits", [0x7FC00000, 0xFFC00000, 0x7F800001, 0x7FA00000, 0xFF800001, 0xFFBFFFFF])
+def test_a_log_sigma_that_is_nan_counts_as_the_smallest(codec, blob, bits):
+    """Quiet or signalling, -8 is what it counts as in the tables; and a bias like it leaves the network as a quiet one."""
+    from paper_2212_01185_amd import binding
+    heads = np.random.default_rng(21).normal(0, 1, (4, 60)).astype(np.float32)
+    smallest, words = heads.copy(), heads.view(np.uint32)
+    for s in (10, 12, 26, 44):
+        smallest[:, s], words[:, s] = -8.0, bits
+    rg = np.zeros((4, 2), dtype=np.uint8)
+    got, want = (codec.pcc_cdf_tables(torch.from_numpy(h.view(np.int32)).cuda().view(torch.float32), _dev(rg)) for h in (heads, smallest))
+    assert torch.equal(got, want)
+    weights = np.frombuffer(blob, dtype=np.uint32).copy()
+    weights[-60 + 10] = bits
+    other = binding.Codec(weights.tobytes(), 0)
+    try:
+        params, _ = other.pcc_encode_probs(torch.full((1, 3, 40, 3), 90, dtype=torch.uint8, device="cuda"))
+        out = params.cpu().numpy().reshape(-1, 60).view(np.uint32)[:, 10]
+        assert ((out & 0x7FC00000) == 0x7FC00000).all()
+    finally:
+        other.close()
+
+
 # ----------------------------------------------------------------- logistic mixture (Eq. (8))
 
 def test_logistic_mixture(codec, codec_logistic, orc_logistic):
