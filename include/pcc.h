@@ -120,8 +120,11 @@ int pcc_encode_probs(pcc_ctx *ctx, const uint8_t *d_img, int n, int H, int W,
 /* Encoder (Sec. IV-C first paragraph): parameters for all pixels in parallel,
  * integer CDF values of the true sub-pixels, row-wise rANS, stream assembly.
  * Writes at most cap_bytes to d_stream and the byte count to *h_nbytes_out.
- * Synchronises hip_stream before returning (the size is read back).  When
- * hip_stream is idle at the call and the job has at most 3072 rows, the row
+ * Synchronises hip_stream before returning (the size is read back).  The
+ * stream may be written over the images: d_stream may point into them or they
+ * may lie inside the buffer.  When
+ * hip_stream is idle at the call, the job has at most 3072 rows and the images
+ * and the stream buffer share no bytes, the row
  * coder and the stream assembly run on a stream the ctx owns, beside the
  * pixel kernel; both streams have been waited for when the call returns, so
  * the caller's view is the same.  The pixel kernel is queued first: where the

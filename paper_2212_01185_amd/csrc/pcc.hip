@@ -2300,8 +2300,12 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
     // the context's own; nothing orders that stream after the caller's, so this is only done when the caller's
     // stream is idle and the pixel kernel starts at once.  A large job's row coder needs the whole chip and
     // runs after the pixel kernel, on the caller's stream.
+    // Beside the pixel kernel the stream's first rows are written while pixels are still being read.  A stream buffer that shares bytes
+    // with the images therefore gets the kernels one after the other: the compaction, the last, is the only one that writes it.
+    const uintptr_t img_at = (uintptr_t)d_img, stream_at = (uintptr_t)d_stream;
+    const bool apart = img_at + P * 3 <= stream_at || stream_at + std::min<size_t>(cap_bytes, pcc_stream_bound(n, H, W)) <= img_at;
     const uint32_t cus = ctx->num_cus > 0 ? (uint32_t)ctx->num_cus : 256u;
-    bool beside = ctx->overlap && groups <= kRansBesideMaxGroups && cus >= 2 * kRansBesideMaxGroups;
+    bool beside = ctx->overlap && apart && groups <= kRansBesideMaxGroups && cus >= 2 * kRansBesideMaxGroups;
     if (beside) {
         const hipError_t busy = hipStreamQuery(st);
         if (busy != hipSuccess) { (void)hipGetLastError(); beside = false; }

@@ -97,3 +97,32 @@ def test_row_coder_places_rows_as_the_compaction_does(codec, n, h, w, monkeypatc
         assert torch.equal(codec.pcc_encode(imgs), want)
     finally:
         other.close()
+
+
+# A stream buffer that shares bytes with the images is written when all pixels have been read: by the compaction, behind the pixel
+# kernel.  Stream's and image's first byte within one buffer: the same; the stream into the image's last bytes, and just behind them; the
+# image into the stream's last possible byte, just behind it, and in its middle.
+@pytest.mark.parametrize("h,w", [(40, 24), (512, 768)])
+@pytest.mark.parametrize("where,shared", [("same", True), ("into end", True), ("behind", False), ("before", False), ("into front", True), ("inside", True)])
+def test_stream_over_the_images(codec, h, w, where, shared):
+    from paper_2212_01185_amd import binding
+    imgs = torch.from_numpy(np.random.default_rng(h).integers(0, 256, (1, h, w, 3), dtype=np.uint8)).cuda()
+    torch.cuda.synchronize()
+    want = codec.pcc_encode(imgs).clone()
+    size, bound = imgs.numel(), binding.pcc_stream_bound(1, h, w)
+    assert size % 8 == 0
+    img_at, stream_at = {"same": (0, 0), "into end": (0, size - 8), "behind": (0, size), "before": (bound, 0), "into front": (bound - 1, 0),
+                         "inside": (bound // 3, 0)}[where]
+    room = torch.empty(max(img_at + size, stream_at + bound), dtype=torch.uint8, device="cuda")
+    view = room[img_at:img_at + size].view(1, h, w, 3)
+    codec.pcc_set_profiling(True)
+    try:
+        for _ in range(3):
+            view.copy_(imgs)
+            torch.cuda.synchronize()
+            got = codec.pcc_encode(view, out=room[stream_at:stream_at + bound])
+            ms = codec.pcc_last_timings()
+            assert torch.equal(got, want)
+            assert ms["encode_rans"] > 0 and (ms["encode_compact"] > 0) == shared, ms
+    finally:
+        codec.pcc_set_profiling(False)
