@@ -86,8 +86,10 @@ typedef struct pcc_ctx pcc_ctx;
  * On success *out owns device memory until pcc_destroy.
  * Reads these environment variables, which exist for tests and measurements and
  * never change a result: PCC_ENCODE_OVERLAP (0: the row coder
- * always runs after the pixel kernel), PCC_RANS_PATIENCE (polls before a row
- * coder running beside the pixel kernel stands down), PCC_DECODE_VARIANT (1, 2:
+ * always runs after the pixel kernel), PCC_RANS_PATIENCE (polls for a symbol
+ * before a row coder running beside the pixel kernel stands down),
+ * PCC_RANS_SUMS_PATIENCE (polls of a row coder's workgroup for the sizes of
+ * those before it, four times as many unless set), PCC_DECODE_VARIANT (1, 2:
  * decoder workgroups per compute unit; 3: one, with bands of eight rows;
  * 0: chosen per job), PCC_DECODE_SPIN_LIMIT
  * (polls of a band for the band above before pcc_decode fails with
@@ -134,8 +136,13 @@ int pcc_encode_probs(pcc_ctx *ctx, const uint8_t *d_img, int n, int H, int W,
  * profiler that collects counters and runs the kernels one at a time in an order
  * of its own), the row coder gives up after PCC_RANS_PATIENCE polls (a few
  * milliseconds with the default) and is launched again behind the pixel kernel:
- * the result is the same, but such a call pays that wait.  PCC_ENCODE_OVERLAP=0
- * avoids the mode altogether.
+ * the result is the same, but such a call pays that wait.  With images of up to
+ * 1024 columns the row coder's workgroups, which place their rows in the stream
+ * themselves, also wait for the sizes of those before them: where the chip, full
+ * of other work, starts one late, the others hold their compute units until it
+ * ends or PCC_RANS_SUMS_PATIENCE polls (some 10 ms) are over, and then all rows
+ * are coded again in the same way.  PCC_ENCODE_OVERLAP=0 avoids the mode
+ * altogether.
  * One call at a time per ctx.  On an error return no kernel of the call is
  * still running on either stream. */
 int pcc_encode(pcc_ctx *ctx, const uint8_t *d_img, int n, int H, int W,

@@ -558,6 +558,7 @@ struct StreamOut {
     uint64_t* total_bytes;
     EncodeResult* result;
     uint64_t* sums;            // of the row coder's groups: epoch << 32 | words (kSumStoodDown: none)
+    uint32_t sums_patience;    // polls of a group for the sums of those before it
 };
 constexpr uint32_t kSumStoodDown = 0xFFFFFFFFu;
 
@@ -859,11 +860,14 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
             if (lane == 63) { group_len = upto; good = over ? 0u : 1u; }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // the slabs are written: all waves read them next
         } else if (wave == 2) {
-            // The sums of the groups before, two to a lane.  All groups end within a few us of each other, and those before
-            // this one were started before it; should one not come (the chip is taken), this one stands down as from a missing symbol.
+            // The sums of the groups before, two to a lane.  On a chip with room for all groups they end within a few us of each
+            // other.  Where other work holds a die's units, a group of that die may still wait for its start when later ones, on other
+            // dies, are here: they hold their units until it has ended, or stand down when their patience is over (some 10 ms), as
+            // from a missing symbol, and the call codes its rows once more.
             static_assert(kRansBesideMaxGroups <= 128, "two sums to a lane");
-            uint64_t before = 0, spins = 0;
-            bool waiting = true, down = false;
+            uint64_t before = 0;
+            uint32_t polls = 0;
+            bool down = blockIdx.x != 0 && out.sums_patience == 0, waiting = !down;
             while (waiting) {
                 waiting = false;
                 before = 0;
@@ -879,7 +883,7 @@ rans_rows_kernel(const uint32_t* __restrict__ sf, const uint64_t* sf_tagged, uin
                 down = __any(down) != 0;
                 waiting = __any(waiting) != 0 && !down;
                 if (waiting) {
-                    if (++spins > 4ull * patience) { down = true; break; }
+                    if (++polls == out.sums_patience) { down = true; break; }
                     __builtin_amdgcn_s_sleep(2);
                 }
             }
@@ -1745,7 +1749,8 @@ struct pcc_ctx {
     int decode_variant = 0;              // 0: chosen per job; 1: one workgroup per CU; 2: two; 3: one, bands of eight rows (PCC_DECODE_VARIANT, for measurements)
     // the row coder of a small job runs beside the pixel kernel, on a stream of its own
     bool overlap = true;
-    uint32_t patience = kRansPatience;        // polls before a row coder beside the pixel kernel stands down
+    uint32_t patience = kRansPatience;        // polls for a symbol before a row coder beside the pixel kernel stands down
+    uint32_t sums_patience = 4 * kRansPatience;      // ... and for the words of its groups before (shorter polls: some 10 ms)
     hipStream_t side = nullptr;
     hipEvent_t ev_joined = nullptr;           // the pixel kernel's first part is done: the row coder may join
     // symbols handed from the pixel kernel to a row coder running beside it: epoch << 32 | start | (freq - 1) << 16.
@@ -2218,7 +2223,11 @@ int pcc_create(pcc_ctx** out, const void* h_blob, size_t blob_bytes, int hip_dev
         if (v >= 0 && v <= 3) ctx->decode_variant = v;
     }
     if (const char* e = getenv("PCC_ENCODE_OVERLAP")) ctx->overlap = atoi(e) != 0;
-    if (const char* e = getenv("PCC_RANS_PATIENCE")) ctx->patience = env_limit(e);
+    if (const char* e = getenv("PCC_RANS_PATIENCE")) {
+        ctx->patience = env_limit(e);
+        ctx->sums_patience = (uint32_t)std::min<uint64_t>(4ull * ctx->patience, 0xFFFFFFFFull);
+    }
+    if (const char* e = getenv("PCC_RANS_SUMS_PATIENCE")) ctx->sums_patience = env_limit(e);
     ok = ok && hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->ev_joined, hipEventDisableTiming) == hipSuccess;
     if (!ok) { (void)hipGetLastError(); pcc_destroy(ctx); return PCC_E_HIP; }
@@ -2331,7 +2340,7 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
     prof_reset(ctx);
     int* d_status = ctx->status(kBlockEncode);
     const uint32_t tag = with_net(ctx->net, [](auto net) { return model_tag<decltype(net)>(); });
-    const StreamOut out = {d_stream, (uint64_t)cap_bytes, n, H, tag, ctx->dist, ctx->d_total, ctx->d_result, ctx->d_sums};
+    const StreamOut out = {d_stream, (uint64_t)cap_bytes, n, H, tag, ctx->dist, ctx->d_total, ctx->d_result, ctx->d_sums, ctx->sums_patience};
     bool assembles = beside && W <= kRansAssembleWidth;
     auto launch_rans = [&](hipStream_t s) {
         prof_begin(ctx, PCC_T_ENCODE_RANS, s);
@@ -2411,7 +2420,8 @@ int pcc_encode(pcc_ctx* ctx, const uint8_t* d_img, int n, int H, int W, uint8_t*
         rc = finish(ctx->side);
         if (rc != PCC_OK) return drain(rc);
         if (ctx->h_result->err == 0 && ctx->h_result->defer != 0) {
-            // The row coder saw nothing of the pixel kernel for a long time and stood down.  The symbols are all there now; code them on the caller's stream.
+            // A group of the row coder saw nothing of the pixel kernel, or of a group before it, for a long time and stood down.  The
+            // symbols are all there now; code them on the caller's stream.
             assembles = false;           // (the groups that stood down have said so in this epoch's sums)
             launch_rans(st);
             rc = finish(st);

@@ -126,3 +126,33 @@ def test_stream_over_the_images(codec, h, w, where, shared):
             assert ms["encode_rans"] > 0 and (ms["encode_compact"] > 0) == shared, ms
     finally:
         codec.pcc_set_profiling(False)
+
+
+# The two ways in which a row coder's workgroup stands down while it places its rows: the sizes of those before it do not come (a
+# limit of 0 polls: all but the first stand down at once), and one before it has stood down for want of a symbol (a few polls for
+# those: some workgroups find theirs, some do not, differently in every call).  All rows are then coded again, the compaction places
+# them, and the next call starts clean.
+@pytest.mark.parametrize("symbols,sums", [(None, "0"), (None, "1")] + [(p, "100000") for p in ("0", "1", "2", "3", "5", "8", "12", "20")])
+def test_workgroups_that_stand_down(codec, symbols, sums, monkeypatch):
+    from paper_2212_01185_amd import binding
+    if symbols is not None:
+        monkeypatch.setenv("PCC_RANS_PATIENCE", symbols)
+    monkeypatch.setenv("PCC_RANS_SUMS_PATIENCE", sums)
+    other = binding.Codec(synth.make_blob(0), 0)
+    rng = np.random.default_rng(9)
+    try:
+        other.pcc_set_profiling(True)
+        for n, h, w in [(1, 32, 50), (1, 33, 7), (1, 512, 100), (3, 1000, 20), (1, 512, 768)]:
+            imgs = torch.from_numpy(rng.integers(0, 256, (n, h, w, 3), dtype=np.uint8)).cuda()
+            want = codec.pcc_encode(imgs).clone()
+            out = torch.empty(binding.pcc_stream_bound(n, h, w), dtype=torch.uint8, device="cuda")
+            for _ in range(6):
+                out.fill_(0xA5)
+                torch.cuda.synchronize()                 # (the row coder runs beside the pixel kernel only where the stream is idle)
+                assert torch.equal(other.pcc_encode(imgs, out=out), want)
+                assert bool((out[want.numel():] == 0xA5).all())
+                placed_by_compaction = other.pcc_last_timings()["encode_compact"] > 0
+                if sums == "0":
+                    assert placed_by_compaction == (n * h > 32)
+    finally:
+        other.close()
