@@ -518,9 +518,10 @@
         // coupling coefficients: canonical head outputs 9K.. (alpha), 10K.. (beta), 11K.. (gamma), wherever the head's
         // (group, register) layout put them; for a component that the lane's part does not have it is the padding behind them
         auto coupling = [&](auto first, auto kc) __attribute__((always_inline)) {
-            constexpr int c = decltype(first)::value, k = decltype(kc)::value, mine = head_slot<Net>(c + k);
-            static_assert(D::kParts == 1 || head_slot<Net>(c + K - 1) == mine + 3 * (K - 1 - k), "one distance between the parts");
-            static_assert(head_slot<Net>(c) + 3 * (D::kParts * PK - 1) < D::kHeadStride, "the padding is there");
+            using Head = std::conditional_t<(MINBLOCKS > 1 && Net::kSharedByCoefficient), SharedHead<Net>, Net>;
+            constexpr int c = decltype(first)::value, k = decltype(kc)::value, mine = head_slot<Net, Head>(c + k);
+            static_assert(D::kParts == 1 || head_slot<Net, Head>(c + K - 1) == mine + 3 * (K - 1 - k), "one distance between the parts");
+            static_assert(D::kParts == 1 || head_slot<Net, Head>(c) + 3 * (D::kParts * PK - 1) < D::kHeadStride, "the padding is there");
             return coupling_at[mine];
         };
         auto load_g = [&]() __attribute__((always_inline)) {

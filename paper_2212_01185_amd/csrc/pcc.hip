@@ -128,12 +128,12 @@ __device__ __forceinline__ void copy_to_lds(uint8_t* lds, const uint8_t* __restr
     }
 }
 
-// Lane group and register (g * kHeadSlots + s) that hold canonical head output c.
-template <class Net>
+// Lane group and register (g * kHeadSlots + s) that hold canonical head output c, in the order of Head.
+template <class Net, class Head = Net>
 __host__ __device__ constexpr int head_slot(int c) {
     for (int g = 0; g < 4; ++g)
         for (int s = 0; s < Layout<Net>::kHeadSlots; ++s)
-            if (Net::head_index(g, s) == c) return g * Layout<Net>::kHeadSlots + s;
+            if (Head::head_index(g, s) == c) return g * Layout<Net>::kHeadSlots + s;
     return -1;
 }
 
@@ -1912,7 +1912,9 @@ int pack_model(const uint8_t* p, size_t blob_bytes, uint32_t dist, std::vector<u
     auto Wat = [&](int l, int o, int i) { return rdf(wsrc[l] + 4 * ((size_t)o * Net::dim(l) + i)); };
     auto Bat = [&](int l, int o) { return rdf(bsrc[l] + 4 * (size_t)o); };
 
-    image.assign(2 * Lay::kModelBytes, 0);        // the decoder's image; behind it the encoder's, with the head's rows in another order
+    // the decoder's image; behind it, with the head's rows in other orders, the encoder's and, where it has its own, that of the decoder
+    // with two workgroups per unit
+    image.assign((Net::kSharedByCoefficient ? 3 : 2) * Lay::kModelBytes, 0);
     uint16_t* w16 = reinterpret_cast<uint16_t*>(image.data());
     for (int l = 0; l < NL; ++l) {
         const int nob = Net::ob(l), nkb = Net::kb(l);
@@ -1964,23 +1966,28 @@ int pack_model(const uint8_t* p, size_t blob_bytes, uint32_t dist, std::vector<u
     lut[2 * kLutEntries] = 1.0f;
     lut[2 * kLutEntries + 1] = 0.0f;
 
-    uint8_t* enc = image.data() + Lay::kModelBytes;
-    memcpy(enc, image.data(), Lay::kModelBytes);
+    // head_index(g, s): canonical output in register s of lane group g, or -1
     constexpr int kHead = NL - 1;
-    for (int s = 0; s < 16 * Net::ob(kHead); ++s) {
-        const int ob = s >> 4, m = s & 15, c = EncHead<Net>::head_index(m >> 2, 4 * ob + (m & 3));
-        // the row of the decoder's head that holds this output, or one that holds none
-        int from = -1;
-        for (int k = 0; k < 16 * Net::ob(kHead); ++k) if (Net::head_index((k & 15) >> 2, 4 * (k >> 4) + (k & 3)) == c) from = k;
-        for (int kb = 0; kb < Net::kb(kHead); ++kb)
-            for (int g = 0; g < 4; ++g) {
-                uint8_t* to = enc + Lay::w_off(kHead) + ((ob * Net::kb(kHead) + kb) * 64 + 16 * g + m) * 16;
-                if (c < 0) memset(to, 0, 16);
-                else memcpy(to, image.data() + Lay::w_off(kHead) + (((from >> 4) * Net::kb(kHead) + kb) * 64 + 16 * g + (from & 15)) * 16, 16);
-            }
-        if (c < 0) memset(enc + Lay::b_off(kHead) + 4 * s, 0, 4);
-        else memcpy(enc + Lay::b_off(kHead) + 4 * s, image.data() + Lay::b_off(kHead) + 4 * from, 4);
-    }
+    auto reordered = [&](uint8_t* copy, auto head_index) {
+        memcpy(copy, image.data(), Lay::kModelBytes);
+        for (int s = 0; s < 16 * Net::ob(kHead); ++s) {
+            const int ob = s >> 4, m = s & 15, c = head_index(m >> 2, 4 * ob + (m & 3));
+            // the row of the first image's head that holds this output, or one that holds none
+            int from = -1;
+            for (int k = 0; k < 16 * Net::ob(kHead); ++k) if (Net::head_index((k & 15) >> 2, 4 * (k >> 4) + (k & 3)) == c) from = k;
+            for (int kb = 0; kb < Net::kb(kHead); ++kb)
+                for (int g = 0; g < 4; ++g) {
+                    uint8_t* to = copy + Lay::w_off(kHead) + ((ob * Net::kb(kHead) + kb) * 64 + 16 * g + m) * 16;
+                    if (c < 0) memset(to, 0, 16);
+                    else memcpy(to, image.data() + Lay::w_off(kHead) + (((from >> 4) * Net::kb(kHead) + kb) * 64 + 16 * g + (from & 15)) * 16, 16);
+                }
+            if (c < 0) memset(copy + Lay::b_off(kHead) + 4 * s, 0, 4);
+            else memcpy(copy + Lay::b_off(kHead) + 4 * s, image.data() + Lay::b_off(kHead) + 4 * from, 4);
+        }
+    };
+    reordered(image.data() + Lay::kModelBytes, [](int g, int s) { return EncHead<Net>::head_index(g, s); });
+    if constexpr (Net::kSharedByCoefficient)
+        reordered(image.data() + 2 * Lay::kModelBytes, [](int g, int s) { return SharedHead<Net>::head_index(g, s); });
     return PCC_OK;
 }
 
@@ -2121,7 +2128,8 @@ void launch_decode(pcc_ctx* ctx, const DecodeLaunch& how, const uint8_t* d_strea
         hipLaunchKernelGGL((decode_kernel<Net, 1>), dim3(how.grid), dim3(kDecThreads), kLds, st, ctx->d_model, d_stream,
                            (uint64_t)nbytes, n, H, W, how.nbands, ctx->dist, d_img_out, d_mail, status, spin_limit);
     else if (how.kernel == DecodeLaunch::kTwo)
-        hipLaunchKernelGGL((decode_kernel<Net, 2>), dim3(how.grid), dim3(kDecThreads), kLdsShared, st, ctx->d_model, d_stream,
+        hipLaunchKernelGGL((decode_kernel<Net, 2>), dim3(how.grid), dim3(kDecThreads), kLdsShared, st,
+                           ctx->d_model + (Net::kSharedByCoefficient ? 2 * Layout<Net>::kModelBytes : 0), d_stream,
                            (uint64_t)nbytes, n, H, W, how.nbands, ctx->dist, d_img_out, d_mail, status, spin_limit);
     else {
         constexpr int kLdsNarrow = DecLds<Net, kNarrowRows>::kBytes;

@@ -88,6 +88,11 @@ struct NetWorkload {
     // (Seven mixtures: the first layer and the head do not fit a CU twice, `all` is the biases and the first layer.)
     static constexpr int kEncodeThreads = 512;    // pixel kernel: threads of a workgroup
     static constexpr int kSharedCuLds = 6;
+    // Two workgroups per unit: does that kernel read a head whose coupling coefficients stand coefficient by coefficient (SharedHead)?
+    // 20 images of 768x512, us with the other order and with this one: this network 6,096 and 6,072, with the predictor's weights 6,066
+    // and 6,011, 64 filters 5,501 and 5,449, five mixtures of the ablation 8,262 and 8,386; the others within 0.2 %.  (One workgroup per unit:
+    // this network 6,594 and 6,717, 64 filters 5,767 and 5,809.)
+    static constexpr bool kSharedByCoefficient = true;
     // Time of a decode step with two workgroups per CU, in percent of a step with one, while the other workgroup waits and
     // while both are busy (fitted to whole jobs; the host chooses between the launches with them: choose_decode).
     static constexpr unsigned kSharedAlonePercent = 112, kSharedStepPercent = 138;
@@ -132,6 +137,7 @@ struct NetPaper {
     static constexpr bool kLeaky = true;
     static constexpr int kEncodeThreads = 512;
     static constexpr int kSharedCuLds = 6;
+    static constexpr bool kSharedByCoefficient = false;
     static constexpr unsigned kSharedAlonePercent = 108, kSharedStepPercent = 137;
     static constexpr unsigned kNarrowPercent = 91;
     static constexpr bool kKeepAwake = true;
@@ -200,6 +206,7 @@ struct NetAblation : NetPaper {
     static constexpr int kSharedCuLds = MIXTURES >= 7 || LAYERS >= 6 ? 7 : MIXTURES >= 5 ? 6 : 4;
     static constexpr unsigned kNarrowPercent = MIXTURES >= 7 ? 82 : MIXTURES >= 5 ? 88 : 91;
     static constexpr bool kKeepAwake = C >= 128;
+    static constexpr bool kSharedByCoefficient = C < 128;
     // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch.)
     static constexpr unsigned kSharedAlonePercent = C > 128 ? 1000 : MIXTURES >= 7 ? 126 : MIXTURES >= 5 ? 107 : LAYERS >= 6 ? 114 : LAYERS <= 4 ? 104 : 101;
     static constexpr unsigned kSharedStepPercent = C > 128 ? 1000 : MIXTURES >= 7 ? 149 : MIXTURES >= 5 ? 135 : LAYERS >= 6 ? 141 : LAYERS <= 4 ? 130 : 123;
@@ -306,6 +313,32 @@ struct EncHead {
 };
 static_assert(EncHead<NetWorkload>::placed_once() && EncHead<NetPaper>::placed_once() && EncHead<NetMostMixtures>::placed_once(),
               "encoder's head layout");
+
+// The head of the decoder with two workgroups per unit where Net::kSharedByCoefficient says so: groups 1 and 2 hold the first alphas and
+// betas in the registers behind their channel's parameters, group 3 the others, one coefficient behind the other, then the gammas.  With
+// five components the alphas, betas and gammas of a pixel are then a vector and a value each for a lane that takes them all (with
+// component by component a value is read by itself, or with another in one instruction).
+template <class Net>
+struct SharedHead {
+    static constexpr int K = Net::K, kSlots = Layout<Net>::kHeadSlots, kRoom = kSlots - 3 * K, kRest = K - kRoom;
+    static_assert(kRoom >= 0 && kRest >= 0 && 2 * kRest + K <= kSlots, "the coefficients fit");
+    __host__ __device__ static constexpr int head_index(int g, int s) {
+        if (g < 3 && s < 3 * K) return 3 * K * g + s;
+        if (g < 3) return g == 0 ? -1 : (8 + g) * K + s - 3 * K;
+        if (s < kRest) return 9 * K + kRoom + s;
+        if (s < 2 * kRest) return 10 * K + kRoom + s - kRest;
+        return s < 2 * kRest + K ? 11 * K + s - 2 * kRest : -1;
+    }
+    static constexpr bool placed_once() {
+        for (int c = 0; c < 12 * K; ++c) {
+            int n = 0;
+            for (int g = 0; g < 4; ++g) for (int s = 0; s < kSlots; ++s) n += head_index(g, s) == c ? 1 : 0;
+            if (n != 1) return false;
+        }
+        return true;
+    }
+};
+static_assert(SharedHead<NetWorkload>::placed_once() && SharedHead<NetFewerFilters>::placed_once(), "shared decoder's head layout");
 
 // Feature index (within a 32-wide k-block) held in slot i of lane group g for
 // the layers after the first: the two 16-row output tiles of the previous layer,

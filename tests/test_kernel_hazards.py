@@ -449,6 +449,15 @@ def test_spilled_registers_of_the_shared_decoder():
 
 
 @needs_hipcc
+def test_the_shared_decoder_reads_coupling_coefficients_as_vectors():
+    """The measured workloads' network, whose steps are built for three roles of a wave: four instructions each that read two
+    single values, none of them for coefficients but the last ones.  Component by component there were eight, and 24 images of
+    768x512 took 6,253 us instead of 6,219."""
+    (body, _), = [(b, l) for name, b, l in _functions(_assembly().split("\n")) if "decode_kernelINS_11NetWorkloadELi2E" in name]
+    assert sum(ins.startswith("ds_read2_b32") for ins in body) <= 12
+
+
+@needs_hipcc
 def test_no_other_kernel_spills_registers():
     """The decoder with 192 filters and two workgroups per unit, which no rule chooses, aside.  The row coder that runs by itself
     keeps one register in scratch, which it stores ahead of its rounds and reads again behind them."""
