@@ -1993,8 +1993,9 @@ int pack_model(const uint8_t* p, size_t blob_bytes, uint32_t dist, std::vector<u
 
 template <class Net>
 bool set_kernel_attributes() {
-    constexpr int enc = encode_model_lds_bytes<Net>() + kTakenBytes + params_stage_bytes<Net>(), dec = DecLds<Net>::kBytes;
-    static_assert(enc <= kLdsBytes && dec <= kLdsBytes && DecLds<Net>::kBytesShared <= kLdsBytes,
+    constexpr int enc = encode_model_lds_bytes<Net>() + kTakenBytes + params_stage_bytes<Net>(), dec = DecLds<Net>::kBytes,
+                  narrow = DecLds<Net, kNarrowRows>::kBytes;
+    static_assert(enc <= kLdsBytes && dec <= kLdsBytes && narrow <= kLdsBytes && DecLds<Net>::kBytesShared <= kLdsBytes,
                   "the network does not fit a compute unit's LDS");
     bool ok = true;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&encode_kernel<Net>),
@@ -2004,12 +2005,12 @@ bool set_kernel_attributes() {
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_kernel<Net, 2>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net>::kBytesShared) == hipSuccess;
     ok = ok && hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, DecLds<Net, kNarrowRows>::kBytes) == hipSuccess;
-    // The decoders read the CDF table at LDS address 0 (cq_lookup<K, true>): their dynamic array must begin there, that is,
-    // they must have no static one in front of it.
-    static_assert(DecLds<Net>::kLutOff == 0, "the table's LDS address is a literal in cq_lookup");
-    std::vector<const void*> decoders = {reinterpret_cast<const void*>(&decode_kernel<Net, 1>), reinterpret_cast<const void*>(&decode_kernel<Net, 2>)};
-    decoders.push_back(reinterpret_cast<const void*>(&decode_narrow_kernel<Net>));
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, narrow) == hipSuccess;
+    // The decoders read the CDF table, or its copies, from LDS address 0 on (cq_lookup, Table::kSpread and kCopies): their dynamic
+    // array must begin there, that is, they must have no static one in front of it.
+    static_assert(DecLds<Net>::kLutOff == 0 && DecLds<Net, kNarrowRows>::kLutOff == 0, "the table's LDS address is a literal in cq_lookup");
+    const void* const decoders[] = {reinterpret_cast<const void*>(&decode_kernel<Net, 1>), reinterpret_cast<const void*>(&decode_kernel<Net, 2>),
+                                    reinterpret_cast<const void*>(&decode_narrow_kernel<Net>)};
     for (const void* decoder : decoders) {
         hipFuncAttributes attr;
         ok = ok && hipFuncGetAttributes(&attr, decoder) == hipSuccess && attr.sharedSizeBytes == 0;
