@@ -56,7 +56,8 @@
     // this wave's weights stay in registers (all that is not staged above), for every band the workgroup decodes
     WaveNet<Net, (MINBLOCKS > 1), 0> net;
     net.load(model, lds, lane, wave);
-    using KeepAwake = Awake<(MINBLOCKS == 1 && Net::kKeepAwake)>;
+    constexpr bool kFilled = MINBLOCKS == 1 && (D::kParts > 1 ? Net::kKeepAwake : Net::kKeepAwakeWide);
+    using KeepAwake = Awake<kFilled>;
     KeepAwake awake;
     const float lut_scale = *reinterpret_cast<const float*>(model + Lay::kLutScaleOff);
     const int total_bands = n * nbands;
@@ -579,7 +580,7 @@
         // Made where it is stored.  Not where every wave makes it: two workgroups per unit (spilled registers, above), and bands of 16 rows
         // without fills of the waits, in whose place it is (us, 8 and 12 images of 768x512 and one of 4096x2160: diagonal 3,492, 4,536, 16,398, by
         // every wave 3,444, 4,480, 16,192; 64 filters 5,031, 5,038, 22,578 and 4,943, 4,980, 22,273; with fills 1 % less to 1 % more).
-        constexpr bool kMailEverywhere = MINBLOCKS > 1 || (D::kParts == 1 && !Net::kKeepAwake);
+        constexpr bool kMailEverywhere = MINBLOCKS > 1 || (D::kParts == 1 && !kFilled);
         if constexpr (kMailEverywhere || Role::kStores) mail_px = (uint32_t)sr | ((uint32_t)sg << 8) | ((uint32_t)sb << 16) | kMailTag;
         settle_active = active;
         asm volatile("" : "+v"(found_b.c2), "+v"(mail_px), "+v"(settle_active));   // scheduling only: while the ring is written

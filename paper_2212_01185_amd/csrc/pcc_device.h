@@ -103,8 +103,12 @@ struct NetWorkload {
     static constexpr unsigned kNarrowPercent = 89;
     // Decoder with one workgroup per unit: are the waits for LDS filled with MFMAs (Awake)?  512x512 with bands of eight rows, us without and
     // with: this network 3,600 and 3,500, the paper's 4,905 and 4,734, six layers (256x256) 2,643 and 2,621, four 2,155 and 2,140, 192 filters
-    // 3,094 and 3,060, five mixtures 2,672 and 2,650, seven 2,770 and 2,772; not with 64 filters 3,980 and 4,005 and in diagonal order (768x512) 3,168 and 3,238.
+    // 3,094 and 3,060, five mixtures 2,672 and 2,650, seven 2,770 and 2,772 (but 8,257 and 8,118 for twelve of 768x512, with bands of 16); not
+    // with 64 filters 3,980 and 4,005 and in diagonal order (768x512) 3,168 and 3,238.
     static constexpr bool kKeepAwake = true;
+    // And with bands of 16 rows?  768x512, 8 to 20 images, us without and with: this network 4,977 and 4,847, 6,698 and 6,558, the paper's 6,070 and
+    // 6,043, 6,882 and 6,861; four layers 5,452 and 5,516, 6,202 and 6,304.
+    static constexpr bool kKeepAwakeWide = true;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 30 : l == 1 ? 160 : l == 2 ? 160 : l == 3 ? 128 : 60; }
     __host__ __device__ static constexpr int ob(int l) { return l == 0 ? 10 : l == 1 ? 10 : l == 2 ? 8 : 4; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 1 : l == 1 ? 5 : l == 2 ? 5 : 4; }
@@ -140,7 +144,7 @@ struct NetPaper {
     static constexpr bool kSharedByCoefficient = false;
     static constexpr unsigned kSharedAlonePercent = 108, kSharedStepPercent = 137;
     static constexpr unsigned kNarrowPercent = 91;
-    static constexpr bool kKeepAwake = true;
+    static constexpr bool kKeepAwake = true, kKeepAwakeWide = true;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
     __host__ __device__ static constexpr int kb(int l) { return l == 0 ? 2 : 4; }
@@ -164,7 +168,7 @@ struct NetDiagonal : NetPaper {
     static constexpr int kRingPad = 4;
     static constexpr unsigned kSharedAlonePercent = 118, kSharedStepPercent = 138;
     static constexpr unsigned kNarrowPercent = 95;
-    static constexpr bool kKeepAwake = false;
+    static constexpr bool kKeepAwake = false, kKeepAwakeWide = false;
     __host__ __device__ static constexpr bool run_desc(int kbi, int g, int half, int& dr, int& off) {
         if (kbi == 0) {
             if (g == 0) { dr = -2; off = 4 * half; }                          // row r-2, bytes 0..7
@@ -205,7 +209,7 @@ struct NetAblation : NetPaper {
     static constexpr int kEncodeThreads = C > 128 ? 256 : 512;
     static constexpr int kSharedCuLds = MIXTURES >= 7 || LAYERS >= 6 ? 7 : MIXTURES >= 5 ? 6 : 4;
     static constexpr unsigned kNarrowPercent = MIXTURES >= 7 ? 82 : MIXTURES >= 5 ? 88 : 91;
-    static constexpr bool kKeepAwake = C >= 128;
+    static constexpr bool kKeepAwake = C >= 128, kKeepAwakeWide = C >= 128 && LAYERS > 4;
     static constexpr bool kSharedByCoefficient = C < 128;
     // (C = 192: a wave's weight slices alone are 264 registers; two workgroups per CU are never the better launch.)
     static constexpr unsigned kSharedAlonePercent = C > 128 ? 1000 : MIXTURES >= 7 ? 126 : MIXTURES >= 5 ? 107 : LAYERS >= 6 ? 114 : LAYERS <= 4 ? 104 : 101;
