@@ -48,10 +48,14 @@ def test_a_call_that_fails_leaves_no_trace(codec):
     imgs = torch.from_numpy(rng.integers(0, 256, (1, 70, 40, 3), dtype=np.uint8)).cuda()
     want = codec.pcc_encode(imgs).clone()
     for size in (want.numel() - 8, 32 + 8 * 71 + 64):
-        for _ in range(2):
+        for busy in (False, False, True):                # (the row coder runs beside the pixel kernel only where the stream is idle)
+            out = torch.zeros(size // 8 * 8, dtype=torch.uint8, device="cuda")
+            if not busy:
+                torch.cuda.synchronize()
             with pytest.raises(binding.PccError) as e:
-                codec.pcc_encode(imgs, out=torch.zeros(size // 8 * 8, dtype=torch.uint8, device="cuda"))
+                codec.pcc_encode(imgs, out=out)
             assert e.value.code == binding.PCC_E_CAP
+            torch.cuda.synchronize()
             assert torch.equal(codec.pcc_encode(imgs), want)
 
 
@@ -86,16 +90,24 @@ def test_row_coder_places_rows_as_the_compaction_does(codec, n, h, w, monkeypatc
     imgs = torch.from_numpy(imgs).cuda()
     try:
         want = other.pcc_encode(imgs).clone()
+        codec.pcc_set_profiling(True)
         for _ in range(3):
             out = torch.full((binding.pcc_stream_bound(n, h, w),), 0xA5, dtype=torch.uint8, device="cuda")
+            torch.cuda.synchronize()                                  # (an idle stream: beside the pixel kernel)
             got = codec.pcc_encode(imgs, out=out)
+            ms = codec.pcc_last_timings()
+            assert ms["encode_rans"] > 0 and (ms["encode_compact"] == 0) == (w <= 1024 and n * h <= 3072), ms
             assert torch.equal(got, want)
             assert bool((out[want.numel():] == 0xA5).all())           # nothing behind the stream
+        small = (want.numel() - 4) // 8 * 8
+        out.fill_(0xA5)
+        torch.cuda.synchronize()
         with pytest.raises(binding.PccError) as e:                    # and nothing behind a buffer that is too small
-            codec.pcc_encode(imgs, out=out.fill_(0xA5)[:(want.numel() - 4) // 8 * 8])
-        assert e.value.code == binding.PCC_E_CAP and bool((out[(want.numel() - 4) // 8 * 8:] == 0xA5).all())
+            codec.pcc_encode(imgs, out=out[:small])
+        assert e.value.code == binding.PCC_E_CAP and bool((out[small:] == 0xA5).all())
         assert torch.equal(codec.pcc_encode(imgs), want)
     finally:
+        codec.pcc_set_profiling(False)
         other.close()
 
 
