@@ -79,7 +79,8 @@
         }
     }
 
-    // The grid has at most as many workgroups as the chip holds at once, and a workgroup decodes band after band:
+    // The grid has at most as many workgroups as the chip holds at once, with one per unit also no more than bands can
+    // run at a time (choose_decode), and a workgroup decodes band after band:
     // it takes a ticket, decodes that band, takes the next.  A band only ever waits for the band above it (same
     // image), which has a smaller ticket.  Tickets come from a counter, in the order they are asked for, so every
     // ticket below a held one is held by some workgroup or finished.  With two workgroups per compute unit a

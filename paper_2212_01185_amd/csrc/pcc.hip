@@ -2117,7 +2117,17 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     if (ctx->decode_variant == 2) kernel = DecodeLaunch::kTwo;
     if (ctx->decode_variant == 3) kernel = narrow_fits ? DecodeLaunch::kNarrow : DecodeLaunch::kOne;
     const int per_image = kernel == DecodeLaunch::kNarrow ? narrow_bands : nbands;
-    return {kernel, per_image, (uint32_t)std::min((uint64_t)n * per_image, kernel == DecodeLaunch::kTwo ? 2 * cus : cus)};
+    if (kernel == DecodeLaunch::kTwo) return {kernel, per_image, (uint32_t)std::min((uint64_t)n * per_image, 2 * cus)};
+    // Workgroups: one for each band that can run at a time, and two for the turn from one band to the next.  One for every band held units
+    // for bands that were not to begin for a long time, and polled there: with bands of eight rows a decode that started alone then left none
+    // for one that came behind it.  ms until each thread has decoded four times, with bands of 16 rows alone, with a workgroup a band and now:
+    // the paper's network, two threads with four images of 768x512 6.24, 6.74, 6.08, with one of 4096x2160 27.6, 30.0, 27.3, three with one of
+    // 2048x1365 16.2, 17.1, 15.8; six layers, two with four of 768x512 6.97, 7.45, 6.77.  A decode by itself is not slower for it (33 jobs with
+    // three networks): four images of 768x512 4.38 and 4.28, the paper's network 5.66 and 5.47, 4096x2160 19.98 and 19.65.
+    const int rows = kernel == DecodeLaunch::kNarrow ? kNarrowRows : kBandRows;
+    const uint64_t stride = (uint64_t)Net::kDelay * rows;
+    const uint64_t at_once = std::min((uint64_t)per_image, ((uint64_t)W + (uint64_t)Net::kDelay * ((H < rows ? H : rows) - 1) + stride - 1) / stride + 2);
+    return {kernel, per_image, (uint32_t)std::min((uint64_t)n * at_once, cus)};
 }
 
 template <class Net>

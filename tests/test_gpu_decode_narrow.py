@@ -152,3 +152,41 @@ def test_decodes_that_run_at_once_share_the_chip(h, w, threads, monkeypatch):
     print("%d threads, %dx%d: chosen against bands of 16 rows %s" % (threads, w, h, " ".join("%.3f" % r for r in ratios)), flush=True)
     if h * w > 1 << 20:                # (the small ones take a few ms: only their images are looked at)
         assert sorted(ratios)[2] <= 1.15
+
+
+def test_a_decode_leaves_units_for_another():
+    """Two threads decode four images of 768x512 of the paper's network each.  The one that starts alone takes bands of eight
+    rows, 256 of them, of which 33 of an image's 64 can run at a time: with a workgroup for each of those the other one finds
+    units.  (With one for every band it found none until the first bands had ended, after a third of the decode.)"""
+    from paper_2212_01185_amd import binding
+    imgs = torch.from_numpy(np.random.default_rng(89).integers(0, 256, (4, 512, 768, 3), dtype=np.uint8)).cuda()
+    codecs = [binding.Codec(synth.make_paper_blob(0), 0) for _ in range(2)]
+    outs = [torch.zeros_like(imgs) for _ in codecs]
+    ratios = []
+    try:
+        stream = codecs[0].pcc_encode(imgs)
+        for c, out in zip(codecs, outs):
+            c.pcc_decode(stream, 4, 512, 768, out=out)
+        for _ in range(7):
+            streams = [torch.cuda.Stream() for _ in codecs]
+            torch.cuda.synchronize()
+
+            def work(c, s, out):
+                with torch.cuda.stream(s):
+                    c.pcc_decode(stream, 4, 512, 768, out=out)
+            seconds = []
+            for count in (1, 2):
+                workers = [threading.Thread(target=work, args=a) for a in list(zip(codecs, streams, outs))[:count]]
+                start = time.perf_counter()
+                for t in workers:
+                    t.start()
+                for t in workers:
+                    t.join()
+                seconds.append(time.perf_counter() - start)
+            ratios.append(seconds[1] / seconds[0])
+            assert all(torch.equal(out, imgs) for out in outs)
+    finally:
+        for c in codecs:
+            c.close()
+    print("two decodes against one %s" % " ".join("%.3f" % r for r in ratios), flush=True)
+    assert sorted(ratios)[3] <= 1.25
