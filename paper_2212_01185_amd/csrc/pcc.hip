@@ -2111,7 +2111,7 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     const bool narrow_fits = mailbox_bytes(n, narrow_bands, W) <= most_bytes;
     const double steps_narrow = (double)steps(cus, kNarrowRows, narrow_bands);
     const double narrow_busy = (double)n * narrow_bands * (W + (double)Net::kDelay * ((H < kNarrowRows ? H : kNarrowRows) - 1)) / steps_narrow;    // places, on average
-    const bool narrow_room = sharers <= 1 || 4.0 * narrow_busy <= 0.75 * (double)cus;
+    const bool narrow_room = narrow_busy <= (sharers <= 1 ? Net::kNarrowAlonePercent / 100.0 : 0.75 / 4.0) * (double)cus;
     if (narrow_fits && narrow_room && (double)Net::kNarrowPercent * steps_narrow < best) kernel = DecodeLaunch::kNarrow;
     if (ctx->decode_variant == 1) kernel = DecodeLaunch::kOne;
     if (ctx->decode_variant == 2) kernel = DecodeLaunch::kTwo;

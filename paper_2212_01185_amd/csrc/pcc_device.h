@@ -101,6 +101,12 @@ struct NetWorkload {
     // the paper's 5,181 and 4,730, diagonal 2,734 and 2,587, five mixtures 6,003 and 5,313, seven 6,814 and 5,560, four layers 4,688 and
     // 4,281, six 5,773 and 5,261, 64 filters 4,383 and 3,989, 192 6,738 and 6,132.
     static constexpr unsigned kNarrowPercent = 89;
+    // And the percentage of the chip that they may keep busy, on average, in a decode that is alone when it starts: less than all in diagonal order,
+    // where all bands of an image run at a time and eight rows gain little.  With 16 and with eight rows, us of a decode alone, and ms until each of two
+    // threads has decoded four times where the first one starts so: one of 768x512 (15 %) 3,340 and 3,158, 3.40 and 3.24; one of 2048x1365 (40 %) 8,873 and
+    // 8,537, 9.13 and 9.40; four of 512x512 (51 %) 2,709 and 2,670, 2.85 and 3.15; two of 1024x1024 (50 %) 5,462 and 5,372, 5.70 and 6.27; four of 768x512
+    // (61 %) 3,363 and 3,297, 3.51 and 3.96.
+    static constexpr unsigned kNarrowAlonePercent = 100;
     // Decoder with one workgroup per unit: are the waits for LDS filled with MFMAs (Awake)?  512x512 with bands of eight rows, us without and
     // with: this network 3,600 and 3,500, the paper's 4,905 and 4,734, six layers (256x256) 2,643 and 2,621, four 2,155 and 2,140, 192 filters
     // 3,094 and 3,060, five mixtures 2,672 and 2,650, seven 2,770 and 2,772 (but 8,257 and 8,118 for twelve of 768x512, with bands of 16); not
@@ -143,7 +149,7 @@ struct NetPaper {
     static constexpr int kSharedCuLds = 6;
     static constexpr bool kSharedByCoefficient = false;
     static constexpr unsigned kSharedAlonePercent = 108, kSharedStepPercent = 137;
-    static constexpr unsigned kNarrowPercent = 91;
+    static constexpr unsigned kNarrowPercent = 91, kNarrowAlonePercent = 100;
     static constexpr bool kKeepAwake = true, kKeepAwakeWide = true;
     __host__ __device__ static constexpr int dim(int l) { return l == 0 ? 36 : l == 5 ? 36 : 128; }
     __host__ __device__ static constexpr int ob(int l) { return l == 4 ? 3 : 8; }
@@ -167,7 +173,7 @@ struct NetDiagonal : NetPaper {
     static constexpr int kRingCols = 8;
     static constexpr int kRingPad = 4;
     static constexpr unsigned kSharedAlonePercent = 118, kSharedStepPercent = 138;
-    static constexpr unsigned kNarrowPercent = 95;
+    static constexpr unsigned kNarrowPercent = 95, kNarrowAlonePercent = 48;
     static constexpr bool kKeepAwake = false, kKeepAwakeWide = false;
     __host__ __device__ static constexpr bool run_desc(int kbi, int g, int half, int& dr, int& off) {
         if (kbi == 0) {

@@ -154,13 +154,15 @@ def test_decodes_that_run_at_once_share_the_chip(h, w, threads, monkeypatch):
         assert sorted(ratios)[2] <= 1.15
 
 
-def test_a_decode_leaves_units_for_another():
-    """Two threads decode four images of 768x512 of the paper's network each.  The one that starts alone takes bands of eight
+@pytest.mark.parametrize("net", ["paper", "diagonal"])
+def test_a_decode_leaves_units_for_another(net):
+    """Two threads decode four images of 768x512 each.  With the paper's network the one that starts alone takes bands of eight
     rows, 256 of them, of which 33 of an image's 64 can run at a time: with a workgroup for each of those the other one finds
-    units.  (With one for every band it found none until the first bands had ended, after a third of the decode.)"""
+    units.  (With one for every band it found none until the first bands had ended, after a third of the decode.)  In diagonal
+    order all of them run at a time, so it takes bands of 16 rows."""
     from paper_2212_01185_amd import binding
     imgs = torch.from_numpy(np.random.default_rng(89).integers(0, 256, (4, 512, 768, 3), dtype=np.uint8)).cuda()
-    codecs = [binding.Codec(synth.make_paper_blob(0), 0) for _ in range(2)]
+    codecs = [binding.Codec(BLOBS[net](0), 0) for _ in range(2)]
     outs = [torch.zeros_like(imgs) for _ in codecs]
     ratios = []
     try:
@@ -188,5 +190,5 @@ def test_a_decode_leaves_units_for_another():
     finally:
         for c in codecs:
             c.close()
-    print("two decodes against one %s" % " ".join("%.3f" % r for r in ratios), flush=True)
+    print("%s: two decodes against one %s" % (net, " ".join("%.3f" % r for r in ratios)), flush=True)
     assert sorted(ratios)[3] <= 1.25
