@@ -490,15 +490,15 @@ __device__ __forceinline__ void rans_round_toward_zero() {
     asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 3" ::: "memory");
 }
 
-// Keeps a wave's SIMD from falling idle while the wave waits for LDS.  Behind a gap of more than some 16 cycles without a vector or
-// matrix instruction the four SIMDs of a compute unit share one issue slot for vector instructions for about 140 cycles: where four waves
-// go through such gaps together, as behind every barrier, the first ten instructions of each take 14 cycles instead of 4 (with one
-// wave at work they take 4).  Matrix instructions are not slowed and prevent it: ten vector instructions, a read and a
-// barrier take 219 cycles in a loop, with six 4x4x4 MFMAs (8 cycles each) in the read's wait 136, with five 219.  So a wait that
+// Keeps a wave's SIMD from falling idle while the wave waits for LDS.  Where all four SIMDs of a compute unit have been without a vector or
+// matrix instruction, as behind every barrier, the first ten or so vector instructions of each wave take 14 cycles instead of 4, as if the SIMDs
+// shared one issue slot for some 140 cycles.  (Measured, not documented: a loop of a read, a barrier and K vector instructions takes four waves 145, 281, 321 and 401
+// cycles for K = 0, 10, 20 and 40, one wave at work 140, 180, 220 and 300, two 140, 213, 299 and 372.)  Matrix instructions are not slowed and prevent it: with four 4x4x4
+// MFMAs (8 cycles each) in the read's wait the loop takes four waves 165, 245, 285 and 365, with six, which outlast the wait, 215, 282, 322 and 402.  So a wait that
 // vector instructions follow is filled with MFMAs of zeros, as long as the wait at least takes anyway.  (Not in the searches, whose own
 // instructions fill the look-ups' waits: one MFMA each 4,076 -> 4,155 us; in the gather, behind a layer's reads, which MFMAs follow, or
 // at the step's end 4,102 to 4,142.)  768x512 4,187 -> 4,076 us, with bands of 16 rows 4,733 -> 4,586; the paper's network in 512x512
-// 4,909 -> 4,722.
+// 4,909 -> 4,722.  Why some networks lose by it (kKeepAwake, kKeepAwakeWide) is not known.
 template <bool ON>
 struct Awake {
     static constexpr int kBehindWrite = 4, kBehindHeadReads = 6, kBehindMixtureReads = 10;      // MFMAs, of 2 to 14 tried each
@@ -1512,8 +1512,7 @@ struct WaveNet<Net, SHARED, L, true> {
 // With 32 lanes to a pixel two rows of 16 lanes share an edge's components: the first row looks up the first kPartK of them and
 // sums them, the second row looks up the others meanwhile and goes on with the first row's sum, so that the sum is made in
 // the order of the components as everywhere; what a sweep finds is in the second row.  A vector instruction in a search costs more
-// than its 4 cycles: behind a gap (a look-up's wait) the four SIMDs of a unit share one issue slot for some 140 cycles (ten
-// instructions of each take 95 cycles longer).  So the forms with fewest of them: plain copies of the table instead of spread entries (one a look-up),
+// than its 4 cycles: behind a look-up's wait the first ten of each wave take 14 (Awake).  So the forms with fewest of them: plain copies of the table instead of spread entries (one a look-up),
 // no copy of the sum before the lane swap, and rows without sums that never pass instead of a mask on the ballot: 768x512 4,318 -> 4,210 us,
 // the paper's network in 512x512 4,987 -> 4,899.
 struct SearchLane {            // a lane's constants
@@ -2085,13 +2084,13 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     // measured time with one workgroup per CU.  With two the time per step goes from one figure to the other with the
     // share of the places that are busy on average, from a fifth of them to four fifths.
     // Fitted per network to 57 jobs of 192 to 2,000 bands (6 to 48 images of 768x512, 65 to 500 of 64x64, 2 to 4 of
-    // 4096x2160, images of a few rows and of a few columns): the launch chosen takes 0.1 % longer than the better one on
-    // average and 3.6 % at most.  768x512, ms with one and with two per CU: 16 images 5.66 and 6.02, 18 images 6.56 and
-    // 5.96, 48 images 12.68 and 9.93; the paper's shape, 9 images 6.27 and 6.66, 24 images 7.53 and 7.51.
+    // 4096x2160, images of a few rows and of a few columns).  768x512, ms with one and with two per CU: 16 images 5.38 and 5.84, 18 images
+    // 6.31 and 5.91, 48 images 12.4 and 10.0; the paper's shape, 8 images 6.08 and 6.44, 24 images 7.38 and 7.35.  Of 170 jobs with ten models
+    // (one to 300 images, 64x64 to 4096x2160) the launch chosen of the three takes as long as the best one on average and 2.4 % longer at most.
     // Bands of eight rows take Net::kNarrowPercent of the time of a step, and are twice as many: they are for jobs whose chain of
-    // steps, not whose work per CU, sets the time.  768x512, ms with bands of 16 and of 8 rows: 1 image 4.57 and 4.08, 8 images 4.84
-    // and 4.77 (the hand-overs of 500 bands), 10 images 4.89 and 6.01; 4096x2160 21.4 and 19.3; 768x512 with seven mixtures, 8 images
-    // 8.00 and 6.50, 10 images 8.24 and 7.40.
+    // steps, not whose work per CU, sets the time.  768x512, ms with bands of 16 and of 8 rows: 1 image 4.60 and 4.08, 4 images 4.69
+    // and 4.25, 8 images 4.82 and 4.85 (the hand-overs of 500 bands), 10 images 4.81 and 5.84; 4096x2160 21.8 and 19.6; 768x512 with seven
+    // mixtures, 8 images 8.00 and 6.60, 12 images 8.06 and 8.02.
     // They hold twice the places for it, which other decodes then wait for: beside another decode (threads with a context and a stream
     // each) they are for jobs of which four, the hardware queues of a process, keep three quarters of the chip busy at most.  ms until each
     // thread has decoded an image, with 16 rows and with 8: 4096x2160, two threads 22.5 and 24.3, three 24.6 and 34.4, four 26.0
@@ -2120,7 +2119,7 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     if (kernel == DecodeLaunch::kTwo) return {kernel, per_image, (uint32_t)std::min((uint64_t)n * per_image, 2 * cus)};
     // Workgroups: one for each band that can run at a time, and two for the turn from one band to the next.  One for every band held units
     // for bands that were not to begin for a long time, and polled there: with bands of eight rows a decode that started alone then left none
-    // for one that came behind it.  ms until each thread has decoded four times, with bands of 16 rows alone, with a workgroup a band and now:
+    // for one that came behind it.  ms a decode where each thread decodes four times, with bands of 16 rows alone, with a workgroup a band and now:
     // the paper's network, two threads with four images of 768x512 6.24, 6.74, 6.08, with one of 4096x2160 27.6, 30.0, 27.3, three with one of
     // 2048x1365 16.2, 17.1, 15.8; six layers, two with four of 768x512 6.97, 7.45, 6.77.  A decode by itself is not slower for it (33 jobs with
     // three networks): four images of 768x512 4.38 and 4.28, the paper's network 5.66 and 5.47, 4096x2160 19.98 and 19.65.

@@ -102,8 +102,8 @@ struct NetWorkload {
     // 4,281, six 5,773 and 5,261, 64 filters 4,383 and 3,989, 192 6,738 and 6,132.
     static constexpr unsigned kNarrowPercent = 89;
     // And the percentage of the chip that they may keep busy, on average, in a decode that is alone when it starts: less than all in diagonal order,
-    // where all bands of an image run at a time and eight rows gain little.  With 16 and with eight rows, us of a decode alone, and ms until each of two
-    // threads has decoded four times where the first one starts so: one of 768x512 (15 %) 3,340 and 3,158, 3.40 and 3.24; one of 2048x1365 (40 %) 8,873 and
+    // where all bands of an image run at a time and eight rows gain little.  With 16 and with eight rows, us of a decode alone, and ms a decode where two
+    // threads decode four times each and the first one starts so: one of 768x512 (15 %) 3,340 and 3,158, 3.40 and 3.24; one of 2048x1365 (40 %) 8,873 and
     // 8,537, 9.13 and 9.40; four of 512x512 (51 %) 2,709 and 2,670, 2.85 and 3.15; two of 1024x1024 (50 %) 5,462 and 5,372, 5.70 and 6.27; four of 768x512
     // (61 %) 3,363 and 3,297, 3.51 and 3.96.
     static constexpr unsigned kNarrowAlonePercent = 100;
