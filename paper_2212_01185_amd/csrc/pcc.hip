@@ -2093,8 +2093,8 @@ DecodeLaunch choose_decode(const pcc_ctx* ctx, int n, int H, int W, size_t most_
     // mixtures, 8 images 8.00 and 6.60, 12 images 8.06 and 8.02.
     // They hold twice the places for it, which other decodes then wait for: beside another decode (threads with a context and a stream
     // each) they are for jobs of which four, the hardware queues of a process, keep three quarters of the chip busy at most.  ms until each
-    // thread has decoded an image, with 16 rows and with 8: 4096x2160, two threads 22.5 and 24.3, three 24.6 and 34.4, four 26.0
-    // and 45.2; 2048x1365, two 12.7 and 12.7, three 12.8 and 13.3, four 13.4 and 15.0; 1024x1024, four 8.55 and 8.51.
+    // thread has decoded an image, with 16 rows and with 8: 4096x2160, two threads 22.2 and 22.5, three 24.8 and 31.6, four 25.9
+    // and 41.1; 2048x1365, two 12.5 and 11.3, three 12.6 and 12.7, four 13.3 and 14.0; 1024x1024, four 8.14 and 7.67.
     auto steps = [&](uint64_t places, int rows, int per_image) {
         const uint64_t hold = (uint64_t)W + (uint64_t)Net::kDelay * ((H < rows ? H : rows) - 1), stride = (uint64_t)Net::kDelay * rows;
         const uint64_t last = (uint64_t)n * per_image - 1;
